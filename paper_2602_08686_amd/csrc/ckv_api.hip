@@ -103,7 +103,7 @@ void layout(const ckv_params *p, const Shape &s, Workspace *w) {
   w->vsum_bytes = (p->flags & CKV_FLAG_VALUE_NORM) ? units * vnorm_blocks_per_unit(s) * sizeof(float) : 0;
   off = align256(off + w->vsum_bytes);
   w->select_off = off;
-  w->select_bytes = select_workspace_bytes(s);
+  w->select_bytes = select_workspace_bytes(p, s);
   off = align256(off + w->select_bytes);
   w->total = off;
 }
@@ -317,8 +317,12 @@ extern "C" ckv_status ckv_select_topk(const ckv_params *params, const float *uti
   // workspace lets the selection split a unit over several workgroups.
   Workspace w;
   layout(params, s, &w);
-  const bool split = workspace && w.select_bytes > 0;
-  if (split && workspace_ok(w, workspace, workspace_bytes) != CKV_OK) return CKV_EWORKSPACE;
+  bool split = workspace && w.select_bytes > 0;
+  if (split && workspace_ok(w, workspace, workspace_bytes) != CKV_OK) {
+    // rows of a length that is no multiple of four have always been taken with any workspace
+    if (s.P % 4 == 0) return CKV_EWORKSPACE;
+    split = false;
+  }
   if (launch_select(params, s, utility, budget, tau, idx, count, split ? (char *)workspace + w.select_off : nullptr,
                     (hipStream_t)hip_stream) != hipSuccess)
     return CKV_EHIP;

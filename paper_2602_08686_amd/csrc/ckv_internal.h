@@ -124,9 +124,9 @@ hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float 
                                const float *vnorm_ratio, const float *w_head, const float *head_share,
                                const float *t_gate, int n_ent, int n_ppl, const int32_t *risk_bins,
                                float *utility, int32_t *budget, float *tau, hipStream_t stream);
-// ws: nullptr, or select_workspace_bytes(s) bytes (256-byte aligned) that let long prefixes be split
+// ws: nullptr, or select_workspace_bytes() bytes (256-byte aligned) that let long prefixes be split
 // over several workgroups per unit; the result is the same either way.
-size_t select_workspace_bytes(const Shape &s);
+size_t select_workspace_bytes(const ckv_params *p, const Shape &s);
 hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utility,
                          const int32_t *budget, const float *tau, int32_t *idx, int32_t *count,
                          char *ws, hipStream_t stream);

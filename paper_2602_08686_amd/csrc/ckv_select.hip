@@ -1,19 +1,44 @@
 // Elastic candidate pool with budget clamp (paper Eq. 8, Alg. 1 Select) as a radix select.
 //
-// One 1024-thread workgroup per (batch, KV head). Utilities are non-negative floats, so their bit
-// patterns order like unsigned integers. The kp-th largest candidate key is found MSB-first with an
-// LDS histogram per pass (integer LDS atomics: the counts, and so the result, do not depend on
-// scheduling). The final pass emits the kept positions in ascending order with ranks from prefix
-// counts in position order. Equal keys at the threshold are taken lowest position first, which is
-// exactly "utility descending, position ascending".
+// Utilities are non-negative floats, so their bit patterns order like integers: a key is the pattern of a
+// candidate and -1 of anything else. Everything is counted with integers (order-independent, so the result
+// does not depend on scheduling), kept positions leave in ascending order, and equal keys at the threshold
+// are taken lowest position first, which is exactly "utility descending, position ascending".
 //
-// Two kernels. select_reg_kernel (prefixes of up to 65536 positions, rows 16-byte aligned) reads the
-// utilities once, with 128-bit loads, and keeps them in registers for all passes: digits of 11, 10
-// and 10 bits, so the first one already splits the mantissa and same-address atomics stay rare.
-// select_kernel streams the utilities from L2 in every pass (any length): digits of 8 bits.
+// select_keys() is the core, one workgroup with its keys in registers (thread tid holds slots i * NT + tid, so the
+// lane mask of a comparison is 64 consecutive slots). What bounds it is vector instructions per key, the chain of
+// dependent steps and the fetch of its code, not bytes: the keys are gone over three times (build, maximum,
+// one comparison), everything after that works on the few that can still be kept.
+//   1. A lower bound of the threshold: the kp-th largest of the maxima of more than kp groups of keys (a thread's
+//      keys, or each four of them where kp exceeds half the threads). With 1024 groups of 32 and kp = 480 about 2 %
+//      of the keys lie above it, so the keys themselves need no histogram. The maxima's histogram spans their own
+//      range: pooled window masses lie within +-30 %, where bins on fixed bits of the float would be a
+//      handful of counters (same-address atomics, thousands of undecided keys in the threshold's bin).
+//   2. Slots of keys at or above the bound go to a list in LDS, in order: a wave's masks are dealt to its lanes and
+//      each lane walks the set bits of its own.
+//   3. The threshold among the list's keys (read again, by slot): a histogram; where its bin holds at most 64 keys,
+//      a comparison of all with all that every wave does for itself; else further digits.
+//   4. The list's kept entries, in its order.
+// Where too few groups hold candidates, the histogram goes over all keys; where the list would exceed its
+// capacity (budgets in the thousands, masses of equal keys) and where a thread holds at most eight keys, the
+// threshold is searched over the registers and every lane writes its own kept slots.
+// Measured, us per call, graph of 20 calls, 32 units (before: 8- and 11-bit digits of all keys in registers): 1k / budget
+// 128: 7.4 -> 4.7, 4k / 512: 8.5 -> 5.8, 16k / 256: 16.1 -> 7.6, 32k / 512: 27.7 -> 9.2; 32737 positions, before by
+// the streaming kernel: 44.3 -> 9.3. Inside a 32k call of 10 us: loads 1.9, keys and maxima 1.6, their histogram 1.0,
+// list 2.5, threshold 1.5, output 1.3. A launch costs 4.6 of them.
+//
+// Who calls the core: select_reg_kernel, one workgroup per (batch, KV head) with up to 65536 positions;
+// select_slice_kernel + select_merge_kernel, for longer rows a workgroup per 8192 or 16384 positions and one per unit
+// on what the slices kept. select_split_kernel (budgets so large that slices keep nearly everything) and
+// select_kernel (no workspace) stay for the rest.
 #include "ckv_internal.h"
 
+// x with lane `lane` (a constant) replaced by the wave-uniform v: one instruction, which has no builtin of its own.
+extern "C" __device__ int ckv_llvm_writelane(int v, int lane, int x) __asm("llvm.amdgcn.writelane.i32");
+
 namespace ckv {
+
+__device__ __forceinline__ int write_lane(int v, int lane, int x) { return ckv_llvm_writelane(v, lane, x); }
 
 struct SelectArgs {
   const float *utility;   // [units][P]
@@ -24,9 +49,500 @@ struct SelectArgs {
   int Hkv, T, W, P, cap;
 };
 
-__device__ __forceinline__ uint32_t key_of(float u) {
-  const uint32_t bits = __builtin_bit_cast(uint32_t, u);
-  return (bits & 0x80000000u) ? 0u : bits;  // -0.0 orders like +0.0
+// -0.0 and anything negative order like +0.0; NaN is no candidate
+__device__ __forceinline__ int key_of(float u, float tau) { return u >= tau ? max(__float_as_int(u), 0) : -1; }
+
+// Prefix slots of a unit: its budget without the window's.
+__device__ __forceinline__ int prefix_quota(const SelectArgs &a, int unit) {
+  return max(a.W, min(a.budget[unit], min(a.cap, a.T))) - a.W;
+}
+
+// Scans and reductions over the wave with lane moves inside the vector unit (row shifts by 1, 2, 4, 8, then the
+// last lane of a row of 16 to the next row and of the lower half to the upper): a shuffle through LDS costs over
+// a hundred cycles per step, and these chains are most of what a short selection waits for.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t identity, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)x, CTRL, ROWS, 0xF, false);
+}
+template <class Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {  // inclusive; lane 63: the total
+  x = op(x, dpp_from<0x111, 0xF>(identity, x));
+  x = op(x, dpp_from<0x112, 0xF>(identity, x));
+  x = op(x, dpp_from<0x114, 0xF>(identity, x));
+  x = op(x, dpp_from<0x118, 0xF>(identity, x));
+  x = op(x, dpp_from<0x142, 0xA>(identity, x));
+  x = op(x, dpp_from<0x143, 0xC>(identity, x));
+  return x;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane) {  // lane is wave-uniform
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
+}
+__device__ __forceinline__ int wave_inclusive(int x) {
+  return (int)wave_scan((uint32_t)x, 0u, [](uint32_t p, uint32_t q) { return p + q; });
+}
+
+// c + the set bits of the mask below this lane
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long mask, uint32_t c) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, c));
+}
+
+constexpr int kBins = 2048;
+constexpr int kFewKeys = 64;  // undecided keys that a wave settles by comparing all with all
+
+template <int NK, int NT>
+struct SelectShared {
+  static constexpr int NW = NT / kWave;
+  static constexpr int NE = NK * NW;   // 64-slot entries
+  static constexpr int NQ = 4;         // list entries per thread
+  static constexpr int CAP = NQ * NT;  // list capacity
+  int hist[kBins];
+  int list[CAP];
+  int cnt[NE > 64 ? NE : 64], cnt_eq[NE > 64 ? NE : 64];
+  uint32_t red_max[NW], red_min[NW];
+  int red_cnt[NW], bin_cnt[NW];
+  __attribute__((aligned(16))) int few[kFewKeys];
+  int n_few, bin, above, in_bin;
+};
+
+template <class Shared>
+__device__ __forceinline__ void clear_hist(Shared &sh, int tid) {
+  constexpr int NT = Shared::NW * kWave;
+#pragma unroll
+  for (int i = 0; i < kBins / NT; ++i) sh.hist[i * NT + tid] = 0;
+}
+
+// Bin of the histogram where the running count from the top first reaches k (1-based), the count above it and its
+// own, into sh.bin / above / in_bin. All threads call it; hist is complete (behind a barrier); ends behind a barrier.
+template <class Shared>
+__device__ __forceinline__ void find_bin_block(Shared &sh, int k, int tid, int lane, int wave) {
+  constexpr int NW = Shared::NW, PER = kBins / (NW * kWave);
+  int c[PER], sum = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    c[e] = sh.hist[kBins - 1 - PER * tid - e];
+    sum += c[e];
+  }
+  const int incl = wave_inclusive(sum);
+  if (lane == kWave - 1) sh.bin_cnt[wave] = incl;
+  __syncthreads();
+  const int waves = lane < NW ? sh.bin_cnt[lane] : 0;
+  int run = (int)lane_value((uint32_t)(wave_inclusive(waves) - waves), wave) + incl - sum;
+  if (run < k && k <= run + sum) {
+    bool found = false;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      if (!found && run + c[e] >= k) {
+        found = true;
+        sh.bin = kBins - 1 - PER * tid - e;
+        sh.above = run;
+        sh.in_bin = c[e];
+      }
+      run += c[e];
+    }
+  }
+  __syncthreads();
+}
+
+// For lane i: the sum of cnt in front of entry i * NW + wave (lanes at and beyond NK: anything). Every wave scans
+// the NE entries for itself.
+template <int NK, int NW>
+__device__ __forceinline__ int entries_before(const int *cnt, int lane, int wave, int &total) {
+  constexpr int NE = NK * NW, PER = (NE + kWave - 1) / kWave;
+  static_assert(NW % PER == 0 || PER % NW == 0, "a wave's entries sit at one place of their lanes' runs");
+  int sum = 0, part = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int c = lane * PER + e < NE ? cnt[lane * PER + e] : 0;
+    if (PER <= NW && e == wave % PER) part = sum;
+    sum += c;
+  }
+  const int incl = wave_inclusive(sum);
+  total = (int)lane_value((uint32_t)incl, kWave - 1);
+  return __shfl(incl - sum + part, (lane * NW + wave) / PER & (kWave - 1));
+}
+
+// The k-th largest of the workgroup's keys, which lie in [low, low + 2048 << shift) where they are at least low; k becomes
+// how many of the keys equal to it are among the k. hist is clear; begins with a use of it. All threads call it.
+template <int N, int NT, class Shared>
+__device__ __forceinline__ int find_threshold(const int (&key)[N], int low, int shift, int &k, Shared &sh, int tid, int lane, int wave) {
+  uint32_t prefix = 0u;       // digits of (threshold - low) found so far
+  int rem = shift, b = 31;    // bits of this round's digit: the first one takes all that the shift leaves
+  while (true) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const uint32_t off = (uint32_t)(key[q] - low);
+      if (key[q] >= low && (off >> rem >> b) == prefix) atomicAdd(&sh.hist[(off >> rem) & ((1u << b) - 1u)], 1);
+    }
+    __syncthreads();
+    find_bin_block(sh, k, tid, lane, wave);
+    prefix = prefix << b | (uint32_t)sh.bin;
+    k -= sh.above;
+    if (rem == 0) return low + (int)prefix;
+    const int in_bin = sh.in_bin;
+    if (in_bin <= kFewKeys) {
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        if (key[q] >= low && ((uint32_t)(key[q] - low) >> rem) == prefix) sh.few[atomicAdd(&sh.n_few, 1)] = key[q];
+      __syncthreads();
+      const int my = lane < in_bin ? sh.few[lane] : -1;
+      int above = 0, equal = 0;
+      for (int i = 0; i < in_bin; i += 4) {  // the same four words for every lane; beyond in_bin whatever is there
+        const int4 other = *reinterpret_cast<const int4 *>(&sh.few[i]);
+        const bool y = i + 1 < in_bin, z = i + 2 < in_bin, w = i + 3 < in_bin;
+        above += (other.x > my) + (y && other.y > my) + (z && other.z > my) + (w && other.w > my);
+        equal += (other.x == my) + (y && other.y == my) + (z && other.z == my) + (w && other.w == my);
+      }
+      const int src = __ffsll((long long)__ballot(lane < in_bin && above < k && k <= above + equal)) - 1;
+      k -= (int)lane_value((uint32_t)above, src);
+      return (int)lane_value((uint32_t)my, src);
+    }
+    __syncthreads();
+    clear_hist(sh, tid);
+    __syncthreads();
+    b = min(rem, 11);
+    rem -= b;
+  }
+}
+
+// Kept slots in slot order, where few of a wave's keys are kept: write(rank, slot) of the keys at or above bound. A
+// wave's masks are dealt to its lanes, lane i takes row i and walks its set bits. Returns how many there are.
+template <int NK, int NT, class Write>
+__device__ __forceinline__ int emit_sparse(SelectShared<NK, NT> &sh, const int (&key)[NK], int bound, Write write, int lane, int wave) {
+  constexpr int NW = NT / kWave;
+  static_assert(NK <= kWave, "a lane per mask");
+  int lo = 0, hi = 0;
+#pragma unroll
+  for (int i = 0; i < NK; ++i) {
+    const unsigned long long mask = __ballot(key[i] >= bound);
+    lo = write_lane((int)(uint32_t)mask, i, lo);
+    hi = write_lane((int)(uint32_t)(mask >> 32), i, hi);
+  }
+  if (lane < NK) sh.cnt[lane * NW + wave] = __popc(lo) + __popc(hi);
+  __syncthreads();
+  int total;
+  int rank = entries_before<NK, NW>(sh.cnt, lane, wave, total);
+  if (lane < NK) {
+    unsigned long long mask = (uint32_t)lo | (unsigned long long)(uint32_t)hi << 32;
+    while (mask) {
+      write(rank++, lane * NT + wave * kWave + __ffsll((long long)mask) - 1);
+      mask &= mask - 1;
+    }
+  }
+  return total;
+}
+
+// Kept slots in slot order, any number of them: every lane writes its own, the keys above thr and the first need_eq
+// equal to it, as write(rank, slot, key); base_gt / base_eq count those in front of the workgroup's keys, ranks at or
+// beyond limit are dropped. Returns how many of the workgroup's there are.
+template <int NK, int NT, class Write>
+__device__ __forceinline__ int emit_keys(SelectShared<NK, NT> &sh, const int (&key)[NK], int thr, int need_eq, int limit, int base_gt,
+                                         int base_eq, Write write, int tid, int lane, int wave) {
+  constexpr int NW = NT / kWave;
+  int counts = 0, counts_eq = 0;
+#pragma unroll
+  for (int i = 0; i < NK; ++i) {
+    counts = write_lane(__popcll(__ballot(key[i] > thr)), i, counts);
+    counts_eq = write_lane(__popcll(__ballot(key[i] == thr)), i, counts_eq);
+  }
+  if (lane < NK) {
+    sh.cnt[lane * NW + wave] = counts;
+    sh.cnt_eq[lane * NW + wave] = counts_eq;
+  }
+  __syncthreads();
+  int total, total_eq;
+  const int g0 = entries_before<NK, NW>(sh.cnt, lane, wave, total), q0 = entries_before<NK, NW>(sh.cnt_eq, lane, wave, total_eq);
+#pragma unroll
+  for (int i = 0; i < NK; ++i) {
+    const int g = base_gt + (int)lanes_below(__ballot(key[i] > thr), lane_value((uint32_t)g0, i));
+    const int q = base_eq + (int)lanes_below(__ballot(key[i] == thr), lane_value((uint32_t)q0, i));
+    const int r = g + min(q, need_eq);
+    if ((key[i] > thr || (key[i] == thr && q < need_eq)) && r < limit) write(r, i * NT + tid, key[i]);
+  }
+  return min(total + min(total_eq, need_eq), limit);
+}
+
+// Keys per thread up to which the threshold is searched and the kept slots are written from the registers.
+constexpr int kDirectKeys = 8;
+// Largest quota that goes by the list (capacity 4096): 16k positions, quota 4064: 18.4 us with the list tried first,
+// 12.4 without.
+constexpr int kListQuota = 3584;
+
+// The kp largest keys (equal ones: lowest slot first), in slot order: write(rank, slot, key). reload(slot) is the key of
+// a slot. kp >= 1. Returns how many were kept. All threads of the workgroup call it.
+template <int NK, int NT, class Reload, class Write>
+__device__ __forceinline__ int select_keys(const int (&key)[NK], int kp, SelectShared<NK, NT> &sh, Reload reload, Write write,
+                                           int tid, int lane, int wave) {
+  using Shared = SelectShared<NK, NT>;
+  constexpr int NW = NT / kWave, NG = NK / 4;
+  const auto larger = [](uint32_t p, uint32_t q) { return max(p, q); };
+  const auto smaller = [](uint32_t p, uint32_t q) { return min(p, q); };
+
+  // -- 1: group maxima (as unsigned numbers: no candidate is the largest, so it never is the smallest maximum)
+  int four[NG], mine = -1;
+#pragma unroll
+  for (int q = 0; q < NG; ++q) {
+    four[q] = max(max(key[4 * q], key[4 * q + 1]), max(key[4 * q + 2], key[4 * q + 3]));
+    mine = max(mine, four[q]);
+  }
+  const bool by_thread = 2 * kp <= NT;
+  uint32_t least = (uint32_t)mine;
+  int groups = mine >= 0;
+  if (!by_thread) {
+    groups = 0;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      least = min(least, (uint32_t)four[q]);
+      groups += four[q] >= 0;
+    }
+  }
+  {
+    const uint32_t top = wave_scan((uint32_t)(mine + 1), 0u, larger);  // + 1: 0 for none
+    const uint32_t low = wave_scan(least, 0xffffffffu, smaller);
+    const int n = wave_inclusive(groups);
+    if (lane == kWave - 1) {
+      sh.red_max[wave] = top;
+      sh.red_min[wave] = low;
+      sh.red_cnt[wave] = n;
+    }
+  }
+  clear_hist(sh, tid);
+  if (tid == 0) sh.n_few = 0;
+  __syncthreads();
+  uint32_t lo;
+  int mx, n_groups;
+  auto block_stats = [&] {
+    const uint32_t top = wave_scan(lane < NW ? sh.red_max[lane] : 0u, 0u, larger);
+    const uint32_t low = wave_scan(lane < NW ? sh.red_min[lane] : 0xffffffffu, 0xffffffffu, smaller);
+    const int n = wave_inclusive(lane < NW ? sh.red_cnt[lane] : 0);
+    mx = (int)lane_value(top, kWave - 1) - 1;
+    lo = lane_value(low, kWave - 1);
+    n_groups = (int)lane_value((uint32_t)n, kWave - 1);
+  };
+  block_stats();
+  const bool by_groups = n_groups > kp;  // then there are more than kp candidates as well
+  bool all = false;                      // keep every candidate
+  if (!by_groups) {                      // uniform: count the candidates
+    uint32_t cand_min = 0xffffffffu;
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      cand_min = min(cand_min, (uint32_t)key[i]);
+      n += key[i] >= 0;
+    }
+    cand_min = wave_scan(cand_min, 0xffffffffu, smaller);
+    n = wave_inclusive(n);
+    __syncthreads();
+    if (lane == kWave - 1) {
+      sh.red_min[wave] = cand_min;
+      sh.red_cnt[wave] = n;
+    }
+    __syncthreads();
+    block_stats();
+    all = n_groups <= kp;
+  }
+  const auto shift_for = [](uint32_t range) { return max(0, 21 - __clz((int)range | 1)); };  // range >> shift < kBins
+  int k = kp, thr = -1;
+  if constexpr (NK <= kDirectKeys) {
+    if (all) k = 0;
+    else thr = find_threshold<NK, NT>(key, (int)lo, shift_for((uint32_t)mx - lo), k, sh, tid, lane, wave);
+    return emit_keys<NK, NT>(sh, key, thr, k, kp, 0, 0, write, tid, lane, wave);
+  }
+  // a quota that leaves the list no room for the undecided keys: straight to the registers
+  int m = Shared::CAP + 1, bound = (int)lo, shift = shift_for((uint32_t)mx - lo);
+  if (!all && kp <= kListQuota) {
+    if (!by_groups) {
+#pragma unroll
+      for (int i = 0; i < NK; ++i)
+        if (key[i] >= 0) atomicAdd(&sh.hist[((uint32_t)key[i] - lo) >> shift], 1);
+    } else if (by_thread) {
+      if (mine >= 0) atomicAdd(&sh.hist[((uint32_t)mine - lo) >> shift], 1);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NG; ++q)
+        if (four[q] >= 0) atomicAdd(&sh.hist[((uint32_t)four[q] - lo) >> shift], 1);
+    }
+    __syncthreads();
+    find_bin_block(sh, kp, tid, lane, wave);
+    bound = (int)(lo + ((uint32_t)sh.bin << shift));  // at least kp keys are at or above it
+    clear_hist(sh, tid);  // find_bin_block ended behind a barrier: hist has been read
+
+    // -- 2: slots of the keys at or above the bound
+    m = emit_sparse<NK, NT>(
+        sh, key, bound,
+        [&](int rank, int slot) {
+          if (rank < Shared::CAP) sh.list[rank] = slot;
+        },
+        lane, wave);
+    __syncthreads();
+    shift = shift_for((uint32_t)(mx - bound));
+  }
+  if (all || m > Shared::CAP) {  // uniform
+    if (all) k = 0;
+    else thr = find_threshold<NK, NT>(key, bound, shift, k, sh, tid, lane, wave);
+    return emit_keys<NK, NT>(sh, key, thr, k, kp, 0, 0, write, tid, lane, wave);
+  }
+
+  // -- 3: the list's keys; the threshold among them
+  constexpr int NQ = Shared::NQ;
+  int slot[NQ], lk[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    slot[q] = -1;
+    lk[q] = -1;
+    if (q * NT + tid < m) {
+      slot[q] = sh.list[q * NT + tid];
+      lk[q] = reload(slot[q]);
+    }
+  }
+  thr = find_threshold<NQ, NT>(lk, bound, shift, k, sh, tid, lane, wave);
+
+  // -- 4: kept entries of the list: those above thr and the first k equal to it
+  uint32_t gt_before[NQ], eq_before[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const unsigned long long mg = __ballot(lk[q] > thr), mq = __ballot(lk[q] == thr);
+    gt_before[q] = lanes_below(mg, 0u);
+    eq_before[q] = lanes_below(mq, 0u);
+    if (lane == 0) sh.cnt[q * NW + wave] = __popcll(mg) | __popcll(mq) << 16;
+  }
+  __syncthreads();
+  static_assert(NQ * NW <= kWave, "an entry per lane");
+  const int packed = lane < NQ * NW ? sh.cnt[lane] : 0;
+  const int gi = wave_inclusive(packed & 0xffff), qi = wave_inclusive((int)((uint32_t)packed >> 16));
+  const int gx = gi - (packed & 0xffff), qx = qi - (int)((uint32_t)packed >> 16);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int g = (int)gt_before[q] + (int)lane_value((uint32_t)gx, q * NW + wave);
+    const int e = (int)eq_before[q] + (int)lane_value((uint32_t)qx, q * NW + wave);
+    if (lk[q] > thr || (lk[q] == thr && e < k)) write(g + min(e, k), slot[q], lk[q]);
+  }
+  return kp;
+}
+
+template <int NK, int NT>
+__device__ __forceinline__ void load_keys(const float *u, int P, int base, float tau, int (&key)[NK], int tid) {
+  float x[NK];
+#pragma unroll
+  for (int i = 0; i < NK; ++i) {
+    const int t = base + i * NT + tid;
+    x[i] = t < P ? u[t] : __int_as_float(0x7fc00000);  // NaN: no candidate
+  }
+#pragma unroll
+  for (int i = 0; i < NK; ++i) key[i] = key_of(x[i], tau);
+}
+
+// One workgroup per unit; all positions in registers.
+template <int NK, int NT>
+__global__ void __launch_bounds__(NT) select_reg_kernel(SelectArgs a) {
+  __shared__ SelectShared<NK, NT> sh;
+  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float *u = a.utility + (size_t)unit * a.P;
+  const float tau = a.tau[unit / a.Hkv];
+  int key[NK];
+  load_keys<NK, NT>(u, a.P, 0, tau, key, tid);  // in flight while the budget arrives
+  const int kp = prefix_quota(a, unit);
+  int32_t *out = a.idx + (size_t)unit * a.cap;
+  int kept = 0;
+  if (kp > 0)
+    kept = select_keys<NK, NT>(
+        key, kp, sh, [&](int slot) { return key_of(u[slot], tau); }, [&](int rank, int slot, int) { out[rank] = slot; }, tid, lane, wave);
+  for (int j = tid; j < a.W; j += NT) out[kept + j] = a.P + j;
+  if (tid == 0) a.count[unit] = kept + a.W;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Long rows in two launches. A slice of 8192 or 16384 positions per workgroup keeps its own kp best (what the unit keeps
+// is among them) as (key, position) pairs in the workspace, in position order, padded with "no candidate" to
+// a length that both kernels know from the budget; one workgroup per unit then selects among the slices' pairs.
+// No counter has to be cleared beforehand and no workgroup waits for another. Worth it while the slices drop
+// most keys: slices_pay() draws the line.
+// ---------------------------------------------------------------------------------------------
+struct SliceArgs {
+  SelectArgs a;
+  int2 *pairs;  // [units][S][region] (key, position)
+  int S, region, slice;  // slices per unit, pairs per slice, positions per slice
+};
+
+// Pairs that a slice hands over, a multiple of 64 (so is the region).
+__device__ __forceinline__ int slice_pairs(int kp, int slice) { return (min(kp, slice) + kWave - 1) / kWave * kWave; }
+
+template <int NK>
+__global__ void __launch_bounds__(kSelectThreads) select_slice_kernel(SliceArgs sa) {
+  __shared__ SelectShared<NK, kSelectThreads> sh;
+  const SelectArgs &a = sa.a;
+  const int unit = blockIdx.x / sa.S, slice = blockIdx.x % sa.S;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float *u = a.utility + (size_t)unit * a.P;
+  const float tau = a.tau[unit / a.Hkv];
+  const int base = slice * sa.slice;
+  int key[NK];
+  load_keys<NK, kSelectThreads>(u, min(a.P, base + sa.slice), base, tau, key, tid);
+  const int kp = prefix_quota(a, unit);
+  if (kp <= 0) return;
+  int2 *out = sa.pairs + (size_t)blockIdx.x * sa.region;
+  const int kept = select_keys<NK, kSelectThreads>(
+      key, kp, sh, [&](int slot) { return key_of(u[base + slot], tau); },
+      [&](int rank, int slot, int k) { out[rank] = make_int2(k, base + slot); }, tid, lane, wave);
+  for (int i = kept + tid; i < slice_pairs(kp, sa.slice); i += kSelectThreads) out[i] = make_int2(-1, 0);
+}
+
+// Defined with the streaming kernel below.
+struct StreamShared {
+  int hist[256];
+  int wave_gt[kSelectThreads / kWave], wave_eq[kSelectThreads / kWave];
+  uint32_t prefix;
+  int k, state;  // state: 0 = keep all candidates, 1 = select, 2 = keep none
+};
+template <class Key, class Emit>
+__device__ __forceinline__ int select_stream(int n, int kp, StreamShared &sh, Key key_at, Emit emit, int tid, int lane, int wave);
+
+template <int NK>
+__device__ __forceinline__ int merge_slices(const int2 *pairs, int S, int region, int per_slice, int kp,
+                                            SelectShared<NK, kSelectThreads> &sh, int32_t *out, int tid, int lane, int wave) {
+  // the unit's pairs, slices back to back without the regions' rests; 64 slots never straddle two slices
+  int key[NK];
+  int slice = 0, off = wave * kWave;
+#pragma unroll
+  for (int i = 0; i < NK; ++i) {
+    while (off >= per_slice) {  // uniform
+      off -= per_slice;
+      ++slice;
+    }
+    key[i] = slice < S ? pairs[(size_t)slice * region + off + lane].x : -1;
+    off += kSelectThreads;
+  }
+  const auto at = [&](int slot) { return pairs[(size_t)(slot / per_slice) * region + slot % per_slice]; };
+  return select_keys<NK, kSelectThreads>(
+      key, kp, sh, [&](int slot) { return at(slot).x; }, [&](int rank, int slot, int) { out[rank] = at(slot).y; }, tid, lane, wave);
+}
+
+constexpr int kMergeKeys = 32;
+
+__global__ void __launch_bounds__(kSelectThreads) select_merge_kernel(SliceArgs sa) {
+  __shared__ union {
+    SelectShared<8, kSelectThreads> few;
+    SelectShared<kMergeKeys, kSelectThreads> most;
+    StreamShared stream;
+  } sh;
+  const SelectArgs &a = sa.a;
+  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int2 *pairs = sa.pairs + (size_t)unit * sa.S * sa.region;
+  const int kp = prefix_quota(a, unit);
+  int32_t *out = a.idx + (size_t)unit * a.cap;
+  int kept = 0;
+  if (kp > 0) {
+    const int per_slice = slice_pairs(kp, sa.slice), n = sa.S * per_slice;
+    if (n <= 8 * kSelectThreads) kept = merge_slices<8>(pairs, sa.S, sa.region, per_slice, kp, sh.few, out, tid, lane, wave);
+    else if (n <= kMergeKeys * kSelectThreads)
+      kept = merge_slices<kMergeKeys>(pairs, sa.S, sa.region, per_slice, kp, sh.most, out, tid, lane, wave);
+    else {  // a head's share far above the nominal budget that slices_pay() goes by
+      const auto at = [&](int i) { return pairs[(size_t)(i / per_slice) * sa.region + i % per_slice]; };
+      kept = select_stream(
+          n, kp, sh.stream, [&](int i) { return at(i).x; }, [&](int rank, int i) { out[rank] = at(i).y; }, tid, lane, wave);
+    }
+  }
+  for (int j = tid; j < a.W; j += kSelectThreads) out[kept + j] = a.P + j;
+  if (tid == 0) a.count[unit] = kept + a.W;
 }
 
 // Adds one count per active lane to hist[digit]. Utilities cluster in a few exponent bins, so plain
@@ -92,233 +608,27 @@ __device__ __forceinline__ BinResult find_bin(const int *hist, int k, int lane) 
   return r;
 }
 
-// ---------------------------------------------------------------------------------------------
-// Register-resident select: thread tid holds positions 4 * (j * 1024 + tid) + e, j < NV, e < 4, as
-// keys k' = candidate ? bits + 1 : 0 (so "not a candidate" sorts below every candidate).
-// ---------------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(4))) float f32x4_sel;
-
-// AGGREGATE: lanes that share a digit are counted with one atomic (hist_add). With digits this fine
-// the plain atomics measured faster even in the first pass, where every candidate takes part.
-template <int NV, int SHIFT, int BITS, bool AGGREGATE>
-__device__ __forceinline__ void digit_histogram(int *hist, const uint32_t (&key)[NV][4], uint32_t prefix_hi,
-                                                int lane) {
+// Counts digit SHIFT .. SHIFT + BITS - 1 of the candidates whose higher bits are prefix_hi.
+template <int NK, int SHIFT, int BITS>
+__device__ __forceinline__ void digit_histogram(int *hist, const int (&key)[NK], uint32_t prefix_hi) {
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t k = key[j][e];
-      const bool active = k != 0u && (k >> (SHIFT + BITS)) == prefix_hi;
-      const int digit = (int)((k >> SHIFT) & ((1u << BITS) - 1u));
-      if (AGGREGATE) hist_add(hist, active, digit, lane);
-      else if (active) atomicAdd(&hist[digit], 1);
-    }
+  for (int i = 0; i < NK; ++i) {
+    const uint32_t k = (uint32_t)key[i];
+    if (key[i] >= 0 && (k >> (SHIFT + BITS)) == prefix_hi) atomicAdd(&hist[(k >> SHIFT) & ((1u << BITS) - 1u)], 1);
   }
 }
 
-// Scratch of ranked_write, in LDS.
-template <int NV>
-struct RankScratch {
-  static constexpr int N = NV * (kSelectThreads / kWave);
-  int wave_tot[N];             // per (block of 4096 positions, wave): kept-above count | equal count << 16
-  int pre_gt[N + 1], pre_eq[N + 1];  // their exclusive prefixes, unpacked, then the totals
-};
-struct BlockTotals {
-  int gt, eq;  // keys above / equal to the threshold among the workgroup's positions
-};
-
-// Writes the kept positions of the workgroup's NV * 4096 positions (thread tid holds positions
-// t_base + 4 * (j * 1024 + tid) + e) in ascending order: every key above thr, and the first need_eq keys
-// equal to it, at the rank they have among all kept positions. base_gt / base_eq count the keys above /
-// equal that lie before t_base; ranks at or beyond kp are dropped. All threads of the workgroup call it.
-template <int NV>
-__device__ __forceinline__ BlockTotals ranked_write(const uint32_t (&key)[NV][4], uint32_t thr, int need_eq, int kp,
-                                                    int base_gt, int base_eq, int t_base, int32_t *out,
-                                                    RankScratch<NV> &rs, int tid, int lane, int wave) {
-  constexpr int NW = kSelectThreads / kWave;
-  int *wave_tot = rs.wave_tot, *pre_gt = rs.pre_gt, *pre_eq = rs.pre_eq;
-  // Ranks in position order: block j, then wave, then lane, then element. A wave's counts come from the
-  // lane masks of the comparisons themselves (population counts on the scalar unit, no cross-lane traffic);
-  // they travel packed as (above | equal << 16): a wave covers 256 positions, so neither half overflows.
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    int c = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      c += __popcll(__ballot(key[j][e] > thr)) + (__popcll(__ballot(key[j][e] == thr)) << 16);
-    if (lane == 0) wave_tot[j * NW + wave] = c;
-  }
-  __syncthreads();
-  // exclusive prefix over the (block, wave) totals in position order, by wave 0; the grand totals
-  // end up behind the last entry
-  if (wave == 0) {
-    constexpr int PER = (NV * NW + kWave - 1) / kWave;
-    int g[PER], q[PER], sg = 0, sq = 0;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int i = lane * PER + e;
-      const int c = i < NV * NW ? wave_tot[i] : 0;
-      g[e] = c & 0xffff;
-      q[e] = c >> 16;
-      sg += g[e];
-      sq += q[e];
-    }
-    int ig = sg, iq = sq;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int ug = __shfl_up(ig, o), uq = __shfl_up(iq, o);
-      if (lane >= o) {
-        ig += ug;
-        iq += uq;
-      }
-    }
-    int rg = ig - sg, rq = iq - sq;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int i = lane * PER + e;
-      if (i < NV * NW) {
-        pre_gt[i] = rg;
-        pre_eq[i] = rq;
-      }
-      rg += g[e];
-      rq += q[e];
-    }
-    if (lane == 63) {
-      pre_gt[NV * NW] = ig;
-      pre_eq[NV * NW] = iq;
-    }
-  }
-  __syncthreads();
-  const int tot_gt = pre_gt[NV * NW], tot_eq = pre_eq[NV * NW];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    // kept keys above / equal in front of this lane's four: the blocks and waves before, then the lower
-    // lanes of this wave (bits of the comparison masks below the lane, counted per element)
-    uint32_t gt_before = (uint32_t)(base_gt + pre_gt[j * NW + wave]);
-    uint32_t eq_before = (uint32_t)(base_eq + pre_eq[j * NW + wave]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const unsigned long long mg = __ballot(key[j][e] > thr), me = __ballot(key[j][e] == thr);
-      gt_before = __builtin_amdgcn_mbcnt_hi((uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, gt_before));
-      eq_before = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, eq_before));
-    }
-    const int t = 4 * (j * kSelectThreads + tid);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool gt = key[j][e] > thr, eq = key[j][e] == thr;
-      if (gt || (eq && (int)eq_before < need_eq)) {
-        const int pos = (int)gt_before + min((int)eq_before, need_eq);
-        if (pos < kp) out[pos] = t_base + t + e;
-      }
-      gt_before += gt;
-      eq_before += eq;
-    }
-  }
-  return BlockTotals{tot_gt, tot_eq};
-}
-
-template <int NV>
-__global__ void __launch_bounds__(kSelectThreads) select_reg_kernel(SelectArgs a) {
-  __shared__ int hist[2048 + 1024 + 1024];  // one histogram per digit, all cleared up front
-  __shared__ RankScratch<NV> ranks;
-  __shared__ uint32_t s_prefix;
-  __shared__ int s_k, s_state;  // s_state: 0 = keep all candidates, 1 = select, 2 = keep none
-
-  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int P = a.P, W = a.W;
-  const float *u = a.utility + (size_t)unit * P;
-  const float tau = a.tau[unit / a.Hkv];
-  int bud = a.budget[unit];
-  bud = max(W, min(bud, min(a.cap, a.T)));
-  const int kp = bud - W;
-
-  uint32_t key[NV][4];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int t = 4 * (j * kSelectThreads + tid);
-    f32x4_sel x = {-1.0f, -1.0f, -1.0f, -1.0f};
-    if (t < P) x = *reinterpret_cast<const f32x4_sel *>(u + t);  // P % 4 == 0: whole vectors only
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float xe = x[e];
-      key[j][e] = (t < P && xe >= tau) ? key_of(xe) + 1u : 0u;
-    }
-  }
-
-  for (int i = tid; i < 4096; i += kSelectThreads) hist[i] = 0;
-  __syncthreads();
-  digit_histogram<NV, 20, 11, false>(hist, key, 0u, lane);
-  __syncthreads();
-  if (wave == 0) {
-    const BinResult r = find_bin<2048>(hist, max(kp, 1), lane);
-    if (lane == 0) {
-      if (r.total <= kp) s_state = 0;
-      else if (kp == 0) s_state = 2;
-      else {
-        s_state = 1;
-        s_prefix = (uint32_t)r.bin;  // bits 30..20 of the threshold
-        s_k = kp - r.above;          // still needed from inside the chosen bin
-      }
-    }
-  }
-  __syncthreads();
-  const int state = s_state;
-  uint32_t thr = 0u;  // keep-all: every candidate has k' > 0
-  int need_eq = 0;    // how many keys equal to thr are kept
-  if (state == 2) {
-    thr = 0xffffffffu;
-  } else if (state == 1) {
-    {
-      const uint32_t prefix = s_prefix;
-      const int k = s_k;
-      digit_histogram<NV, 10, 10, false>(hist + 2048, key, prefix, lane);
-      __syncthreads();
-      if (wave == 0) {
-        const BinResult r = find_bin<1024>(hist + 2048, k, lane);
-        if (lane == 0) {
-          s_prefix = (prefix << 10) | (uint32_t)r.bin;
-          s_k = k - r.above;
-        }
-      }
-      __syncthreads();
-    }
-    {
-      const uint32_t prefix = s_prefix;
-      const int k = s_k;
-      digit_histogram<NV, 0, 10, false>(hist + 3072, key, prefix, lane);
-      __syncthreads();
-      if (wave == 0) {
-        const BinResult r = find_bin<1024>(hist + 3072, k, lane);
-        if (lane == 0) {
-          s_prefix = (prefix << 10) | (uint32_t)r.bin;
-          s_k = k - r.above;
-        }
-      }
-      __syncthreads();
-    }
-    thr = s_prefix;
-    need_eq = s_k;
-  }
-
-  int32_t *out = a.idx + (size_t)unit * a.cap;
-  const BlockTotals tot = ranked_write<NV>(key, thr, need_eq, kp, 0, 0, 0, out, ranks, tid, lane, wave);
-  const int tot_gt = tot.gt, tot_eq = tot.eq;
-  const int kept = min(tot_gt + min(tot_eq, need_eq), kp);
-  for (int j = tid; j < W; j += kSelectThreads) out[kept + j] = P + j;
-  if (tid == 0) a.count[unit] = kept + W;
-}
-
 // ---------------------------------------------------------------------------------------------
-// Split select: prefixes beyond 32768 positions, when the caller passes a workspace. A unit's positions are cut into slices of 8192, one workgroup each, so that long contexts
-// with few (batch, head) units still fill the chip. Five launches walk the same steps as the register
-// kernel: three digit histograms (slices merge theirs into the unit's histogram in global memory with
-// integer atomics: order-independent, so the result is deterministic), the slices' counts of keys above
-// / equal to the threshold, and the ranked write. Every workgroup derives the threshold digits from
+// Split select: long rows whose budgets are so large that slices could drop few keys. The same slices, one
+// workgroup each; five launches walk three digits of the key (11, 10 and 10 bits: slices merge their histograms
+// into the unit's in global memory with integer atomics), the slices' counts of keys above / equal to the
+// threshold, and the ranked write. Every workgroup derives the threshold digits from
 // the merged histograms itself (4096 integers per unit), which saves the launches in between.
 // ---------------------------------------------------------------------------------------------
-constexpr int kSplitNV = 2;
-constexpr int kSplitSlice = kSplitNV * 4 * kSelectThreads;  // positions per workgroup
 constexpr int kSplitHist = 2048 + 1024 + 1024;              // merged histogram words per unit
+
+constexpr int kSplitKeys = 8;
+constexpr int kSplitSlice = kSplitKeys * kSelectThreads;  // positions per workgroup
 
 struct SplitArgs {
   SelectArgs a;
@@ -337,36 +647,24 @@ __global__ void __launch_bounds__(kSelectThreads) select_split_zero_kernel(int *
 // digits found so far. PHASE 3: per-slice counts and the unit's threshold. PHASE 4: ranked write.
 template <int PHASE>
 __global__ void __launch_bounds__(kSelectThreads) select_split_kernel(SplitArgs sa) {
-  __shared__ int hist[2048];
-  __shared__ RankScratch<kSplitNV> ranks;
+  __shared__ SelectShared<kSplitKeys, kSelectThreads> sh;
+  int *const hist = sh.hist;
   __shared__ uint32_t s_prefix;
   __shared__ int s_k, s_state;  // s_state: 0 = keep all candidates, 1 = select, 2 = keep none
   __shared__ int s_red[kSelectThreads / kWave];
 
   const SelectArgs &a = sa.a;
   const int unit = blockIdx.x / sa.S, slice = blockIdx.x % sa.S;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int P = a.P, W = a.W;
   const float *u = a.utility + (size_t)unit * P;
   const float tau = a.tau[unit / a.Hkv];
-  int bud = a.budget[unit];
-  bud = max(W, min(bud, min(a.cap, a.T)));
-  const int kp = bud - W;
-  const int t_base = slice * kSplitSlice;
+  const int kp = prefix_quota(a, unit);
+  const int base = slice * kSplitSlice;
   int *gh = sa.hist + (size_t)unit * kSplitHist;
 
-  uint32_t key[kSplitNV][4];
-#pragma unroll
-  for (int j = 0; j < kSplitNV; ++j) {
-    const int t = t_base + 4 * (j * kSelectThreads + tid);
-    f32x4_sel x = {-1.0f, -1.0f, -1.0f, -1.0f};
-    if (t < P) x = *reinterpret_cast<const f32x4_sel *>(u + t);  // P % 4 == 0: whole vectors only
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float xe = x[e];
-      key[j][e] = (t < P && xe >= tau) ? key_of(xe) + 1u : 0u;
-    }
-  }
+  int key[kSplitKeys];
+  load_keys<kSplitKeys, kSelectThreads>(u, P, base, tau, key, tid);
 
   // Threshold digits: phase p finds digit p - 1 from the histogram that phase p - 1 merged (the same
   // arithmetic in every workgroup of the unit) and takes the digits before it from the record that
@@ -426,7 +724,7 @@ __global__ void __launch_bounds__(kSelectThreads) select_split_kernel(SplitArgs 
     __syncthreads();
     for (int i = tid; i < NB; i += kSelectThreads) hist[i] = 0;
     __syncthreads();
-    digit_histogram<kSplitNV, 20 - 10 * PHASE, PHASE == 0 ? 11 : 10, false>(hist, key, prefix, lane);
+    digit_histogram<kSplitKeys, 20 - 10 * PHASE, PHASE == 0 ? 11 : 10>(hist, key, prefix);
     __syncthreads();
     int *g = gh + (PHASE == 0 ? 0 : 2048 + 1024 * (PHASE - 1));
     for (int i = tid; i < NB; i += kSelectThreads) {
@@ -436,21 +734,18 @@ __global__ void __launch_bounds__(kSelectThreads) select_split_kernel(SplitArgs 
     return;
   }
 
+  // threshold: the digits found; keep-all (state 0): every candidate is above -1; keep-none (state 2)
+  const int thr = state == 0 ? -1 : state == 2 ? 0x7fffffff : (int)prefix;
+  const int need_eq = state == 1 ? k : 0;
   if constexpr (PHASE == 3) {
-    uint32_t thr = 0u;  // keep-all: every candidate has k' > 0
-    if (state == 2) thr = 0xffffffffu;
-    else if (state == 1) thr = prefix;
     int c = 0;
 #pragma unroll
-    for (int j = 0; j < kSplitNV; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) c += (key[j][e] > thr ? 1 : 0) + (key[j][e] == thr ? 0x10000 : 0);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);  // 256 positions a wave: neither half overflows
-    if (lane == 0) s_red[wave] = c;
+    for (int i = 0; i < kSplitKeys; ++i) c += (key[i] > thr ? 1 : 0) + (need_eq && key[i] == thr ? 0x10000 : 0);
+    c = wave_inclusive(c);  // 512 positions a wave, 8192 a slice: neither half overflows
+    if (lane == kWave - 1) s_red[wave] = c;
     __syncthreads();
     if (tid == 0) {
-      int tot = 0;  // 8192 positions a slice: neither half overflows
+      int tot = 0;
       for (int w = 0; w < kSelectThreads / kWave; ++w) tot += s_red[w];
       sa.slice_cnt[(size_t)unit * sa.S + slice] = tot;
     }
@@ -458,13 +753,6 @@ __global__ void __launch_bounds__(kSelectThreads) select_split_kernel(SplitArgs 
   }
 
   if constexpr (PHASE == 4) {
-    uint32_t thr = 0u;  // as in phase 3, from its record
-    int need_eq = 0;
-    if (state == 2) thr = 0xffffffffu;
-    else if (state == 1) {
-      thr = prefix;
-      need_eq = k;
-    }
     int base_gt = 0, base_eq = 0, all_gt = 0, all_eq = 0;
     for (int i = 0; i < sa.S; ++i) {  // same address in every lane: one broadcast load each
       const int c = sa.slice_cnt[(size_t)unit * sa.S + i];
@@ -476,7 +764,8 @@ __global__ void __launch_bounds__(kSelectThreads) select_split_kernel(SplitArgs 
       all_eq += c >> 16;
     }
     int32_t *out = a.idx + (size_t)unit * a.cap;
-    ranked_write<kSplitNV>(key, thr, need_eq, kp, base_gt, base_eq, t_base, out, ranks, tid, lane, wave);
+    emit_keys<kSplitKeys, kSelectThreads>(
+        sh, key, thr, need_eq, kp, base_gt, base_eq, [&](int rank, int slot, int) { out[rank] = base + slot; }, tid, lane, wave);
     if (slice == 0) {
       const int kept = min(all_gt + min(all_eq, need_eq), kp);
       for (int j = tid; j < W; j += kSelectThreads) out[kept + j] = P + j;
@@ -485,166 +774,163 @@ __global__ void __launch_bounds__(kSelectThreads) select_split_kernel(SplitArgs 
   }
 }
 
-size_t select_workspace_bytes(const Shape &s) {
-  // up to 32768 positions the register kernel (one workgroup per unit, one launch) is the faster one
-  if (s.P <= 8 * 4 * kSelectThreads || s.P % 4 != 0) return 0;
-  const size_t units = (size_t)s.Bz * s.Hkv, S = (s.P + kSplitSlice - 1) / kSplitSlice;
-  return units * (kSplitHist + S + 16) * sizeof(int);
-}
-
 // ---------------------------------------------------------------------------------------------
-// Streaming select: any length.
+// Streaming select: any length, nothing kept on chip but counters. Keys come from key_at(i) (-1: no candidate),
+// several at a time, once per 8-bit digit and twice for the ranks; emit(rank, i) for the kept ones.
 // ---------------------------------------------------------------------------------------------
 constexpr int kUnroll = 8;
 
-__global__ void __launch_bounds__(kSelectThreads) select_kernel(SelectArgs a) {
-  __shared__ int hist[256];
-  __shared__ int wave_gt[kSelectThreads / kWave], wave_eq[kSelectThreads / kWave];
-  __shared__ uint32_t s_prefix;
-  __shared__ int s_k, s_state;  // s_state: 0 = keep all candidates, 1 = select, 2 = keep none
-
-  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int P = a.P, W = a.W;
-  const float *u = a.utility + (size_t)unit * P;
-  const float tau = a.tau[unit / a.Hkv];
-  int bud = a.budget[unit];
-  bud = max(W, min(bud, min(a.cap, a.T)));
-  const int kp = bud - W;
-
-  // pass 0: histogram of the top byte over the candidates (also counts them)
-  if (tid < 256) hist[tid] = 0;
-  __syncthreads();
-  // eight loads in flight per thread: the pass is bound by L2 latency, not by arithmetic
-  for (int t0 = 0; t0 < P; t0 += kUnroll * kSelectThreads) {
-    float x[kUnroll];
+template <class Key, class Emit>
+__device__ __forceinline__ int select_stream(int n, int kp, StreamShared &sh, Key key_at, Emit emit, int tid, int lane, int wave) {
+  // digits from the top; the first histogram also counts the candidates
+  int thr = -1;  // keep-all: every candidate's key is above -1
+  int need_eq = 0;
+  int k = max(kp, 1);
+  uint32_t prefix = 0u;
+  for (int shift = 24; shift >= 0; shift -= 8) {
+    if (tid < 256) sh.hist[tid] = 0;
+    __syncthreads();
+    const uint32_t hi_mask = shift == 24 ? 0u : 0xffffffffu << (shift + 8);
+    // eight loads in flight per thread: the pass is bound by L2 latency, not by arithmetic
+    for (int t0 = 0; t0 < n; t0 += kUnroll * kSelectThreads) {
+      int x[kUnroll];
 #pragma unroll
-    for (int e = 0; e < kUnroll; ++e) {
-      const int t = t0 + e * kSelectThreads + tid;
-      x[e] = t < P ? u[t] : -INFINITY;  // never a candidate
+      for (int e = 0; e < kUnroll; ++e) {
+        const int t = t0 + e * kSelectThreads + tid;
+        x[e] = t < n ? key_at(t) : -1;
+      }
+#pragma unroll
+      for (int e = 0; e < kUnroll; ++e)
+        hist_add(sh.hist, x[e] >= 0 && ((uint32_t)x[e] & hi_mask) == prefix, (x[e] >> shift) & 255, lane);
     }
-#pragma unroll
-    for (int e = 0; e < kUnroll; ++e) hist_add(hist, x[e] >= tau, (int)(key_of(x[e]) >> 24), lane);
-  }
-  __syncthreads();
-  if (wave == 0) {
-    const BinResult r = find_bin<256>(hist, max(kp, 1), lane);
-    if (lane == 0) {
-      if (r.total <= kp) s_state = 0;
-      else if (kp == 0) s_state = 2;
-      else {
-        s_state = 1;
-        s_prefix = (uint32_t)r.bin << 24;
-        s_k = kp - r.above;  // still needed from inside the chosen bin
+    __syncthreads();
+    if (wave == 0) {
+      const BinResult r = find_bin<256>(sh.hist, k, lane);
+      if (lane == 0) {
+        if (shift == 24) sh.state = r.total <= kp ? 0 : kp == 0 ? 2 : 1;
+        sh.prefix = prefix | ((uint32_t)max(r.bin, 0) << shift);
+        sh.k = k - r.above;
       }
     }
+    __syncthreads();
+    if (sh.state != 1) break;
+    prefix = sh.prefix;
+    k = sh.k;
+    thr = (int)prefix;
+    need_eq = k;  // how many keys equal to thr are kept (>= 1)
   }
-  __syncthreads();
-  const int state = s_state;
+  if (sh.state == 2) thr = 0x7fffffff;
 
-  uint32_t thr = 0u;   // keep-all: every candidate has key > 0 or ties at 0 with unlimited quota
-  int need_eq = 0x7fffffff;
-  if (state == 2) {
-    thr = 0xffffffffu;
-    need_eq = 0;
-  } else if (state == 1) {
-    for (int shift = 16; shift >= 0; shift -= 8) {
-      const uint32_t prefix = s_prefix;
-      const int k = s_k;
-      if (tid < 256) hist[tid] = 0;
-      __syncthreads();
-      const uint32_t hi_mask = 0xffffffffu << (shift + 8);
-      for (int t0 = 0; t0 < P; t0 += kUnroll * kSelectThreads) {
-        float x[kUnroll];
-#pragma unroll
-        for (int e = 0; e < kUnroll; ++e) {
-          const int t = t0 + e * kSelectThreads + tid;
-          x[e] = t < P ? u[t] : -INFINITY;
-        }
-#pragma unroll
-        for (int e = 0; e < kUnroll; ++e) {
-          const uint32_t key = key_of(x[e]);
-          hist_add(hist, x[e] >= tau && (key & hi_mask) == prefix, (int)((key >> shift) & 255u), lane);
-        }
-      }
-      __syncthreads();
-      if (wave == 0) {
-        const BinResult r = find_bin<256>(hist, k, lane);
-        if (lane == 0) {
-          s_prefix = prefix | ((uint32_t)r.bin << shift);
-          s_k = k - r.above;
-        }
-      }
-      __syncthreads();
-    }
-    thr = s_prefix;
-    need_eq = s_k;  // how many keys equal to thr are kept (>= 1)
-  }
-
-  // Final pass. Wave w owns positions [w*seg, (w+1)*seg); seg is a multiple of 64.
+  // ranks: wave w owns keys [w * seg, (w + 1) * seg); seg is a multiple of 64
   const int n_waves = kSelectThreads / kWave;
-  const int seg = ((P + n_waves - 1) / n_waves + kWave - 1) / kWave * kWave;
-  const int lo = wave * seg, hi = min(lo + seg, P);
+  const int seg = ((n + n_waves - 1) / n_waves + kWave - 1) / kWave * kWave;
+  const int lo = wave * seg, hi = min(lo + seg, n);
   int n_gt = 0, n_eq = 0;
   for (int t0 = lo; t0 < hi; t0 += kUnroll * kWave) {
-    float x[kUnroll];
+    int x[kUnroll];
 #pragma unroll
     for (int e = 0; e < kUnroll; ++e) {
       const int t = t0 + e * kWave + lane;
-      x[e] = t < hi ? u[t] : -INFINITY;
+      x[e] = t < hi ? key_at(t) : -1;
     }
 #pragma unroll
     for (int e = 0; e < kUnroll; ++e) {
-      const uint32_t key = key_of(x[e]);
-      const bool cand = x[e] >= tau;
-      n_gt += __popcll(__ballot(cand && key > thr));
-      n_eq += __popcll(__ballot(cand && key == thr));
+      n_gt += __popcll(__ballot(x[e] > thr));
+      n_eq += __popcll(__ballot(need_eq && x[e] == thr));
     }
   }
   if (lane == 0) {
-    wave_gt[wave] = n_gt;
-    wave_eq[wave] = n_eq;
+    sh.wave_gt[wave] = n_gt;
+    sh.wave_eq[wave] = n_eq;
   }
   __syncthreads();
-  int base_gt = 0, base_eq = 0;
-  for (int w = 0; w < wave; ++w) {
-    base_gt += wave_gt[w];
-    base_eq += wave_eq[w];
+  int base_gt = 0, base_eq = 0, tot_gt = 0, tot_eq = 0;
+  for (int w = 0; w < n_waves; ++w) {
+    base_gt += w < wave ? sh.wave_gt[w] : 0;
+    base_eq += w < wave ? sh.wave_eq[w] : 0;
+    tot_gt += sh.wave_gt[w];
+    tot_eq += sh.wave_eq[w];
   }
-  int32_t *out = a.idx + (size_t)unit * a.cap;
-  const unsigned long long below = (1ull << lane) - 1ull;
   for (int t0 = lo; t0 < hi; t0 += kUnroll * kWave) {
-    float x[kUnroll];
+    int x[kUnroll];
 #pragma unroll
     for (int e = 0; e < kUnroll; ++e) {
       const int t = t0 + e * kWave + lane;
-      x[e] = t < hi ? u[t] : -INFINITY;
+      x[e] = t < hi ? key_at(t) : -1;
     }
 #pragma unroll
     for (int e = 0; e < kUnroll; ++e) {
-      const uint32_t key = key_of(x[e]);
-      const bool cand = x[e] >= tau;
-      const bool gt = cand && key > thr, eq = cand && key == thr;
+      const bool gt = x[e] > thr, eq = need_eq && x[e] == thr;
       const unsigned long long bg = __ballot(gt), be = __ballot(eq);
-      const int gt_before = base_gt + __popcll(bg & below);
-      const int eq_before = base_eq + __popcll(be & below);
+      const int gt_before = (int)lanes_below(bg, (uint32_t)base_gt), eq_before = (int)lanes_below(be, (uint32_t)base_eq);
       if (gt || (eq && eq_before < need_eq)) {
         const int pos = gt_before + min(eq_before, need_eq);
-        if (pos < kp) out[pos] = t0 + e * kWave + lane;
+        if (pos < kp) emit(pos, t0 + e * kWave + lane);
       }
       base_gt += __popcll(bg);
       base_eq += __popcll(be);
     }
   }
-  // kept prefix tokens, then the window
-  __syncthreads();
-  int tot_gt = 0, tot_eq = 0;
-  for (int w = 0; w < n_waves; ++w) {
-    tot_gt += wave_gt[w];
-    tot_eq += wave_eq[w];
-  }
-  const int kept = min(tot_gt + min(tot_eq, need_eq), kp);
-  for (int j = tid; j < W; j += kSelectThreads) out[kept + j] = P + j;
-  if (tid == 0) a.count[unit] = kept + W;
+  return min(tot_gt + min(tot_eq, need_eq), kp);
+}
+
+__global__ void __launch_bounds__(kSelectThreads) select_kernel(SelectArgs a) {
+  __shared__ StreamShared sh;
+  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float *u = a.utility + (size_t)unit * a.P;
+  const float tau = a.tau[unit / a.Hkv];
+  const int kp = prefix_quota(a, unit);
+  int32_t *out = a.idx + (size_t)unit * a.cap;
+  const int kept = select_stream(
+      a.P, kp, sh,
+      [&](int t) { return key_of(u[t], tau); },
+      [&](int rank, int t) { out[rank] = t; }, tid, lane, wave);
+  for (int j = tid; j < a.W; j += kSelectThreads) out[kept + j] = a.P + j;
+  if (tid == 0) a.count[unit] = kept + a.W;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Which kernel
+// ---------------------------------------------------------------------------------------------
+// Up to 32768 positions one workgroup per unit in one launch is the faster form, and no workspace is touched
+// (callers need not pass one).
+constexpr int kOneLaunch = 32 * kSelectThreads;
+static int slices(const Shape &s, int size) { return (s.P + size - 1) / size; }
+// Most positions of a slice: 8192 where the merge then has at most 8192 pairs per unit (by the nominal budget and a
+// quarter, for heads with more than their share), which it takes eight to a thread; else 16384, which halves the
+// pairs.
+// Trace, slices + merge: 128k, W = 64, max pooling, budget 512: 11.9 + 16.8 us with 8192, 13.4 + 10.8 with 16384.
+static int slice_limit(const Shape &s, int budget) {
+  const int half = 8 * kSelectThreads, quota = max(0, budget - s.W);
+  return (int64_t)slices(s, half) * min(half, quota + quota / 4) <= 8 * kSelectThreads ? half : 2 * half;
+}
+// Slices of equal length: a short last one would keep all it has.
+static int slice_length(const Shape &s, int limit) {
+  const int n = slices(s, limit);
+  return ((s.P + n - 1) / n + kWave - 1) / kWave * kWave;
+}
+static int slice_region(const Shape &s, int cap, int limit) {
+  return (max(1, min(limit, min(cap, s.T) - s.W)) + kWave - 1) / kWave * kWave;
+}
+// Slices pay where they drop most keys and neither kernel leaves the list (by the nominal budget, so with room for
+// heads that have more than their share). Slices + merge against the split selection, us, 32 units: 128k positions, budget
+// 512: 17.0 / 41.1, 1024: 19.5 / 41.7, 2048: 24.7 / 41.7, 4096: 54.0 / 42.1; 64k, 1024: 18.0 / 28.0, 4096: 49.8 / 28.3.
+static bool slices_pay(const Shape &s, int budget) {
+  const int limit = slice_limit(s, budget);
+  return budget - s.W <= 3072 && (int64_t)slices(s, limit) * max(0, min(limit, budget - s.W)) <= 32768;
+}
+
+size_t select_workspace_bytes(const ckv_params *p, const Shape &s) {
+  if (s.P <= kOneLaunch) return 0;
+  const size_t units = (size_t)s.Bz * s.Hkv;
+  const int limit = slice_limit(s, p->budget_per_kv_head);
+  if (slices_pay(s, p->budget_per_kv_head)) return units * slices(s, limit) * slice_region(s, p->cap, limit) * sizeof(int2);
+  return units * (kSplitHist + slices(s, kSplitSlice) + 16) * sizeof(int);
+}
+
+template <int NK, int NT>
+static void launch_reg(const SelectArgs &a, int units, hipStream_t stream) {
+  hipLaunchKernelGGL((select_reg_kernel<NK, NT>), dim3(units), dim3(NT), 0, stream, a);
 }
 
 hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utility,
@@ -658,19 +944,28 @@ hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utili
   a.count = count;
   a.Hkv = s.Hkv; a.T = s.T; a.W = s.W; a.P = s.P;
   a.cap = p->cap;
-  const dim3 grid(s.Bz * s.Hkv), block(kSelectThreads);
-  const int vectors = (s.P + 4 * kSelectThreads - 1) / (4 * kSelectThreads);  // 128-bit loads per thread
-  const bool aligned = s.P % 4 == 0 && (uintptr_t)utility % 16 == 0 && s.P > 0;
-  const bool split = aligned && ws && select_workspace_bytes(s) > 0;
-  if (split) {
+  const int units = s.Bz * s.Hkv;
+  const dim3 block(kSelectThreads);
+  if (ws && s.P > kOneLaunch && slices_pay(s, p->budget_per_kv_head)) {
+    SliceArgs sa;
+    sa.a = a;
+    const int limit = slice_limit(s, p->budget_per_kv_head);
+    sa.S = slices(s, limit);
+    sa.slice = slice_length(s, limit);
+    sa.region = slice_region(s, p->cap, limit);
+    sa.pairs = reinterpret_cast<int2 *>(ws);
+    const dim3 slice_grid((unsigned)(units * sa.S));
+    if (limit == 8 * kSelectThreads) hipLaunchKernelGGL(select_slice_kernel<8>, slice_grid, block, 0, stream, sa);
+    else hipLaunchKernelGGL(select_slice_kernel<16>, slice_grid, block, 0, stream, sa);
+    hipLaunchKernelGGL(select_merge_kernel, dim3(units), block, 0, stream, sa);
+  } else if (ws && s.P > kOneLaunch) {
     SplitArgs sa;
     sa.a = a;
-    sa.S = (s.P + kSplitSlice - 1) / kSplitSlice;
-    const size_t units = (size_t)s.Bz * s.Hkv;
+    sa.S = slices(s, kSplitSlice);
     sa.hist = reinterpret_cast<int *>(ws);
-    sa.slice_cnt = sa.hist + units * kSplitHist;
-    sa.thr = sa.slice_cnt + units * sa.S;
-    const int n_zero = (int)(units * kSplitHist);
+    sa.slice_cnt = sa.hist + (size_t)units * kSplitHist;
+    sa.thr = sa.slice_cnt + (size_t)units * sa.S;
+    const int n_zero = units * kSplitHist;
     const dim3 split_grid((unsigned)(units * sa.S));
     hipLaunchKernelGGL(select_split_zero_kernel, dim3((n_zero + kSelectThreads - 1) / kSelectThreads), block, 0,
                        stream, sa.hist, n_zero);
@@ -679,12 +974,13 @@ hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utili
     hipLaunchKernelGGL(select_split_kernel<2>, split_grid, block, 0, stream, sa);
     hipLaunchKernelGGL(select_split_kernel<3>, split_grid, block, 0, stream, sa);
     hipLaunchKernelGGL(select_split_kernel<4>, split_grid, block, 0, stream, sa);
-  } else if (aligned && vectors <= 1) hipLaunchKernelGGL(select_reg_kernel<1>, grid, block, 0, stream, a);
-  else if (aligned && vectors <= 2) hipLaunchKernelGGL(select_reg_kernel<2>, grid, block, 0, stream, a);
-  else if (aligned && vectors <= 4) hipLaunchKernelGGL(select_reg_kernel<4>, grid, block, 0, stream, a);
-  else if (aligned && vectors <= 8) hipLaunchKernelGGL(select_reg_kernel<8>, grid, block, 0, stream, a);
-  else if (aligned && vectors <= 16) hipLaunchKernelGGL(select_reg_kernel<16>, grid, block, 0, stream, a);
-  else hipLaunchKernelGGL(select_kernel, grid, block, 0, stream, a);
+  } else if (s.P <= 4 * 256) launch_reg<4, 256>(a, units, stream);
+  else if (s.P <= 8 * 512) launch_reg<8, 512>(a, units, stream);
+  else if (s.P <= 8 * kSelectThreads) launch_reg<8, kSelectThreads>(a, units, stream);
+  else if (s.P <= 16 * kSelectThreads) launch_reg<16, kSelectThreads>(a, units, stream);
+  else if (s.P <= 32 * kSelectThreads) launch_reg<32, kSelectThreads>(a, units, stream);
+  else if (s.P <= 64 * kSelectThreads) launch_reg<64, kSelectThreads>(a, units, stream);
+  else hipLaunchKernelGGL(select_kernel, dim3(units), block, 0, stream, a);
   return hipGetLastError();
 }
 

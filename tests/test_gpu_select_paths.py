@@ -1,0 +1,54 @@
+"""Selection at the sizes where its kernels change: positions per thread, one launch against slices and merge, quotas at the
+list's capacity, rows that start at any multiple of four bytes; values with ties, outliers and few candidates. Exact
+against the oracle: the result is unique."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2602_08686_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+SIZES = (1, 63, 1024, 1025, 4096, 4097, 8192, 8193, 16384, 16385, 32768, 32769, 49157, 65536, 65537, 131071)
+QUOTAS = (0, 1, 63, 512, 513, 3072, 3584, 3585)
+
+
+def _values(rng, kind, shape):
+    if kind == "ties":
+        return rng.choice(np.linspace(0.0, 2.0, 9).astype(np.float32), size=shape)
+    if kind == "outliers":
+        u = np.exp(0.5 * rng.standard_normal(shape))
+        u[..., : min(3, shape[-1])] *= 1e4
+        return u.astype(np.float32)
+    return (1.0 + 0.08 * np.abs(rng.standard_normal(shape))).astype(np.float32)   # pooled masses: all close together
+
+
+@pytest.mark.parametrize("workspace", [False, True], ids=["plain", "workspace"])
+@pytest.mark.parametrize("kind", ["close", "ties", "outliers"])
+@pytest.mark.parametrize("P", SIZES)
+def test_select_matches_oracle_at_the_borders(P, kind, workspace):
+    print(f"case P={P} {kind} workspace={workspace}", flush=True)
+    rng = np.random.default_rng(P + len(kind))
+    W, Hkv, T = 4, 2, P + 4
+    u = _values(rng, kind, (1, Hkv, P))
+    flat = torch.empty(u.size + 1, device=DEV)
+    ut = flat[1:].view(u.shape)       # one float past an aligned address
+    ut.copy_(torch.from_numpy(u))
+    for quota in sorted({min(q, P) for q in QUOTAS}):
+        for tau in (0.0, 1.3):
+            cap = W + quota
+            # one head at its nominal budget, one at the smallest: the other way round beside it
+            budget = np.array([[W + quota, W + min(quota, 1)]], np.int32)
+            p = B.make_params(batch=1, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=T, window=W, dtype="bf16",
+                              pool=B.POOL_NONE, pool_kernel=1, budget=W + quota // 2, cap=cap)
+            ws = None
+            if workspace:   # contents on entry are ignored: ones
+                ws = torch.full((max(256, B.ckv_workspace_bytes(p)),), 255, dtype=torch.uint8, device=DEV)
+            idx = torch.full((1, Hkv, cap), -1, dtype=torch.int32, device=DEV)
+            count = torch.empty(1, Hkv, dtype=torch.int32, device=DEV)
+            B.ckv_select_topk(p, ut, torch.from_numpy(budget).to(DEV), torch.full((1,), tau, device=DEV), idx, count, ws)
+            torch.cuda.synchronize()
+            oi, oc = oracle.select(u, np.array([tau], np.float32), budget, W, cap)
+            np.testing.assert_array_equal(count.cpu().numpy(), oc)
+            np.testing.assert_array_equal(idx.cpu().numpy(), oi)
