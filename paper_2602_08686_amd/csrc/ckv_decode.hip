@@ -3,15 +3,25 @@
 // attention row is the full row restricted to S and renormalised (p~ of the Proposition), and the mass
 // the full row had outside S is m = 1 - exp(lse_S - lse_full).
 //
-// decode_partial_kernel: attention of one decoding query per (batch, query head) over a ragged KV set
-// (the first count[b,g] rows of each (batch, KV head)), the query heads of a GQA group sharing each K/V
-// row they read. HBM-bound (every valid K and V row once, 2 * rows * d * e bytes per unit); the
-// arithmetic is 4 * G * d flops per row pair, far below the vector rate needed to keep up, so the
-// products run on the vector ALUs in fp32 -- with one to eight query rows per K row there is no
-// matrix-core tile to fill. A 16-byte piece of a row per lane (d * e / 16 lanes per row, several rows
-// per wave step, whole rows coalesced), four row steps in flight, online softmax in the log2 domain;
-// the key axis is cut into chunks over workgroups and decode_merge_kernel combines the partial
-// (max, sum, weighted V) triples in a fixed order (bit-stable).
+// Attention of decoding queries over a ragged KV set (the first count[b,g] rows of each (batch, KV head)). HBM-bound:
+// every valid K and V row once, 2 * rows * d * e bytes per unit.
+//
+// bf16 (decode_mfma_kernel): both products on the matrix cores. All decoding queries of a KV head, G * n_q of them, are
+// the columns of one 16-wide tile, so a row is read once for all heads and queries, and the cost of a
+// row does not grow with them (on the vector ALUs four heads take ~110 instructions per four rows and
+// hold the sweep at 5 TB/s; here 32 rows take ~130 instructions and 32 MFMAs). Keys x queries leaves a lane with
+// the logits of eight keys of one query, which is the operand layout of the second product; the rows
+// of V come with whole rows per load and are transposed in registers (32 byte permutes per 32 rows). The
+// weights enter it as three bf16 terms that add up to the fp32 value exactly. A wave takes 32 rows at a time and
+// asks for the next 32 as soon as the registers of the current ones are free. Waves are combined in LDS in wave
+// order, chunks by decode_merge_kernel in chunk order (bit-stable).
+// Measured, us per call, before (vector ALUs, a sweep per query and two to eight heads) -> now: batch 4, 32/8 heads, 32k rows
+// 118.0 -> 86.1 (6.2 TB/s); 544 rows, batch 16: 13.6 -> 10.0; 20000 rows, batch 8, 32/4 heads, two queries 372 -> 60.
+// RMS error against 64 bits 2.7e-7 -> 2.0e-7 on the first of them. Not faster: both blocks of two in registers at once
+// (85.2, and 11.2 on 544 rows).
+//
+// f32 (decode_partial_kernel): dot products on the vector ALUs, a 16-byte piece of a row per lane, online softmax in the
+// log2 domain, the query heads of a group sharing each row.
 #include "ckv_internal.h"
 
 namespace ckv {
@@ -25,6 +35,7 @@ struct DecodeArgs {
   float *out;            // [Bz][Hq][n_q][d]
   float *lse;            // [Bz][Hq][n_q] natural log
   int Hq, Hkv, G, n_q, n_rows, rows_per_chunk, n_chunks, head_chunks;
+  int cols, col_chunks;  // bf16: query columns per KV head (G * n_q) and 16-column tiles of them
   float scale2;          // softmax scale * log2(e)
 };
 
@@ -32,40 +43,23 @@ constexpr int kXcds = 8;  // accelerator dies of the part; workgroup i of a laun
 constexpr int kDecodeThreads = 256;
 constexpr int kDecodeWaves = kDecodeThreads / kWave;
 
-template <int DT>
-struct Piece;  // a 16-byte piece of a row as floats
-template <>
-struct Piece<CKV_BF16> {
-  static constexpr int E = 8;
-  __device__ static __forceinline__ void to_float(const uint4 &raw, float (&f)[8]) {
-    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f[2 * i] = __uint_as_float(w[i] << 16);
-      f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-};
-template <>
-struct Piece<CKV_F32> {
-  static constexpr int E = 4;
-  __device__ static __forceinline__ void to_float(const uint4 &raw, float (&f)[4]) {
-    f[0] = __uint_as_float(raw.x);
-    f[1] = __uint_as_float(raw.y);
-    f[2] = __uint_as_float(raw.z);
-    f[3] = __uint_as_float(raw.w);
-  }
-};
+// A 16-byte piece of an f32 row.
+constexpr int kPiece = 4;
+__device__ __forceinline__ void piece_to_float(const uint4 &raw, float (&f)[kPiece]) {
+  f[0] = __uint_as_float(raw.x);
+  f[1] = __uint_as_float(raw.y);
+  f[2] = __uint_as_float(raw.z);
+  f[3] = __uint_as_float(raw.w);
+}
 
 // exp2(a - b) with the conventions of an online softmax: a = -inf gives 0 also when b was reset to 0
 __device__ __forceinline__ float exp2_diff(float a, float b) { return exp2f(a - b); }
 
 // NW waves per workgroup, U row steps whose loads are in flight together (PIPE: of the next block too). With one chunk per
 // (unit, query) the workgroup writes the final result itself and no merge kernel follows.
-template <int DT, int DH, int RQ, int NW, int U, bool PIPE>
+template <int DH, int RQ, int NW, int U, bool PIPE>
 __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a) {
-  constexpr int E = Piece<DT>::E;
-  constexpr int ESIZE = 16 / E;
+  constexpr int E = kPiece, ESIZE = 4;
   constexpr int LPR = DH / E;        // lanes per row
   constexpr int KPW = kWave / LPR;   // rows per wave step
   constexpr int ROW = DH + 2;
@@ -106,7 +100,7 @@ __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a)
       const size_t row = ((size_t)b * a.Hq + (size_t)g * a.G + hg) * a.n_q + qi;
       raw = *reinterpret_cast<const uint4 *>(static_cast<const char *>(a.q) + (row * DH + sub * E) * ESIZE);
     }
-    Piece<DT>::to_float(raw, qv[r]);
+    piece_to_float(raw, qv[r]);
 #pragma unroll
     for (int e = 0; e < E; ++e) qv[r][e] *= a.scale2;
   }
@@ -147,8 +141,8 @@ __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float kf[E];
-      Piece<DT>::to_float(kraw[u], kf);
-      Piece<DT>::to_float(vraw[u], vf[u]);
+      piece_to_float(kraw[u], kf);
+      piece_to_float(vraw[u], vf[u]);
       const bool ok = base + u * KPW + slot < r1;
 #pragma unroll
       for (int r = 0; r < RQ; ++r) {
@@ -263,56 +257,295 @@ __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a)
   }
 }
 
-constexpr int kMergeBatch = 16;  // chunks whose partials are loaded together
+// ---------------------------------------------------------------------------------------------
+// bf16: matrix cores
+// ---------------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_d;
+typedef __attribute__((ext_vector_type(4))) float f32x4_dec;
+constexpr int kCols = 16;       // query columns of a tile
+constexpr int kBlockRows = 32;  // rows a wave takes at a time
 
-template <int DH, int RQ>
-__global__ void __launch_bounds__(kDecodeThreads) decode_merge_kernel(DecodeArgs a) {
-  constexpr int ROW = DH + 2;
-  int y = blockIdx.x;
-  const int hc = y % a.head_chunks;
-  y /= a.head_chunks;
-  const int qi = y % a.n_q, unit = y / a.n_q;
+__device__ __forceinline__ void mma16(f32x4_dec &acc, const u32x4_d &x, const u32x4_d &y) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_d, x), __builtin_bit_cast(bf16x8_d, y), acc, 0, 0, 0);
+}
+// Largest value / sum over the four lanes that hold one query column (lane, lane ^ 16, lane ^ 32, lane ^ 48).
+template <class Op>
+__device__ __forceinline__ float over_quarters(float x, Op op) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+// High halves of two words side by side (x below y): two truncated bf16 of an operand.
+__device__ __forceinline__ uint32_t high_halves(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302); }
+__device__ __forceinline__ uint32_t low_halves(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100); }
+
+// SPLIT: workgroups that share a unit's columns, each with all of K and a SPLIT-th of V's components. One CU takes in about
+// 60 GB/s; where units are fewer than CUs this is how more of them read (8 units of 4096 rows, four heads each: 40.6
+// us with one, 34.5 with four).
+template <int DH, int SPLIT, int NW, bool STREAM>
+__global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a) {
+  constexpr int STEPS = DH / 32;     // MFMAs per 16 keys
+  constexpr int DV = DH / SPLIT;     // components of V
+  constexpr int VE = DV / 16;        // elements of a V row per lane: 8, 4 or 2
+  constexpr int VW = VE / 2;         // words of them
+  constexpr int ROW = DV + 2;
+  __shared__ float sm[NW][kCols][ROW];
+  const int chunk = blockIdx.x;
+  int y = blockIdx.y;
+  // Workgroups that read the same rows (the column tiles and splits of a unit) onto one XCD, whose L2 then serves all but the
+  // first: consecutive workgroups go to different XCDs, so within groups of 8 x sharers the index is transposed.
+  const int sharers = a.col_chunks * SPLIT;
+  if (gridDim.x == 1 && sharers > 1) {
+    const int span = kXcds * sharers, base = y / span * span;
+    if (base + span <= (int)gridDim.y) {
+      const int j = y - base;
+      y = base + (j % kXcds) * sharers + j / kXcds;
+    }
+  }
+  const int split = y % SPLIT;
+  y /= SPLIT;
+  const int cc = y % a.col_chunks, unit = y / a.col_chunks;
   const int b = unit / a.Hkv, g = unit % a.Hkv;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), m = lane & 15, quarter = lane >> 4;
+  const int r0 = chunk * a.rows_per_chunk, r_end = min(r0 + a.rows_per_chunk, a.n_rows), base0 = r0 + wave * kBlockRows;
+  const int n_cols = min(kCols, a.cols - cc * kCols);  // columns of this tile that exist
+  const size_t q_row = ((size_t)b * a.Hq + (size_t)g * a.G) * a.n_q + cc * kCols;  // first of them in q, out and lse
+  const bool single = a.n_chunks == 1;
+
+  u32x4_d qf[STEPS];  // lane (m, quarter): column m, the 16-byte pieces 4 * step + quarter of its row
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) {
+    qf[s] = u32x4_d{0u, 0u, 0u, 0u};
+    if (m < n_cols)
+      qf[s] = *reinterpret_cast<const u32x4_d *>(static_cast<const char *>(a.q) + ((q_row + m) * DH + (4 * s + quarter) * 8) * 2);
+  }
+  const char *kb = static_cast<const char *>(a.k) + ((size_t)b * a.ks[0] + (size_t)g * a.ks[1]) * 2 + quarter * 16;
+  const char *vb = static_cast<const char *>(a.v) + ((size_t)b * a.vs[0] + (size_t)g * a.vs[1]) * 2 + (split * DV + m * VE) * 2;
+  const int64_t ks = a.ks[2] * 2, vs = a.vs[2] * 2;  // bytes per row
+
+  // K: key row 16 t + m of the block, as the query pieces. V: the rows whose logits the lane will hold,
+  // j -> 16 (j / 4) + 4 quarter + j % 4, piece m. Rows at and beyond `end` are not read.
+  u32x4_d kraw[2][STEPS];
+  uint32_t vraw[8][VW];
+  auto load_k = [&](int base, int end) {
+    const bool whole = base + kBlockRows <= end;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int row = base + 16 * t + m;
+      const char *p = kb + (int64_t)row * ks;
+#pragma unroll
+      for (int s = 0; s < STEPS; ++s) {
+        if (!whole) kraw[t][s] = u32x4_d{0u, 0u, 0u, 0u};
+        if (whole || row < end) {
+          if (STREAM) kraw[t][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_d *>(p + s * 64));
+          else kraw[t][s] = *reinterpret_cast<const u32x4_d *>(p + s * 64);
+        }
+      }
+    }
+  };
+  typedef __attribute__((ext_vector_type(VW))) uint32_t piece_v;
+  auto load_v = [&](int base, int end) {
+    const bool whole = base + kBlockRows <= end;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int row = base + 16 * (j / 4) + 4 * quarter + j % 4;
+      piece_v v;
+#pragma unroll
+      for (int w = 0; w < VW; ++w) v[w] = 0u;
+      if (whole || row < end) {
+        const piece_v *p = reinterpret_cast<const piece_v *>(vb + (int64_t)row * vs);
+        if (STREAM) v = __builtin_nontemporal_load(p);
+        else v = *p;
+      }
+#pragma unroll
+      for (int w = 0; w < VW; ++w) vraw[j][w] = v[w];
+    }
+  };
+
+  // the first block is asked for before the count is known (the rows exist; what lies beyond the count is masked below)
+  if (base0 < r_end) {
+    load_k(base0, r_end);
+    load_v(base0, r_end);
+  }
+  int n_valid = a.n_rows;
+  if (a.count) n_valid = min(max(a.count[unit], 0), a.n_rows);
+  const int r1 = min(r_end, n_valid);
+  if (r0 >= r1 && !single) return;  // the merge reads the chunks below n_valid only
+
+  float top = -INFINITY, sum = 0.0f;  // of column m: the running maximum (the wave's), this lane's share of the sum
+  f32x4_dec acc[VE];                  // element e: D[4 quarter + r][column m] = component VE (4 quarter + r) + e
+#pragma unroll
+  for (int e = 0; e < VE; ++e) acc[e] = f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int base = base0; base < r1; base += NW * kBlockRows) {
+    const int next = base + NW * kBlockRows;
+    f32x4_dec s2[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {  // two chains per tile: half the truncated additions
+      f32x4_dec half[2] = {f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f}, f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+      for (int s = 0; s < STEPS; ++s) mma16(half[s & 1], kraw[t][s], qf[s]);
+      s2[t] = half[0] + half[1];
+    }
+    if (next < r1) load_k(next, r1);
+    float z[8];  // logits (log2 domain) of rows 16 (j / 4) + 4 quarter + j % 4
+#pragma unroll
+    for (int j = 0; j < 8; ++j) z[j] = s2[j / 4][j % 4] * a.scale2;
+    if (base + kBlockRows > r1) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (base + 16 * (j / 4) + 4 * quarter + j % 4 >= r1) {
+          z[j] = -INFINITY;
+#pragma unroll
+          for (int w = 0; w < VW; ++w) vraw[j][w] = 0u;  // weight 0 times whatever is there must be 0
+        }
+    }
+    float mx = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
+    mx = over_quarters(mx, [](float p, float q) { return fmaxf(p, q); });
+    if (__any(mx > top)) {  // after the first blocks a new maximum is rare
+      const float t_new = fmaxf(top, mx);
+      const float keep = exp2_diff(top, t_new == -INFINITY ? 0.0f : t_new);
+      sum *= keep;
+#pragma unroll
+      for (int e = 0; e < VE; ++e) acc[e] *= keep;
+      top = t_new;
+    }
+    const float ref = top == -INFINITY ? 0.0f : top;
+    // weights, and their three bf16 terms: truncations, each of what the ones before left
+    u32x4_d w1, w2, w3;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      uint32_t t1[2], t2[2], t3[2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const float p = __builtin_amdgcn_exp2f(z[2 * h + x] - ref);
+        sum += p;
+        t1[x] = __float_as_uint(p);
+        const float r = p - __uint_as_float(t1[x] & 0xffff0000u);
+        t2[x] = __float_as_uint(r);
+        t3[x] = __float_as_uint(r - __uint_as_float(t2[x] & 0xffff0000u));
+      }
+      w1[h] = high_halves(t1[0], t1[1]);
+      w2[h] = high_halves(t2[0], t2[1]);
+      w3[h] = high_halves(t3[0], t3[1]);
+    }
+    u32x4_d vt[VE];  // V transposed: component e of the lane's piece, its eight rows
+#pragma unroll
+    for (int e = 0; e < VE; ++e)
+#pragma unroll
+      for (int h = 0; h < 4; ++h)
+        vt[e][h] = e % 2 ? high_halves(vraw[2 * h][e / 2], vraw[2 * h + 1][e / 2]) : low_halves(vraw[2 * h][e / 2], vraw[2 * h + 1][e / 2]);
+    if (next < r1) load_v(next, r1);
+    // the block's sum by itself, then one rounded addition: the matrix cores truncate what they add to an accumulator
+    // that is larger than the products, and over a long sweep that adds up (7e-7 instead of 3e-7 after 8192 rows)
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+      f32x4_dec head = {0.0f, 0.0f, 0.0f, 0.0f}, rest = head;
+      mma16(head, vt[e], w1);
+      mma16(rest, vt[e], w3);
+      mma16(rest, vt[e], w2);
+      acc[e] += head + rest;
+    }
+  }
+  sum = over_quarters(sum, [](float p, float q) { return p + q; });
+
+  if (m < n_cols) {
+    float *to = sm[wave][m];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int e = 0; e < VE; ++e) to[VE * (4 * quarter + r) + e] = acc[e][r];
+    if (quarter == 0) {
+      to[DV] = top;
+      to[DV + 1] = sum;
+    }
+  }
+  __syncthreads();
+  // the waves, in wave order (more than one chunk: SPLIT is 1)
+  float *part = single ? nullptr : a.part + (((size_t)blockIdx.y * a.n_chunks + chunk) * kCols) * ROW;
+  for (int i = threadIdx.x; i < n_cols * DV; i += NW * kWave) {
+    const int c = i / DV, x = i % DV;
+    float mx = sm[0][c][DV];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mx = fmaxf(mx, sm[w][c][DV]);
+    const float ref = mx == -INFINITY ? 0.0f : mx;
+    float num = 0.0f, den = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float *from = sm[w][c];
+      const float f = exp2_diff(from[DV], ref);
+      num = fmaf(from[x], f, num);
+      den = fmaf(from[DV + 1], f, den);
+    }
+    if (single) {
+      a.out[(q_row + c) * DH + split * DV + x] = den > 0.0f ? num / den : 0.0f;
+      if (x == 0 && split == 0) a.lse[q_row + c] = den > 0.0f ? (mx + log2f(den)) * kLn2 : -INFINITY;
+    } else {
+      part[c * ROW + x] = num;
+      if (x == 0) {
+        part[c * ROW + DV] = mx;
+        part[c * ROW + DV + 1] = den;
+      }
+    }
+  }
+}
+
+// Chunks of one (unit, query row): a lane per chunk for the maximum and the weights, a thread per component for the
+// sum, its loads independent. One workgroup per query row (the first form, one per unit, kept 32 workgroups of the
+// chip busy for 16.7 us on the 32k / batch-4 cache).
+// FLAT: partials of the bf16 kernel, [(unit, column tile)][chunk][16][d + 2]; else [(unit, query, head chunk)][chunk][RQ][d + 2].
+constexpr int kMaxChunks = 64;
+template <int DH, int RQ, bool FLAT>
+__global__ void __launch_bounds__(DH) decode_merge_kernel(DecodeArgs a) {
+  constexpr int ROW = DH + 2;
+  __shared__ float s_weight[kMaxChunks];
+  __shared__ float s_top, s_den;
+  const int row = blockIdx.x;  // of [Bz][Hq][n_q]
+  const int head = row / a.n_q, qi = row % a.n_q, b = head / a.Hq, h = head % a.Hq, g = h / a.G, hg = h % a.G;
+  const int unit = b * a.Hkv + g;
+  size_t first;  // partial row of chunk 0
+  if (FLAT) {
+    const int c = hg * a.n_q + qi;
+    first = ((size_t)unit * a.col_chunks + c / kCols) * a.n_chunks * kCols + c % kCols;
+  } else {
+    first = (((size_t)unit * a.n_q + qi) * a.head_chunks + hg / RQ) * a.n_chunks * RQ + hg % RQ;
+  }
+  constexpr int STRIDE = (FLAT ? kCols : RQ) * ROW;
+  const float *part = a.part + first * ROW;
   int n_valid = a.n_rows;
   if (a.count) n_valid = min(max(a.count[unit], 0), a.n_rows);
   const int n_chunks = (n_valid + a.rows_per_chunk - 1) / a.rows_per_chunk;  // the chunks that were written
-  const float *part = a.part + (size_t)blockIdx.x * a.n_chunks * RQ * ROW;
-  for (int i = threadIdx.x; i < RQ * DH; i += kDecodeThreads) {
-    const int r = i / DH, c = i % DH;
-    const int hg = hc * RQ + r;
-    if (hg >= a.G) continue;
-    // online merge in chunk order, a batch of independent loads at a time
-    float top = -INFINITY, num = 0.0f, den = 0.0f;
-    for (int c0 = 0; c0 < n_chunks; c0 += kMergeBatch) {
-      float pm[kMergeBatch], pl[kMergeBatch], pa[kMergeBatch];
+  if (threadIdx.x < kWave) {
+    const int c = threadIdx.x;
+    const float top = c < n_chunks ? part[(size_t)c * STRIDE + DH] : -INFINITY;
+    const float sum = c < n_chunks ? part[(size_t)c * STRIDE + DH + 1] : 0.0f;
+    float mx = top;
 #pragma unroll
-      for (int j = 0; j < kMergeBatch; ++j) {
-        const bool ok = c0 + j < n_chunks;
-        const float *p = part + ((size_t)(ok ? c0 + j : 0) * RQ + r) * ROW;
-        pm[j] = ok ? p[DH] : -INFINITY;
-        pl[j] = ok ? p[DH + 1] : 0.0f;
-        pa[j] = ok ? p[c] : 0.0f;
-      }
-      float mx = pm[0];
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    const float w = exp2_diff(top, mx == -INFINITY ? 0.0f : mx);
+    float den = sum * w;
 #pragma unroll
-      for (int j = 1; j < kMergeBatch; ++j) mx = fmaxf(mx, pm[j]);
-      const float m_new = fmaxf(top, mx);
-      const float ref = m_new == -INFINITY ? 0.0f : m_new;
-      const float keep = exp2_diff(top, ref);
-      num *= keep;
-      den *= keep;
-#pragma unroll
-      for (int j = 0; j < kMergeBatch; ++j) {
-        const float f = exp2_diff(pm[j], ref);
-        num = fmaf(pa[j], f, num);
-        den = fmaf(pl[j], f, den);
-      }
-      top = m_new;
+    for (int o = 32; o > 0; o >>= 1) den += __shfl_xor(den, o);
+    s_weight[c] = w;
+    if (c == 0) {
+      s_top = mx;
+      s_den = den;
     }
-    const size_t row = ((size_t)b * a.Hq + (size_t)g * a.G + hg) * a.n_q + qi;
-    a.out[row * DH + c] = den > 0.0f ? num / den : 0.0f;
-    if (c == 0) a.lse[row] = den > 0.0f ? (top + log2f(den)) * kLn2 : -INFINITY;
   }
+  __syncthreads();
+  float num = 0.0f;
+  const int x = threadIdx.x;
+  constexpr int BATCH = 16;
+  for (int c0 = 0; c0 < n_chunks; c0 += BATCH) {
+    float v[BATCH];
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) v[j] = c0 + j < n_chunks ? part[(size_t)(c0 + j) * STRIDE + x] : 0.0f;
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) num = fmaf(v[j], c0 + j < n_chunks ? s_weight[c0 + j] : 0.0f, num);
+  }
+  const float den = s_den;
+  a.out[(size_t)row * DH + x] = den > 0.0f ? num / den : 0.0f;
+  if (x == 0) a.lse[row] = den > 0.0f ? (s_top + log2f(den)) * kLn2 : -INFINITY;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -325,10 +558,11 @@ DecodePlan plan_decode(const Shape &s, int n_q, int n_rows) {
   p.rq = query_rows_per_pass(s.G);
   p.head_chunks = (s.G + p.rq - 1) / p.rq;
   p.grid_y = (int64_t)s.Bz * s.Hkv * n_q * p.head_chunks;
-  // Short KV sets (a compact cache): one large workgroup per (unit, query, pair of heads) finishes the job
-  // in one launch -- a decoding step is a chain of dependent layers, so a second launch costs more than
-  // reading the few rows once per pair of heads, and two heads per workgroup leave registers for sixteen
-  // waves with the loads of two blocks of rows in flight each.
+  p.col_chunks = (int)(((int64_t)s.G * n_q + kCols - 1) / kCols);
+  p.workgroups = (int64_t)s.Bz * s.Hkv * p.col_chunks;
+  // Short KV sets (a compact cache): one large workgroup per unit and query tile (f32: per query and pair of heads)
+  // finishes the job in one launch -- a decoding step is a chain of dependent layers, and a second launch
+  // costs more than it saves.
   if (n_rows <= 4096 || (p.grid_y >= 1024 && n_rows <= 16384)) {
     p.rq = s.G >= 2 ? 2 : 1;
     p.head_chunks = (s.G + p.rq - 1) / p.rq;
@@ -338,41 +572,66 @@ DecodePlan plan_decode(const Shape &s, int n_q, int n_rows) {
     p.workspace_bytes = 0;
     return p;
   }
-  // enough workgroups to fill the chip several times, chunks of at least 64 rows (one step of a
-  // workgroup's four waves), at most 64 chunks
-  const int64_t want = (4096 + p.grid_y - 1) / p.grid_y;
-  int64_t chunks = (n_rows + 63) / 64;
+  // Enough workgroups to fill the chip, at most 64 chunks. bf16: three workgroups of four waves per CU, all of them
+  // resident at once, chunks of whole steps of theirs (128 rows). f32: several times the chip, chunks of at least 64 rows.
+  const bool mfma = s.esize == 2;
+  const int64_t per_chunk = mfma ? p.workgroups : p.grid_y, target = mfma ? 2 * kComputeUnits : 4096;
+  const int64_t step = mfma ? kDecodeWaves * kBlockRows : 64;
+  int64_t chunks = (n_rows + step - 1) / step;
+  const int64_t want = mfma ? target / per_chunk : (target + per_chunk - 1) / per_chunk;
   if (chunks > want) chunks = want;
-  if (chunks > 64) chunks = 64;
+  if (chunks > kMaxChunks) chunks = kMaxChunks;
   if (chunks < 1) chunks = 1;
   int64_t rows = (n_rows + chunks - 1) / chunks;
-  rows = (rows + 63) / 64 * 64;
+  rows = (rows + step - 1) / step * step;
   p.rows_per_chunk = (int)rows;
   p.n_chunks = (int)((n_rows + rows - 1) / rows);
-  p.workspace_bytes = (size_t)p.grid_y * p.n_chunks * p.rq * (s.d + 2) * sizeof(float);
+  const size_t part_rows = mfma ? (size_t)p.workgroups * kCols : (size_t)p.grid_y * p.rq;
+  p.workspace_bytes = part_rows * p.n_chunks * (s.d + 2) * sizeof(float);
   return p;
 }
 
-template <int DT, int DH, int RQ>
-static void launch_decode_t(const DecodeArgs &a, const DecodePlan &p, hipStream_t stream) {
+template <int DH, int SPLIT, int NW>
+static void launch_decode_short(const DecodeArgs &a, const DecodePlan &p, hipStream_t stream) {
+  hipLaunchKernelGGL((decode_mfma_kernel<DH, SPLIT, NW, false>), dim3(1, (unsigned)p.workgroups * SPLIT), dim3(NW * kWave), 0,
+                     stream, a);
+}
+
+template <int DH>
+static void launch_decode_bf16(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
+  if (p.workspace_bytes == 0) {
+    // as many splits as leave every workgroup a CU of its own
+    if (DH == 128 && p.workgroups * 4 <= kComputeUnits) launch_decode_short<DH, DH / 32, 16>(a, p, stream);
+    else if (p.workgroups * 2 <= kComputeUnits) launch_decode_short<DH, 2, DH == 64 ? 16 : 8>(a, p, stream);
+    else launch_decode_short<DH, 1, 8>(a, p, stream);
+    return;
+  }
+  hipLaunchKernelGGL((decode_mfma_kernel<DH, 1, kDecodeWaves, true>), dim3(p.n_chunks, (unsigned)p.workgroups),
+                     dim3(kDecodeThreads), 0, stream, a);
+  if (p.n_chunks > 1)  // one chunk: the workgroups wrote the results
+    hipLaunchKernelGGL((decode_merge_kernel<DH, 1, true>), dim3((unsigned)rows), dim3(DH), 0, stream, a);
+}
+
+template <int DH, int RQ>
+static void launch_decode_f32(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
   if (p.n_chunks == 1) {
     if constexpr (RQ <= 2)
-      hipLaunchKernelGGL((decode_partial_kernel<DT, DH, RQ, 16, 2, true>), dim3(1, (unsigned)p.grid_y),
+      hipLaunchKernelGGL((decode_partial_kernel<DH, RQ, 16, 2, true>), dim3(1, (unsigned)p.grid_y),
                          dim3(16 * kWave), 0, stream, a);
     return;
   }
-  hipLaunchKernelGGL((decode_partial_kernel<DT, DH, RQ, kDecodeWaves, 4, false>), dim3(p.n_chunks, (unsigned)p.grid_y),
+  hipLaunchKernelGGL((decode_partial_kernel<DH, RQ, kDecodeWaves, 4, false>), dim3(p.n_chunks, (unsigned)p.grid_y),
                      dim3(kDecodeThreads), 0, stream, a);
-  hipLaunchKernelGGL((decode_merge_kernel<DH, RQ>), dim3((unsigned)p.grid_y), dim3(kDecodeThreads), 0, stream, a);
+  hipLaunchKernelGGL((decode_merge_kernel<DH, RQ, false>), dim3((unsigned)rows), dim3(DH), 0, stream, a);
 }
 
-template <int DT, int DH>
-static void launch_decode_rq(const DecodeArgs &a, const DecodePlan &p, hipStream_t stream) {
+template <int DH>
+static void launch_decode_rq(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
   switch (p.rq) {
-    case 1: launch_decode_t<DT, DH, 1>(a, p, stream); break;
-    case 2: launch_decode_t<DT, DH, 2>(a, p, stream); break;
-    case 4: launch_decode_t<DT, DH, 4>(a, p, stream); break;
-    default: launch_decode_t<DT, DH, 8>(a, p, stream); break;
+    case 1: launch_decode_f32<DH, 1>(a, p, rows, stream); break;
+    case 2: launch_decode_f32<DH, 2>(a, p, rows, stream); break;
+    case 4: launch_decode_f32<DH, 4>(a, p, rows, stream); break;
+    default: launch_decode_f32<DH, 8>(a, p, rows, stream); break;
   }
 }
 
@@ -399,12 +658,15 @@ hipError_t launch_decode_attention(const ckv_params *p, const Shape &s, const vo
   a.n_chunks = plan.n_chunks;
   a.head_chunks = plan.head_chunks;
   a.scale2 = s.scale * kLog2e;
+  a.cols = s.G * n_q;
+  a.col_chunks = plan.col_chunks;
+  const int rows = s.Bz * s.Hq * n_q;
   if (p->dtype == CKV_BF16) {
-    if (s.d == 128) launch_decode_rq<CKV_BF16, 128>(a, plan, stream);
-    else launch_decode_rq<CKV_BF16, 64>(a, plan, stream);
+    if (s.d == 128) launch_decode_bf16<128>(a, plan, rows, stream);
+    else launch_decode_bf16<64>(a, plan, rows, stream);
   } else {
-    if (s.d == 128) launch_decode_rq<CKV_F32, 128>(a, plan, stream);
-    else launch_decode_rq<CKV_F32, 64>(a, plan, stream);
+    if (s.d == 128) launch_decode_rq<128>(a, plan, rows, stream);
+    else launch_decode_rq<64>(a, plan, rows, stream);
   }
   return hipGetLastError();
 }

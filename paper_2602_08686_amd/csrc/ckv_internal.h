@@ -149,6 +149,8 @@ struct DecodePlan {
   int head_chunks;     // ceil(G / rq)
   int rows_per_chunk, n_chunks;
   int64_t grid_y;      // Bz * Hkv * n_q * head_chunks
+  int col_chunks;      // bf16: 16-wide tiles of a KV head's G * n_q query columns
+  int64_t workgroups;  // bf16: Bz * Hkv * col_chunks
   size_t workspace_bytes;
 };
 DecodePlan plan_decode(const Shape &s, int n_q, int n_rows);
