@@ -247,13 +247,15 @@ extern "C" ckv_status ckv_apply_tables(const ckv_params *params, const float *sc
 
 // Whether ckv_window_utility can run its fused second pass for this call (else it runs the two
 // unfused steps through the scratch buffer): the pipelined bf16 kernels with at most two 32-row tiles per
-// head and all query tiles of a group in one wave (at most eight), pooling kernels of at most 7 taps, rows that keep the
-// 128-bit and 64-bit accesses aligned. With the value-norm flag the ratio, which is common to a group's
-// heads and non-negative, multiplies the group maximum afterwards (in the value-norm scaling pass).
-static bool utility_fast_path(const ckv_params *p, const Shape &s, const float *scratch, const float *utility) {
+// head and all query tiles of a group in one wave (at most eight), pooling kernels of at most 7 taps. Rows may start
+// at any multiple of four bytes: with lengths that are no multiple of four the stores cover five lines where they
+// would four (us, both passes and tables, fused / unfused: 32767 positions, batch 16: 383 / 392; 32768: 356 / 397; 20011,
+// batch 2: 45.3 / 45.4). With the value-norm flag the ratio, which is common to
+// a group's heads and non-negative, multiplies the group maximum afterwards (in the value-norm scaling pass).
+static bool utility_fast_path(const ckv_params *p, const Shape &s) {
   const int kernel = p->pool == CKV_POOL_NONE ? 1 : p->pool_kernel;
-  return p->dtype == CKV_BF16 && s.n_groups == 1 && s.WT <= 2 && kernel / 2 <= 3 && s.T % 4 == 0 && s.P % 4 == 0 && s.P > 0 && (uintptr_t)scratch % 16 == 0 &&
-         (uintptr_t)utility % 16 == 0 && (int64_t)s.Hkv * s.P < (1 << 29);
+  return p->dtype == CKV_BF16 && s.n_groups == 1 && s.WT <= 2 && kernel / 2 <= kUtilMaxRadius && s.P > 0 && s.T >= 4 &&
+         (int64_t)s.Hkv * s.P < (1 << 29);
 }
 
 extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q_win, const void *k,
@@ -276,7 +278,7 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
   st = workspace_ok(w, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
   hipStream_t stream = (hipStream_t)hip_stream;
-  if (utility_fast_path(params, s, scores_scratch, utility)) {
+  if (utility_fast_path(params, s)) {
     UtilityFusion fuse;
     fuse.w_row = w_head + (size_t)params->layer * s.Hq;
     fuse.utility = utility;

@@ -90,7 +90,7 @@ void derive(const ckv_params *p, Shape *s);
 
 // Workspace layout (bytes, 256-aligned sections), all sized from Shape.
 struct Workspace {
-  size_t part_off, part_bytes;   // float2 [units][n_tiles*32][n_chunks] row-stat partials
+  size_t part_off, part_bytes;   // float2 [units][groups][n_chunks][NQ*32] row-stat partials
   size_t lse_off, lse_bytes;     // float  [Bz][Hq][W]
   size_t vsum_off, vsum_bytes;   // float  [units][vnorm blocks] partial sums of value norms
   size_t select_off, select_bytes;  // int: the split selection's merged histograms, slice counts, thresholds

@@ -38,7 +38,7 @@ struct ScoreArgs {
   int WT, n_tiles, n_groups, keys_per_wave, n_chunks;
   float c2;     // softmax scale * log2(e): logits are kept in the log2 domain
   float norm;   // T / W
-  float2 *part;      // [unit][group][NQ*32][n_chunks] (max, sum) in the log2 domain
+  float2 *part;      // [unit][group][n_chunks][NQ*32] (max, sum) in the log2 domain
   const float *lse;  // [Bz][Hq][W] natural log
   int lse_from_part; // pass 2 merges the row partials of pass 1 itself (no lse_kernel in between)
   float *lse_out;
@@ -178,8 +178,7 @@ __device__ __forceinline__ void store_row_partials(const ScoreArgs &a, const Blo
     float2 s = sm[0][threadIdx.x];
 #pragma unroll
     for (int w = 1; w < kScoreWaves; ++w) merge_stats(s.x, s.y, sm[w][threadIdx.x].x, sm[w][threadIdx.x].y);
-    const size_t row = ((size_t)bc.unit * a.n_groups + bc.grp) * (NQ * kTile) + threadIdx.x;
-    a.part[row * a.n_chunks + bc.chunk] = s;
+    a.part[(((size_t)bc.unit * a.n_groups + bc.grp) * a.n_chunks + bc.chunk) * (NQ * kTile) + threadIdx.x] = s;
   }
 }
 
@@ -235,12 +234,23 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, 2) rowstats_kernel(ScoreAr
   store_row_partials<NQ>(a, bc, wave, m, hh, rm, rl);
 }
 
-// LSE_j = ln2 * (M + log2 sum_c l_c 2^(m_c - M)) from the n_chunks partials of one row, in chunk order.
-__device__ __forceinline__ float merge_row_partials(const float2 *p, int n_chunks) {
-  float M = -1e30f;
-  for (int c = 0; c < n_chunks; ++c) M = fmaxf(M, p[c].x);
-  float L = 0.0f;
-  for (int c = 0; c < n_chunks; ++c) L += p[c].y * __builtin_amdgcn_exp2f(p[c].x - M);
+// LSE_j = ln2 * (M + log2 sum_c l_c 2^(m_c - M)) from the n_chunks partials of one row (`stride` apart), in chunk order,
+// eight loads in flight.
+__device__ __forceinline__ float merge_row_partials(const float2 *p, int n_chunks, int stride) {
+  constexpr int BATCH = 8;
+  float M = -1e30f, L = 0.0f;
+  for (int c0 = 0; c0 < n_chunks; c0 += BATCH) {
+    float2 v[BATCH];
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) v[e] = c0 + e < n_chunks ? p[(size_t)(c0 + e) * stride] : make_float2(-1e30f, 0.0f);
+    float top = M;
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) top = fmaxf(top, v[e].x);
+    L *= __builtin_amdgcn_exp2f(M - top);
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) L += v[e].y * __builtin_amdgcn_exp2f(v[e].x - top);
+    M = top;
+  }
   return (M + __log2f(L)) * kLn2;
 }
 
@@ -250,14 +260,15 @@ __global__ void lse_kernel(ScoreArgs a, int n_rows_total) {
   const int row = blockIdx.x * blockDim.x + threadIdx.x;
   if (row >= n_rows_total) return;
   const int per_group = NQ * kTile;
-  const int in_group = row % per_group;
-  const int grp = (row / per_group) % a.n_groups;
-  const int unit = row / (per_group * a.n_groups);
+  const int in_group = row % per_group, ug = row / per_group;
+  const int grp = ug % a.n_groups;
+  const int unit = ug / a.n_groups;
   const int tile = grp * NQ + in_group / kTile;
   const int j = (tile % a.WT) * kTile + in_group % kTile;
   if (tile >= a.n_tiles || j >= a.W) return;
   const int b = unit / a.Hkv, g = unit % a.Hkv, h = g * a.G + tile / a.WT;
-  a.lse_out[((size_t)b * a.Hq + h) * a.W + j] = merge_row_partials(a.part + (size_t)row * a.n_chunks, a.n_chunks);
+  a.lse_out[((size_t)b * a.Hq + h) * a.W + j] =
+      merge_row_partials(a.part + (size_t)ug * a.n_chunks * per_group + in_group, a.n_chunks, per_group);
 }
 
 // One 32-row x 32-key tile of pass 2 for the plain kernel. The accumulator starts at -LSE_row / scale
@@ -1004,22 +1015,26 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
   st.start(a, bc, wr, ring, lane, m, hh, qf, jrow);
+  // Both passes in one call: every workgroup merges the first pass's row partials, a thread per row (NQ * 32 <= 256 of
+  // them), while its first key tiles are on their way. (A kernel in between cost 5 us, 11 with eight tiles and 32
+  // workgroups along the keys; a lane merging all its rows by itself cost more than that from 16 partials on.)
+  __shared__ float s_lse[NQ * kTile];
+  static_assert(NQ * kTile <= kScoreWaves * kWave, "a thread per row");
+  if (threadIdx.x < NQ * kTile) {
+    const int tile = bc.grp * NQ + threadIdx.x / kTile, j = (tile % WT) * kTile + threadIdx.x % kTile;
+    float v = 0.0f;
+    if (a.lse_from_part)
+      v = merge_row_partials(a.part + ((size_t)bc.unit * a.n_groups + bc.grp) * a.n_chunks * (NQ * kTile) + threadIdx.x,
+                             a.n_chunks, NQ * kTile);
+    else if (tile < a.n_tiles && j < a.W) v = a.lse[((size_t)bc.b * a.Hq + bc.g * a.G + tile / WT) * a.W + j];
+    s_lse[threadIdx.x] = v;
+  }
+  __syncthreads();
   // bias of this lane's query row in every tile; padding rows (q = 0) get exp2(-1000) = 0 as weight
   Bias<DT> bias[NQ];
   const float to_raw = -kLog2e / a.c2;  // LSE (natural log) -> units of the raw dot product, negated
 #pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    const int h = bc.g * a.G + (bc.grp * NQ + i) / WT;
-    float lse_j = 0.0f;
-    if (jrow[i] >= 0) {
-      // same arithmetic as lse_kernel, which this saves when both passes run in one call
-      if (a.lse_from_part)
-        lse_j = merge_row_partials(
-            a.part + (((size_t)bc.unit * a.n_groups + bc.grp) * (NQ * kTile) + i * kTile + m) * a.n_chunks, a.n_chunks);
-      else lse_j = a.lse[((size_t)bc.b * a.Hq + h) * a.W + jrow[i]];
-    }
-    bias[i].set(jrow[i] >= 0 ? lse_j * to_raw : -1000.0f / a.c2, hh);
-  }
+  for (int i = 0; i < NQ; ++i) bias[i].set(jrow[i] >= 0 ? s_lse[i * kTile + m] * to_raw : -1000.0f / a.c2, hh);
   const chunk_t ones = Bias<DT>::ones(hh);
   // Descriptor over scores[b]: Hq * T floats (the host checks that this stays below 2 GiB). Lanes with
   // nothing to store present an offset outside it, which the hardware drops: no branch splits the
@@ -1181,13 +1196,6 @@ static void launch_colsum(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 bl
   hipLaunchKernelGGL((colsum_kernel<DT, DH, NQ>), grid, block, 0, stream, a);
 }
 
-// Where a lane has at most this many row partials to merge (query tiles per wave x workgroups along the key
-// axis), the second pass merges the first pass's partials in its own prologue: every workgroup of a unit
-// repeats the merge, which is cheaper than a launch while the partials are few. Beyond it the small merge
-// kernel runs in between (measured at 8 tiles x 32 workgroups, T = 128k with 8 units: 26 us of prologue
-// against 11 us for the kernel; at 4 x 8 the kernel still wins, at 4 x 2 and 1 x 8 the prologue does).
-constexpr int kMergeInPassTwo = 16;
-
 // Launches for the query-tile counts NQ_LO..NQ_HI (the instantiations are spread over several translation
 // units, each covering a range, to keep compile times apart).
 template <int DT, int DH, int NQ_LO, int NQ_HI>
@@ -1197,8 +1205,7 @@ static hipError_t launch_scores_t(const Shape &s, ScoreArgs &a, bool need_lse, b
 #define CKV_LAUNCH_NQ(NQ)                                                          \
   case NQ:                                                                         \
     if constexpr (NQ >= NQ_LO && NQ <= NQ_HI) {                                    \
-      a.lse_from_part = need_lse && need_scores && colsum_is_staged<DT, NQ>(s) && \
-                        NQ * s.n_chunks <= kMergeInPassTwo;                         \
+      a.lse_from_part = need_lse && need_scores && colsum_is_staged<DT, NQ>(s);     \
       if (need_lse) launch_rowstats<DT, DH, NQ>(s, a, grid, block, stream);        \
       if (need_scores) launch_colsum<DT, DH, NQ>(s, a, grid, block, stream);       \
       break;                                                                       \

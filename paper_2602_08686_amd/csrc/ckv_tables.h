@@ -12,7 +12,9 @@ constexpr int kTablesThreads = 256;
 constexpr int kTablesPerThread = 4;
 constexpr int kTablesTile = kTablesThreads * kTablesPerThread;  // 1024 positions
 constexpr int kMaxHalo = 31;                                    // pool_kernel <= 63
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+// Four floats at any multiple of four bytes: rows of T and P floats start on such addresses when the length is no
+// multiple of four, and the 128-bit global accesses need no more.
+typedef float f32x4_t __attribute__((ext_vector_type(4), aligned(4)));
 
 struct TablesArgs {
   const float *scores;  // [Bz][Hq][T]
@@ -88,50 +90,59 @@ __device__ __forceinline__ void write_tau_and_budgets(const TablesArgs &a, int b
   write_budgets(a, b);
 }
 
-// Fast path for pooling kernels of at most 9 taps on 16-byte aligned rows (T % 4 == 0): a thread owns
-// four consecutive positions and reads them plus the four on either side as three 128-bit loads per
-// head (the neighbours' loads hit L1), pools from registers with the taps unrolled, and writes one
-// 128-bit store (or scalars where P is not a multiple of four). No LDS and no barriers.
+// Fast path for pooling kernels of at most kWindowTaps taps: a thread owns four consecutive positions and reads them
+// plus what the window needs on either side as 128-bit loads per head (the neighbours' loads hit L1), pools
+// from registers with the taps unrolled, and writes one 128-bit store. No LDS and no barriers, and no branch around
+// a load (they would go out one after the other): addresses are clamped into the row, what lies outside the prefix is
+// masked afterwards. Only a prefix that ends less than four elements before its row reads vectors that would not
+// fit element by element. The caller has checked T >= 4.
 // Utilities of the four positions t .. t + 3 (t a multiple of four, t < P) of one (batch, KV head).
+constexpr int kWindowTaps = 17;
 template <int POOL, int R>
 __device__ __forceinline__ void pool_four(const TablesArgs &a, int unit, int t) {
+  constexpr int SIDE = (R + 3) / 4;  // vectors on either side
   const int b = unit / a.Hkv, g = unit % a.Hkv;
   const float pad = POOL == CKV_POOL_MAX ? -INFINITY : 0.0f;
+  const bool short_end = a.W < 4;  // the same for the whole launch
   float rho[4] = {1.0f, 1.0f, 1.0f, 1.0f};
   if (a.rho) {
-    const f32x4_t r4 = *reinterpret_cast<const f32x4_t *>(a.rho + (size_t)unit * a.T + t);
+    const float *row = a.rho + (size_t)unit * a.T;
+    const f32x4_t r4 = *reinterpret_cast<const f32x4_t *>(row + min(t, a.T - 4));
 #pragma unroll
-    for (int e = 0; e < 4; ++e) rho[e] = r4[e];
+    for (int e = 0; e < 4; ++e) rho[e] = short_end ? row[min(t + e, a.T - 1)] : r4[e];
   }
   float best[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
   for (int hg = 0; hg < a.G; ++hg) {
     const int h = g * a.G + hg;
     const float *row = a.scores + ((size_t)b * a.Hq + h) * a.T;
-    // w[0..11] = positions t-4 .. t+7; everything outside [0, P) counts as padding. Rows hold T >= P + 1
-    // floats and T % 4 == 0, so the three loads stay inside the row whenever their first index is < T.
-    float w[12];
-    const f32x4_t mid = *reinterpret_cast<const f32x4_t *>(row + t);
-    f32x4_t lo = {pad, pad, pad, pad}, hi = {pad, pad, pad, pad};
-    if (R > 0 && t >= 4) lo = *reinterpret_cast<const f32x4_t *>(row + t - 4);
-    if (R > 0 && t + 4 < a.T) hi = *reinterpret_cast<const f32x4_t *>(row + t + 4);
+    float w[4 * (2 * SIDE + 1)];  // positions t - 4 SIDE ..
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      w[e] = lo[e];
-      w[4 + e] = (t + e < a.P) ? mid[e] : pad;
-      w[8 + e] = (t + 4 + e < a.P) ? hi[e] : pad;
+    for (int q = 0; q < 2 * SIDE + 1; ++q) {
+      const f32x4_t v = *reinterpret_cast<const f32x4_t *>(row + max(0, min(t + 4 * (q - SIDE), a.T - 4)));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[4 * q + e] = v[e];
+    }
+    if (short_end) {
+#pragma unroll
+      for (int x = 0; x < 4 * (2 * SIDE + 1); ++x) w[x] = row[max(0, min(t - 4 * SIDE + x, a.T - 1))];
+    }
+#pragma unroll
+    for (int x = 0; x < 4 * (2 * SIDE + 1); ++x) {
+      const int at = t - 4 * SIDE + x;
+      w[x] = at >= 0 && at < a.P ? w[x] : pad;
     }
     const float wgt = a.w_row[h];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float c = w[4 + e - R];
+      float c = w[4 * SIDE + e - R];
 #pragma unroll
-      for (int d = 1 - R; d <= R; ++d) c = POOL == CKV_POOL_MAX ? fmaxf(c, w[4 + e + d]) : c + w[4 + e + d];
+      for (int d = 1 - R; d <= R; ++d) c = POOL == CKV_POOL_MAX ? fmaxf(c, w[4 * SIDE + e + d]) : c + w[4 * SIDE + e + d];
       if (POOL == CKV_POOL_AVG) c = c / (float)(2 * R + 1);
       best[e] = fmaxf(best[e], wgt * (c * rho[e]));
     }
   }
   float *out = a.utility + (size_t)unit * a.P + t;
-  if (a.P % 4 == 0) {
+  if (t + 4 <= a.P) {
     *reinterpret_cast<f32x4_t *>(out) = f32x4_t{best[0], best[1], best[2], best[3]};
   } else {
 #pragma unroll

@@ -1,10 +1,12 @@
 // Pooling + compiled-table application (paper Eq. 4 u = alpha * rho, Eq. 6 weighted max over heads,
 // Sec. 4.3 gate lookup; 1-D pooling and the per-head budget split are workload definitions).
 //
-// One workgroup owns one tile of kTablesTile prefix positions of one (batch, KV head). For each query
-// head of the group it stages the tile plus a halo of pool_kernel/2 positions in LDS, pools, multiplies
-// by rho and by the head's weight, and keeps the running maximum in registers, so the window mass
-// is read from HBM once and the utility written once.
+// Windows of up to 17 taps are pooled from registers, four positions to a thread (tables_window_kernel), whatever the
+// alignment of the rows. Longer ones: one workgroup owns one tile of kTablesTile prefix positions of one (batch, KV
+// head); for each query head of the group it stages the tile plus a halo of pool_kernel/2 positions in LDS, pools,
+// multiplies by rho and by the head's weight, and keeps the running maximum in registers. Two barriers per head and a
+// read of LDS per tap make that the slower form (10006 positions, 32 units, 7 taps: 15.1 us against 5.7), so it is
+// left where the register window would not fit.
 #include "ckv_tables.h"
 
 namespace ckv {
@@ -85,13 +87,12 @@ __global__ void __launch_bounds__(kFixupThreads) tables_fixup_kernel(TablesArgs 
 template <int POOL>
 static bool launch_window_pool(const TablesArgs &a, dim3 grid, hipStream_t stream) {
   const dim3 block(kTablesThreads);
+#define CKV_WINDOW(R) \
+  case R: hipLaunchKernelGGL((tables_window_kernel<POOL, R>), grid, block, 0, stream, a); return true;
   switch (a.radius) {
-    case 0: hipLaunchKernelGGL((tables_window_kernel<POOL, 0>), grid, block, 0, stream, a); return true;
-    case 1: hipLaunchKernelGGL((tables_window_kernel<POOL, 1>), grid, block, 0, stream, a); return true;
-    case 2: hipLaunchKernelGGL((tables_window_kernel<POOL, 2>), grid, block, 0, stream, a); return true;
-    case 3: hipLaunchKernelGGL((tables_window_kernel<POOL, 3>), grid, block, 0, stream, a); return true;
-    case 4: hipLaunchKernelGGL((tables_window_kernel<POOL, 4>), grid, block, 0, stream, a); return true;
+    CKV_WINDOW(0) CKV_WINDOW(1) CKV_WINDOW(2) CKV_WINDOW(3) CKV_WINDOW(4) CKV_WINDOW(5) CKV_WINDOW(6) CKV_WINDOW(7) CKV_WINDOW(8)
   }
+#undef CKV_WINDOW
   return false;
 }
 
@@ -102,10 +103,8 @@ hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float 
   const TablesArgs a = tables_args(p, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins,
                                    utility, budget, tau);
   const dim3 grid(a.n_tiles, s.Bz * s.Hkv), block(kTablesThreads);
-  const bool aligned = s.T % 4 == 0 && ((uintptr_t)scores % 16 == 0) && ((uintptr_t)utility % 16 == 0) &&
-                       (!a.rho || (uintptr_t)a.rho % 16 == 0);
   bool done = false;
-  if (aligned && s.P > 0 && a.radius <= 4)
+  if (s.P > 0 && s.T >= 4 && a.kernel <= kWindowTaps)
     done = p->pool == CKV_POOL_MAX ? launch_window_pool<CKV_POOL_MAX>(a, grid, stream)
                                    : launch_window_pool<CKV_POOL_AVG>(a, grid, stream);
   if (!done) hipLaunchKernelGGL(tables_kernel, grid, block, 0, stream, a);
@@ -123,8 +122,7 @@ static void launch_fixup_pool(const TablesArgs &a, const FixupArgs &f, dim3 grid
   }
 }
 
-// The caller has checked utility_fast_path(): no value norm, radius <= 3, T and P multiples of four,
-// 16-byte aligned scores and utility.
+// The caller has checked utility_fast_path(); the ratio is applied afterwards.
 hipError_t launch_utility_fixup(const ckv_params *p, const Shape &s, const float *sparse_scores,
                                 const float *w_head, const float *head_share, const float *t_gate, int n_ent,
                                 int n_ppl, const int32_t *risk_bins, float *utility, int32_t *budget, float *tau,

@@ -1,0 +1,46 @@
+"""Rows that start and end anywhere: every residue of the length and the prefix modulo four, windows shorter than a vector,
+prefixes of a few positions, pooling kernels up to and beyond what is pooled from registers, and enough workgroups along
+the keys that the second scan pass merges many row partials -- through the one-call and the separate calls, against the
+oracle with the tolerances of the chain tests."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_08686_amd import workloads as wl
+from parity_util import assert_index_sets_match, assert_scores_close, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _w(dtype, Bz, Hq, Hkv, d, T, W, pool, kernel, budget, **kw):
+    return wl.Workload(f"rag_{dtype}_{Hq}x{Hkv}_d{d}_T{T}_W{W}_p{pool}k{kernel}", dtype, Bz, Hq, Hkv, d, T, W, pool, kernel, budget, 1,
+                       seed=40 + T + W + kernel, **kw)
+
+
+AVG, MAX = wl.POOL_AVG, wl.POOL_MAX
+CASES = [
+    (_w("bf16", 2, 8, 2, 128, 2049, 32, AVG, 7, 128, shares=True), False), (_w("bf16", 2, 8, 2, 128, 2050, 32, MAX, 5, 128), False),
+    (_w("bf16", 1, 8, 2, 64, 2051, 32, AVG, 3, 128), True), (_w("bf16", 1, 4, 2, 128, 2048, 1, AVG, 7, 64), False),
+    (_w("bf16", 1, 4, 2, 128, 2047, 2, MAX, 7, 64), True), (_w("bf16", 1, 4, 1, 128, 1030, 3, AVG, 17, 64), False),
+    (_w("bf16", 1, 2, 1, 64, 4, 3, AVG, 7, 4), False), (_w("bf16", 1, 2, 1, 64, 3, 2, AVG, 3, 3), False),
+    (_w("bf16", 1, 2, 2, 64, 37, 32, MAX, 9, 36), False), (_w("f32", 2, 4, 2, 64, 1001, 32, AVG, 13, 100), True),
+    (_w("f32", 1, 4, 2, 64, 1002, 7, MAX, 15, 100), False), (_w("bf16", 1, 4, 2, 128, 1501, 32, AVG, 19, 100), False),
+    (_w("bf16", 1, 8, 1, 128, 40003, 32, AVG, 7, 200), False),   # eight tiles per wave, tens of partials per row
+    (_w("bf16", 1, 4, 1, 64, 30002, 64, MAX, 7, 200), False),
+]
+
+
+@pytest.mark.parametrize("w,vn", CASES, ids=lambda x: x.name if isinstance(x, wl.Workload) else str(int(x)))
+def test_ragged_rows_match_oracle(w, vn):
+    print(f"case {w.name} value_norm={vn}", flush=True)
+    t, tabs = wl.make_layer(w, 0, DEV), wl.make_tables(w, DEV)
+    ref = run_oracle(w, t, tabs, value_norm=vn)
+    for fused in (False, True):
+        p, buf = run_gpu(w, t, tabs, flags=1 if vn else 0, fused_utility=fused)
+        if not fused:
+            assert_scores_close(buf.scores.cpu().numpy(), ref["scores"], "scores")
+        assert_scores_close(buf.utility.cpu().numpy(), ref["utility"].astype(np.float64), f"utility (one call: {fused})")
+        np.testing.assert_array_equal(buf.budget.cpu().numpy(), ref["budget"])
+        assert_index_sets_match(buf.idx.cpu().numpy(), buf.count.cpu().numpy(), ref["idx"], ref["count"], ref["utility"],
+                                ref["tau"], ref["budget"], w.window)
