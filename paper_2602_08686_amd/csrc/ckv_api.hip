@@ -47,6 +47,35 @@ ckv_status validate(const ckv_params *p) {
   return CKV_OK;
 }
 
+// f32: two workgroups per CU are resident (one with several query tiles of 512-byte rows per wave), so what counts is
+// full rounds of that many. Keys per wave (whole tiles)
+// with the least rounds x (keys + a tile's worth of set-up); the larger of equal ones. The row partials stay within
+// 1 MiB or what ranges of T * units / 8192 keys need, whichever is more, so that a caller's or the library's fixed
+// scratch goes as far as it did.
+// Measured, us, both passes and tables, before (ranges for 2048 workgroups, at least 64 keys) -> now: 1024 keys, 4/4 heads of 64
+// 16.5 -> 12.8; 8192 keys, 32/32 heads of 64 53.4 -> 38.3; 4099 keys, 32/8 heads of 128 70.5 -> 55.6.
+static int64_t f32_keys_per_wave(const Shape &s, int64_t units) {
+  const auto workgroups = [&](int64_t kpw) { return units * ((s.T + kScoreWaves * kpw - 1) / (kScoreWaves * kpw)); };
+  int64_t plain = ((int64_t)s.T * units + kScoreWaves * 2048 - 1) / (kScoreWaves * 2048);
+  plain = (plain + kTile - 1) / kTile * kTile;
+  if (plain < 2 * kTile) plain = 2 * kTile;
+  if (plain > 4096) plain = 4096;
+  const int64_t part_bytes = (int64_t)s.NQ * kTile * (int64_t)sizeof(float2);  // per workgroup
+  const int64_t most = workgroups(plain) * part_bytes > (1 << 20) ? workgroups(plain) : (1 << 20) / part_bytes;
+  const int64_t resident = s.d == 128 && s.NQ >= 2 ? kComputeUnits : 2 * kComputeUnits;
+  int64_t best = plain, best_cost = INT64_MAX;
+  for (int64_t kpw = kTile; kpw <= 4096; kpw += kTile) {
+    const int64_t n = workgroups(kpw);
+    const int64_t cost = (n + resident - 1) / resident * (kpw + kTile);
+    if (n <= most && cost <= best_cost) {
+      best = kpw;
+      best_cost = cost;
+    }
+    if (kpw >= s.T) break;
+  }
+  return best;
+}
+
 void derive(const ckv_params *p, Shape *s) {
   s->Bz = p->batch;
   s->Hq = p->n_q_heads;
@@ -60,9 +89,13 @@ void derive(const ckv_params *p, Shape *s) {
   s->WT = (s->W + kTile - 1) / kTile;
   s->n_tiles = s->G * s->WT;
   // Tiles a wave keeps in registers, whole heads only: eight for bf16 (a wave alone on its SIMD has 512
-  // registers, and the matrix cores read operands from either half), four for f32 rows of 256 bytes,
-  // one head's tiles for f32 rows of 512 bytes.
-  const int budget_tiles = p->dtype == CKV_BF16 ? kMaxQTiles : s->d * s->esize <= 256 ? kMaxQTilesF32 : 1;
+  // registers, and the matrix cores read operands from either half), four for f32 rows of 256 bytes, two for f32 rows of
+  // 512 bytes where that leaves every SIMD two tile products (us, both passes and tables, one tile / two: 4099 keys, 32/8
+  // heads 55.1 / 45.7, 16384 keys, 16/8 heads 64.8 / 54.5, but 700 keys 20.6 / 27.6; with up to four 59.7 for the first)
+  // and pads no tile, else one head's tiles.
+  const int64_t products = (int64_t)s->Bz * s->Hkv * s->n_tiles * ((s->T + kTile - 1) / kTile);
+  const bool two = s->n_tiles % 2 == 0 && products >= 2 * kScoreWaves * kComputeUnits;
+  const int budget_tiles = p->dtype == CKV_BF16 ? kMaxQTiles : s->d * s->esize <= 256 ? kMaxQTilesF32 : two ? 2 : 1;
   const int per_wave_max = budget_tiles >= s->WT ? (budget_tiles / s->WT) * s->WT : s->WT;
   s->n_groups = (s->n_tiles + per_wave_max - 1) / per_wave_max;
   int nq = (s->n_tiles + s->n_groups - 1) / s->n_groups;
@@ -71,15 +104,18 @@ void derive(const ckv_params *p, Shape *s) {
   s->n_groups = (s->n_tiles + nq - 1) / nq;
   // Split the key axis. The bf16 kernels keep one workgroup per CU busy for the whole launch (their
   // set-up is not overlapped with anything, so there is one workgroup per CU and its waves sweep long
-  // ranges, a whole number of four-tile pipeline rounds); the f32 kernels run two workgroups per CU
-  // and like a few thousand of them.
+  // ranges, a whole number of four-tile pipeline rounds).
   const int64_t units = (int64_t)s->Bz * s->Hkv * s->n_groups;
-  const int64_t target_wgs = p->dtype == CKV_BF16 ? kComputeUnits : 2048;
-  int64_t kpw = ((int64_t)s->T * units + kScoreWaves * target_wgs - 1) / (kScoreWaves * target_wgs);
-  const int64_t quantum = p->dtype == CKV_BF16 && kpw > 4 * kTile ? 4 * kTile : kTile;
-  kpw = (kpw + quantum - 1) / quantum * quantum;
-  if (kpw < 2 * kTile) kpw = 2 * kTile;
-  if (kpw > 4096) kpw = 4096;
+  int64_t kpw;
+  if (p->dtype == CKV_BF16) {
+    kpw = ((int64_t)s->T * units + kScoreWaves * kComputeUnits - 1) / (kScoreWaves * kComputeUnits);
+    const int64_t quantum = kpw > 4 * kTile ? 4 * kTile : kTile;
+    kpw = (kpw + quantum - 1) / quantum * quantum;
+    if (kpw < 2 * kTile) kpw = 2 * kTile;
+    if (kpw > 4096) kpw = 4096;
+  } else {
+    kpw = f32_keys_per_wave(*s, units);
+  }
   s->keys_per_wave = (int)kpw;
   s->n_chunks = (int)((s->T + kScoreWaves * kpw - 1) / (kScoreWaves * kpw));
   s->scale = p->softmax_scale > 0.0f ? p->softmax_scale : 1.0f / sqrtf((float)s->d);

@@ -40,7 +40,7 @@ struct ScoreArgs {
   float norm;   // T / W
   float2 *part;      // [unit][group][n_chunks][NQ*32] (max, sum) in the log2 domain
   const float *lse;  // [Bz][Hq][W] natural log
-  int lse_from_part; // pass 2 merges the row partials of pass 1 itself (no lse_kernel in between)
+  int lse_from_part; // both passes in one call: pass 2 merges the row partials of pass 1 itself
   float *lse_out;
   float *scores;     // [Bz][Hq][T]; with group_sum: [Bz][Hkv][T], the sum over each KV head's query heads
   int group_sum;
@@ -183,10 +183,12 @@ __device__ __forceinline__ void store_row_partials(const ScoreArgs &a, const Blo
 }
 
 // ---------------------------------------------------------------------------------------------
-// Plain kernels: every dtype / tile count. Two waves per SIMD, K double-buffered in registers.
+// Plain kernels: every dtype / tile count. Two waves per SIMD, K double-buffered in registers; one wave where two or
+// more query tiles of 512-byte rows would not fit 256 registers beside it (they spilled 100 to 400).
 // ---------------------------------------------------------------------------------------------
+__host__ __device__ constexpr int plain_waves(int dt, int dh, int nq) { return dt == CKV_F32 && dh == 128 && nq >= 2 ? 1 : 2; }
 template <int DT, int DH, int NQ>
-__global__ void __launch_bounds__(kScoreWaves *kWave, 2) rowstats_kernel(ScoreArgs a) {
+__global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) rowstats_kernel(ScoreArgs a) {
   constexpr int NCH = DH * (DT == CKV_BF16 ? 2 : 4) / 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 31, hh = lane >> 5;
   const BlockCoord bc = decode_block(a);
@@ -298,7 +300,7 @@ __device__ __forceinline__ float colsum_tile(const chunk_t (&qf)[NCH], const chu
 }
 
 template <int DT, int DH, int NQ>
-__global__ void __launch_bounds__(kScoreWaves *kWave, 2) colsum_kernel(ScoreArgs a) {
+__global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) colsum_kernel(ScoreArgs a) {
   constexpr int NCH = DH * (DT == CKV_BF16 ? 2 : 4) / 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 31, hh = lane >> 5;
   const BlockCoord bc = decode_block(a);
@@ -311,7 +313,12 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, 2) colsum_kernel(ScoreArgs
     const int j = (tile % a.WT) * kTile + threadIdx.x % kTile;
     const int h = bc.g * a.G + tile / a.WT;
     const bool valid = tile < a.n_tiles && j < a.W;
-    s_init[threadIdx.x] = valid ? -a.lse[((size_t)bc.b * a.Hq + h) * a.W + j] * (kLog2e / a.c2) : -INFINITY;
+    float lse_j = 0.0f;
+    if (a.lse_from_part)  // as lse_kernel would have it, which this saves when both passes run in one call
+      lse_j = merge_row_partials(a.part + ((size_t)bc.unit * a.n_groups + bc.grp) * a.n_chunks * (NQ * kTile) + threadIdx.x,
+                                 a.n_chunks, NQ * kTile);
+    else if (valid) lse_j = a.lse[((size_t)bc.b * a.Hq + h) * a.W + j];
+    s_init[threadIdx.x] = valid ? -lse_j * (kLog2e / a.c2) : -INFINITY;
   }
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
@@ -1155,13 +1162,6 @@ static void launch_rowstats(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 
   hipLaunchKernelGGL(lse_kernel<NQ>, dim3((rows + 255) / 256), dim3(256), 0, stream, a, rows);
 }
 
-// Whether launch_colsum takes the LDS-staged kernel (the one that can merge the row partials itself).
-template <int DT, int NQ>
-static bool colsum_is_staged(const Shape &s) {
-  if (DT != CKV_BF16) return false;
-  return s.WT >= 1 && s.WT <= kMaxWindowTiles && NQ % s.WT == 0;
-}
-
 template <int DT, int DH, int NQ>
 static void launch_colsum(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 block, hipStream_t stream) {
   if constexpr (DT == CKV_BF16) {
@@ -1205,7 +1205,7 @@ static hipError_t launch_scores_t(const Shape &s, ScoreArgs &a, bool need_lse, b
 #define CKV_LAUNCH_NQ(NQ)                                                          \
   case NQ:                                                                         \
     if constexpr (NQ >= NQ_LO && NQ <= NQ_HI) {                                    \
-      a.lse_from_part = need_lse && need_scores && colsum_is_staged<DT, NQ>(s);     \
+      a.lse_from_part = need_lse && need_scores;                                   \
       if (need_lse) launch_rowstats<DT, DH, NQ>(s, a, grid, block, stream);        \
       if (need_scores) launch_colsum<DT, DH, NQ>(s, a, grid, block, stream);       \
       break;                                                                       \
