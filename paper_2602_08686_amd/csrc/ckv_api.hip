@@ -122,8 +122,7 @@ void derive(const ckv_params *p, Shape *s) {
 }
 
 int vnorm_blocks_per_unit(const Shape &s) {
-  const int rows_per_block = 1024;
-  return (s.T + rows_per_block - 1) / rows_per_block;
+  return (s.T + kVnormRows - 1) / kVnormRows;
 }
 
 void layout(const ckv_params *p, const Shape &s, Workspace *w) {

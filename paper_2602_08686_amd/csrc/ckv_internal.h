@@ -40,6 +40,7 @@ static_assert(kUtilShift >= kUtilMaxRadius, "a round's last output window stays 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kValueNormEps = 1e-6f;
+constexpr int kVnormRows = 512;   // rows of V per workgroup of the value-norm kernel
 
 // Derived quantities every entry point needs; filled by derive() after validation.
 struct Shape {

@@ -28,6 +28,7 @@ __global__ void __launch_bounds__(256) alpha_accumulate_kernel(AlphaArgs a) {
     const int t = (blockIdx.x * 256 + threadIdx.x) * 4;
     if (t >= a.T) return;
     f32x4_s acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 8
     for (int h = 0; h < a.Hq; ++h) acc += *reinterpret_cast<const f32x4_s *>(s + (size_t)h * a.T + t);
     f32x4_s cur = *reinterpret_cast<const f32x4_s *>(al + t);
 #pragma unroll
@@ -37,6 +38,7 @@ __global__ void __launch_bounds__(256) alpha_accumulate_kernel(AlphaArgs a) {
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= a.T) return;
     float acc = 0.0f;
+#pragma unroll 8
     for (int h = 0; h < a.Hq; ++h) acc += s[(size_t)h * a.T + t];
     al[t] = fmaf(a.weight, acc, al[t]);
   }
@@ -58,11 +60,20 @@ __global__ void __launch_bounds__(kRiskThreads) risk_struct_kernel(RiskArgs a) {
   const int b = blockIdx.x, tid = threadIdx.x;
   const float *al = a.alpha + (size_t)b * a.T;
   double p1 = 0.0, p2 = 0.0;
-  for (int t = tid; t < a.T; t += kRiskThreads) {
-    const double x = (double)al[t];
-    if (x > 0.0) {
-      p1 += x;
-      p2 += x * log(x);
+  // sixteen loads in flight: one at a time, the latency of each was most of the kernel (16384 positions: 17.8 -> 15.0 us, the rest
+  // is the logarithms)
+  constexpr int BATCH = 16;
+  for (int t0 = tid; t0 < a.T; t0 += BATCH * kRiskThreads) {
+    float v[BATCH];
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) v[e] = t0 + e * kRiskThreads < a.T ? al[t0 + e * kRiskThreads] : 0.0f;
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) {
+      const double x = (double)v[e];
+      if (x > 0.0) {
+        p1 += x;
+        p2 += x * log(x);
+      }
     }
   }
   s1[tid] = p1;
@@ -99,6 +110,7 @@ struct SharedUtilArgs {
   int Hkv, G, T, P;
 };
 
+// One position per thread; the KV heads' ratios are read together (up to eight at a time), not one behind the other (6.8 -> 4.8 us).
 __global__ void __launch_bounds__(256) shared_utility_kernel(SharedUtilArgs a) {
   const int b = blockIdx.y, t = blockIdx.x * 256 + threadIdx.x;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -113,9 +125,17 @@ __global__ void __launch_bounds__(256) shared_utility_kernel(SharedUtilArgs a) {
   if (t >= a.P) return;
   const float al = a.alpha[(size_t)b * a.T + t];
   float best = -INFINITY;
-  for (int g = 0; g < a.Hkv; ++g) {
-    const float u = al * a.rho[((size_t)b * a.Hkv + g) * a.T + t];  // u^(l,h) of every head of the group
-    for (int hg = 0; hg < a.G; ++hg) best = fmaxf(best, a.w_row[g * a.G + hg] * u);
+  constexpr int BATCH = 8;
+  for (int g0 = 0; g0 < a.Hkv; g0 += BATCH) {
+    float rho[BATCH];
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) rho[e] = g0 + e < a.Hkv ? a.rho[((size_t)b * a.Hkv + g0 + e) * a.T + t] : 0.0f;
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) {
+      if (g0 + e >= a.Hkv) break;
+      const float u = al * rho[e];  // u^(l,h) of every head of the group
+      for (int hg = 0; hg < a.G; ++hg) best = fmaxf(best, a.w_row[(g0 + e) * a.G + hg] * u);
+    }
   }
   a.utility[(size_t)b * a.P + t] = best;
 }
