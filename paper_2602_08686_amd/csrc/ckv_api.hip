@@ -47,33 +47,41 @@ ckv_status validate(const ckv_params *p) {
   return CKV_OK;
 }
 
-// f32: two workgroups per CU are resident (one with several query tiles of 512-byte rows per wave), so what counts is
-// full rounds of that many. Keys per wave (whole tiles)
-// with the least rounds x (keys + a tile's worth of set-up); the larger of equal ones. The row partials stay within
-// 1 MiB or what ranges of T * units / 8192 keys need, whichever is more, so that a caller's or the library's fixed
-// scratch goes as far as it did.
-// Measured, us, both passes and tables, before (ranges for 2048 workgroups, at least 64 keys) -> now: 1024 keys, 4/4 heads of 64
-// 16.5 -> 12.8; 8192 keys, 32/32 heads of 64 53.4 -> 38.3; 4099 keys, 32/8 heads of 128 70.5 -> 55.6.
-static int64_t f32_keys_per_wave(const Shape &s, int64_t units) {
+// Keys per wave: the split of the key axis. `resident` workgroups run at a time (bf16: one per CU, whose four waves sweep
+// long ranges, since nothing overlaps a workgroup's set-up; f32: two, or one with several query tiles of 512-byte rows
+// per wave), so what counts is full rounds of that many: the least rounds x (keys + set-up), set-up being worth about
+// 192 keys of a bf16 sweep and a tile of an f32 one. bf16 ranges beyond 128 keys are whole four-tile pipeline rounds. The
+// row partials stay within 1 MiB or what the plain even split needs, whichever is more, so that a caller's or the
+// library's fixed scratch goes as far as it did.
+// Measured against the even split alone, us, both passes and tables: bf16, 97280 keys,
+// 24 units 324 -> 226 (264 workgroups became 240), 51200 keys, 40 units 328 -> 210, 5003 keys, 96 units 91.5 -> 65.8; f32
+// (even split for 2048
+// workgroups, at least 64 keys): 1024 keys, 4/4 heads of 64 16.5 -> 12.8; 8192 keys, 32/32 heads of 64 53.4 -> 38.3; 4099
+// keys, 32/8 heads of 128 70.5 -> 55.6.
+static int64_t split_keys(const Shape &s, bool bf16, int64_t units) {
+  const int64_t resident = bf16 || (s.d == 128 && s.NQ >= 2) ? kComputeUnits : 2 * kComputeUnits;
+  const int64_t set_up = bf16 ? 192 : kTile, waves = kScoreWaves * (bf16 ? (int64_t)kComputeUnits : 2048);
   const auto workgroups = [&](int64_t kpw) { return units * ((s.T + kScoreWaves * kpw - 1) / (kScoreWaves * kpw)); };
-  int64_t plain = ((int64_t)s.T * units + kScoreWaves * 2048 - 1) / (kScoreWaves * 2048);
-  plain = (plain + kTile - 1) / kTile * kTile;
+  int64_t plain = ((int64_t)s.T * units + waves - 1) / waves;
+  const int64_t quantum = bf16 && plain > 4 * kTile ? 4 * kTile : kTile;
+  plain = (plain + quantum - 1) / quantum * quantum;
   if (plain < 2 * kTile) plain = 2 * kTile;
   if (plain > 4096) plain = 4096;
   const int64_t part_bytes = (int64_t)s.NQ * kTile * (int64_t)sizeof(float2);  // per workgroup
   const int64_t most = workgroups(plain) * part_bytes > (1 << 20) ? workgroups(plain) : (1 << 20) / part_bytes;
-  const int64_t resident = s.d == 128 && s.NQ >= 2 ? kComputeUnits : 2 * kComputeUnits;
   int64_t best = plain, best_cost = INT64_MAX;
-  for (int64_t kpw = kTile; kpw <= 4096; kpw += kTile) {
+  for (int64_t kpw = bf16 ? 2 * kTile : kTile; kpw <= 4096; kpw += bf16 && kpw >= 4 * kTile ? 4 * kTile : kTile) {
     const int64_t n = workgroups(kpw);
-    const int64_t cost = (n + resident - 1) / resident * (kpw + kTile);
+    const int64_t cost = (n + resident - 1) / resident * (kpw + set_up);
     if (n <= most && cost <= best_cost) {
       best = kpw;
       best_cost = cost;
     }
     if (kpw >= s.T) break;
   }
-  return best;
+  // bf16, no round less: the even split stays (shorter ranges for more of a workgroup's waves: 4096 keys, 512 units 186 -> 192 us)
+  const auto rounds = [&](int64_t kpw) { return (workgroups(kpw) + resident - 1) / resident; };
+  return bf16 && rounds(best) >= rounds(plain) ? plain : best;
 }
 
 void derive(const ckv_params *p, Shape *s) {
@@ -102,20 +110,7 @@ void derive(const ckv_params *p, Shape *s) {
   nq = (nq + s->WT - 1) / s->WT * s->WT;
   s->NQ = nq;
   s->n_groups = (s->n_tiles + nq - 1) / nq;
-  // Split the key axis. The bf16 kernels keep one workgroup per CU busy for the whole launch (their
-  // set-up is not overlapped with anything, so there is one workgroup per CU and its waves sweep long
-  // ranges, a whole number of four-tile pipeline rounds).
-  const int64_t units = (int64_t)s->Bz * s->Hkv * s->n_groups;
-  int64_t kpw;
-  if (p->dtype == CKV_BF16) {
-    kpw = ((int64_t)s->T * units + kScoreWaves * kComputeUnits - 1) / (kScoreWaves * kComputeUnits);
-    const int64_t quantum = kpw > 4 * kTile ? 4 * kTile : kTile;
-    kpw = (kpw + quantum - 1) / quantum * quantum;
-    if (kpw < 2 * kTile) kpw = 2 * kTile;
-    if (kpw > 4096) kpw = 4096;
-  } else {
-    kpw = f32_keys_per_wave(*s, units);
-  }
+  const int64_t kpw = split_keys(*s, p->dtype == CKV_BF16, (int64_t)s->Bz * s->Hkv * s->n_groups);
   s->keys_per_wave = (int)kpw;
   s->n_chunks = (int)((s->T + kScoreWaves * kpw - 1) / (kScoreWaves * kpw));
   s->scale = p->softmax_scale > 0.0f ? p->softmax_scale : 1.0f / sqrtf((float)s->d);

@@ -28,6 +28,8 @@ CASES = [
     (_w("f32", 1, 4, 2, 64, 1002, 7, MAX, 15, 100), False), (_w("bf16", 1, 4, 2, 128, 1501, 32, AVG, 19, 100), False),
     (_w("bf16", 1, 8, 1, 128, 40003, 32, AVG, 7, 200), False),   # eight tiles per wave, tens of partials per row
     (_w("bf16", 1, 4, 1, 64, 30002, 64, MAX, 7, 200), False),
+    (_w("bf16", 3, 16, 8, 64, 2111, 32, AVG, 7, 100), False),    # 24 units: the even split would take 264 workgroups
+    (_w("bf16", 16, 16, 16, 64, 1111, 32, MAX, 5, 100), False),  # as many units as CUs
     (_w("f32", 2, 8, 4, 128, 8193, 32, AVG, 7, 200), False),     # f32 rows of 512 bytes: two query tiles per wave
     (_w("f32", 1, 3, 1, 128, 3001, 64, MAX, 5, 200), False), (_w("f32", 1, 2, 1, 128, 1000, 128, AVG, 7, 200), False),
 ]
