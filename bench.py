@@ -305,7 +305,7 @@ def decode_bench(args, w, n_layers, torch, B, wl) -> int:
                    "seq_len": w.seq_len, "budget_per_kv_head": w.budget, "kept_rows_per_layer": kept,
                    "algorithmic_bytes_per_layer": int(compact_bytes), "launch": "HIP graph replay",
                    "ms_per_step_eager_launches": round(ms_eager, 4)},
-        "roofline": {"bound": "hbm", "kernel": "decode_partial_kernel (full cache)", "achieved": round(full_gbs, 1),
+        "roofline": {"bound": "hbm", "kernel": "decode_mfma_kernel (full cache)", "achieved": round(full_gbs, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(full_gbs / HBM_PEAK_GBS, 4), "traffic": None,
                      "ms_per_launch": round(ms_full, 4), "discarded_mass_ms": round(ms_mass, 4),
                      "compact_cache_frac_of_hbm_peak": round(value / HBM_PEAK_GBS, 4)},

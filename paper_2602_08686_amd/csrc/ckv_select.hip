@@ -619,8 +619,8 @@ __device__ __forceinline__ void digit_histogram(int *hist, const int (&key)[NK],
 }
 
 // ---------------------------------------------------------------------------------------------
-// Split select: long rows whose budgets are so large that slices could drop few keys. The same slices, one
-// workgroup each; five launches walk three digits of the key (11, 10 and 10 bits: slices merge their histograms
+// Split select: long rows whose budgets are so large that slices could drop few keys. Slices of 8192
+// positions, one workgroup each; five launches walk three digits of the key (11, 10 and 10 bits: slices merge their histograms
 // into the unit's in global memory with integer atomics), the slices' counts of keys above / equal to the
 // threshold, and the ranked write. Every workgroup derives the threshold digits from
 // the merged histograms itself (4096 integers per unit), which saves the launches in between.
