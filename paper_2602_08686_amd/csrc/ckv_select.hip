@@ -915,6 +915,8 @@ static int slice_region(const Shape &s, int cap, int limit) {
 // Slices pay where they drop most keys and neither kernel leaves the list (by the nominal budget, so with room for
 // heads that have more than their share). Slices + merge against the split selection, us, 32 units: 128k positions, budget
 // 512: 17.0 / 41.1, 1024: 19.5 / 41.7, 2048: 24.7 / 41.7, 4096: 54.0 / 42.1; 64k, 1024: 18.0 / 28.0, 4096: 49.8 / 28.3.
+// With budgets that differ by head (the largest decides: its merge works on the most pairs) 512 keeps its lead (24 / 31 in
+// a trace of whole layers) and 2048 is even (48 / 47).
 static bool slices_pay(const Shape &s, int budget) {
   const int limit = slice_limit(s, budget);
   return budget - s.W <= 3072 && (int64_t)slices(s, limit) * max(0, min(limit, budget - s.W)) <= 32768;
