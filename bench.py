@@ -396,6 +396,9 @@ def main() -> int:
     # a whole model at the end of prefill can queue them on more than one stream: the short, latency-bound
     # kernels of one layer (selection, fix-up, gather) and the ends of its scans then overlap the next layer's
     # scan. All streams have the default priority.
+    # The inputs are still being made on the default stream, and outputs and scratch lie in blocks that its temporaries
+    # gave back: nothing may run beside it before it is through.
+    torch.cuda.synchronize()
     side_streams = [torch.cuda.Stream() for _ in range(args.streams)] if args.streams > 1 else None
 
     def time_whole_pass(prm, lse, steps, warmup, fused=True, streams=None):
