@@ -614,15 +614,17 @@ static void launch_decode_bf16(const DecodeArgs &a, const DecodePlan &p, int row
 
 template <int DH, int RQ>
 static void launch_decode_f32(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
-  if (p.n_chunks == 1) {
-    if constexpr (RQ <= 2)
+  if constexpr (RQ <= 2) {
+    if (p.n_chunks == 1) {
       hipLaunchKernelGGL((decode_partial_kernel<DH, RQ, 16, 2, true>), dim3(1, (unsigned)p.grid_y),
                          dim3(16 * kWave), 0, stream, a);
-    return;
+      return;
+    }
   }
   hipLaunchKernelGGL((decode_partial_kernel<DH, RQ, kDecodeWaves, 4, false>), dim3(p.n_chunks, (unsigned)p.grid_y),
                      dim3(kDecodeThreads), 0, stream, a);
-  hipLaunchKernelGGL((decode_merge_kernel<DH, RQ, false>), dim3((unsigned)rows), dim3(DH), 0, stream, a);
+  if (p.n_chunks > 1)  // one chunk: the workgroups wrote the results
+    hipLaunchKernelGGL((decode_merge_kernel<DH, RQ, false>), dim3((unsigned)rows), dim3(DH), 0, stream, a);
 }
 
 template <int DH>
