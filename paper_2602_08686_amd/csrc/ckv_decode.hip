@@ -22,6 +22,8 @@
 //
 // f32 (decode_partial_kernel): dot products on the vector ALUs, a 16-byte piece of a row per lane, online softmax in the
 // log2 domain, the query heads of a group sharing each row.
+#include <type_traits>
+
 #include "ckv_internal.h"
 
 namespace ckv {
@@ -375,77 +377,107 @@ __global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a)
 
   float top = -INFINITY, sum = 0.0f;  // of column m: the running maximum (the wave's), this lane's share of the sum
   f32x4_dec acc[VE];                  // element e: D[4 quarter + r][column m] = component VE (4 quarter + r) + e
+  // WITH_INFINITIES: infinite and NaN components of V by themselves, times one where the weight is above zero (the second and
+  // third term of a weight may be zero, and zero times infinity is none of the results that the weight itself would give).
+  auto sweep = [&](auto with_infinities) {
+    constexpr bool WITH_INFINITIES = decltype(with_infinities)::value;
+    top = -INFINITY;
+    sum = 0.0f;
 #pragma unroll
-  for (int e = 0; e < VE; ++e) acc[e] = f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f};
-  for (int base = base0; base < r1; base += NW * kBlockRows) {
-    const int next = base + NW * kBlockRows;
-    f32x4_dec s2[2];
+    for (int e = 0; e < VE; ++e) acc[e] = f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int base = base0; base < r1; base += NW * kBlockRows) {
+      const int next = base + NW * kBlockRows;
+      f32x4_dec s2[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {  // two chains per tile: half the truncated additions
-      f32x4_dec half[2] = {f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f}, f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f}};
+      for (int t = 0; t < 2; ++t) {  // two chains per tile: half the truncated additions
+        f32x4_dec half[2] = {f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f}, f32x4_dec{0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
-      for (int s = 0; s < STEPS; ++s) mma16(half[s & 1], kraw[t][s], qf[s]);
-      s2[t] = half[0] + half[1];
-    }
-    if (next < r1) load_k(next, r1);
-    float z[8];  // logits (log2 domain) of rows 16 (j / 4) + 4 quarter + j % 4
-#pragma unroll
-    for (int j = 0; j < 8; ++j) z[j] = s2[j / 4][j % 4] * a.scale2;
-    if (base + kBlockRows > r1) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (base + 16 * (j / 4) + 4 * quarter + j % 4 >= r1) {
-          z[j] = -INFINITY;
-#pragma unroll
-          for (int w = 0; w < VW; ++w) vraw[j][w] = 0u;  // weight 0 times whatever is there must be 0
-        }
-    }
-    float mx = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
-    mx = over_quarters(mx, [](float p, float q) { return fmaxf(p, q); });
-    if (__any(mx > top)) {  // after the first blocks a new maximum is rare
-      const float t_new = fmaxf(top, mx);
-      const float keep = exp2_diff(top, t_new == -INFINITY ? 0.0f : t_new);
-      sum *= keep;
-#pragma unroll
-      for (int e = 0; e < VE; ++e) acc[e] *= keep;
-      top = t_new;
-    }
-    const float ref = top == -INFINITY ? 0.0f : top;
-    // weights, and their three bf16 terms: truncations, each of what the ones before left
-    u32x4_d w1, w2, w3;
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      uint32_t t1[2], t2[2], t3[2];
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        const float p = __builtin_amdgcn_exp2f(z[2 * h + x] - ref);
-        sum += p;
-        t1[x] = __float_as_uint(p);
-        const float r = p - __uint_as_float(t1[x] & 0xffff0000u);
-        t2[x] = __float_as_uint(r);
-        t3[x] = __float_as_uint(r - __uint_as_float(t2[x] & 0xffff0000u));
+        for (int s = 0; s < STEPS; ++s) mma16(half[s & 1], kraw[t][s], qf[s]);
+        s2[t] = half[0] + half[1];
       }
-      w1[h] = high_halves(t1[0], t1[1]);
-      w2[h] = high_halves(t2[0], t2[1]);
-      w3[h] = high_halves(t3[0], t3[1]);
+      if (next < r1) load_k(next, r1);
+      float z[8];  // logits (log2 domain) of rows 16 (j / 4) + 4 quarter + j % 4
+#pragma unroll
+      for (int j = 0; j < 8; ++j) z[j] = s2[j / 4][j % 4] * a.scale2;
+      if (base + kBlockRows > r1) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (base + 16 * (j / 4) + 4 * quarter + j % 4 >= r1) {
+            z[j] = -INFINITY;
+#pragma unroll
+            for (int w = 0; w < VW; ++w) vraw[j][w] = 0u;  // weight 0 times whatever is there must be 0
+          }
+      }
+      float mx = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
+      mx = over_quarters(mx, [](float p, float q) { return fmaxf(p, q); });
+      if (__any(mx > top)) {  // after the first blocks a new maximum is rare
+        const float t_new = fmaxf(top, mx);
+        const float keep = exp2_diff(top, t_new == -INFINITY ? 0.0f : t_new);
+        sum *= keep;
+#pragma unroll
+        for (int e = 0; e < VE; ++e) acc[e] *= keep;
+        top = t_new;
+      }
+      const float ref = top == -INFINITY ? 0.0f : top;
+      // weights, and their three bf16 terms: truncations, each of what the ones before left
+      u32x4_d w0, w1, w2, w3;
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        uint32_t t0[2], t1[2], t2[2], t3[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const float p = __builtin_amdgcn_exp2f(z[2 * h + x] - ref);
+          sum += p;
+          t1[x] = __float_as_uint(p);
+          const float r = p - __uint_as_float(t1[x] & 0xffff0000u);
+          t2[x] = __float_as_uint(r);
+          t3[x] = __float_as_uint(r - __uint_as_float(t2[x] & 0xffff0000u));
+          if (WITH_INFINITIES) t0[x] = z[2 * h + x] - ref > -150.0f ? 0x3f800000u : 0u;  // 2^-150 rounds to zero
+        }
+        w1[h] = high_halves(t1[0], t1[1]);
+        w2[h] = high_halves(t2[0], t2[1]);
+        w3[h] = high_halves(t3[0], t3[1]);
+        if (WITH_INFINITIES) w0[h] = high_halves(t0[0], t0[1]);
+      }
+      u32x4_d vt[VE];  // V transposed: component e of the lane's piece, its eight rows
+#pragma unroll
+      for (int e = 0; e < VE; ++e)
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          vt[e][h] = e % 2 ? high_halves(vraw[2 * h][e / 2], vraw[2 * h + 1][e / 2]) : low_halves(vraw[2 * h][e / 2], vraw[2 * h + 1][e / 2]);
+      if (next < r1) load_v(next, r1);
+      // the block's sum by itself, then one rounded addition: the matrix cores truncate what they add to an accumulator
+      // that is larger than the products, and over a long sweep that adds up (7e-7 instead of 3e-7 after 8192 rows)
+#pragma unroll
+      for (int e = 0; e < VE; ++e) {
+        f32x4_dec head = {0.0f, 0.0f, 0.0f, 0.0f}, rest = head;
+        if (WITH_INFINITIES) {
+          u32x4_d beyond;  // the components that are not finite, the others zero
+#pragma unroll
+          for (int h = 0; h < 4; ++h) {
+            const uint32_t x = vt[e][h];
+            beyond[h] = ((x & 0x7f800000u) == 0x7f800000u ? x & 0xffff0000u : 0u) | ((x & 0x7f80u) == 0x7f80u ? x & 0xffffu : 0u);
+            vt[e][h] = x ^ beyond[h];
+          }
+          mma16(rest, beyond, w0);
+        }
+        mma16(head, vt[e], w1);
+        mma16(rest, vt[e], w3);
+        mma16(rest, vt[e], w2);
+        acc[e] += head + rest;
+      }
     }
-    u32x4_d vt[VE];  // V transposed: component e of the lane's piece, its eight rows
+  };
+  sweep(std::false_type{});
+  bool undefined = false;
 #pragma unroll
-    for (int e = 0; e < VE; ++e)
+  for (int e = 0; e < VE; ++e)
 #pragma unroll
-      for (int h = 0; h < 4; ++h)
-        vt[e][h] = e % 2 ? high_halves(vraw[2 * h][e / 2], vraw[2 * h + 1][e / 2]) : low_halves(vraw[2 * h][e / 2], vraw[2 * h + 1][e / 2]);
-    if (next < r1) load_v(next, r1);
-    // the block's sum by itself, then one rounded addition: the matrix cores truncate what they add to an accumulator
-    // that is larger than the products, and over a long sweep that adds up (7e-7 instead of 3e-7 after 8192 rows)
-#pragma unroll
-    for (int e = 0; e < VE; ++e) {
-      f32x4_dec head = {0.0f, 0.0f, 0.0f, 0.0f}, rest = head;
-      mma16(head, vt[e], w1);
-      mma16(rest, vt[e], w3);
-      mma16(rest, vt[e], w2);
-      acc[e] += head + rest;
-    }
+    for (int r = 0; r < 4; ++r) undefined |= acc[e][r] != acc[e][r];
+  if (__any(undefined)) {  // V has components that are not finite (or the logits have): once more, for what they give
+    load_k(base0, r1);
+    load_v(base0, r1);
+    sweep(std::true_type{});
   }
   sum = over_quarters(sum, [](float p, float q) { return p + q; });
 
