@@ -316,7 +316,8 @@ ckv_status ckv_map_table_depth(const float *table, int32_t n_layers_src, int32_t
  *     z[j]   = softmax_scale * <q_dec[b,h,i,:], k_rows[b,g,j,:]>          j < n_valid(b,g)
  *     lse    = log sum_j exp z[j]
  *     out    = sum_j exp(z[j] - lse) * v_rows[b,g,j,:]
- * with n_valid(b,g) = count[b,g] clamped to [0, n_rows] (n_rows if count is NULL). Over the compact
+ * with n_valid(b,g) = count[b,g] clamped to [0, n_rows] (n_rows if count is NULL); rows behind n_valid are
+ * not read (they need not be mapped). Over the compact
  * cache written by ckv_compact_kv (strides {Hkv*cap*d, cap*d, d}, n_rows = cap, the call's count) this
  * is the compressed row of Proposition 1, p~ = p restricted to the retained set and renormalised,
  * applied to V; over the full cache (params' k_stride / v_stride, n_rows = T, count = NULL) it is the

@@ -365,15 +365,15 @@ __global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a)
     }
   };
 
-  // the first block is asked for before the count is known (the rows exist; what lies beyond the count is masked below)
-  if (base0 < r_end) {
-    load_k(base0, r_end);
-    load_v(base0, r_end);
-  }
+  // nothing behind the count is read: its rows need not even be mapped
   int n_valid = a.n_rows;
   if (a.count) n_valid = min(max(a.count[unit], 0), a.n_rows);
   const int r1 = min(r_end, n_valid);
   if (r0 >= r1 && !single) return;  // the merge reads the chunks below n_valid only
+  if (base0 < r1) {
+    load_k(base0, r1);
+    load_v(base0, r1);
+  }
 
   float top = -INFINITY, sum = 0.0f;  // of column m: the running maximum (the wave's), this lane's share of the sum
   f32x4_dec acc[VE];                  // element e: D[4 quarter + r][column m] = component VE (4 quarter + r) + e
@@ -399,14 +399,10 @@ __global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a)
       float z[8];  // logits (log2 domain) of rows 16 (j / 4) + 4 quarter + j % 4
 #pragma unroll
       for (int j = 0; j < 8; ++j) z[j] = s2[j / 4][j % 4] * a.scale2;
-      if (base + kBlockRows > r1) {
+      if (base + kBlockRows > r1) {  // rows that are not there were not read either: zeros
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          if (base + 16 * (j / 4) + 4 * quarter + j % 4 >= r1) {
-            z[j] = -INFINITY;
-#pragma unroll
-            for (int w = 0; w < VW; ++w) vraw[j][w] = 0u;  // weight 0 times whatever is there must be 0
-          }
+          if (base + 16 * (j / 4) + 4 * quarter + j % 4 >= r1) z[j] = -INFINITY;
       }
       float mx = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
       mx = over_quarters(mx, [](float p, float q) { return fmaxf(p, q); });
