@@ -182,7 +182,7 @@ __device__ __forceinline__ int find_threshold(const int (&key)[N], int low, int 
     if (in_bin <= kFewKeys) {
 #pragma unroll
       for (int q = 0; q < N; ++q)
-        if (key[q] >= low && ((uint32_t)(key[q] - low) >> rem) == prefix) sh.few[atomicAdd(&sh.n_few, 1) & (kFewKeys - 1)] = key[q];
+        if (key[q] >= low && ((uint32_t)(key[q] - low) >> rem) == prefix) sh.few[atomicAdd(&sh.n_few, 1)] = key[q];
       __syncthreads();
       const int my = lane < in_bin ? sh.few[lane] : -1;
       int above = 0, equal = 0;
@@ -192,7 +192,7 @@ __device__ __forceinline__ int find_threshold(const int (&key)[N], int low, int 
         above += (other.x > my) + (y && other.y > my) + (z && other.z > my) + (w && other.w > my);
         equal += (other.x == my) + (y && other.y == my) + (z && other.z == my) + (w && other.w == my);
       }
-      const int src = (__ffsll((long long)__ballot(lane < in_bin && above < k && k <= above + equal)) - 1) & (kWave - 1);
+      const int src = __ffsll((long long)__ballot(lane < in_bin && above < k && k <= above + equal)) - 1;
       k -= (int)lane_value((uint32_t)above, src);
       return (int)lane_value((uint32_t)my, src);
     }
@@ -382,7 +382,9 @@ __device__ __forceinline__ int select_keys(const int (&key)[NK], int kp, SelectS
     return emit_keys<NK, NT>(sh, key, thr, k, kp, 0, 0, write, tid, lane, wave);
   }
 
-  // -- 3: the list's keys; the threshold among them
+  // -- 3: the list's keys, read again; the threshold among them. The first read found all of them between the bound and the
+  // maximum. They are held there: the bins, the ranks and the number kept depend on it, and a caller may be writing its
+  // input meanwhile (the result is then anybody's guess, but it stays inside its buffers).
   constexpr int NQ = Shared::NQ;
   int slot[NQ], lk[NQ];
 #pragma unroll
@@ -391,7 +393,7 @@ __device__ __forceinline__ int select_keys(const int (&key)[NK], int kp, SelectS
     lk[q] = -1;
     if (q * NT + tid < m) {
       slot[q] = sh.list[q * NT + tid];
-      lk[q] = reload(slot[q]);
+      lk[q] = min(max(reload(slot[q]), bound), mx);
     }
   }
   thr = find_threshold<NQ, NT>(lk, bound, shift, k, sh, tid, lane, wave);
@@ -414,9 +416,7 @@ __device__ __forceinline__ int select_keys(const int (&key)[NK], int kp, SelectS
   for (int q = 0; q < NQ; ++q) {
     const int g = (int)gt_before[q] + (int)lane_value((uint32_t)gx, q * NW + wave);
     const int e = (int)eq_before[q] + (int)lane_value((uint32_t)qx, q * NW + wave);
-    // the list's keys were read a second time: ranks stay inside the quota also where somebody writes the input meanwhile
-    const int r = g + min(e, k);
-    if ((lk[q] > thr || (lk[q] == thr && e < k)) && r < kp) write(r, slot[q], lk[q]);
+    if (lk[q] > thr || (lk[q] == thr && e < k)) write(g + min(e, k), slot[q], lk[q]);
   }
   return kp;
 }

@@ -167,12 +167,13 @@ void launch(dim3 grid, dim3 block, const std::function<void()> &body) {
       block_idx = dim3(x, y);
       fibers.assign(n, Fiber());
       waves.assign((n + 63) / 64, Wave());
+      if (hook) hook((int)(x + y * grid.x), -1);
       run_block(n);
     }
 }
 }  // namespace emu
 
-// A call before each barrier of a workgroup lets go (nullptr: none), for tests that change memory meanwhile.
+// A call before a workgroup starts (barrier -1) and before each of its barriers lets go (nullptr: none), for tests that change memory meanwhile.
 extern "C" void emu_set_hook(void (*h)(int block, int barrier)) { emu::hook = h; }
 // x with lane `lane` replaced by the wave-uniform v.
 extern "C" int emu_write_lane(int v, int lane, int x) __asm("llvm.amdgcn.writelane.i32");

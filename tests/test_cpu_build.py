@@ -1,5 +1,6 @@
 """Kernels on the host CPU, where an access out of bounds ends a child process instead of a GPU: decode attention reads no
-row behind the count (the memory there has no access)."""
+row behind the count (the memory there has no access), and the selection stays inside its buffers whatever another stream
+writes over its input meanwhile."""
 import ctypes
 import multiprocessing
 
@@ -72,3 +73,52 @@ def _decode_before_a_fence(path, dtype, d, heads, n_q, n_rows, counts):
 ])
 def test_decode_reads_no_row_behind_the_count(lib_path, dtype, d, heads, n_q, n_rows, counts):
     in_child(_decode_before_a_fence, lib_path, dtype, d, heads, n_q, n_rows, counts)
+
+
+def _select_while_the_input_changes(path, P, nominal, budgets, with_workspace, one_read):
+    lib = cpu.load(path)
+    W, Hkv, guard = 4, 2, 4096
+    rng = np.random.default_rng(P)
+    before = (1.0 + 0.08 * np.abs(rng.standard_normal((1, Hkv, P)))).astype(np.float32)
+    u = before.copy()
+    cap = min(P + W, max(nominal * Hkv - W, max(budgets)))
+    p = B.make_params(batch=1, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=P + W, window=W, dtype="bf16",
+                      pool=B.POOL_NONE, pool_kernel=1, budget=nominal, cap=cap)
+    need = lib.ckv_workspace_bytes(ctypes.byref(p))
+    ws = cpu.aligned(need) if with_workspace else None
+    budget, tau = np.array([budgets], np.int32), np.zeros(1, np.float32)
+    changes = {"zeros": np.zeros_like(u), "large": np.full_like(u, 3e38), "nan": np.full_like(u, np.nan),
+               "mixed": np.where(rng.random(u.shape) < 0.5, u, 1e30 * u).astype(np.float32)}
+    for name, after in changes.items():
+        for at in (0, 3):  # barriers: behind the first read, and inside the search on one of the forms that read several times
+            def write(block, barrier):
+                if barrier in (-1, at):
+                    u[:] = before if barrier < 0 else after
+
+            hook = cpu.HOOK(write)
+            lib.emu_set_hook(hook)
+            idx, count = np.full(2 * guard + Hkv * cap, -1, np.int32), np.full(2 * guard + Hkv, -1, np.int32)
+            st = lib.ckv_select_topk(ctypes.byref(p), cpu.ptr(u), cpu.ptr(budget), cpu.ptr(tau), cpu.ptr(idx[guard:]), cpu.ptr(count[guard:]),
+                                     cpu.ptr(ws), ctypes.c_size_t(need), None)
+            lib.emu_set_hook(ctypes.cast(None, cpu.HOOK))
+            assert st == B.CKV_OK
+            for a in (idx, count):
+                assert (a[:guard] == -1).all() and (a[-guard:] == -1).all(), (name, at)
+            lists, counts = idx[guard:-guard].reshape(Hkv, cap), count[guard:-guard]
+            assert ((lists >= -1) & (lists < P + W)).all(), (name, at)
+            for h in range(Hkv):
+                assert W <= counts[h] <= min(cap, budgets[h]) and (lists[h, counts[h]:] == -1).all(), (name, at)
+                if one_read:  # the decisions rest on one read: whatever it saw, every entry that is counted was written
+                    assert (lists[h, :counts[h]] >= 0).all() and counts[h] == budgets[h], (name, at)
+
+
+@pytest.mark.parametrize("P,nominal,budgets,with_workspace,one_read", [
+    (8200, 200, [200, 380], False, True),       # 16 positions per thread, the list
+    (20001, 500, [500, 900], False, True),      # 32
+    (33000, 1600, [1600, 700], False, True),    # 64
+    (35001, 1600, [1600, 700], True, True),     # slices of 16 per thread, merge
+    (35001, 4000, [4004, 700], True, False),    # split: several reads
+    (66001, 300, [300, 80], False, False),      # streaming: several reads
+])
+def test_selection_stays_inside_its_buffers_while_the_input_changes(lib_path, P, nominal, budgets, with_workspace, one_read):
+    in_child(_select_while_the_input_changes, lib_path, P, nominal, budgets, with_workspace, one_read)
