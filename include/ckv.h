@@ -88,9 +88,13 @@ typedef struct {
   uint32_t flags;         /* CKV_FLAG_*                                                            */
 } ckv_params;
 
-/* Bytes of scratch that ckv_window_scores and ckv_select_topk need for `params` (the larger of the
- * two; the calls of one layer may share one buffer because they run in stream order).
- * Returns 0 if `params` is NULL or invalid. The buffer must be 256-byte aligned. */
+/* Bytes of scratch for the calls of one layer with `params` (they may share one buffer because they run in stream
+ * order). Returns 0 if `params` is NULL or invalid. The buffer must be 256-byte aligned.
+ * Beyond 32768 prefix positions the figure depends on budget_per_kv_head and cap too: for small budgets the selection
+ * keeps up to min(cap, 16384) pairs of 8 bytes per slice of 8192 or 16384 positions, 133 MB at batch 16, 8 KV heads, 131072
+ * positions, budget 2048. A buffer of what this returns for any one budget and cap serves every other of the same
+ * shape (a caller with budgets that differ by layer needs one): where it has no room for the pairs, the selection takes its
+ * form with 16 KiB per unit. */
 size_t ckv_workspace_bytes(const ckv_params *params);
 
 /*
@@ -222,10 +226,10 @@ ckv_status ckv_window_utility(const ckv_params *params, const void *q_win, const
  *   idx      out  [Bz,Hkv,cap] int32; entries at and beyond count[b,g] are not written
  *   count    out  [Bz,Hkv] int32
  *   workspace     optional (NULL allowed). Up to 32768 prefix positions it is not used. Beyond that,
- *                 with ckv_workspace_bytes(params) bytes (256-byte aligned; CKV_EWORKSPACE if
- *                 misaligned or smaller) a unit's positions are split over several workgroups, which is
- *                 several times faster for long contexts with few (batch, head) units; the result is
- *                 the same either way. Contents on entry are ignored.
+ *                 with ckv_workspace_bytes() bytes for this shape and any budget (256-byte aligned;
+ *                 CKV_EWORKSPACE if misaligned or smaller) a unit's positions are split over several
+ *                 workgroups, which is several times faster for long contexts with few (batch, head)
+ *                 units; the result is the same either way. Contents on entry are ignored.
  */
 ckv_status ckv_select_topk(const ckv_params *params, const float *utility, const int32_t *budget,
                            const float *tau, int32_t *idx, int32_t *count, void *workspace,

@@ -134,12 +134,15 @@ void layout(const ckv_params *p, const Shape &s, Workspace *w) {
   off = align256(off + w->vsum_bytes);
   w->select_off = off;
   w->select_bytes = select_workspace_bytes(p, s);
+  // Asked of every call is what the shape alone decides, so that one buffer serves a shape with any budget (prefixes
+  // of a length that is no multiple of four: nothing for the selection, which takes them with any workspace).
+  w->least = align256(off + (s.P % 4 == 0 ? select_split_bytes(s) : 0));
   off = align256(off + w->select_bytes);
   w->total = off;
 }
 
 static ckv_status workspace_ok(const Workspace &w, const void *ws, size_t bytes) {
-  if (!ws || ((uintptr_t)ws & 255) || bytes < w.total) return CKV_EWORKSPACE;
+  if (!ws || ((uintptr_t)ws & 255) || bytes < w.least) return CKV_EWORKSPACE;
   return CKV_OK;
 }
 
@@ -350,13 +353,12 @@ extern "C" ckv_status ckv_select_topk(const ckv_params *params, const float *uti
   Workspace w;
   layout(params, s, &w);
   bool split = workspace && w.select_bytes > 0;
-  if (split && workspace_ok(w, workspace, workspace_bytes) != CKV_OK) {
-    // rows of a length that is no multiple of four have always been taken with any workspace
+  if (split && (((uintptr_t)workspace & 255) || workspace_bytes < w.select_off + select_split_bytes(s))) {
     if (s.P % 4 == 0) return CKV_EWORKSPACE;
     split = false;
   }
   if (launch_select(params, s, utility, budget, tau, idx, count, split ? (char *)workspace + w.select_off : nullptr,
-                    (hipStream_t)hip_stream) != hipSuccess)
+                    split ? workspace_bytes - w.select_off : 0, (hipStream_t)hip_stream) != hipSuccess)
     return CKV_EHIP;
   return CKV_OK;
 }

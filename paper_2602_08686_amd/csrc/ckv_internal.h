@@ -94,7 +94,8 @@ struct Workspace {
   size_t part_off, part_bytes;   // float2 [units][groups][n_chunks][NQ*32] row-stat partials
   size_t lse_off, lse_bytes;     // float  [Bz][Hq][W]
   size_t vsum_off, vsum_bytes;   // float  [units][vnorm blocks] partial sums of value norms
-  size_t select_off, select_bytes;  // int: the split selection's merged histograms, slice counts, thresholds
+  size_t select_off, select_bytes;  // the long selection's: slices' pairs, or the split's histograms, counts and thresholds
+  size_t least;  // what a call has to be given: less than total where total has room for the slices' pairs
   size_t total;
 };
 void layout(const ckv_params *p, const Shape &s, Workspace *w);
@@ -125,12 +126,14 @@ hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float 
                                const float *vnorm_ratio, const float *w_head, const float *head_share,
                                const float *t_gate, int n_ent, int n_ppl, const int32_t *risk_bins,
                                float *utility, int32_t *budget, float *tau, hipStream_t stream);
-// ws: nullptr, or select_workspace_bytes() bytes (256-byte aligned) that let long prefixes be split
-// over several workgroups per unit; the result is the same either way.
+// ws: nullptr, or ws_bytes bytes (256-byte aligned), at least select_split_bytes(), that let long prefixes be split
+// over several workgroups per unit; with select_workspace_bytes() it is the form that suits the budget. The
+// result is the same either way. The split's bytes follow from the shape alone, so one buffer serves any budget.
+size_t select_split_bytes(const Shape &s);
 size_t select_workspace_bytes(const ckv_params *p, const Shape &s);
 hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utility,
                          const int32_t *budget, const float *tau, int32_t *idx, int32_t *count,
-                         char *ws, hipStream_t stream);
+                         char *ws, size_t ws_bytes, hipStream_t stream);
 hipError_t launch_gather(const ckv_params *p, const Shape &s, const void *k, const void *v,
                          const int32_t *idx, const int32_t *count, void *k_out, void *v_out,
                          hipStream_t stream, bool shared_list = false);

@@ -924,13 +924,19 @@ static bool slices_pay(const Shape &s, int budget) {
   return budget - s.W <= 3072 && (int64_t)slices(s, limit) * max(0, min(limit, budget - s.W)) <= 32768;
 }
 
-size_t select_workspace_bytes(const ckv_params *p, const Shape &s) {
+size_t select_split_bytes(const Shape &s) {
   if (s.P <= kOneLaunch) return 0;
-  const size_t units = (size_t)s.Bz * s.Hkv;
-  const int limit = slice_limit(s, p->budget_per_kv_head);
-  if (slices_pay(s, p->budget_per_kv_head)) return units * slices(s, limit) * slice_region(s, p->cap, limit) * sizeof(int2);
-  return units * (kSplitHist + slices(s, kSplitSlice) + 16) * sizeof(int);
+  return (size_t)s.Bz * s.Hkv * (kSplitHist + slices(s, kSplitSlice) + 16) * sizeof(int);
 }
+
+// Bytes of the slices' pairs, 0 where slices do not pay.
+static size_t slice_pair_bytes(const ckv_params *p, const Shape &s) {
+  if (s.P <= kOneLaunch || !slices_pay(s, p->budget_per_kv_head)) return 0;
+  const int limit = slice_limit(s, p->budget_per_kv_head);
+  return (size_t)s.Bz * s.Hkv * slices(s, limit) * slice_region(s, p->cap, limit) * sizeof(int2);
+}
+
+size_t select_workspace_bytes(const ckv_params *p, const Shape &s) { return max(select_split_bytes(s), slice_pair_bytes(p, s)); }
 
 template <int NK, int NT>
 static void launch_reg(const SelectArgs &a, int units, hipStream_t stream) {
@@ -939,7 +945,7 @@ static void launch_reg(const SelectArgs &a, int units, hipStream_t stream) {
 
 hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utility,
                          const int32_t *budget, const float *tau, int32_t *idx, int32_t *count,
-                         char *ws, hipStream_t stream) {
+                         char *ws, size_t ws_bytes, hipStream_t stream) {
   SelectArgs a;
   a.utility = utility;
   a.budget = budget;
@@ -950,7 +956,8 @@ hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utili
   a.cap = p->cap;
   const int units = s.Bz * s.Hkv;
   const dim3 block(kSelectThreads);
-  if (ws && s.P > kOneLaunch && slices_pay(s, p->budget_per_kv_head)) {
+  const size_t pair_bytes = slice_pair_bytes(p, s);
+  if (ws && pair_bytes > 0 && ws_bytes >= pair_bytes) {
     SliceArgs sa;
     sa.a = a;
     const int limit = slice_limit(s, p->budget_per_kv_head);

@@ -1,6 +1,6 @@
 """Kernels on the host CPU, where an access out of bounds ends a child process instead of a GPU: decode attention reads no
 row behind the count (the memory there has no access), and the selection stays inside its buffers whatever another stream
-writes over its input meanwhile."""
+writes over its input meanwhile, and with a workspace that was sized for another budget."""
 import ctypes
 import multiprocessing
 
@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import cpu_build as cpu
+import oracle
 from paper_2602_08686_amd import binding as B
 
 pytestmark = pytest.mark.skipif(cpu.CXX is None, reason="no clang++ for the host")
@@ -122,3 +123,33 @@ def _select_while_the_input_changes(path, P, nominal, budgets, with_workspace, o
 ])
 def test_selection_stays_inside_its_buffers_while_the_input_changes(lib_path, P, nominal, budgets, with_workspace, one_read):
     in_child(_select_while_the_input_changes, lib_path, P, nominal, budgets, with_workspace, one_read)
+
+
+def _select_with_the_workspace_of_another_budget(path, P, budgets):
+    lib = cpu.load(path)
+    W, Hkv = 4, 2
+    rng = np.random.default_rng(P)
+    u = np.exp(0.6 * rng.standard_normal((1, Hkv, P))).astype(np.float32)
+    tau = np.zeros(1, np.float32)
+
+    def params(b):
+        return B.make_params(batch=1, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=P + W, window=W, dtype="bf16",
+                             pool=B.POOL_NONE, pool_kernel=1, budget=b, cap=min(P + W, b * Hkv - (Hkv - 1) * W))
+
+    for sized_for in budgets:
+        need = lib.ckv_workspace_bytes(ctypes.byref(params(sized_for)))
+        for b in budgets:
+            p = params(b)
+            ws = cpu.fenced(need)   # a multiple of 256 before a page's end: aligned
+            idx, count = np.full((1, Hkv, p.cap), -1, np.int32), np.zeros((1, Hkv), np.int32)
+            budget = np.array([[b, min(p.cap, b + 7)]], np.int32)
+            st = lib.ckv_select_topk(ctypes.byref(p), cpu.ptr(u), cpu.ptr(budget), cpu.ptr(tau), cpu.ptr(idx), cpu.ptr(count),
+                                     cpu.ptr(ws), ctypes.c_size_t(need), None)
+            assert st == B.CKV_OK, (sized_for, b, st)
+            oi, oc = oracle.select(u, tau, budget, W, p.cap)
+            np.testing.assert_array_equal(count, oc)
+            np.testing.assert_array_equal(idx, oi)
+
+
+def test_one_workspace_serves_every_budget_of_its_shape(lib_path):
+    in_child(_select_with_the_workspace_of_another_budget, lib_path, 40000, (20, 600, 5000))
