@@ -1,6 +1,7 @@
 // C-ABI entry points of libckv: argument validation on the host, then kernel launches.
 // Nothing here allocates or synchronises; every entry point either enqueues all of its kernels on
 // the caller's stream or returns an error before the first launch.
+#include <float.h>
 #include <math.h>
 
 #include <mutex>
@@ -318,7 +319,10 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
     fuse.pool = params->pool;
     const int kernel = params->pool == CKV_POOL_NONE ? 1 : params->pool_kernel;
     fuse.radius = kernel / 2;
+    // rounded down, so that the rest is positive (never zero: an infinite sum stays infinite)
     fuse.inv_kernel = 1.0f / (float)kernel;
+    if ((double)fuse.inv_kernel * kernel > 1.0) fuse.inv_kernel = nextafterf(fuse.inv_kernel, 0.0f);
+    fuse.inv_kernel_rest = fmaxf((float)(1.0 / kernel - (double)fuse.inv_kernel), FLT_MIN);
     if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores_scratch, (char *)workspace, stream,
                              &fuse) != hipSuccess)
       return CKV_EHIP;

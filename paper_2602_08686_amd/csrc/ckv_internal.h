@@ -110,7 +110,7 @@ struct UtilityFusion {
   const float *w_row;  // w_head + layer * Hq
   float *utility;      // [Bz][Hkv][P]
   int pool, radius;
-  float inv_kernel;
+  float inv_kernel, inv_kernel_rest;  // 1 / kernel: the largest float that is not above it, and what that leaves
 };
 hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Workspace &w, const void *q,
                                 const void *k, const float *lse_in, float *lse_out, float *scores,

@@ -48,7 +48,7 @@ struct ScoreArgs {
   const float *w_row;  // w_head + layer * Hq
   float *utility;      // [Bz][Hkv][P]
   int pool, radius;    // pooling mode and radius (kernel / 2, at most kUtilMaxRadius)
-  float inv_kernel;    // 1 / pool_kernel
+  float inv_kernel, inv_kernel_rest;  // 1 / pool_kernel in two terms
 };
 
 template <int DT> struct Mma;
@@ -908,7 +908,9 @@ __device__ __forceinline__ void pooled_group_max(const ScoreArgs &a, const float
       float c = win[hp][4 + e - R];
 #pragma unroll
       for (int d = 1 - R; d <= R; ++d) c = POOL == CKV_POOL_MAX ? fmaxf(c, win[hp][4 + e + d]) : c + win[hp][4 + e + d];
-      if (POOL == CKV_POOL_AVG) c *= a.inv_kernel;
+      // the quotient to the last bit, as the tables kernel's division has it (c times the rounded reciprocal was up to 9 % further
+      // from 64 bits over whole layers: a bias of its own)
+      if (POOL == CKV_POOL_AVG) c = fmaf(c, a.inv_kernel, c * a.inv_kernel_rest);
       // a select, not a branch: heads that do not exist leave the maximum alone
       best[e] = fmaxf(best[e], live ? wg * c : -INFINITY);
     }

@@ -48,3 +48,16 @@ def test_ragged_rows_match_oracle(w, vn):
         np.testing.assert_array_equal(buf.budget.cpu().numpy(), ref["budget"])
         assert_index_sets_match(buf.idx.cpu().numpy(), buf.count.cpu().numpy(), ref["idx"], ref["count"], ref["utility"],
                                 ref["tau"], ref["budget"], w.window)
+
+
+@pytest.mark.parametrize("kernel", [3, 5, 7])
+@pytest.mark.parametrize("T,Hq", [(20011, 8), (20012, 14)])
+def test_one_call_pools_as_exactly_as_the_separate_calls(T, Hq, kernel):
+    """The mean of a window is the quotient to the last bit in both: the same sums, so the same utilities. (A quotient from the two
+    terms of 1 / kernel misses the rounded one only within 2^-24 of a unit in the last place of a tie: one in millions. With the
+    rounded reciprocal alone 17 to 42 % differed.)"""
+    print(f"case T={T} Hq={Hq} kernel={kernel}", flush=True)
+    w = _w("bf16", 2, Hq, 2, 128, T, 32, AVG, kernel, 128, shares=True)
+    t, tabs = wl.make_layer(w, 0, DEV), wl.make_tables(w, DEV)
+    one, separate = (run_gpu(w, t, tabs, fused_utility=f)[1].utility for f in (True, False))
+    assert (one != separate).float().mean().item() <= 1e-5
