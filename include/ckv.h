@@ -91,10 +91,9 @@ typedef struct {
 /* Bytes of scratch for the calls of one layer with `params` (they may share one buffer because they run in stream
  * order). Returns 0 if `params` is NULL or invalid. The buffer must be 256-byte aligned.
  * Beyond 32768 prefix positions the figure depends on budget_per_kv_head and cap too: for small budgets the selection
- * keeps up to min(cap, 16384) pairs of 8 bytes per slice of 8192 or 16384 positions, 133 MB at batch 16, 8 KV heads, 131072
- * positions, budget 2048. A buffer of what this returns for any one budget and cap serves every other of the same
- * shape (a caller with budgets that differ by layer needs one): where it has no room for the pairs, the selection takes its
- * form with 16 KiB per unit. */
+ * keeps (key, position) pairs, up to 512 KiB per (batch, KV head). A buffer of what this returns for any one budget
+ * and cap serves every other of the same shape (a caller with budgets that differ by layer needs one): where it has no
+ * room for the pairs, the selection takes its form with 16 KiB per (batch, KV head). */
 size_t ckv_workspace_bytes(const ckv_params *params);
 
 /*

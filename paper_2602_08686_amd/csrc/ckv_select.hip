@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(NT) select_reg_kernel(SelectArgs a) {
 // is among them) as (key, position) pairs in the workspace, in position order, padded with "no candidate" to
 // a length that both kernels know from the budget; one workgroup per unit then selects among the slices' pairs.
 // No counter has to be cleared beforehand and no workgroup waits for another. Worth it while the slices drop
-// most keys: slices_pay() draws the line.
+// most keys: plan_slices() draws the line.
 // ---------------------------------------------------------------------------------------------
 struct SliceArgs {
   SelectArgs a;
@@ -480,7 +480,7 @@ __global__ void __launch_bounds__(kSelectThreads) select_slice_kernel(SliceArgs 
   int key[NK];
   load_keys<NK, kSelectThreads>(u, min(a.P, base + sa.slice), base, tau, key, tid);
   const int kp = prefix_quota(a, unit);
-  if (kp <= 0) return;
+  if (kp <= 0 || slice_pairs(kp, sa.slice) > sa.region) return;
   int2 *out = sa.pairs + (size_t)blockIdx.x * sa.region;
   const int kept = select_keys<NK, kSelectThreads>(
       key, kp, sh, [&](int slot) { return key_of(u[base + slot], tau); },
@@ -518,12 +518,14 @@ __device__ __forceinline__ int merge_slices(const int2 *pairs, int S, int region
       key, kp, sh, [&](int slot) { return at(slot).x; }, [&](int rank, int slot, int) { out[rank] = at(slot).y; }, tid, lane, wave);
 }
 
-constexpr int kMergeKeys = 32;
+// Most pairs of a unit; one whose budget would give more of them (its slices write none) goes over its row by itself.
+constexpr int kMergePairs = 64 * kSelectThreads;
 
 __global__ void __launch_bounds__(kSelectThreads) select_merge_kernel(SliceArgs sa) {
   __shared__ union {
     SelectShared<8, kSelectThreads> few;
-    SelectShared<kMergeKeys, kSelectThreads> most;
+    SelectShared<32, kSelectThreads> more;
+    SelectShared<64, kSelectThreads> most;
     StreamShared stream;
   } sh;
   const SelectArgs &a = sa.a;
@@ -534,14 +536,14 @@ __global__ void __launch_bounds__(kSelectThreads) select_merge_kernel(SliceArgs 
   int kept = 0;
   if (kp > 0) {
     const int per_slice = slice_pairs(kp, sa.slice), n = sa.S * per_slice;
-    if (n <= 8 * kSelectThreads) kept = merge_slices<8>(pairs, sa.S, sa.region, per_slice, kp, sh.few, out, tid, lane, wave);
-    else if (n <= kMergeKeys * kSelectThreads)
-      kept = merge_slices<kMergeKeys>(pairs, sa.S, sa.region, per_slice, kp, sh.most, out, tid, lane, wave);
-    else {  // a head's share far above the nominal budget that slices_pay() goes by
-      const auto at = [&](int i) { return pairs[(size_t)(i / per_slice) * sa.region + i % per_slice]; };
+    if (per_slice > sa.region) {
+      const float *u = a.utility + (size_t)unit * a.P;
+      const float tau = a.tau[unit / a.Hkv];
       kept = select_stream(
-          n, kp, sh.stream, [&](int i) { return at(i).x; }, [&](int rank, int i) { out[rank] = at(i).y; }, tid, lane, wave);
-    }
+          a.P, kp, sh.stream, [&](int t) { return key_of(u[t], tau); }, [&](int rank, int t) { out[rank] = t; }, tid, lane, wave);
+    } else if (n <= 8 * kSelectThreads) kept = merge_slices<8>(pairs, sa.S, sa.region, per_slice, kp, sh.few, out, tid, lane, wave);
+    else if (n <= 32 * kSelectThreads) kept = merge_slices<32>(pairs, sa.S, sa.region, per_slice, kp, sh.more, out, tid, lane, wave);
+    else kept = merge_slices<64>(pairs, sa.S, sa.region, per_slice, kp, sh.most, out, tid, lane, wave);  // a head with far more than its share
   }
   for (int j = tid; j < a.W; j += kSelectThreads) out[kept + j] = a.P + j;
   if (tid == 0) a.count[unit] = kept + a.W;
@@ -898,30 +900,38 @@ __global__ void __launch_bounds__(kSelectThreads) select_kernel(SelectArgs a) {
 // (callers need not pass one).
 constexpr int kOneLaunch = 32 * kSelectThreads;
 static int slices(const Shape &s, int size) { return (s.P + size - 1) / size; }
-// Most positions of a slice: 8192 where the merge then has at most 8192 pairs per unit (by the nominal budget and a
-// quarter, for heads with more than their share), which it takes eight to a thread; else 16384, which halves the
-// pairs.
-// Trace, slices + merge: 128k, W = 64, max pooling, budget 512: 11.9 + 16.8 us with 8192, 13.4 + 10.8 with 16384.
-static int slice_limit(const Shape &s, int budget) {
-  const int half = 8 * kSelectThreads, quota = max(0, budget - s.W);
-  return (int64_t)slices(s, half) * min(half, quota + quota / 4) <= 8 * kSelectThreads ? half : 2 * half;
-}
-// Slices of equal length: a short last one would keep all it has.
-static int slice_length(const Shape &s, int limit) {
-  const int n = slices(s, limit);
-  return ((s.P + n - 1) / n + kWave - 1) / kWave * kWave;
-}
-static int slice_region(const Shape &s, int cap, int limit) {
-  return (max(1, min(limit, min(cap, s.T) - s.W)) + kWave - 1) / kWave * kWave;
-}
-// Slices pay where they drop most keys and neither kernel leaves the list (by the nominal budget, so with room for
-// heads that have more than their share). Slices + merge against the split selection, us, 32 units: 128k positions, budget
-// 512: 17.0 / 41.1, 1024: 19.5 / 41.7, 2048: 24.7 / 41.7, 4096: 54.0 / 42.1; 64k, 1024: 18.0 / 28.0, 4096: 49.8 / 28.3.
-// With budgets that differ by head (the largest decides: its merge works on the most pairs) 512 keeps its lead (24 / 31 in
-// a trace of whole layers) and 2048 is even (48 / 47).
-static bool slices_pay(const Shape &s, int budget) {
-  const int limit = slice_limit(s, budget);
-  return budget - s.W <= 3072 && (int64_t)slices(s, limit) * max(0, min(limit, budget - s.W)) <= 32768;
+
+// Slices, where they pay: S of them (0: they do not), `slice` positions each, at most `limit`, `region` pairs.
+struct SlicePlan {
+  int S, limit, slice, region;
+};
+// The budgets are on the device, so the rule goes by what heads are likely to have: twice the nominal quota, and with room for
+// eight times. Slices + merge / split selection, us, 34000 to 262144 positions, 8 heads, batch 1 and 4, two distributions, where the
+// largest quota of a unit's heads is up to 2048: 15-25 / 24-35 and 15-34 / 25-89; where it is 3072: 27-45 / 24-35 and 28-46 /
+// 25-49. So twice the nominal quota has to be at most 2048. With half of a nominal 8 x 1024 in one head 35-45 / 24-49, with all
+// of it 40-75 / 24-49.
+// A unit has at most 65536 pairs, which the merge takes in registers (streaming more of them, as it did, took one workgroup
+// 90-600 us). There is room in them for eight times the nominal quota, or the split is taken; a head with more than the room is
+// selected from its row by one workgroup (32 heads, all of the budget in one, 128k: 219-247 / 43-49; before 223-295).
+// 8192 positions per slice where the merge then has at most 8192 pairs, which it takes eight to a thread; else 16384, which
+// halves the pairs (98304 positions, 32 units, 512: 20 -> 17 us; one head at twice that 23 -> 18).
+static SlicePlan plan_slices(const ckv_params *p, const Shape &s) {
+  SlicePlan plan = {0, 0, 0, 0};
+  const int64_t quota = p->budget_per_kv_head - s.W;
+  if (s.P <= kOneLaunch || 2 * quota > 2048) return plan;
+  const int most = max(1, min(p->cap, s.T) - s.W);
+  const auto up = [](int64_t x) { return (x + kWave - 1) / kWave * kWave; };
+  const auto least = [](int64_t x, int64_t y) { return x < y ? x : y; };
+  for (int limit = 8 * kSelectThreads; limit <= 16 * kSelectThreads; limit *= 2) {
+    const int64_t n = slices(s, limit), room = kMergePairs / n / kWave * kWave, top = least(limit, most);
+    if (up(least(top, 8 * quota)) > room || (limit == 8 * kSelectThreads && n * least(top, 2 * quota) > 8 * kSelectThreads)) continue;
+    plan.S = (int)n;
+    plan.limit = limit;
+    plan.slice = (int)up((s.P + n - 1) / n);  // equal lengths: a short last one would keep all it has
+    plan.region = (int)least(up(top), room);
+    break;
+  }
+  return plan;
 }
 
 size_t select_split_bytes(const Shape &s) {
@@ -929,14 +939,13 @@ size_t select_split_bytes(const Shape &s) {
   return (size_t)s.Bz * s.Hkv * (kSplitHist + slices(s, kSplitSlice) + 16) * sizeof(int);
 }
 
-// Bytes of the slices' pairs, 0 where slices do not pay.
-static size_t slice_pair_bytes(const ckv_params *p, const Shape &s) {
-  if (s.P <= kOneLaunch || !slices_pay(s, p->budget_per_kv_head)) return 0;
-  const int limit = slice_limit(s, p->budget_per_kv_head);
-  return (size_t)s.Bz * s.Hkv * slices(s, limit) * slice_region(s, p->cap, limit) * sizeof(int2);
+static size_t slice_pair_bytes(const Shape &s, const SlicePlan &plan) {
+  return (size_t)s.Bz * s.Hkv * plan.S * plan.region * sizeof(int2);
 }
 
-size_t select_workspace_bytes(const ckv_params *p, const Shape &s) { return max(select_split_bytes(s), slice_pair_bytes(p, s)); }
+size_t select_workspace_bytes(const ckv_params *p, const Shape &s) {
+  return max(select_split_bytes(s), slice_pair_bytes(s, plan_slices(p, s)));
+}
 
 template <int NK, int NT>
 static void launch_reg(const SelectArgs &a, int units, hipStream_t stream) {
@@ -956,17 +965,16 @@ hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utili
   a.cap = p->cap;
   const int units = s.Bz * s.Hkv;
   const dim3 block(kSelectThreads);
-  const size_t pair_bytes = slice_pair_bytes(p, s);
-  if (ws && pair_bytes > 0 && ws_bytes >= pair_bytes) {
+  const SlicePlan plan = plan_slices(p, s);
+  if (ws && plan.S > 0 && ws_bytes >= slice_pair_bytes(s, plan)) {
     SliceArgs sa;
     sa.a = a;
-    const int limit = slice_limit(s, p->budget_per_kv_head);
-    sa.S = slices(s, limit);
-    sa.slice = slice_length(s, limit);
-    sa.region = slice_region(s, p->cap, limit);
+    sa.S = plan.S;
+    sa.slice = plan.slice;
+    sa.region = plan.region;
     sa.pairs = reinterpret_cast<int2 *>(ws);
     const dim3 slice_grid((unsigned)(units * sa.S));
-    if (limit == 8 * kSelectThreads) hipLaunchKernelGGL(select_slice_kernel<8>, slice_grid, block, 0, stream, sa);
+    if (plan.limit == 8 * kSelectThreads) hipLaunchKernelGGL(select_slice_kernel<8>, slice_grid, block, 0, stream, sa);
     else hipLaunchKernelGGL(select_slice_kernel<16>, slice_grid, block, 0, stream, sa);
     hipLaunchKernelGGL(select_merge_kernel, dim3(units), block, 0, stream, sa);
   } else if (ws && s.P > kOneLaunch) {

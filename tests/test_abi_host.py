@@ -230,3 +230,16 @@ def test_static_scratch_rejects_shapes_beyond_its_array():
     assert need > B.STATIC_SCRATCH_BYTES
     d = ctypes.c_void_p(256)
     assert lib.ckv_window_lse_static(ctypes.byref(p), d, d, d, None) == B.CKV_EWORKSPACE
+
+
+@pytest.mark.parametrize("P", [32769, 65536, 131072, 262144, 1 << 20, (1 << 24) - 64])
+def test_scratch_of_the_long_selection_is_bounded(P):
+    """At most 65536 pairs of 8 bytes per (batch, KV head), whatever budget and cap: what one workgroup merges on chip."""
+    W, Hkv = 32, 8
+    for budget in (33, 100, 512, 1056, 1057, 2048, 5000):
+        for cap in (budget * Hkv, 40000, P + W):
+            cap = max(min(P + W, budget * Hkv), min(cap, P + W))
+            p = _good(n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=P + W, budget=budget, cap=cap)
+            scan = B.ckv_window_lse_static_bytes(p) + 2 * Hkv * W * 4   # row partials, normalisers
+            of_selection = B.ckv_workspace_bytes(p) - scan
+            assert 0 < of_selection <= 2 * Hkv * max(65536 * 8, (4096 + P // 8192 + 17) * 4) + 512

@@ -52,3 +52,40 @@ def test_select_matches_oracle_at_the_borders(P, kind, workspace):
             oi, oc = oracle.select(u, np.array([tau], np.float32), budget, W, cap)
             np.testing.assert_array_equal(count.cpu().numpy(), oc)
             np.testing.assert_array_equal(idx.cpu().numpy(), oi)
+
+
+def _bytes(units, P, W, budget, cap, Hkv):
+    return B.ckv_workspace_bytes(B.make_params(batch=units // Hkv, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=P + W, window=W,
+                                               dtype="bf16", pool=B.POOL_NONE, pool_kernel=1, budget=budget, cap=cap))
+
+
+@pytest.mark.parametrize("form", ["slices", "split"])
+@pytest.mark.parametrize("kind", ["close", "ties", "outliers", "equal", "mantissa", "few"])
+@pytest.mark.parametrize("P,top", [(32769, 8192), (65540, 15000), (70001, 12000), (131040, 9000), (200000, 7000)])
+def test_select_over_long_rows_by_both_forms(P, top, kind, form):
+    """Slices and merge, and the split selection, on the same rows: budgets from nothing to `top` for one head (beyond 32768
+    pairs for the merge, and beyond the room for pairs), heads with fewer candidates than their budget, candidates that only position or the last bits of
+    the mantissa tell apart. The nominal budget decides the form; the size of the workspace tells which one it is."""
+    print(f"case P={P} top={top} {kind} {form}", flush=True)
+    rng = np.random.default_rng(P + len(kind))
+    W, Hkv, bz = 4, 5, 2
+    cap = W + top
+    nominal = W + (600 if form == "slices" else 3500)
+    u = _values(rng, kind, (bz, Hkv, P))
+    if kind == "equal":
+        u = np.full((bz, Hkv, P), 0.75, np.float32)
+    elif kind == "mantissa":
+        u = (np.float32(1.0) + (np.arange(P, dtype=np.float32) % 97 * np.float32(1.2e-7))) * np.ones((bz, Hkv, 1), np.float32)
+    tau = np.array([0.0, float(np.partition(u[1, 0], -200)[-200]) if kind == "few" else 0.0], np.float32)
+    budget = np.array([[W + top, W, W + 1, W + 777, W + 2048], [W + 63, W + top, W + top // 2, W + 64, W]], np.int32)
+    p = B.make_params(batch=bz, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=P + W, window=W, dtype="bf16",
+                      pool=B.POOL_NONE, pool_kernel=1, budget=nominal, cap=max(cap, Hkv * nominal - (Hkv - 1) * W))
+    assert (B.ckv_workspace_bytes(p) > _bytes(bz * Hkv, P, W, W + 3500, Hkv * (W + 3500), Hkv)) == (form == "slices")
+    ws = torch.full((B.ckv_workspace_bytes(p),), 255, dtype=torch.uint8, device=DEV)
+    idx = torch.full((bz, Hkv, p.cap), -1, dtype=torch.int32, device=DEV)
+    count = torch.empty(bz, Hkv, dtype=torch.int32, device=DEV)
+    B.ckv_select_topk(p, torch.from_numpy(u).to(DEV), torch.from_numpy(budget).to(DEV), torch.from_numpy(tau).to(DEV), idx, count, ws)
+    torch.cuda.synchronize()
+    oi, oc = oracle.select(u, tau, budget, W, p.cap)
+    np.testing.assert_array_equal(count.cpu().numpy(), oc)
+    np.testing.assert_array_equal(idx.cpu().numpy(), oi)
