@@ -282,6 +282,13 @@ __device__ __forceinline__ float over_quarters(float x, Op op) {
 __device__ __forceinline__ uint32_t high_halves(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302); }
 __device__ __forceinline__ uint32_t low_halves(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100); }
 
+// Rows of a chunk: a unit's chunks share its valid rows evenly, in whole steps of the workgroup. (With chunks of n_rows instead, a
+// cache with many more rows than counts left most of its workgroups without any.)
+__device__ __forceinline__ int flat_chunk_rows(const DecodeArgs &a, int n_valid) {
+  constexpr int STEP = kDecodeWaves * kBlockRows;
+  return max(1, (int)((uint32_t)(n_valid + a.n_chunks * STEP - 1) / (uint32_t)(a.n_chunks * STEP))) * STEP;
+}
+
 // SPLIT: workgroups that share a unit's columns, each with all of K and a SPLIT-th of V's components. One CU takes in about
 // 60 GB/s; where units are fewer than CUs this is how more of them read (8 units of 4096 rows, four heads each: 40.6
 // us with one, 34.5 with four).
@@ -310,7 +317,6 @@ __global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a)
   const int cc = y % a.col_chunks, unit = y / a.col_chunks;
   const int b = unit / a.Hkv, g = unit % a.Hkv;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), m = lane & 15, quarter = lane >> 4;
-  const int r0 = chunk * a.rows_per_chunk, r_end = min(r0 + a.rows_per_chunk, a.n_rows), base0 = r0 + wave * kBlockRows;
   const int n_cols = min(kCols, a.cols - cc * kCols);  // columns of this tile that exist
   const size_t q_row = ((size_t)b * a.Hq + (size_t)g * a.G) * a.n_q + cc * kCols;  // first of them in q, out and lse
   const bool single = a.n_chunks == 1;
@@ -368,7 +374,8 @@ __global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a)
   // nothing behind the count is read: its rows need not even be mapped
   int n_valid = a.n_rows;
   if (a.count) n_valid = min(max(a.count[unit], 0), a.n_rows);
-  const int r1 = min(r_end, n_valid);
+  const int rows = single ? n_valid : flat_chunk_rows(a, n_valid);
+  const int r0 = chunk * rows, r1 = min(r0 + rows, n_valid), base0 = r0 + wave * kBlockRows;
   if (r0 >= r1 && !single) return;  // the merge reads the chunks below n_valid only
   if (base0 < r1) {
     load_k(base0, r1);
@@ -542,7 +549,8 @@ __global__ void __launch_bounds__(DH) decode_merge_kernel(DecodeArgs a) {
   const float *part = a.part + first * ROW;
   int n_valid = a.n_rows;
   if (a.count) n_valid = min(max(a.count[unit], 0), a.n_rows);
-  const int n_chunks = (n_valid + a.rows_per_chunk - 1) / a.rows_per_chunk;  // the chunks that were written
+  const int rows = FLAT ? flat_chunk_rows(a, n_valid) : a.rows_per_chunk;
+  const int n_chunks = (n_valid + rows - 1) / rows;  // the chunks that were written
   if (threadIdx.x < kWave) {
     const int c = threadIdx.x;
     const float top = c < n_chunks ? part[(size_t)c * STRIDE + DH] : -INFINITY;
@@ -600,7 +608,7 @@ DecodePlan plan_decode(const Shape &s, int n_q, int n_rows) {
     p.workspace_bytes = 0;
     return p;
   }
-  // Enough workgroups to fill the chip, at most 64 chunks. bf16: three workgroups of four waves per CU, all of them
+  // Enough workgroups to fill the chip, at most 64 chunks. bf16: two workgroups of four waves per CU, all of them
   // resident at once, chunks of whole steps of theirs (128 rows). f32: several times the chip, chunks of at least 64 rows.
   const bool mfma = s.esize == 2;
   const int64_t per_chunk = mfma ? p.workgroups : p.grid_y, target = mfma ? 2 * kComputeUnits : 4096;
