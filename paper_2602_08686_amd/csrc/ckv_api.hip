@@ -48,19 +48,18 @@ ckv_status validate(const ckv_params *p) {
   return CKV_OK;
 }
 
-// Keys per wave: the split of the key axis. `resident` workgroups run at a time (bf16: one per CU, whose four waves sweep
-// long ranges, since nothing overlaps a workgroup's set-up; f32: two, or one with several query tiles of 512-byte rows
-// per wave), so what counts is full rounds of that many: the least rounds x (keys + set-up), set-up being worth about
-// 192 keys of a bf16 sweep and a tile of an f32 one. bf16 ranges beyond 128 keys are whole four-tile pipeline rounds. The
-// row partials stay within 1 MiB or what the plain even split needs, whichever is more, so that a caller's or the
-// library's fixed scratch goes as far as it did.
-// Measured against the even split alone, us, both passes and tables: bf16, 97280 keys,
-// 24 units 324 -> 226 (264 workgroups became 240), 51200 keys, 40 units 328 -> 210, 5003 keys, 96 units 91.5 -> 65.8; f32
-// (even split for 2048
-// workgroups, at least 64 keys): 1024 keys, 4/4 heads of 64 16.5 -> 12.8; 8192 keys, 32/32 heads of 64 53.4 -> 38.3; 4099
-// keys, 32/8 heads of 128 70.5 -> 55.6.
+// Keys per wave: the split of the key axis. One workgroup per CU runs at full speed (bf16: its four waves sweep long ranges, since
+// nothing overlaps a workgroup's set-up; f32: two would fit a CU, but they halve each other's rate), so what counts is full
+// rounds of that many: the least rounds x (keys + set-up), set-up being worth about 192 keys of a bf16 sweep and a tile of an f32
+// one. bf16 ranges beyond 128 keys are whole four-tile pipeline rounds. The row partials stay within 1 MiB or what the plain
+// even split needs, whichever is more, so that a caller's or the library's fixed scratch goes as far as it did.
+// Measured against the even split alone, us: bf16, both passes and tables, 97280 keys, 24 units 324 -> 226 (264 workgroups
+// became 240), 51200 keys, 40 units 328 -> 210, 5003 keys, 96 units 91.5 -> 65.8; f32 (even split for 2048 workgroups, at least 64
+// keys), both passes: 1024 keys, 4/4 heads of 64 14.2 -> 10.4, 8192 keys, 32/32 heads of 64 51.7 -> 29.0, 4099 keys, 32/8 heads of
+// 128 60.0 -> 42.0. (Rounds of 512 workgroups for f32: 10.4, 35.9, 41.7, and slower than the even split in 13 of 70 shapes, by up
+// to 23 %: 1244 keys, 32/8 heads of 128 24.4 -> 30.1 with 320 workgroups, 21.6 with 160.)
 static int64_t split_keys(const Shape &s, bool bf16, int64_t units) {
-  const int64_t resident = bf16 || (s.d == 128 && s.NQ >= 2) ? kComputeUnits : 2 * kComputeUnits;
+  const int64_t resident = kComputeUnits;
   const int64_t set_up = bf16 ? 192 : kTile, waves = kScoreWaves * (bf16 ? (int64_t)kComputeUnits : 2048);
   const auto workgroups = [&](int64_t kpw) { return units * ((s.T + kScoreWaves * kpw - 1) / (kScoreWaves * kpw)); };
   int64_t plain = ((int64_t)s.T * units + waves - 1) / waves;

@@ -243,3 +243,16 @@ def test_scratch_of_the_long_selection_is_bounded(P):
             scan = B.ckv_window_lse_static_bytes(p) + 2 * Hkv * W * 4   # row partials, normalisers
             of_selection = B.ckv_workspace_bytes(p) - scan
             assert 0 < of_selection <= 2 * Hkv * max(65536 * 8, (4096 + P // 8192 + 17) * 4) + 512
+
+
+@pytest.mark.parametrize("batch,heads,kv,d,T,W,tiles", [
+    (1, 32, 8, 128, 1244, 32, 1), (1, 32, 8, 128, 2000, 32, 1), (2, 40, 8, 64, 704, 64, 4), (2, 8, 1, 64, 3000, 128, 4),
+    (4, 32, 8, 64, 700, 64, 4), (2, 32, 32, 64, 600, 32, 1), (1, 4, 1, 128, 10167, 32, 1), (1, 8, 8, 128, 5649, 16, 1),
+])
+def test_f32_scan_takes_one_round_of_workgroups_where_it_can(batch, heads, kv, d, T, W, tiles):
+    """A second, nearly empty round costs as much as a full one: shapes that were split into 288 to 512 workgroups and were
+    slower for it than with 144 to 256. The row partials (`tiles` query tiles of 32 rows per wave, 8 bytes) tell how many."""
+    p = _good(batch=batch, n_q_heads=heads, n_kv_heads=kv, head_dim=d, seq_len=T, window=W, dtype=torch.float32, budget=W + 32,
+              cap=T)
+    workgroups, rest = divmod(B.ckv_window_lse_static_bytes(p), tiles * 32 * 8)
+    assert rest == 0 and 0 < workgroups <= 256
