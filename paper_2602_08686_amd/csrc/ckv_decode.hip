@@ -36,8 +36,9 @@ struct DecodeArgs {
   float *part;           // [grid.y][n_chunks][RQ][d + 2]: weighted V sum, running max (log2), sum
   float *out;            // [Bz][Hq][n_q][d]
   float *lse;            // [Bz][Hq][n_q] natural log
-  int Hq, Hkv, G, n_q, n_rows, rows_per_chunk, n_chunks, head_chunks;
+  int Hq, Hkv, G, n_q, n_rows, n_chunks, head_chunks;
   int cols, col_chunks;  // bf16: query columns per KV head (G * n_q) and 16-column tiles of them
+  int part_cols;         // columns of a tile's partial: min(16, cols)
   float scale2;          // softmax scale * log2(e)
 };
 
@@ -46,13 +47,20 @@ constexpr int kDecodeThreads = 256;
 constexpr int kDecodeWaves = kDecodeThreads / kWave;
 
 // A 16-byte piece of an f32 row.
-constexpr int kPiece = 4;
-__device__ __forceinline__ void piece_to_float(const uint4 &raw, float (&f)[kPiece]) {
+__device__ __forceinline__ void piece_to_float(const uint4 &raw, float (&f)[4]) {
   f[0] = __uint_as_float(raw.x);
   f[1] = __uint_as_float(raw.y);
   f[2] = __uint_as_float(raw.z);
   f[3] = __uint_as_float(raw.w);
 }
+
+// Rows of a chunk: a unit's chunks share its valid rows evenly, in whole steps of the workgroup. (With chunks of n_rows instead, a
+// cache with many more rows than counts left most of its workgroups without any.)
+template <int STEP>
+__device__ __forceinline__ int chunk_rows(const DecodeArgs &a, int n_valid) {
+  return max(1, (int)((uint32_t)(n_valid + a.n_chunks * STEP - 1) / (uint32_t)(a.n_chunks * STEP))) * STEP;
+}
+constexpr int kVectorStep = 64;
 
 // exp2(a - b) with the conventions of an online softmax: a = -inf gives 0 also when b was reset to 0
 __device__ __forceinline__ float exp2_diff(float a, float b) { return exp2f(a - b); }
@@ -61,7 +69,7 @@ __device__ __forceinline__ float exp2_diff(float a, float b) { return exp2f(a - 
 // (unit, query) the workgroup writes the final result itself and no merge kernel follows.
 template <int DH, int RQ, int NW, int U, bool PIPE>
 __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a) {
-  constexpr int E = kPiece, ESIZE = 4;
+  constexpr int ESIZE = 4, E = 16 / ESIZE;
   constexpr int LPR = DH / E;        // lanes per row
   constexpr int KPW = kWave / LPR;   // rows per wave step
   constexpr int ROW = DH + 2;
@@ -89,8 +97,9 @@ __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a)
   const int sub = lane % LPR, slot = lane / LPR;
   int n_valid = a.n_rows;
   if (a.count) n_valid = min(max(a.count[unit], 0), a.n_rows);
-  const int r0 = chunk * a.rows_per_chunk, r1 = min(r0 + a.rows_per_chunk, n_valid);
   const bool single = a.n_chunks == 1;
+  const int rows = single ? n_valid : chunk_rows<kVectorStep>(a, n_valid);
+  const int r0 = chunk * rows, r1 = min(r0 + rows, n_valid);
   if (r0 >= r1 && !single) return;  // the merge reads the chunks below n_valid only
 
   float qv[RQ][E];
@@ -266,6 +275,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_d;
 typedef __attribute__((ext_vector_type(4))) float f32x4_dec;
 constexpr int kCols = 16;       // query columns of a tile
 constexpr int kBlockRows = 32;  // rows a wave takes at a time
+constexpr int kFlatStep = kDecodeWaves * kBlockRows;
 
 __device__ __forceinline__ void mma16(f32x4_dec &acc, const u32x4_d &x, const u32x4_d &y) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_d, x), __builtin_bit_cast(bf16x8_d, y), acc, 0, 0, 0);
@@ -281,13 +291,6 @@ __device__ __forceinline__ float over_quarters(float x, Op op) {
 // High halves of two words side by side (x below y): two truncated bf16 of an operand.
 __device__ __forceinline__ uint32_t high_halves(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302); }
 __device__ __forceinline__ uint32_t low_halves(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100); }
-
-// Rows of a chunk: a unit's chunks share its valid rows evenly, in whole steps of the workgroup. (With chunks of n_rows instead, a
-// cache with many more rows than counts left most of its workgroups without any.)
-__device__ __forceinline__ int flat_chunk_rows(const DecodeArgs &a, int n_valid) {
-  constexpr int STEP = kDecodeWaves * kBlockRows;
-  return max(1, (int)((uint32_t)(n_valid + a.n_chunks * STEP - 1) / (uint32_t)(a.n_chunks * STEP))) * STEP;
-}
 
 // SPLIT: workgroups that share a unit's columns, each with all of K and a SPLIT-th of V's components. One CU takes in about
 // 60 GB/s; where units are fewer than CUs this is how more of them read (8 units of 4096 rows, four heads each: 40.6
@@ -374,7 +377,7 @@ __global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a)
   // nothing behind the count is read: its rows need not even be mapped
   int n_valid = a.n_rows;
   if (a.count) n_valid = min(max(a.count[unit], 0), a.n_rows);
-  const int rows = single ? n_valid : flat_chunk_rows(a, n_valid);
+  const int rows = single ? n_valid : chunk_rows<kFlatStep>(a, n_valid);
   const int r0 = chunk * rows, r1 = min(r0 + rows, n_valid), base0 = r0 + wave * kBlockRows;
   if (r0 >= r1 && !single) return;  // the merge reads the chunks below n_valid only
   if (base0 < r1) {
@@ -497,7 +500,7 @@ __global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a)
   }
   __syncthreads();
   // the waves, in wave order (more than one chunk: SPLIT is 1)
-  float *part = single ? nullptr : a.part + (((size_t)blockIdx.y * a.n_chunks + chunk) * kCols) * ROW;
+  float *part = single ? nullptr : a.part + (((size_t)blockIdx.y * a.n_chunks + chunk) * a.part_cols) * ROW;
   for (int i = threadIdx.x; i < n_cols * DV; i += NW * kWave) {
     const int c = i / DV, x = i % DV;
     float mx = sm[0][c][DV];
@@ -528,7 +531,7 @@ __global__ void __launch_bounds__(NW *kWave, 2) decode_mfma_kernel(DecodeArgs a)
 // Chunks of one (unit, query row): a lane per chunk for the maximum and the weights, a thread per component for the
 // sum, its loads independent. One workgroup per query row (the first form, one per unit, kept 32 workgroups of the
 // chip busy for 16.7 us on the 32k / batch-4 cache).
-// FLAT: partials of the bf16 kernel, [(unit, column tile)][chunk][16][d + 2]; else [(unit, query, head chunk)][chunk][RQ][d + 2].
+// FLAT: partials of the bf16 kernel, [(unit, column tile)][chunk][part_cols][d + 2]; else [(unit, query, head chunk)][chunk][RQ][d + 2].
 constexpr int kMaxChunks = 64;
 template <int DH, int RQ, bool FLAT>
 __global__ void __launch_bounds__(DH) decode_merge_kernel(DecodeArgs a) {
@@ -541,20 +544,20 @@ __global__ void __launch_bounds__(DH) decode_merge_kernel(DecodeArgs a) {
   size_t first;  // partial row of chunk 0
   if (FLAT) {
     const int c = hg * a.n_q + qi;
-    first = ((size_t)unit * a.col_chunks + c / kCols) * a.n_chunks * kCols + c % kCols;
+    first = ((size_t)unit * a.col_chunks + c / kCols) * a.n_chunks * a.part_cols + c % kCols;
   } else {
     first = (((size_t)unit * a.n_q + qi) * a.head_chunks + hg / RQ) * a.n_chunks * RQ + hg % RQ;
   }
-  constexpr int STRIDE = (FLAT ? kCols : RQ) * ROW;
+  const int stride = (FLAT ? a.part_cols : RQ) * ROW;
   const float *part = a.part + first * ROW;
   int n_valid = a.n_rows;
   if (a.count) n_valid = min(max(a.count[unit], 0), a.n_rows);
-  const int rows = FLAT ? flat_chunk_rows(a, n_valid) : a.rows_per_chunk;
+  const int rows = chunk_rows<FLAT ? kFlatStep : kVectorStep>(a, n_valid);
   const int n_chunks = (n_valid + rows - 1) / rows;  // the chunks that were written
   if (threadIdx.x < kWave) {
     const int c = threadIdx.x;
-    const float top = c < n_chunks ? part[(size_t)c * STRIDE + DH] : -INFINITY;
-    const float sum = c < n_chunks ? part[(size_t)c * STRIDE + DH + 1] : 0.0f;
+    const float top = c < n_chunks ? part[(size_t)c * stride + DH] : -INFINITY;
+    const float sum = c < n_chunks ? part[(size_t)c * stride + DH + 1] : 0.0f;
     float mx = top;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
@@ -575,7 +578,7 @@ __global__ void __launch_bounds__(DH) decode_merge_kernel(DecodeArgs a) {
   for (int c0 = 0; c0 < n_chunks; c0 += BATCH) {
     float v[BATCH];
 #pragma unroll
-    for (int j = 0; j < BATCH; ++j) v[j] = c0 + j < n_chunks ? part[(size_t)(c0 + j) * STRIDE + x] : 0.0f;
+    for (int j = 0; j < BATCH; ++j) v[j] = c0 + j < n_chunks ? part[(size_t)(c0 + j) * stride + x] : 0.0f;
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) num = fmaf(v[j], c0 + j < n_chunks ? s_weight[c0 + j] : 0.0f, num);
   }
@@ -589,8 +592,34 @@ __global__ void __launch_bounds__(DH) decode_merge_kernel(DecodeArgs a) {
 // ---------------------------------------------------------------------------------------------
 static int query_rows_per_pass(int G) { return G >= 8 ? 8 : G > 2 ? 4 : G; }  // 1, 2, 4, 8 (G = 3 pads to 4)
 
+static int64_t least64(int64_t x, int64_t y) { return x < y ? x : y; }
+
+// bf16, long rows: rows per chunk. Two workgroups of four waves fit a CU, but one of them takes in nearly as much as both, so the
+// work of the fullest CU counts: ceil(workgroups / 256) x (rows + set-up), the set-up (its partial's way through the merge
+// included) being worth 16 rows per query column; a tenth more where a CU has one workgroup only, and a tenth of a chunk's rows
+// where not all workgroups are resident from the start.
+// Measured against what fills the chip once (512 / workgroups chunks, rounded down), us, rows of 128: 264 workgroups, 4200 rows 142
+// -> 94 (11 chunks), 320, 9000 rows 315 -> 235 (4 or 8), 136, 9000 rows 118 -> 104 (15), 96, 9000 rows 80 -> 76 (8); the same chunks as
+// before for 32 x 32768, 56 x 9000, 128 x 9000 and 512 x 4200.
+static int64_t mfma_chunk_rows(int64_t workgroups, int64_t cols, int n_rows, int most) {
+  constexpr int STEP = kFlatStep;
+  const int64_t set_up = 4 + 16 * cols;
+  int64_t best = 0, best_cost = INT64_MAX;
+  for (int chunks = 1; chunks <= most; ++chunks) {
+    const int64_t rows = (n_rows + chunks * STEP - 1) / (chunks * STEP) * STEP;
+    const int64_t n = workgroups * ((n_rows + rows - 1) / rows), per_cu = (n + kComputeUnits - 1) / kComputeUnits;
+    const int64_t cost = (per_cu == 1 ? 11 : 10 * per_cu) * (rows + set_up) + (n > 2 * kComputeUnits ? rows : 0);
+    if (cost < best_cost) {
+      best = rows;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 DecodePlan plan_decode(const Shape &s, int n_q, int n_rows) {
   DecodePlan p;
+  p.mfma = s.esize == 2;
   p.rq = query_rows_per_pass(s.G);
   p.head_chunks = (s.G + p.rq - 1) / p.rq;
   p.grid_y = (int64_t)s.Bz * s.Hkv * n_q * p.head_chunks;
@@ -603,26 +632,21 @@ DecodePlan plan_decode(const Shape &s, int n_q, int n_rows) {
     p.rq = s.G >= 2 ? 2 : 1;
     p.head_chunks = (s.G + p.rq - 1) / p.rq;
     p.grid_y = (int64_t)s.Bz * s.Hkv * n_q * p.head_chunks;
-    p.rows_per_chunk = (n_rows + 63) / 64 * 64;
     p.n_chunks = 1;
     p.workspace_bytes = 0;
     return p;
   }
-  // Enough workgroups to fill the chip, at most 64 chunks. bf16: two workgroups of four waves per CU, all of them
-  // resident at once, chunks of whole steps of theirs (128 rows). f32: several times the chip, chunks of at least 64 rows.
-  const bool mfma = s.esize == 2;
-  const int64_t per_chunk = mfma ? p.workgroups : p.grid_y, target = mfma ? 2 * kComputeUnits : 4096;
-  const int64_t step = mfma ? kDecodeWaves * kBlockRows : 64;
-  int64_t chunks = (n_rows + step - 1) / step;
-  const int64_t want = mfma ? target / per_chunk : (target + per_chunk - 1) / per_chunk;
-  if (chunks > want) chunks = want;
-  if (chunks > kMaxChunks) chunks = kMaxChunks;
-  if (chunks < 1) chunks = 1;
-  int64_t rows = (n_rows + chunks - 1) / chunks;
-  rows = (rows + step - 1) / step * step;
-  p.rows_per_chunk = (int)rows;
+  // At most 64 chunks, of whole steps of a workgroup. On the vector ALUs: workgroups for several times the chip.
+  const int64_t step = p.mfma ? kFlatStep : kVectorStep, most = least64(kMaxChunks, (n_rows + step - 1) / step);
+  int64_t rows;
+  if (p.mfma) {
+    rows = mfma_chunk_rows(p.workgroups, least64(kCols, (int64_t)s.G * n_q), n_rows, (int)most);
+  } else {
+    const int64_t chunks = least64(most, (4096 + p.grid_y - 1) / p.grid_y);
+    rows = ((n_rows + chunks - 1) / chunks + step - 1) / step * step;
+  }
   p.n_chunks = (int)((n_rows + rows - 1) / rows);
-  const size_t part_rows = mfma ? (size_t)p.workgroups * kCols : (size_t)p.grid_y * p.rq;
+  const size_t part_rows = p.mfma ? (size_t)p.workgroups * least64(kCols, (int64_t)s.G * n_q) : (size_t)p.grid_y * p.rq;
   p.workspace_bytes = part_rows * p.n_chunks * (s.d + 2) * sizeof(float);
   return p;
 }
@@ -649,7 +673,7 @@ static void launch_decode_bf16(const DecodeArgs &a, const DecodePlan &p, int row
 }
 
 template <int DH, int RQ>
-static void launch_decode_f32(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
+static void launch_decode_vector(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
   if constexpr (RQ <= 2) {
     if (p.n_chunks == 1) {
       hipLaunchKernelGGL((decode_partial_kernel<DH, RQ, 16, 2, true>), dim3(1, (unsigned)p.grid_y),
@@ -666,10 +690,10 @@ static void launch_decode_f32(const DecodeArgs &a, const DecodePlan &p, int rows
 template <int DH>
 static void launch_decode_rq(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
   switch (p.rq) {
-    case 1: launch_decode_f32<DH, 1>(a, p, rows, stream); break;
-    case 2: launch_decode_f32<DH, 2>(a, p, rows, stream); break;
-    case 4: launch_decode_f32<DH, 4>(a, p, rows, stream); break;
-    default: launch_decode_f32<DH, 8>(a, p, rows, stream); break;
+    case 1: launch_decode_vector<DH, 1>(a, p, rows, stream); break;
+    case 2: launch_decode_vector<DH, 2>(a, p, rows, stream); break;
+    case 4: launch_decode_vector<DH, 4>(a, p, rows, stream); break;
+    default: launch_decode_vector<DH, 8>(a, p, rows, stream); break;
   }
 }
 
@@ -692,12 +716,12 @@ hipError_t launch_decode_attention(const ckv_params *p, const Shape &s, const vo
   a.Hq = s.Hq; a.Hkv = s.Hkv; a.G = s.G;
   a.n_q = n_q;
   a.n_rows = n_rows;
-  a.rows_per_chunk = plan.rows_per_chunk;
   a.n_chunks = plan.n_chunks;
   a.head_chunks = plan.head_chunks;
   a.scale2 = s.scale * kLog2e;
   a.cols = s.G * n_q;
   a.col_chunks = plan.col_chunks;
+  a.part_cols = (int)least64(kCols, a.cols);
   const int rows = s.Bz * s.Hq * n_q;
   if (p->dtype == CKV_BF16) {
     if (s.d == 128) launch_decode_bf16<128>(a, plan, rows, stream);

@@ -151,7 +151,8 @@ hipError_t launch_map_depth(const float *src, int n_src, int row, float *dst, in
 struct DecodePlan {
   int rq;              // query heads of a group that share one sweep over the rows (1, 2, 4 or 8)
   int head_chunks;     // ceil(G / rq)
-  int rows_per_chunk, n_chunks;
+  bool mfma;           // the bf16 matrix-core kernel, else the vector kernel
+  int n_chunks;
   int64_t grid_y;      // Bz * Hkv * n_q * head_chunks
   int col_chunks;      // bf16: 16-wide tiles of a KV head's G * n_q query columns
   int64_t workgroups;  // bf16: Bz * Hkv * col_chunks

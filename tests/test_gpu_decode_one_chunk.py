@@ -1,6 +1,7 @@
-"""Decode attention over long KV sets with so many (unit, query) workgroups that the rows are not cut: one chunk per
-workgroup, which writes the result itself (no merge follows). f32 with every count of heads a workgroup takes, bf16 with one and
-several column tiles and unit counts that are no multiple of eight; counts of zero, one and all. All units read the same rows
+"""Decode attention over long KV sets of many units: so many (unit, query) workgroups that the rows are not cut (one chunk per
+workgroup, which writes the result itself; no merge follows), or few chunks each. f32 with every count of heads a workgroup
+takes, bf16 with one column, one and several column tiles, unit counts that are no multiple of
+eight; counts of zero, one and all. All units read the same rows
 (strides of zero), which keeps the memory small. Against the oracle with the tolerances of test_gpu_decode.py; every output is
 prefilled with NaN, so one that nobody writes shows up."""
 import numpy as np
@@ -14,21 +15,25 @@ from test_gpu_decode import _close_rows
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
-# dtype, batch, query heads, KV heads, head_dim, rows, queries
+# dtype, batch, query heads, KV heads, head_dim, rows, queries, partial rows of the workspace per unit and chunk: one chunk or more
 CASES = [
-    ("f32", 64, 32, 8, 64, 20000, 8),      # 4096 workgroups of four heads
-    ("f32", 513, 64, 8, 128, 16385, 1),    # 4104 of eight
-    ("f32", 4097, 2, 1, 64, 16400, 1),     # two heads
-    ("f32", 4097, 1, 1, 64, 16400, 1),     # one
-    ("bf16", 40, 8, 8, 128, 5000, 1),      # 320 workgroups
-    ("bf16", 27, 20, 5, 128, 4200, 5),     # 135 units, two column tiles each, 20 columns
-    ("bf16", 67, 68, 4, 64, 4161, 1),      # 268 units of 17 heads: two column tiles
-    ("bf16", 263, 16, 4, 128, 16420, 1),   # more than 1024 workgroups
+    ("f32", 64, 32, 8, 64, 20000, 8, 32, True),      # 4096 workgroups of four heads
+    ("f32", 513, 64, 8, 128, 16385, 1, 8, True),     # 4104 of eight
+    ("f32", 4097, 2, 1, 64, 16400, 1, 2, True),      # two heads
+    ("f32", 4097, 1, 1, 64, 16400, 1, 1, True),      # one
+    ("bf16", 64, 32, 8, 128, 4200, 1, 4, True),      # 512 workgroups
+    ("bf16", 127, 16, 4, 64, 4161, 2, 8, True),      # 508
+    ("bf16", 85, 60, 3, 128, 4200, 1, 32, True),     # 255 units of 20 columns: two tiles
+    ("bf16", 67, 68, 4, 64, 4161, 1, 32, False),     # 268 units of 17
+    ("bf16", 27, 20, 5, 128, 4200, 5, 32, False),    # 135 units of 20 columns
+    ("bf16", 33, 16, 8, 128, 5000, 1, 2, False),     # 264 units
+    ("bf16", 263, 16, 4, 128, 16420, 1, 4, False),   # 1052
+    ("bf16", 40, 8, 8, 128, 5000, 1, 1, False),      # one column
 ]
 
 
-@pytest.mark.parametrize("dtype,Bz,Hq,Hkv,d,rows,n_q", CASES)
-def test_decode_with_one_chunk_over_long_rows(dtype, Bz, Hq, Hkv, d, rows, n_q):
+@pytest.mark.parametrize("dtype,Bz,Hq,Hkv,d,rows,n_q,part_rows,one", CASES)
+def test_decode_with_few_chunks_over_long_rows(dtype, Bz, Hq, Hkv, d, rows, n_q, part_rows, one):
     print(f"case {dtype} {Bz}x{Hq}/{Hkv}x{d} rows={rows} n_q={n_q}", flush=True)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     g = torch.Generator().manual_seed(rows + Bz)
@@ -41,7 +46,9 @@ def test_decode_with_one_chunk_over_long_rows(dtype, Bz, Hq, Hkv, d, rows, n_q):
                       pool_kernel=1, budget=rows, cap=rows)
     out = torch.full((Bz, Hq, n_q, d), float("nan"), device=DEV)
     lse = torch.full((Bz, Hq, n_q), float("nan"), device=DEV)
-    ws = torch.full((max(256, B.ckv_decode_workspace_bytes(p, n_q, rows)),), 255, dtype=torch.uint8, device=DEV)
+    need, one_chunk = B.ckv_decode_workspace_bytes(p, n_q, rows), Bz * Hkv * part_rows * (d + 2) * 4
+    assert need - need % 256 in (one_chunk - one_chunk % 256, (one_chunk + 255) // 256 * 256) if one else need >= 2 * one_chunk
+    ws = torch.full((need,), 255, dtype=torch.uint8, device=DEV)
     kd, vd = (x.to(DEV).expand(Bz, Hkv, rows, d) for x in (k, v))
     B.ckv_decode_attention(p, q.to(DEV), kd, vd, count.to(DEV), out, lse, ws)
     torch.cuda.synchronize()
