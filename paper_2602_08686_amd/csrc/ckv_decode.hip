@@ -20,8 +20,8 @@
 // RMS error against 64 bits 2.7e-7 -> 2.0e-7 on the first of them. Not faster: both blocks of two in registers at once
 // (85.2, and 11.2 on 544 rows).
 //
-// f32 (decode_partial_kernel): dot products on the vector ALUs, a 16-byte piece of a row per lane, online softmax in the
-// log2 domain, the query heads of a group sharing each row.
+// f32, and bf16 with one query column (decode_partial_kernel): dot products on the vector ALUs, a 16-byte piece of a row per
+// lane, online softmax in the log2 domain, the query heads of a group sharing each row.
 #include <type_traits>
 
 #include "ckv_internal.h"
@@ -46,12 +46,20 @@ constexpr int kXcds = 8;  // accelerator dies of the part; workgroup i of a laun
 constexpr int kDecodeThreads = 256;
 constexpr int kDecodeWaves = kDecodeThreads / kWave;
 
-// A 16-byte piece of an f32 row.
+// A 16-byte piece of a row: four f32 or eight bf16.
 __device__ __forceinline__ void piece_to_float(const uint4 &raw, float (&f)[4]) {
   f[0] = __uint_as_float(raw.x);
   f[1] = __uint_as_float(raw.y);
   f[2] = __uint_as_float(raw.z);
   f[3] = __uint_as_float(raw.w);
+}
+__device__ __forceinline__ void piece_to_float(const uint4 &raw, float (&f)[8]) {
+  const uint32_t words[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f[2 * i] = __uint_as_float(words[i] << 16);
+    f[2 * i + 1] = __uint_as_float(words[i] & 0xffff0000u);
+  }
 }
 
 // Rows of a chunk: a unit's chunks share its valid rows evenly, in whole steps of the workgroup. (With chunks of n_rows instead, a
@@ -67,9 +75,9 @@ __device__ __forceinline__ float exp2_diff(float a, float b) { return exp2f(a - 
 
 // NW waves per workgroup, U row steps whose loads are in flight together (PIPE: of the next block too). With one chunk per
 // (unit, query) the workgroup writes the final result itself and no merge kernel follows.
-template <int DH, int RQ, int NW, int U, bool PIPE>
+template <int DT, int DH, int RQ, int NW, int U, bool PIPE>
 __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a) {
-  constexpr int ESIZE = 4, E = 16 / ESIZE;
+  constexpr int ESIZE = DT == CKV_BF16 ? 2 : 4, E = 16 / ESIZE;
   constexpr int LPR = DH / E;        // lanes per row
   constexpr int KPW = kWave / LPR;   // rows per wave step
   constexpr int ROW = DH + 2;
@@ -617,9 +625,19 @@ static int64_t mfma_chunk_rows(int64_t workgroups, int64_t cols, int n_rows, int
   return best;
 }
 
+// bf16 with one query column per KV head (no grouped heads, one query) has nothing for the other columns of a tile, and on the
+// vector ALUs sixteen waves per CU keep more rows in flight than the eight that the tile's registers leave. vector / matrix, us,
+// rows of 128: 136 units, counts of 2500 of 5000 35 / 45, of 1050 of 9000 21 / 30, of 410 of 544 8.9 / 9.5; 320 units, 1100 of 9000 37 / 52;
+// 640 units, 4200 rows 219 / 231; 1024 units, 410 of 544 38.0 / 40.7; rows of 64: 320 units, 9000 rows 117 / 164. The matrix form stays
+// where units are fewer than half the CUs (V is shared out over workgroups there), for the shortest sets (97 of 130 rows, 136
+// units 6.4 / 5.7) and for up to 4096 rows of 64 (410 of 544, 1024 units 26.5 / 21.2).
+static bool on_vector_alus(const Shape &s, int n_q, int n_rows) {
+  return s.esize == 4 || (s.G * (int64_t)n_q == 1 && (int64_t)s.Bz * s.Hkv >= kComputeUnits / 2 && n_rows > (s.d == 128 ? 256 : 4096));
+}
+
 DecodePlan plan_decode(const Shape &s, int n_q, int n_rows) {
   DecodePlan p;
-  p.mfma = s.esize == 2;
+  p.mfma = !on_vector_alus(s, n_q, n_rows);
   p.rq = query_rows_per_pass(s.G);
   p.head_chunks = (s.G + p.rq - 1) / p.rq;
   p.grid_y = (int64_t)s.Bz * s.Hkv * n_q * p.head_chunks;
@@ -672,16 +690,16 @@ static void launch_decode_bf16(const DecodeArgs &a, const DecodePlan &p, int row
     hipLaunchKernelGGL((decode_merge_kernel<DH, 1, true>), dim3((unsigned)rows), dim3(DH), 0, stream, a);
 }
 
-template <int DH, int RQ>
+template <int DT, int DH, int RQ>
 static void launch_decode_vector(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
   if constexpr (RQ <= 2) {
     if (p.n_chunks == 1) {
-      hipLaunchKernelGGL((decode_partial_kernel<DH, RQ, 16, 2, true>), dim3(1, (unsigned)p.grid_y),
+      hipLaunchKernelGGL((decode_partial_kernel<DT, DH, RQ, 16, 2, true>), dim3(1, (unsigned)p.grid_y),
                          dim3(16 * kWave), 0, stream, a);
       return;
     }
   }
-  hipLaunchKernelGGL((decode_partial_kernel<DH, RQ, kDecodeWaves, 4, false>), dim3(p.n_chunks, (unsigned)p.grid_y),
+  hipLaunchKernelGGL((decode_partial_kernel<DT, DH, RQ, kDecodeWaves, 4, false>), dim3(p.n_chunks, (unsigned)p.grid_y),
                      dim3(kDecodeThreads), 0, stream, a);
   if (p.n_chunks > 1)  // one chunk: the workgroups wrote the results
     hipLaunchKernelGGL((decode_merge_kernel<DH, RQ, false>), dim3((unsigned)rows), dim3(DH), 0, stream, a);
@@ -690,10 +708,10 @@ static void launch_decode_vector(const DecodeArgs &a, const DecodePlan &p, int r
 template <int DH>
 static void launch_decode_rq(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
   switch (p.rq) {
-    case 1: launch_decode_vector<DH, 1>(a, p, rows, stream); break;
-    case 2: launch_decode_vector<DH, 2>(a, p, rows, stream); break;
-    case 4: launch_decode_vector<DH, 4>(a, p, rows, stream); break;
-    default: launch_decode_vector<DH, 8>(a, p, rows, stream); break;
+    case 1: launch_decode_vector<CKV_F32, DH, 1>(a, p, rows, stream); break;
+    case 2: launch_decode_vector<CKV_F32, DH, 2>(a, p, rows, stream); break;
+    case 4: launch_decode_vector<CKV_F32, DH, 4>(a, p, rows, stream); break;
+    default: launch_decode_vector<CKV_F32, DH, 8>(a, p, rows, stream); break;
   }
 }
 
@@ -724,7 +742,9 @@ hipError_t launch_decode_attention(const ckv_params *p, const Shape &s, const vo
   a.part_cols = (int)least64(kCols, a.cols);
   const int rows = s.Bz * s.Hq * n_q;
   if (p->dtype == CKV_BF16) {
-    if (s.d == 128) launch_decode_bf16<128>(a, plan, rows, stream);
+    if (!plan.mfma && s.d == 128) launch_decode_vector<CKV_BF16, 128, 1>(a, plan, rows, stream);
+    else if (!plan.mfma) launch_decode_vector<CKV_BF16, 64, 1>(a, plan, rows, stream);
+    else if (s.d == 128) launch_decode_bf16<128>(a, plan, rows, stream);
     else launch_decode_bf16<64>(a, plan, rows, stream);
   } else {
     if (s.d == 128) launch_decode_rq<128>(a, plan, rows, stream);

@@ -70,6 +70,7 @@ def _decode_before_a_fence(path, dtype, d, heads, n_q, n_rows, counts):
 @pytest.mark.parametrize("dtype,d,heads,n_q,n_rows,counts", [
     ("bf16", 128, 4, 1, 544, [33, 70]), ("bf16", 64, 2, 2, 300, [0, 1]), ("bf16", 128, 1, 1, 4096, [64]), ("bf16", 128, 17, 1, 96, [95]),
     ("bf16", 128, 4, 1, 4500, [130, 257]), ("bf16", 64, 3, 1, 8000, [0, 0]), ("bf16", 128, 2, 1, 4200, [4200]),
+    ("bf16", 128, 1, 1, 300, [40] * 128 + [17]), ("bf16", 128, 1, 1, 4100, [3] * 132 + [70]),   # one column: the vector kernel
     ("f32", 64, 2, 1, 544, [33, 70]), ("f32", 128, 4, 1, 4500, [1, 100]),
 ])
 def test_decode_reads_no_row_behind_the_count(lib_path, dtype, d, heads, n_q, n_rows, counts):

@@ -1,6 +1,6 @@
 """Decode attention over long KV sets of many units: so many (unit, query) workgroups that the rows are not cut (one chunk per
 workgroup, which writes the result itself; no merge follows), or few chunks each. f32 with every count of heads a workgroup
-takes, bf16 with one column, one and several column tiles, unit counts that are no multiple of
+takes, bf16 with one column (on the vector ALUs), and one and several column tiles, unit counts that are no multiple of
 eight; counts of zero, one and all. All units read the same rows
 (strides of zero), which keeps the memory small. Against the oracle with the tolerances of test_gpu_decode.py; every output is
 prefilled with NaN, so one that nobody writes shows up."""
@@ -28,7 +28,8 @@ CASES = [
     ("bf16", 27, 20, 5, 128, 4200, 5, 32, False),    # 135 units of 20 columns
     ("bf16", 33, 16, 8, 128, 5000, 1, 2, False),     # 264 units
     ("bf16", 263, 16, 4, 128, 16420, 1, 4, False),   # 1052
-    ("bf16", 40, 8, 8, 128, 5000, 1, 1, False),      # one column
+    ("bf16", 40, 8, 8, 128, 5000, 1, 1, False),      # one column: the vector kernel, chunks
+    ("bf16", 4099, 1, 1, 128, 16400, 1, 1, True),    # and one chunk
 ]
 
 
