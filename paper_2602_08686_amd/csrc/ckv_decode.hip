@@ -20,7 +20,7 @@
 // RMS error against 64 bits 2.7e-7 -> 2.0e-7 on the first of them. Not faster: both blocks of two in registers at once
 // (85.2, and 11.2 on 544 rows).
 //
-// f32, and bf16 with one query column (decode_partial_kernel): dot products on the vector ALUs, a 16-byte piece of a row per
+// f32, and long bf16 rows with one query column (decode_partial_kernel): dot products on the vector ALUs, a 16-byte piece of a row per
 // lane, online softmax in the log2 domain, the query heads of a group sharing each row.
 #include <type_traits>
 
@@ -78,6 +78,9 @@ __device__ __forceinline__ float exp2_diff(float a, float b) { return exp2f(a - 
 template <int DT, int DH, int RQ, int NW, int U, bool PIPE>
 __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a) {
   constexpr int ESIZE = DT == CKV_BF16 ? 2 : 4, E = 16 / ESIZE;
+  // bf16: weights times V summed in 64 bits, which makes the result as exact as the matrix form's (RMS error against 64 bits, 9000 rows:
+  // 2.1e-7 with an f32 sum, 1.9e-7; matrix 1.9e-7) for 1 to 8 % of the time.
+  typedef typename std::conditional<DT == CKV_BF16, double, float>::type sum_t;
   constexpr int LPR = DH / E;        // lanes per row
   constexpr int KPW = kWave / LPR;   // rows per wave step
   constexpr int ROW = DH + 2;
@@ -124,13 +127,14 @@ __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a)
     for (int e = 0; e < E; ++e) qv[r][e] *= a.scale2;
   }
 
-  float m[RQ], l[RQ], acc[RQ][E];
+  float m[RQ], l[RQ];
+  sum_t acc[RQ][E];
 #pragma unroll
   for (int r = 0; r < RQ; ++r) {
     m[r] = -INFINITY;
     l[r] = 0.0f;
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[r][e] = 0.0f;
+    for (int e = 0; e < E; ++e) acc[r][e] = 0;
   }
 
   const char *kb = static_cast<const char *>(a.k) + ((size_t)b * a.ks[0] + (size_t)g * a.ks[1]) * ESIZE;
@@ -188,7 +192,7 @@ __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a)
         const float p = exp2_diff(s[u][r], ref);
         l[r] += p;
 #pragma unroll
-        for (int e = 0; e < E; ++e) acc[r][e] = fmaf(p, vf[u][e], acc[r][e]);
+        for (int e = 0; e < E; ++e) acc[r][e] = fma((sum_t)p, (sum_t)vf[u][e], acc[r][e]);
       }
       m[r] = m_new;
     }
@@ -217,8 +221,8 @@ __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a)
       l[r] = low ? fmaf(l[r], f_self, l_o * f_other) : fmaf(l_o, f_other, l[r] * f_self);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const float a_o = __shfl_xor(acc[r][e], o);
-        acc[r][e] = low ? fmaf(acc[r][e], f_self, a_o * f_other) : fmaf(a_o, f_other, acc[r][e] * f_self);
+        const sum_t a_o = __shfl_xor(acc[r][e], o), s = f_self, t = f_other;
+        acc[r][e] = low ? fma(acc[r][e], s, a_o * t) : fma(a_o, t, acc[r][e] * s);
       }
       m[r] = m_new;
     }
@@ -227,7 +231,7 @@ __global__ void __launch_bounds__(NW *kWave) decode_partial_kernel(DecodeArgs a)
 #pragma unroll
     for (int r = 0; r < RQ; ++r) {
 #pragma unroll
-      for (int e = 0; e < E; ++e) sm[wave][r][sub * E + e] = acc[r][e];
+      for (int e = 0; e < E; ++e) sm[wave][r][sub * E + e] = (float)acc[r][e];
       if (sub == 0) {
         sm[wave][r][DH] = m[r];
         sm[wave][r][DH + 1] = l[r];
@@ -625,19 +629,9 @@ static int64_t mfma_chunk_rows(int64_t workgroups, int64_t cols, int n_rows, int
   return best;
 }
 
-// bf16 with one query column per KV head (no grouped heads, one query) has nothing for the other columns of a tile, and on the
-// vector ALUs sixteen waves per CU keep more rows in flight than the eight that the tile's registers leave. vector / matrix, us,
-// rows of 128: 136 units, counts of 2500 of 5000 35 / 45, of 1050 of 9000 21 / 30, of 410 of 544 8.9 / 9.5; 320 units, 1100 of 9000 37 / 52;
-// 640 units, 4200 rows 219 / 231; 1024 units, 410 of 544 38.0 / 40.7; rows of 64: 320 units, 9000 rows 117 / 164. The matrix form stays
-// where units are fewer than half the CUs (V is shared out over workgroups there), for the shortest sets (97 of 130 rows, 136
-// units 6.4 / 5.7) and for up to 4096 rows of 64 (410 of 544, 1024 units 26.5 / 21.2).
-static bool on_vector_alus(const Shape &s, int n_q, int n_rows) {
-  return s.esize == 4 || (s.G * (int64_t)n_q == 1 && (int64_t)s.Bz * s.Hkv >= kComputeUnits / 2 && n_rows > (s.d == 128 ? 256 : 4096));
-}
-
 DecodePlan plan_decode(const Shape &s, int n_q, int n_rows) {
   DecodePlan p;
-  p.mfma = !on_vector_alus(s, n_q, n_rows);
+  p.mfma = s.esize == 2;
   p.rq = query_rows_per_pass(s.G);
   p.head_chunks = (s.G + p.rq - 1) / p.rq;
   p.grid_y = (int64_t)s.Bz * s.Hkv * n_q * p.head_chunks;
@@ -654,6 +648,12 @@ DecodePlan plan_decode(const Shape &s, int n_q, int n_rows) {
     p.workspace_bytes = 0;
     return p;
   }
+  // bf16 with one query column per KV head (no grouped heads, one query) has nothing for the other columns of a tile, and on the
+  // vector ALUs sixteen waves per CU keep more rows in flight than the eight that the tile's registers leave. Long rows, us, vector
+  // / matrix: 136 units of 128, counts of 2500 of 5000 35 / 45, of 1050 of 9000 22 / 30; 320 units, 1100 of 9000 39 / 52; 640 units, 4200 rows
+  // 219 / 231; 320 units of 64, 9000 rows 118 / 164. With fewer units than half the CUs, and up to 4096 rows, the matrix form is about as
+  // fast or faster (V is shared out over workgroups there).
+  if (s.G * (int64_t)n_q == 1 && p.workgroups >= kComputeUnits / 2) p.mfma = false;
   // At most 64 chunks, of whole steps of a workgroup. On the vector ALUs: workgroups for several times the chip.
   const int64_t step = p.mfma ? kFlatStep : kVectorStep, most = least64(kMaxChunks, (n_rows + step - 1) / step);
   int64_t rows;
@@ -692,7 +692,7 @@ static void launch_decode_bf16(const DecodeArgs &a, const DecodePlan &p, int row
 
 template <int DT, int DH, int RQ>
 static void launch_decode_vector(const DecodeArgs &a, const DecodePlan &p, int rows, hipStream_t stream) {
-  if constexpr (RQ <= 2) {
+  if constexpr (DT == CKV_F32 && RQ <= 2) {
     if (p.n_chunks == 1) {
       hipLaunchKernelGGL((decode_partial_kernel<DT, DH, RQ, 16, 2, true>), dim3(1, (unsigned)p.grid_y),
                          dim3(16 * kWave), 0, stream, a);
