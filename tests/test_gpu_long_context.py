@@ -1,6 +1,6 @@
 """Contexts of one and a half and two million tokens (the scan's 32-bit offsets, the selection split over
-hundreds of workgroups, the streaming selection for a prefix that is no multiple of four), through both
-call sequences, every element against the oracle (8-13 s of oracle time per case on 16 cores)."""
+hundreds of workgroups, a prefix that is no multiple of four), through both call sequences, every element
+against the oracle (8-13 s of oracle time per case on 16 cores)."""
 import numpy as np
 import pytest
 import torch
@@ -17,7 +17,7 @@ CASES = [
     # P = 2^21: fused utility pass, 256 selection slices per unit
     wl.Workload("long_2m", "bf16", 1, 4, 1, 128, 2 ** 21 + 32, 32, wl.POOL_AVG, 7, 4096, 2, seed=4242, head_key_scale=True,
                 shares=True, needles=8),
-    # ragged everything: P % 4 = 3 (the two unfused steps, streaming selection), two tiles per head
+    # ragged everything: P % 4 = 3, two tiles per head
     wl.Workload("long_1m5_ragged", "bf16", 1, 6, 2, 128, 1500007, 64, wl.POOL_MAX, 5, 4096, 2, seed=4243, sink_scale=8.0,
                 shares=True, needles=8),
 ]

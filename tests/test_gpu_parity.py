@@ -288,7 +288,8 @@ def test_select_long_context_unit():
 
 
 def test_select_split_over_workgroups_long_prefixes():
-    """Prefixes beyond 65536 positions with a workspace: several workgroups per unit, same unique result."""
+    """Prefixes beyond 65536 positions with a workspace: several workgroups per unit, same unique result. Lists of up to about
+    a thousand entries take slices and their merge, longer ones the split selection."""
     rng = np.random.default_rng(9)
     one, zero = np.ones(1, np.float32), np.zeros(1, np.float32)
     u = (rng.standard_normal((1, 2, 131072 - 64)) ** 2).astype(np.float32)
@@ -306,7 +307,7 @@ def test_select_split_over_workgroups_long_prefixes():
     # values that differ only in the low mantissa bits, 25 slices
     near = (np.float32(1.0) + np.arange(200000, dtype=np.float32) % 97 * np.float32(1.2e-7)).reshape(1, 1, -1)
     _select_case(near.astype(np.float32), zero, np.array([[50032]], np.int32), 32, 50032, True)
-    # a prefix length that is not a multiple of four takes the streaming kernel, workspace or not
+    # a prefix length that is not a multiple of four
     _select_case(rng.random((1, 1, 70001)).astype(np.float32), zero, np.array([[777]], np.int32), 32, 800, True)
 
 

@@ -31,25 +31,25 @@ def test_select_matches_oracle_at_the_borders(P, kind, workspace):
     print(f"case P={P} {kind} workspace={workspace}", flush=True)
     rng = np.random.default_rng(P + len(kind))
     W, Hkv, T = 4, 2, P + 4
-    u = _values(rng, kind, (1, Hkv, P))
+    u = np.repeat(_values(rng, kind, (1, Hkv, P)), 2, axis=0)
     flat = torch.empty(u.size + 1, device=DEV)
     ut = flat[1:].view(u.shape)       # one float past an aligned address
     ut.copy_(torch.from_numpy(u))
     for quota in sorted({min(q, P) for q in QUOTAS}):
         for tau in (0.0, 1.3):
             cap = W + quota
-            # one head at its nominal budget, one at the smallest: the other way round beside it
-            budget = np.array([[W + quota, W + min(quota, 1)]], np.int32)
-            p = B.make_params(batch=1, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=T, window=W, dtype="bf16",
+            # one head at its nominal budget, one at the smallest, and the other way round
+            budget = np.array([[W + quota, W + min(quota, 1)], [W + min(quota, 1), W + quota]], np.int32)
+            p = B.make_params(batch=2, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=T, window=W, dtype="bf16",
                               pool=B.POOL_NONE, pool_kernel=1, budget=W + quota // 2, cap=cap)
             ws = None
             if workspace:   # contents on entry are ignored: ones
                 ws = torch.full((max(256, B.ckv_workspace_bytes(p)),), 255, dtype=torch.uint8, device=DEV)
-            idx = torch.full((1, Hkv, cap), -1, dtype=torch.int32, device=DEV)
-            count = torch.empty(1, Hkv, dtype=torch.int32, device=DEV)
-            B.ckv_select_topk(p, ut, torch.from_numpy(budget).to(DEV), torch.full((1,), tau, device=DEV), idx, count, ws)
+            idx = torch.full((2, Hkv, cap), -1, dtype=torch.int32, device=DEV)
+            count = torch.empty(2, Hkv, dtype=torch.int32, device=DEV)
+            B.ckv_select_topk(p, ut, torch.from_numpy(budget).to(DEV), torch.full((2,), tau, device=DEV), idx, count, ws)
             torch.cuda.synchronize()
-            oi, oc = oracle.select(u, np.array([tau], np.float32), budget, W, cap)
+            oi, oc = oracle.select(u, np.array([tau, tau], np.float32), budget, W, cap)
             np.testing.assert_array_equal(count.cpu().numpy(), oc)
             np.testing.assert_array_equal(idx.cpu().numpy(), oi)
 
