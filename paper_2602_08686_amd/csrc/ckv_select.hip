@@ -908,23 +908,23 @@ struct SlicePlan {
 // The budgets are on the device, so the rule goes by what heads are likely to have: twice the nominal quota, and with room for
 // eight times. Slices + merge / split selection, us, 34000 to 262144 positions, 8 heads, batch 1 and 4, two distributions, where the
 // largest quota of a unit's heads is up to 2048: 15-25 / 24-35 and 15-34 / 25-89; where it is 3072: 27-45 / 24-35 and 28-46 /
-// 25-49. So twice the nominal quota has to be at most 2048. With half of a nominal 8 x 1024 in one head 35-45 / 24-49, with all
-// of it 40-75 / 24-49.
+// 25-49. So twice the nominal quota, or all that cap leaves a head, has to be at most 2048. With half of a nominal 8 x 1024 in
+// one head 35-45 / 24-49, with all of it 40-75 / 24-49. One KV head alone, 65504 to 262112 positions, 1100 to 2016: 18-24 / 28-31.
 // A unit has at most 65536 pairs, which the merge takes in registers (streaming more of them, as it did, took one workgroup
-// 90-600 us). There is room in them for eight times the nominal quota, or the split is taken; a head with more than the room is
+// 90-600 us). There is room in them for eight times the nominal quota (and one), or the split is taken; a head with more than the room is
 // selected from its row by one workgroup (32 heads, all of the budget in one, 128k: 219-247 / 43-49; before 223-295).
 // 8192 positions per slice where the merge then has at most 8192 pairs, which it takes eight to a thread; else 16384, which
 // halves the pairs (98304 positions, 32 units, 512: 20 -> 17 us; one head at twice that 23 -> 18).
 static SlicePlan plan_slices(const ckv_params *p, const Shape &s) {
   SlicePlan plan = {0, 0, 0, 0};
   const int64_t quota = p->budget_per_kv_head - s.W;
-  if (s.P <= kOneLaunch || 2 * quota > 2048) return plan;
   const int most = max(1, min(p->cap, s.T) - s.W);
   const auto up = [](int64_t x) { return (x + kWave - 1) / kWave * kWave; };
   const auto least = [](int64_t x, int64_t y) { return x < y ? x : y; };
+  if (s.P <= kOneLaunch || least(most, 2 * quota) > 2048) return plan;
   for (int limit = 8 * kSelectThreads; limit <= 16 * kSelectThreads; limit *= 2) {
     const int64_t n = slices(s, limit), room = kMergePairs / n / kWave * kWave, top = least(limit, most);
-    if (up(least(top, 8 * quota)) > room || (limit == 8 * kSelectThreads && n * least(top, 2 * quota) > 8 * kSelectThreads)) continue;
+    if (up(least(top, 8 * quota + 1)) > room || (limit == 8 * kSelectThreads && n * least(top, 2 * quota) > 8 * kSelectThreads)) continue;
     plan.S = (int)n;
     plan.limit = limit;
     plan.slice = (int)up((s.P + n - 1) / n);  // equal lengths: a short last one would keep all it has

@@ -288,8 +288,8 @@ def test_select_long_context_unit():
 
 
 def test_select_split_over_workgroups_long_prefixes():
-    """Prefixes beyond 65536 positions with a workspace: several workgroups per unit, same unique result. Lists of up to about
-    a thousand entries take slices and their merge, longer ones the split selection."""
+    """Prefixes beyond 65536 positions with a workspace: several workgroups per unit, same unique result. All by slices
+    and their merge (the nominal budget is the window's), lists beyond the room for pairs by the merge from the row itself."""
     rng = np.random.default_rng(9)
     one, zero = np.ones(1, np.float32), np.zeros(1, np.float32)
     u = (rng.standard_normal((1, 2, 131072 - 64)) ** 2).astype(np.float32)

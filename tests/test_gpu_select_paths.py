@@ -64,8 +64,9 @@ def _bytes(units, P, W, budget, cap, Hkv):
 @pytest.mark.parametrize("P,top", [(32769, 8192), (65540, 15000), (70001, 12000), (131040, 9000), (200000, 7000)])
 def test_select_over_long_rows_by_both_forms(P, top, kind, form):
     """Slices and merge, and the split selection, on the same rows: budgets from nothing to `top` for one head (beyond 32768
-    pairs for the merge, and beyond the room for pairs), heads with fewer candidates than their budget, candidates that only position or the last bits of
-    the mantissa tell apart. The nominal budget decides the form; the size of the workspace tells which one it is."""
+    pairs for the merge, and beyond the room for pairs), heads with fewer candidates than their budget, candidates that only
+    position or the last bits of the mantissa tell apart. The nominal budget decides the form; the size of the workspace
+    tells which one it is."""
     print(f"case P={P} top={top} {kind} {form}", flush=True)
     rng = np.random.default_rng(P + len(kind))
     W, Hkv, bz = 4, 5, 2
@@ -87,5 +88,28 @@ def test_select_over_long_rows_by_both_forms(P, top, kind, form):
     B.ckv_select_topk(p, torch.from_numpy(u).to(DEV), torch.from_numpy(budget).to(DEV), torch.from_numpy(tau).to(DEV), idx, count, ws)
     torch.cuda.synchronize()
     oi, oc = oracle.select(u, tau, budget, W, p.cap)
+    np.testing.assert_array_equal(count.cpu().numpy(), oc)
+    np.testing.assert_array_equal(idx.cpu().numpy(), oi)
+
+
+@pytest.mark.parametrize("P", [32769, 65540, 262145])
+@pytest.mark.parametrize("top", [1025, 1468, 2048])
+def test_select_over_long_rows_of_one_head(P, top):
+    """One KV head: the nominal budget is all that it can have, so slices and their merge serve it up to a list of 2048 entries
+    (half of that where other heads can leave it theirs); the size of the workspace tells."""
+    print(f"case P={P} top={top}", flush=True)
+    W, bz = 4, 2
+    u = _values(np.random.default_rng(P + top), "ties", (bz, 1, P))
+    tau, budget = np.zeros(bz, np.float32), np.array([[W + top], [W + 1]], np.int32)
+    cap = W + top
+    assert _bytes(bz, P, W, cap, cap, 1) > _bytes(bz, P, W, W + 2049, W + 2049, 1)
+    p = B.make_params(batch=bz, n_q_heads=1, n_kv_heads=1, head_dim=64, seq_len=P + W, window=W, dtype="bf16", pool=B.POOL_NONE,
+                      pool_kernel=1, budget=cap, cap=cap)
+    ws = torch.full((B.ckv_workspace_bytes(p),), 255, dtype=torch.uint8, device=DEV)
+    idx = torch.full((bz, 1, cap), -1, dtype=torch.int32, device=DEV)
+    count = torch.empty(bz, 1, dtype=torch.int32, device=DEV)
+    B.ckv_select_topk(p, torch.from_numpy(u).to(DEV), torch.from_numpy(budget).to(DEV), torch.from_numpy(tau).to(DEV), idx, count, ws)
+    torch.cuda.synchronize()
+    oi, oc = oracle.select(u, tau, budget, W, cap)
     np.testing.assert_array_equal(count.cpu().numpy(), oc)
     np.testing.assert_array_equal(idx.cpu().numpy(), oi)
