@@ -86,6 +86,35 @@ __device__ __forceinline__ float row_sum(float x) {
   return x;
 }
 
+// Scans and reductions over the wave with lane moves inside the vector unit (row shifts by 1, 2, 4, 8, then the
+// last lane of a row of 16 to the next row and of the lower half to the upper): a shuffle through LDS costs over
+// a hundred cycles per step, and these chains are most of what a short selection waits for.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t identity, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)x, CTRL, ROWS, 0xF, false);
+}
+template <class Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {  // inclusive; lane 63: the total
+  x = op(x, dpp_from<0x111, 0xF>(identity, x));
+  x = op(x, dpp_from<0x112, 0xF>(identity, x));
+  x = op(x, dpp_from<0x114, 0xF>(identity, x));
+  x = op(x, dpp_from<0x118, 0xF>(identity, x));
+  x = op(x, dpp_from<0x142, 0xA>(identity, x));
+  x = op(x, dpp_from<0x143, 0xC>(identity, x));
+  return x;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane) {  // lane is wave-uniform
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
+}
+__device__ __forceinline__ int wave_inclusive(int x) {
+  return (int)wave_scan((uint32_t)x, 0u, [](uint32_t p, uint32_t q) { return p + q; });
+}
+
+// c + the set bits of the mask below this lane
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long mask, uint32_t c) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, c));
+}
+
 ckv_status validate(const ckv_params *p);
 void derive(const ckv_params *p, Shape *s);
 

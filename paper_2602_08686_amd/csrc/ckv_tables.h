@@ -33,61 +33,84 @@ struct TablesArgs {
   int n_tiles;
 };
 
-// Per-head budgets of one batch element (same rule for every b; written per b for the ABI's layout).
-__device__ inline void write_budgets(const TablesArgs &a, int b) {
+// Per-head budgets of one batch element (same rule for every b; written per b for the ABI's layout), by one whole wave: lane i
+// has heads i, i + 64, ... A thread going over the heads by itself was the longest path of the tables kernels (4 heads
+// 2.5 us, 8 heads 4 to 5 with the shares' loads one behind the other).
+__device__ __forceinline__ void write_budgets(const TablesArgs &a, int b, int lane) {
   int32_t *out = a.budget + (size_t)b * a.Hkv;
   if (!a.share_row) {
-    for (int g = 0; g < a.Hkv; ++g) out[g] = min(a.B, a.T);
+    for (int g = lane; g < a.Hkv; g += kWave) out[g] = min(a.B, a.T);
     return;
   }
+  const auto sum = [](uint32_t p, uint32_t q) { return p + q; };
+  const auto larger = [](uint32_t p, uint32_t q) { return max(p, q); };
+  const auto total_of = [&](uint32_t x) { return (int)lane_value(wave_scan(x, 0u, sum), kWave - 1); };
+  const auto largest_of = [&](uint32_t x) { return (int)lane_value(wave_scan(x, 0u, larger), kWave - 1); };
   const long long b_tot = (long long)a.B * a.Hkv;
-  long long total = 0;
-  for (int g = 0; g < a.Hkv; ++g) {
+  // up to 64 heads a lane's only value stays in a register, beyond that its values are in out
+  const bool one = a.Hkv <= kWave;
+  int mine = 0;
+  const auto get = [&](int g) { return one ? mine : out[g]; };
+  const auto set = [&](int g, int v) {
+    if (one) mine = v;
+    else out[g] = v;
+  };
+  int total = 0;  // Hkv * T < 2^29
+  for (int g = lane; g < a.Hkv; g += kWave) {
     double want = floor((double)a.share_row[g] * (double)b_tot);
     if (!(want >= (double)a.W)) want = (double)a.W;
     if (want > (double)a.T) want = (double)a.T;
-    out[g] = (int32_t)want;
-    total += out[g];
+    set(g, (int)want);
+    total += (int)want;
   }
   // "While the sum exceeds B_tot, the largest budget above W (lowest head on ties) loses one", done
   // a level at a time: the n1 leaders drop together to the runner-up's value (never below W), or,
   // when the excess runs out first, share it evenly with the remainder going to the lowest heads.
-  long long excess = total - b_tot;
-  while (excess > 0) {
+  long long excess = (long long)total_of((uint32_t)total) - b_tot;
+  while (excess > 0) {  // uniform
     int v1 = a.W, v2 = a.W, n1 = 0;
-    for (int g = 0; g < a.Hkv; ++g) v1 = max(v1, out[g]);
+    for (int g = lane; g < a.Hkv; g += kWave) v1 = max(v1, get(g));
+    v1 = largest_of((uint32_t)v1);
     if (v1 <= a.W) break;
-    for (int g = 0; g < a.Hkv; ++g) {
-      if (out[g] == v1) ++n1;
-      else v2 = max(v2, out[g]);
+    for (int g = lane; g < a.Hkv; g += kWave) {
+      const int v = get(g);
+      if (v == v1) ++n1;
+      else v2 = max(v2, v);
     }
+    v2 = largest_of((uint32_t)v2);
+    n1 = total_of((uint32_t)n1);
     const long long drop = v1 - v2;
     if ((long long)n1 * drop <= excess) {
-      for (int g = 0; g < a.Hkv; ++g)
-        if (out[g] == v1) out[g] = v2;
+      for (int g = lane; g < a.Hkv; g += kWave)
+        if (get(g) == v1) set(g, v2);
       excess -= (long long)n1 * drop;
     } else {
-      const int each = (int)(excess / n1);
-      int extra = (int)(excess % n1);
-      for (int g = 0; g < a.Hkv; ++g)
-        if (out[g] == v1) {
-          out[g] = v1 - each - (extra > 0 ? 1 : 0);
-          if (extra > 0) --extra;
-        }
+      const int each = (int)(excess / n1), extra = (int)(excess % n1);
+      int before = 0;  // leaders among the heads in front of these 64
+      for (int g0 = 0; g0 < a.Hkv; g0 += kWave) {
+        const int g = g0 + lane;
+        const bool leads = g < a.Hkv && get(g) == v1;
+        const unsigned long long mask = __ballot(leads);
+        if (leads) set(g, v1 - each - ((int)lanes_below(mask, (uint32_t)before) < extra ? 1 : 0));
+        before += __popcll(mask);
+      }
       excess = 0;
     }
   }
+  if (one && lane < a.Hkv) out[lane] = mine;
 }
 
-__device__ __forceinline__ void write_tau_and_budgets(const TablesArgs &a, int b) {
-  float tau = 0.0f;
-  if (a.gate_layer) {
-    const int be = min(max(a.risk_bins[2 * b], 0), a.n_ent - 1);
-    const int bp = min(max(a.risk_bins[2 * b + 1], 0), a.n_ppl - 1);
-    tau = a.gate_layer[be * a.n_ppl + bp];
+__device__ __forceinline__ void write_tau_and_budgets(const TablesArgs &a, int b, int lane) {
+  if (lane == 0) {
+    float tau = 0.0f;
+    if (a.gate_layer) {
+      const int be = min(max(a.risk_bins[2 * b], 0), a.n_ent - 1);
+      const int bp = min(max(a.risk_bins[2 * b + 1], 0), a.n_ppl - 1);
+      tau = a.gate_layer[be * a.n_ppl + bp];
+    }
+    a.tau[b] = tau;
   }
-  a.tau[b] = tau;
-  write_budgets(a, b);
+  write_budgets(a, b, lane);
 }
 
 // Fast path for pooling kernels of at most kWindowTaps taps: a thread owns four consecutive positions and reads them
@@ -213,7 +236,7 @@ inline TablesArgs tables_args(const ckv_params *p, const Shape &s, const float *
   a.kernel = p->pool == CKV_POOL_NONE ? 1 : p->pool_kernel;
   a.radius = a.kernel / 2;
   a.B = p->budget_per_kv_head;
-  a.n_tiles = s.P > 0 ? (s.P + kTablesTile - 1) / kTablesTile : 1;
+  a.n_tiles = (s.P + kTablesTile - 1) / kTablesTile;
   return a;
 }
 

@@ -17,8 +17,10 @@ __global__ void __launch_bounds__(kTablesThreads) tables_kernel(TablesArgs a) {
   const int b = unit / a.Hkv, g = unit % a.Hkv;
   const int t0 = tile * kTablesTile;
 
-  if (tile == 0 && g == 0 && threadIdx.x == 0) write_tau_and_budgets(a, b);
-  if (a.P == 0) return;
+  if (tile == a.n_tiles) {  // the workgroups behind the tiles: tau and the budgets
+    if (g == 0 && threadIdx.x < kWave) write_tau_and_budgets(a, b, threadIdx.x);
+    return;
+  }
 
   float best[kTablesPerThread];
   float rho[kTablesPerThread];
@@ -68,7 +70,10 @@ template <int POOL, int R>
 __global__ void __launch_bounds__(kTablesThreads) tables_window_kernel(TablesArgs a) {
   const int unit = blockIdx.y;
   const int t = (blockIdx.x * kTablesThreads + threadIdx.x) * 4;  // first of this thread's positions
-  if (blockIdx.x == 0 && unit % a.Hkv == 0 && threadIdx.x == 0) write_tau_and_budgets(a, unit / a.Hkv);
+  if ((int)blockIdx.x == a.n_tiles) {  // the workgroups behind the tiles: tau and the budgets
+    if (unit % a.Hkv == 0 && threadIdx.x < kWave) write_tau_and_budgets(a, unit / a.Hkv, threadIdx.x);
+    return;
+  }
   if (t >= a.P) return;
   pool_four<POOL, R>(a, unit, t);
 }
@@ -80,7 +85,10 @@ constexpr int kFixupThreads = 64;
 template <int POOL, int R>
 __global__ void __launch_bounds__(kFixupThreads) tables_fixup_kernel(TablesArgs a, FixupArgs f) {
   const int unit = blockIdx.y, range = blockIdx.x;
-  if (range == 0 && unit % a.Hkv == 0 && threadIdx.x == 0) write_tau_and_budgets(a, unit / a.Hkv);
+  if (range == f.n_ranges) {
+    if (unit % a.Hkv == 0) write_tau_and_budgets(a, unit / a.Hkv, threadIdx.x);
+    return;
+  }
   fixup_range<POOL, R>(a, f, unit, range, threadIdx.x, kFixupThreads);
 }
 
@@ -102,7 +110,7 @@ hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float 
                                float *utility, int32_t *budget, float *tau, hipStream_t stream) {
   const TablesArgs a = tables_args(p, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins,
                                    utility, budget, tau);
-  const dim3 grid(a.n_tiles, s.Bz * s.Hkv), block(kTablesThreads);
+  const dim3 grid(a.n_tiles + 1, s.Bz * s.Hkv), block(kTablesThreads);
   bool done = false;
   if (s.P > 0 && s.T >= 4 && a.kernel <= kWindowTaps)
     done = p->pool == CKV_POOL_MAX ? launch_window_pool<CKV_POOL_MAX>(a, grid, stream)
@@ -132,7 +140,7 @@ hipError_t launch_utility_fixup(const ckv_params *p, const Shape &s, const float
   FixupArgs f;
   f.keys_per_wave = s.keys_per_wave;
   f.n_ranges = s.n_chunks * kScoreWaves;
-  const dim3 grid(f.n_ranges, s.Bz * s.Hkv);
+  const dim3 grid(f.n_ranges + 1, s.Bz * s.Hkv);
   if (p->pool == CKV_POOL_MAX) launch_fixup_pool<CKV_POOL_MAX>(a, f, grid, stream);
   else launch_fixup_pool<CKV_POOL_AVG>(a, f, grid, stream);
   return hipGetLastError();
