@@ -140,15 +140,16 @@ __device__ __forceinline__ void load_q_tiles(const ScoreArgs &a, const BlockCoor
 // of one tile. The maximum is taken on the raw dot products (the scale is positive); scale and
 // subtraction are one FMA per element.
 template <bool EDGE>
-__device__ __forceinline__ void rowstats_update(const f32x16 &acc, float c2, int t0, int hh, int limit,
+__device__ __forceinline__ void rowstats_update(const f32x16 &acc, float c2, int t0, int hh, int first, int limit,
                                                 float &rm, float &rl) {
   float v[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) v[r] = acc[r];
-  if (EDGE) {
+  if (EDGE) {  // keys in front of `first` and beyond `limit` do not count: one unsigned comparison for both
+    const uint32_t span = (uint32_t)max(limit - first + 1, 0);
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-      if (t0 + acc_row(r, hh) > limit) v[r] = -INFINITY;
+      if ((uint32_t)(t0 - first + acc_row(r, hh)) >= span) v[r] = -INFINITY;
   }
   float t[4];
 #pragma unroll
@@ -213,13 +214,13 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) r
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         mma_chain<DT, NCH>(acc, kf, qf[i]);  // rows: keys, cols: query rows
-        rowstats_update<true>(acc, a.c2, t0, hh, limit[i], rm[i], rl[i]);
+        rowstats_update<true>(acc, a.c2, t0, hh, t0, limit[i], rm[i], rl[i]);
       }
     } else {
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         mma_chain<DT, NCH>(acc, kf, qf[i]);
-        rowstats_update<false>(acc, a.c2, t0, hh, limit[i], rm[i], rl[i]);
+        rowstats_update<false>(acc, a.c2, t0, hh, t0, limit[i], rm[i], rl[i]);
       }
     }
   };
@@ -482,16 +483,15 @@ __device__ __forceinline__ void dma_tile(const char *tile_base, const uint32_t (
              voff[4 * q + 2] + q * 4096, voff[4 * q + 3] + q * 4096);
 }
 
-// A tile whose rows may run past the last key: row indices are clamped (the logits of the clamped
-// rows are masked by the caller). Outside the pipeline, so the plain form will do.
+// The only tile of a sequence shorter than a tile: row indices are clamped (the logits of the clamped rows are masked by
+// the caller).
 template <class G>
-__device__ __forceinline__ void dma_tile_clamped(const char *kbase, int64_t ks_t, int t0, int T, int lane,
-                                                 char *image) {
+__device__ __forceinline__ void dma_tile_clamped(const char *kbase, int64_t ks_t, int T, int lane, char *image) {
 #pragma unroll
   for (int i = 0; i < G::NDMA; ++i) {
     int r, kappa;
     dma_source<G>(i, lane, r, kappa);
-    const char *src = kbase + (int64_t)min(t0 + r, T - 1) * ks_t + kappa * 16;
+    const char *src = kbase + (int64_t)min(r, T - 1) * ks_t + kappa * 16;
     __builtin_amdgcn_global_load_lds((glb_void_t *)src, (lds_void_t *)(uintptr_t)(image + i * 1024), 16, 0, 0);
   }
 }
@@ -532,16 +532,28 @@ static_assert(kRing % 2 == 0, "half a ring cycle starts at an even image");
 __host__ __device__ constexpr int vector_per_mfma_pass1(int nq) { return 6; }
 __host__ __device__ constexpr int vector_per_mfma_pass2(int nq) { return nq > 4 ? 4 : 6; }
 
+// The tiles behind the pipeline run the same two stages over the query tiles of one key tile (the masks make their vector part
+// half as long again).
+constexpr int kTailVectorPerMfma = 8;
+
 // Geometry of a wave's key range: wave-uniform values live in scalar registers.
 struct WaveRange {
-  int wave, t_begin, t_end, n_full;
+  int wave, t_begin, t_end;
+  int n_full;   // tiles wholly inside the prefix
+  int n_whole;  // tiles wholly inside the keys
+  int n_all;    // all tiles: one more than n_whole where the keys end inside a tile
+  // First key of the rows that stand for tile t: a tile that the keys end in is taken from the last 32 rows, so that no load
+  // runs past them (rows in front of the tile are masked).
+  __device__ __forceinline__ int tile_key(int t, int T) const { return t < n_whole ? t_begin + t * kTile : max(0, T - kTile); }
 };
 __device__ __forceinline__ WaveRange wave_range(const ScoreArgs &a, const BlockCoord &bc) {
   WaveRange r;
   r.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   r.t_begin = (bc.chunk * kScoreWaves + r.wave) * a.keys_per_wave;
   r.t_end = min(r.t_begin + a.keys_per_wave, a.T);
-  r.n_full = max(0, (min(r.t_end, a.P) - r.t_begin) / kTile);  // tiles wholly inside the prefix
+  r.n_full = max(0, (min(r.t_end, a.P) - r.t_begin) / kTile);
+  r.n_whole = max(0, r.t_end - r.t_begin) / kTile;
+  r.n_all = (max(0, r.t_end - r.t_begin) + kTile - 1) / kTile;
   return r;
 }
 
@@ -558,7 +570,7 @@ struct Staged {
   int roff[NCH];           // lane's operand chunks inside a tile image
   const char *kbase;       // first key row of the unit
   const char *kcur;        // first row of the key tile the pipeline is working on
-  const char *klast;       // first row of the wave's last full tile
+  const char *kend;        // first row of the wave's last tile (what the loads beyond it fetch again)
   int64_t tile_stride;
   uint32_t lds_ring;       // LDS address of this wave's first image
 
@@ -580,7 +592,8 @@ struct Staged {
     kbase = uniform_ptr(a.k + bc.b * a.ks_b + bc.g * a.ks_h);
     kcur = uniform_ptr(kbase + (int64_t)wr.t_begin * a.ks_t);
     tile_stride = (int64_t)kTile * a.ks_t;
-    klast = uniform_ptr(kcur + max(wr.n_full - 1, 0) * tile_stride);
+    kend = uniform_ptr(wr.n_all > wr.n_whole ? kbase + (int64_t)max(a.T - kTile, 0) * a.ks_t
+                                             : kcur + max(wr.n_whole - 1, 0) * tile_stride);
     lds_ring = (uint32_t)(uintptr_t)&ring[wr.wave][0][0];
 
 #pragma unroll
@@ -600,10 +613,16 @@ struct Staged {
       }
     }
     constexpr int N_PRE = kRing - QI;  // key tiles whose images are free while Q passes through
-    if (wr.n_full > 0) {
+    const bool tiny = a.T < kTile;
+    if (wr.n_all > 0) {
+      if (!tiny) {
 #pragma unroll
-      for (int d = 0; d < N_PRE; ++d)
-        dma_tile<G>(d < wr.n_full ? kcur + d * tile_stride : klast, voff, lds_ring + d * G::TILE);
+        for (int d = 0; d < N_PRE; ++d)
+          dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, lds_ring + d * G::TILE);
+      } else {
+#pragma unroll
+        for (int d = 0; d < N_PRE; ++d) dma_tile_clamped<G>(kbase, a.ks_t, a.T, lane, ring[wr.wave][d]);
+      }
       wait_vm<N_PRE * G::NDMA>();  // Q has landed, the key tiles may still be on their way
     } else {
       wait_vm<0>();
@@ -630,17 +649,29 @@ struct Staged {
       }
     }
     __syncthreads();  // the images that held Q are free for key tiles from here on
-    if (wr.n_full > 0) {
+    if (wr.n_all > 0 && !tiny) {
 #pragma unroll
       for (int d = N_PRE; d < kRing - 1; ++d)
-        dma_tile<G>(d < wr.n_full ? kcur + d * tile_stride : klast, voff, lds_ring + d * G::TILE);
+        dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, lds_ring + d * G::TILE);
     }
   }
 
   // Load of the tile three ahead of the one at kcur (tile index t + 3) into ring image `slot`; past
-  // the last full tile the last one is fetched again (in bounds, unused).
-  __device__ __forceinline__ void prefetch(int t, int n_full, int slot) {
-    dma_tile<G>(t + 3 < n_full ? kcur + 3 * tile_stride : klast, voff, lds_ring + slot * G::TILE);
+  // the last tile the last one is fetched again (in bounds, unused).
+  __device__ __forceinline__ void prefetch(int t, int n_whole, int slot) {
+    dma_tile<G>(t + 3 < n_whole ? kcur + 3 * tile_stride : kend, voff, lds_ring + slot * G::TILE);
+  }
+
+  // Tile t (behind the pipeline, at kcur) into registers: its load was issued three tiles ago, as the pipeline's are.
+  __device__ __forceinline__ void tail_tile(const WaveRange &wr, Ring &ring, int t, chunk_t (&kf)[NCH]) {
+    if (t + 3 < wr.n_all) {
+      prefetch(t, wr.n_whole, (t + 3) % kRing);
+      wait_vm<(kRing - 1) * G::NDMA>();
+    } else {
+      wait_vm<0>();
+    }
+    read_image<G>(kf, ring[wr.wave][t % kRing], roff);
+    kcur += tile_stride;
   }
 };
 
@@ -681,7 +712,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) rowstats_lds_kernel(ScoreA
 #pragma unroll
     for (int v = 0; v < UR; ++v) {  // tile t0 + v lives in image u and in kreg[v & 1]
       const int u = slot0 + v;
-      st.prefetch(t0 + v, wr.n_full, (u + kRing - 1) % kRing);
+      st.prefetch(t0 + v, wr.n_whole, (u + kRing - 1) % kRing);
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         const int cur = (v * NQ + i) & 1;  // accumulator set holding this pair's logits
@@ -692,32 +723,27 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) rowstats_lds_kernel(ScoreA
         // logits of the next pair; the last pair of a key tile already starts the next key tile
         if (i + 1 < NQ) mma_chain<DT, NCH>(acc[cur ^ 1], kreg[v & 1], qf[i + 1]);
         else mma_chain<DT, NCH>(acc[cur ^ 1], kreg[(v + 1) & 1], qf[0]);
-        rowstats_update<false>(acc[cur], a.c2, 0, hh, 0, rm[i], rl[i]);
+        rowstats_update<false>(acc[cur], a.c2, 0, hh, 0, 0, rm[i], rl[i]);
         if (i == READ_AT) interleave_hint<N_MFMA, vector_per_mfma_pass1(NQ), NCH>();
         else interleave_hint<N_MFMA, vector_per_mfma_pass1(NQ), 0>();
       }
       st.kcur += st.tile_stride;
     }
   }
-  // What the pipeline left: up to a ring of whole tiles and the masked ones. Their loads go out a ring at
-  // a time, so the memory latency is paid once per ring and not once per tile.
-  wait_vm<0>();
-  for (int r0 = wr.t_begin + n_piped * kTile; r0 < wr.t_end; r0 += kRing * kTile) {
+  // What the pipeline left: up to a ring of whole tiles and the masked ones.
+  for (int t = n_piped; t < wr.n_all; ++t) {
+    st.tail_tile(wr, ring, t, kreg[0]);
+    const int t0 = wr.t_begin + t * kTile, key0 = wr.tile_key(t, a.T);
+    mma_chain<DT, NCH>(acc[0], kreg[0], qf[0]);
 #pragma unroll
-    for (int j = 0; j < kRing; ++j)
-      if (r0 + j * kTile < wr.t_end) dma_tile_clamped<G>(st.kbase, a.ks_t, r0 + j * kTile, a.T, lane, ring[wr.wave][j]);
-    wait_vm<0>();
-    for (int j = 0; j < kRing && r0 + j * kTile < wr.t_end; ++j) {
-      const int t0 = r0 + j * kTile;
-      read_image<G>(kreg[0], ring[wr.wave][j], st.roff);
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) {
-        mma_chain<DT, NCH>(acc[0], kreg[0], qf[i]);
-        rowstats_update<true>(acc[0], a.c2, t0, hh, limit[i], rm[i], rl[i]);
-      }
+    for (int i = 0; i < NQ; ++i) {
+      if (i + 1 < NQ) mma_chain<DT, NCH>(acc[(i + 1) & 1], kreg[0], qf[i + 1]);
+      rowstats_update<true>(acc[i & 1], a.c2, key0, hh, t0, limit[i], rm[i], rl[i]);
+      if (i + 1 < NQ) interleave_hint<N_MFMA, kTailVectorPerMfma, 0>();
     }
   }
   store_row_partials<NQ>(a, bc, wr.wave, m, hh, rm, rl);
+  wait_vm<0>();  // the loads beyond the last tile write LDS: not after the wave
 }
 
 // The extra contraction step of pass 2 that adds bias_j = -LSE_j / scale to every logit of query row
@@ -1088,7 +1114,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
 #pragma unroll
     for (int v = 0; v < UR; ++v) {
       const int u = slot0 + v;
-      st.prefetch(t0 + v, wr.n_full, (u + kRing - 1) % kRing);
+      st.prefetch(t0 + v, wr.n_whole, (u + kRing - 1) % kRing);
       float cs[NQ];
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
@@ -1126,28 +1152,27 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
       stage_fence();  // and read, before the next cycle's overwrite them
     }
   }
-  wait_vm<0>();
-  for (int r0 = wr.t_begin + n_piped * kTile; r0 < wr.t_end; r0 += kRing * kTile) {  // loads a ring at a time
+  for (int t = n_piped; t < wr.n_all; ++t) {
+    st.tail_tile(wr, ring, t, kreg[0]);
+    const int kt = wr.tile_key(t, a.T) + m;  // this lane's key
+    float cs[NQ];
+    mma_chain<DT, NCH>(acc[0], qf[0], kreg[0]);
+    bias[0].add(acc[0], ones);
 #pragma unroll
-    for (int j = 0; j < kRing; ++j)
-      if (r0 + j * kTile < wr.t_end) dma_tile_clamped<G>(st.kbase, a.ks_t, r0 + j * kTile, a.T, lane, ring[wr.wave][j]);
-    wait_vm<0>();
-    for (int j = 0; j < kRing && r0 + j * kTile < wr.t_end; ++j) {
-      const int t0 = r0 + j * kTile;
-      read_image<G>(kreg[0], ring[wr.wave][j], st.roff);
-      const int kt = t0 + m;
-      float cs[NQ];
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) {
-        const int j0 = ((bc.grp * NQ + i) % WT) * kTile;
-        mma_chain<DT, NCH>(acc[0], qf[i], kreg[0]);
-        bias[i].add(acc[0], ones);
-        cs[i] = colsum_weights<true>(acc[0], a.c2, hh, kt - a.P - j0);
+    for (int i = 0; i < NQ; ++i) {
+      const int j0 = ((bc.grp * NQ + i) % WT) * kTile;
+      if (i + 1 < NQ) {
+        mma_chain<DT, NCH>(acc[(i + 1) & 1], qf[i + 1], kreg[0]);
+        bias[i + 1].add(acc[(i + 1) & 1], ones);
       }
-      if constexpr (GSUM) store_group_sum<NQ>(a, bc, cs, kt, hh);
-      else store_column_sums<NQ>(a, bc, cs, WT, kt, hh);
+      cs[i] = colsum_weights<true>(acc[i & 1], a.c2, hh, kt - a.P - j0);
+      if (i + 1 < NQ) interleave_hint<N_MFMA, kTailVectorPerMfma, 0>();
     }
+    const int kt_out = kt >= wr.t_begin + t * kTile ? kt : a.T;  // keys in front of the tile are another one's
+    if constexpr (GSUM) store_group_sum<NQ>(a, bc, cs, kt_out, hh);
+    else store_column_sums<NQ>(a, bc, cs, WT, kt_out, hh);
   }
+  wait_vm<0>();  // the loads beyond the last tile write LDS: not after the wave
 }
 
 // ---------------------------------------------------------------------------------------------
