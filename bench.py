@@ -394,7 +394,7 @@ def main() -> int:
 
     # Layers are independent of one another (each has its K, V, outputs and scratch), so a caller that compacts
     # a whole model at the end of prefill can queue them on more than one stream: the short, latency-bound
-    # kernels of one layer (selection, fix-up, gather) and the ends of its scans then overlap the next layer's
+    # kernels of one layer (selection, gather) and the ends of its scans then overlap the next layer's
     # scan. All streams have the default priority.
     # The inputs are still being made on the default stream, and outputs and scratch lie in blocks that its temporaries
     # gave back: nothing may run beside it before it is through.
@@ -467,7 +467,7 @@ def main() -> int:
             if args.unfused:
                 B.ckv_window_scores(params[l], t["q"], t["k"], t["v"] if args.value_norm else None, lse_buf, buf.scores,
                                     buf.vnorm_ratio, buf.workspace)
-            else:  # second pass with pooling, weights and group maximum on chip, plus its edge fix-up kernel
+            else:  # second pass with pooling, weights and group maximum on chip
                 B.ckv_window_utility(params[l], t["q"], t["k"], t["v"] if args.value_norm else None, lse_buf,
                                      tables["w_head"], tables.get("head_share"), tables.get("t_gate"),
                                      tables.get("n_ent", 0), tables.get("n_ppl", 0), tables.get("risk_bins"),
@@ -532,7 +532,7 @@ def main() -> int:
         "scan_ms": scan_ms,
         "select_ms": round(ms_select, 4), "gather_ms": round(ms_gather, 4),
         "gather_gbs": round(gather_bytes / (ms_gather * 1e-3) / 1e9, 1),
-        "mfma_tflops": {"rowstats": round(mfma1, 1), "colsum": round(mfma2, 1),  # fused: its fix-up kernel included
+        "mfma_tflops": {"rowstats": round(mfma1, 1), "colsum": round(mfma2, 1),
                         "peak": MFMA_BF16_PEAK_TFLOPS,
                         "frac": round(max(mfma1, mfma2) / MFMA_BF16_PEAK_TFLOPS, 4) if bf16 else None},
         "whole_pass_frac_of_hbm_peak": round(value / HBM_PEAK_GBS, 4),

@@ -199,8 +199,7 @@ ckv_status ckv_apply_tables(const ckv_params *params, const float *scores, const
  *
  *   q_win, k, v, lse                                   as for ckv_window_scores
  *   w_head, head_share, t_gate, n_ent, n_ppl, risk_bins as for ckv_apply_tables
- *   scores_scratch  scratch  [Bz,Hq,T] fp32; contents undefined on return (the fused pass leaves raw
- *                            column sums in parts of it only)
+ *   scores_scratch  scratch  [Bz,Hq,T] fp32; contents undefined on return
  *   vnorm_ratio     out      as for ckv_window_scores (required with CKV_FLAG_VALUE_NORM, else ignored)
  *   utility, budget, tau  out  as for ckv_apply_tables
  *   workspace                ckv_workspace_bytes(params) bytes

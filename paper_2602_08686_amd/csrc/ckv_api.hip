@@ -322,11 +322,9 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
     fuse.inv_kernel = 1.0f / (float)kernel;
     if ((double)fuse.inv_kernel * kernel > 1.0) fuse.inv_kernel = nextafterf(fuse.inv_kernel, 0.0f);
     fuse.inv_kernel_rest = fmaxf((float)(1.0 / kernel - (double)fuse.inv_kernel), FLT_MIN);
+    fuse.bud = budget_args(params, s, head_share, t_gate, n_ent, n_ppl, risk_bins, budget, tau);
     if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores_scratch, (char *)workspace, stream,
                              &fuse) != hipSuccess)
-      return CKV_EHIP;
-    if (launch_utility_fixup(params, s, scores_scratch, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins,
-                             utility, budget, tau, stream) != hipSuccess)
       return CKV_EHIP;
     if (vn && launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream, utility) != hipSuccess)
       return CKV_EHIP;

@@ -21,13 +21,11 @@ constexpr int kScoreWaves = 4;     // waves per workgroup in the scan kernels
 // (which may run where no device is visible) and for the calls that use the workspace.
 constexpr int kComputeUnits = 256;
 constexpr int kSelectThreads = 1024;
-// Geometry of the fused utility form of the scan's second pass, shared by that pass (ckv_scan.h) and by
-// the kernel that finishes what it leaves out (ckv_tables.hip). The pass works in rounds of
+// Geometry of the fused utility form of the scan's second pass (ckv_scan.h). It works in rounds of
 // kRing * kTile keys per wave; each round writes the utilities of the kRing * kTile keys that end
-// kUtilShift keys before the round does, keeps its last kUtilCarry column sums in front of the next
-// round's, and stores raw column sums for the first kUtilHead and the last kUtilCarry keys of a wave's
-// pipelined range; the first four keys of a range, its last kUtilShift pipelined keys and its tail tiles
-// are finished by the other kernel.
+// kUtilShift keys before the round does and keeps its last kUtilCarry column sums in front of the next
+// round's. The first four keys of a wave's range (its first kUtilHead column sums are kept for them), the last
+// kUtilShift keys of its rounds and the keys behind the rounds follow when the workgroup's waves have their sums.
 constexpr int kRing = 4;           // key-tile images per wave, and tiles per pipeline round
 constexpr int kUtilShift = 32;
 constexpr int kUtilCarry = 40;
@@ -132,22 +130,32 @@ int vnorm_blocks_per_unit(const Shape &s);
 
 // Kernel launchers (each returns hipGetLastError() after its launches).
 // lse_in == nullptr: pass 1 first, LSE into lse_out (or the workspace). scores == nullptr: pass 1 only.
-// Fused utility form of pass 2 (see ckv_window_utility): where `fuse` is given, the second pass writes
-// utilities of block-interior keys to fuse->utility and raw column sums only where the fix-up kernel
-// needs them (into `scores`).
+// tau and the per-head budgets of a call (paper Sec. 4.3), written beside the utilities.
+struct BudgetArgs {
+  const float *share_row;   // head_share + layer*Hkv or null
+  const float *gate_layer;  // t_gate + layer*n_ent*n_ppl or null
+  const int32_t *risk_bins;
+  int n_ent, n_ppl;
+  int32_t *budget;
+  float *tau;
+  int Hkv, T, W;
+  int B;  // nominal budget per KV head
+};
+BudgetArgs budget_args(const ckv_params *p, const Shape &s, const float *head_share, const float *t_gate, int n_ent,
+                       int n_ppl, const int32_t *risk_bins, int32_t *budget, float *tau);
+
+// Fused utility form of pass 2 (see ckv_window_utility): where `fuse` is given, the second pass writes the
+// utilities, tau and the budgets, and no column sums.
 struct UtilityFusion {
   const float *w_row;  // w_head + layer * Hq
   float *utility;      // [Bz][Hkv][P]
   int pool, radius;
   float inv_kernel, inv_kernel_rest;  // 1 / kernel: the largest float that is not above it, and what that leaves
+  BudgetArgs bud;
 };
 hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Workspace &w, const void *q,
                                 const void *k, const float *lse_in, float *lse_out, float *scores,
                                 char *ws, hipStream_t stream, const UtilityFusion *fuse = nullptr);
-hipError_t launch_utility_fixup(const ckv_params *p, const Shape &s, const float *sparse_scores,
-                                const float *w_head, const float *head_share, const float *t_gate, int n_ent,
-                                int n_ppl, const int32_t *risk_bins, float *utility, int32_t *budget, float *tau,
-                                hipStream_t stream);
 // utility_scaled: if given, [units][P] utilities that the scaling pass multiplies by the ratio
 hipError_t launch_value_norm(const ckv_params *p, const Shape &s, const Workspace &w, const void *v,
                              float *ratio, char *ws, hipStream_t stream, float *utility_scaled = nullptr);

@@ -21,7 +21,7 @@
 // whose workloads are small), and LDS-staged, software-pipelined ones for bf16.
 #ifndef CKV_SCAN_H_
 #define CKV_SCAN_H_
-#include "ckv_internal.h"
+#include "ckv_tables.h"
 
 namespace ckv {
 
@@ -49,6 +49,7 @@ struct ScoreArgs {
   float *utility;      // [Bz][Hkv][P]
   int pool, radius;    // pooling mode and radius (kernel / 2, at most kUtilMaxRadius)
   float inv_kernel, inv_kernel_rest;  // 1 / pool_kernel in two terms
+  BudgetArgs bud;
 };
 
 template <int DT> struct Mma;
@@ -541,19 +542,20 @@ struct WaveRange {
   int wave, t_begin, t_end;
   int n_full;   // tiles wholly inside the prefix
   int n_whole;  // tiles wholly inside the keys
-  int n_all;    // all tiles: one more than n_whole where the keys end inside a tile
+  int n_all;    // the tiles to take: one more than n_whole where the keys end inside a tile
   // First key of the rows that stand for tile t: a tile that the keys end in is taken from the last 32 rows, so that no load
   // runs past them (rows in front of the tile are masked).
   __device__ __forceinline__ int tile_key(int t, int T) const { return t < n_whole ? t_begin + t * kTile : max(0, T - kTile); }
 };
-__device__ __forceinline__ WaveRange wave_range(const ScoreArgs &a, const BlockCoord &bc) {
+// `last`: the keys whose sums are wanted end here, T or (utilities) P.
+__device__ __forceinline__ WaveRange wave_range(const ScoreArgs &a, const BlockCoord &bc, int last) {
   WaveRange r;
   r.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   r.t_begin = (bc.chunk * kScoreWaves + r.wave) * a.keys_per_wave;
   r.t_end = min(r.t_begin + a.keys_per_wave, a.T);
   r.n_full = max(0, (min(r.t_end, a.P) - r.t_begin) / kTile);
   r.n_whole = max(0, r.t_end - r.t_begin) / kTile;
-  r.n_all = (max(0, r.t_end - r.t_begin) + kTile - 1) / kTile;
+  r.n_all = (max(0, min(r.t_end, last) - r.t_begin) + kTile - 1) / kTile;
   return r;
 }
 
@@ -684,7 +686,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) rowstats_lds_kernel(ScoreA
   __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ>::Ring ring;
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
   const BlockCoord bc = decode_block(a);
-  const WaveRange wr = wave_range(a, bc);
+  const WaveRange wr = wave_range(a, bc, a.T);
 
   Staged<DT, DH, NQ> st;
   chunk_t qf[NQ][NCH];
@@ -839,8 +841,8 @@ __device__ __forceinline__ void store_group_sum(const ScoreArgs &a, const BlockC
 // [head of the group][key of the ring cycle], and once per ring cycle (4 tiles, 128 keys) every lane
 // stores four consecutive keys of one head with one 128-bit buffer store per pair of heads.
 template <int NQ, int WT, int ROW = kRing * kTile>
-__device__ __forceinline__ void stage_column_sums(const float (&cs)[NQ], float norm, float *stage, int u, int m,
-                                                  int hh) {
+__device__ __forceinline__ void stage_column_sums(const float (&cs)[NQ], float norm, float *stage, int at, int hh,
+                                                  bool keep = true) {
   constexpr int NH = NQ / WT;
   float hv[NH];
 #pragma unroll
@@ -854,7 +856,7 @@ __device__ __forceinline__ void stage_column_sums(const float (&cs)[NQ], float n
     const float x = hv[h], y = hv[(h + 1 < NH) ? h + 1 : h];
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
     const float tot = (__uint_as_float(sw[0]) + __uint_as_float(sw[1])) * norm;
-    if (h + hh < NH) stage[(h + hh) * ROW + u * kTile + m] = tot;
+    if (keep && h + hh < NH) stage[(h + hh) * ROW + at] = tot;
   }
 }
 
@@ -908,9 +910,8 @@ __device__ __forceinline__ void flush_group_sums(const ScoreArgs &a, const Block
 // previous block, and each flush covers the 128 keys that END 32 keys before the block does: every
 // pooling window (radius <= 3) lies inside the row and every store covers whole 128-byte lines
 // (partial lines proved expensive). What this leaves out per wave range -- the first four keys, the
-// last 32 keys of the pipelined part, and the tail tiles -- a small kernel computes afterwards from
-// raw column sums, which the first block (its first eight keys), the last block (its last 40 keys)
-// and the tail tiles store. Lanes 0..31 take the even heads of the group, lanes 32..63 the odd ones,
+// last 32 keys of the pipelined part, and the tail tiles -- finish_utility writes behind a barrier, when the
+// neighbours' sums are known. Lanes 0..31 take the even heads of the group, lanes 32..63 the odd ones,
 // four consecutive keys each (three 128-bit reads per head); the halves then swap so that each lane
 // ends up with the group maximum of two adjacent keys and stores them with one 64-bit store. The taps
 // are combined left to right, as the stand-alone tables kernel does.
@@ -943,31 +944,46 @@ __device__ __forceinline__ void pooled_group_max(const ScoreArgs &a, const float
   }
 }
 
-// rows: the wave's stage rows (carry included); t_first: first key of the block just staged. Every LDS
-// read of the flush is issued before anything waits for one (the wave is alone on its SIMD: a read's
+template <int NH>
+__device__ __forceinline__ void pooled_best(const ScoreArgs &a, const float (&win)[(NH + 1) / 2][12], int lane,
+                                            int heads_left, const float (&wgt)[NH], float (&best)[4]) {
+  if (a.pool == CKV_POOL_MAX) {
+    switch (a.radius) {
+      case 1: pooled_group_max<NH, CKV_POOL_MAX, 1>(a, win, lane, heads_left, wgt, best); break;
+      case 2: pooled_group_max<NH, CKV_POOL_MAX, 2>(a, win, lane, heads_left, wgt, best); break;
+      case 3: pooled_group_max<NH, CKV_POOL_MAX, 3>(a, win, lane, heads_left, wgt, best); break;
+      default: pooled_group_max<NH, CKV_POOL_MAX, 0>(a, win, lane, heads_left, wgt, best); break;
+    }
+  } else {
+    switch (a.radius) {
+      case 1: pooled_group_max<NH, CKV_POOL_AVG, 1>(a, win, lane, heads_left, wgt, best); break;
+      case 2: pooled_group_max<NH, CKV_POOL_AVG, 2>(a, win, lane, heads_left, wgt, best); break;
+      case 3: pooled_group_max<NH, CKV_POOL_AVG, 3>(a, win, lane, heads_left, wgt, best); break;
+      default: pooled_group_max<NH, CKV_POOL_AVG, 0>(a, win, lane, heads_left, wgt, best); break;
+    }
+  }
+}
+
+// rows: the wave's stage rows (carry included); edge: where the first block leaves its first kUtilHead sums; t_first:
+// first key of the block just staged. Every LDS read of the flush is issued before anything waits for one (the wave is alone on its SIMD: a read's
 // latency is otherwise paid once per dependent step).
 template <int NQ, int WT>
-__device__ __forceinline__ void flush_utility(const ScoreArgs &a, const BlockCoord &bc, float *rows, int t_first,
-                                              bool first_block, bool last_block, int lane,
-                                              __amdgpu_buffer_rsrc_t rsrc, __amdgpu_buffer_rsrc_t rsrc_u,
+__device__ __forceinline__ void flush_utility(const ScoreArgs &a, const BlockCoord &bc, float *rows, float *edge,
+                                              int t_first, bool first_block, int lane, __amdgpu_buffer_rsrc_t rsrc_u,
                                               const float (&wgt)[NQ / WT]) {
   constexpr int NH = NQ / WT;
   constexpr int NP = (NH + 1) / 2;  // pairs of heads: lanes 0..31 take the even head, lanes 32..63 the odd one
   constexpr int BLK = kRing * kTile;
-  const int head0 = bc.g * a.G + (bc.grp * NQ) / WT;
   const int heads_left = a.G - (bc.grp * NQ) / WT;
   const int half = lane >> 5, grp = lane & 31, key4 = 4 * grp;
-  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
   typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
   typedef __attribute__((ext_vector_type(2))) float f32x2;
-  // -- reads: raw sums of this lane's keys, the pooling windows, the pieces of the carry
-  f32x4 raw[NP];
+  // -- reads: the pooling windows, the pieces of the carry
   float win[NP][12];
 #pragma unroll
   for (int hp = 0; hp < NP; ++hp) {
     const int mine = 2 * hp + half;
     const float *row = rows + (mine < NH ? mine : 0) * kUtilRow;
-    raw[hp] = *reinterpret_cast<const f32x4 *>(row + kUtilCarry + key4);
     const float *w0 = row + (kUtilCarry - kUtilShift - 4) + key4;  // w0[4 .. 7]: keys 4 grp - 32 .. of the block
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -994,31 +1010,17 @@ __device__ __forceinline__ void flush_utility(const ScoreArgs &a, const BlockCoo
     const int piece = lane + i * kWave;
     if (piece < PER * NH) *reinterpret_cast<f32x4 *>(rows + (piece / PER) * kUtilRow + 4 * (piece % PER)) = carry[i];
   }
-  // -- raw column sums for the fix-up kernel: the first block's first eight keys, the last block's last 40
+  if (first_block && key4 < kUtilHead) {
 #pragma unroll
-  for (int hp = 0; hp < NP; ++hp) {
-    const int mine = 2 * hp + half;
-    const bool valid = mine < NH && mine < heads_left &&
-                       ((first_block && key4 < kUtilHead) || (last_block && key4 >= BLK - kUtilCarry));
-    const uint32_t off = valid ? (uint32_t)(((head0 + mine) * a.T + t_first + key4) * 4) : 0x80000000u;
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, raw[hp]), rsrc, off, 0, kOutStoreAux);
+    for (int hp = 0; hp < NP; ++hp) {
+      const int mine = 2 * hp + half;
+      if (mine < NH)
+        *reinterpret_cast<f32x4 *>(edge + mine * kUtilHead + key4) =
+            *reinterpret_cast<const f32x4 *>(rows + mine * kUtilRow + kUtilCarry + key4);
+    }
   }
   float best[4];
-  if (a.pool == CKV_POOL_MAX) {
-    switch (a.radius) {
-      case 1: pooled_group_max<NH, CKV_POOL_MAX, 1>(a, win, lane, heads_left, wgt, best); break;
-      case 2: pooled_group_max<NH, CKV_POOL_MAX, 2>(a, win, lane, heads_left, wgt, best); break;
-      case 3: pooled_group_max<NH, CKV_POOL_MAX, 3>(a, win, lane, heads_left, wgt, best); break;
-      default: pooled_group_max<NH, CKV_POOL_MAX, 0>(a, win, lane, heads_left, wgt, best); break;
-    }
-  } else {
-    switch (a.radius) {
-      case 1: pooled_group_max<NH, CKV_POOL_AVG, 1>(a, win, lane, heads_left, wgt, best); break;
-      case 2: pooled_group_max<NH, CKV_POOL_AVG, 2>(a, win, lane, heads_left, wgt, best); break;
-      case 3: pooled_group_max<NH, CKV_POOL_AVG, 3>(a, win, lane, heads_left, wgt, best); break;
-      default: pooled_group_max<NH, CKV_POOL_AVG, 0>(a, win, lane, heads_left, wgt, best); break;
-    }
-  }
+  pooled_best<NH>(a, win, lane, heads_left, wgt, best);
   // (x, y) -> ([x.lo, y.lo], [x.hi, y.hi]): lanes 0..31 get both halves' values of keys 0 and 1 of their
   // group, lanes 32..63 those of keys 2 and 3
   const auto s02 = __builtin_amdgcn_permlane32_swap(__float_as_uint(best[0]), __float_as_uint(best[2]), false, false);
@@ -1026,11 +1028,84 @@ __device__ __forceinline__ void flush_utility(const ScoreArgs &a, const BlockCoo
   const f32x2 out = {fmaxf(__uint_as_float(s02[0]), __uint_as_float(s02[1])),
                      fmaxf(__uint_as_float(s13[0]), __uint_as_float(s13[1]))};
   // groups 0..7 lie in front of the block; in the range's first block they and group 8 (the range's
-  // first four keys, whose windows reach in front of the range) are left to the fix-up kernel
+  // first four keys, whose windows reach in front of the range) are left to finish_utility
   const bool emit = grp >= kUtilShift / 4 + 1 || !first_block;
   const uint32_t off_u =
       emit ? (uint32_t)((bc.g * a.P + t_first - kUtilShift + 4 * grp + 2 * half) * 4) : 0x80000000u;
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, out), rsrc_u, off_u, 0, kOutStoreAux);
+}
+
+// The first and last keys around a workgroup's range, four on either side, for the pooling windows that reach over its ends:
+// eight rows in a small LDS image, loaded first of all and contracted while the first key tiles are on their way
+// (each wave takes the heads w and w + 4). The neighbours' ranges inside the workgroup go through its stages.
+constexpr int kHaloKeys = 4;
+static_assert(kHaloKeys >= kUtilMaxRadius && 2 * kHaloKeys == kUtilHead, "one row of eight sums");
+template <class G>
+__device__ __forceinline__ void dma_halo(const char *kbase, int64_t ks_t, int begin, int end, int T, int lane, char *image) {
+#pragma unroll
+  for (int i = 0; i < 2 * kHaloKeys * G::ROW / 1024; ++i) {
+    int r, kappa;
+    dma_source<G>(i, lane, r, kappa);
+    const int t = r < kHaloKeys ? max(begin - kHaloKeys + r, 0) : min(end + r - kHaloKeys, T - 1);
+    __builtin_amdgcn_global_load_lds((glb_void_t *)(kbase + (int64_t)min(t, T - 1) * ks_t + kappa * 16),
+                                     (lds_void_t *)(uintptr_t)(image + i * 1024), 16, 0, 0);
+  }
+}
+
+// The utilities a wave's rounds leave out: groups of four keys as in flush_utility, the first at the front of the range
+// (where there were rounds), the others from the last kUtilShift keys of the rounds to the end of the range or of the prefix.
+// A group's twelve sums come from the wave's stage, and over the ends of its range from the wave in front (`prev`, four sums
+// per head), its own first ones (`edge`) and the wave behind (`next`). A separate kernel for them, from sums in global memory,
+// took 5 to 7 us of every call (4096 keys, 32/32 heads 33.6 us with it; 16384 keys with given normalisers 51.8).
+template <int NQ, int WT>
+__device__ __forceinline__ void finish_utility(const ScoreArgs &a, const BlockCoord &bc, const WaveRange &wr, int n_piped,
+                                               const float *rows, const float *edge, const float *prev, int prev_stride,
+                                               const float *next, int next_stride, int lane,
+                                               __amdgpu_buffer_rsrc_t rsrc_u, const float (&wgt)[NQ / WT]) {
+  constexpr int NH = NQ / WT;
+  constexpr int NP = (NH + 1) / 2;
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+  const int heads_left = a.G - (bc.grp * NQ) / WT;
+  const int half = lane >> 5;
+  const int limit = min(wr.t_end, a.P), tail0 = wr.t_begin + n_piped * kTile;
+  const int n_front = n_piped > 0 ? 1 : 0, first = tail0 - (n_piped > 0 ? kUtilShift : 0);
+  const int n = n_front + (limit - first + 3) / 4;
+  const uint32_t pad = a.pool == CKV_POOL_MAX ? 0xff800000u : 0u;
+  for (int g0 = 0; g0 < n; g0 += kWave / 2) {
+    const int grp = g0 + (lane & 31), i = min(grp, n - 1);
+    const bool front = i < n_front;
+    const int t = front ? wr.t_begin : first + 4 * (i - n_front), rel = t - tail0;
+    float win[NP][12];
+#pragma unroll
+    for (int hp = 0; hp < NP; ++hp) {
+      const int head = 2 * hp + half < NH ? 2 * hp + half : 0;
+      const float *row = rows + head * kUtilRow + kUtilCarry + (front ? 0 : rel);
+      const float *own = edge + head * kUtilHead;
+      const float *from[3] = {t == wr.t_begin ? prev + head * prev_stride : row - 4, front ? own : row,
+                              front ? own + 4 : t + 4 >= limit ? next + head * next_stride : row + 4};
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const u32x4_t v = *reinterpret_cast<const u32x4_t *>(from[q]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t x = v[e];  // what lies outside the prefix may be anything: masked as bits
+          win[hp][4 * q + e] = __uint_as_float((uint32_t)(t - 4 + 4 * q + e) < (uint32_t)a.P ? x : pad);
+        }
+      }
+    }
+    float best[4];
+    pooled_best<NH>(a, win, lane, heads_left, wgt, best);
+    const auto s02 = __builtin_amdgcn_permlane32_swap(__float_as_uint(best[0]), __float_as_uint(best[2]), false, false);
+    const auto s13 = __builtin_amdgcn_permlane32_swap(__float_as_uint(best[1]), __float_as_uint(best[3]), false, false);
+    const float out[2] = {fmaxf(__uint_as_float(s02[0]), __uint_as_float(s02[1])),
+                          fmaxf(__uint_as_float(s13[0]), __uint_as_float(s13[1]))};
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int at = t + 2 * half + e;
+      const uint32_t off = grp < n && at < limit ? (uint32_t)((bc.g * a.P + at) * 4) : 0x80000000u;
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(out[e]), rsrc_u, off, 0, kOutStoreAux);
+    }
+  }
 }
 
 template <int DT, int DH, int NQ, int WT, bool UTIL = false, bool GSUM = false>
@@ -1044,8 +1119,18 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
   __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ>::Ring ring;
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
   const BlockCoord bc = decode_block(a);
-  const WaveRange wr = wave_range(a, bc);
+  const WaveRange wr = wave_range(a, bc, UTIL ? a.P : a.T);  // utilities: of the prefix only
 
+  constexpr int NH = NQ / WT;
+  __shared__ __attribute__((aligned(1024))) char s_halo_keys[UTIL ? 2 * kHaloKeys * G::ROW : 16];
+  __shared__ __attribute__((aligned(16))) float s_halo[UTIL ? NH * kUtilHead : 4];
+  __shared__ __attribute__((aligned(16))) float s_edge[UTIL ? kScoreWaves : 1][UTIL ? NH * kUtilHead : 4];
+  if constexpr (UTIL) {
+    const int begin = bc.chunk * kScoreWaves * a.keys_per_wave;
+    if (wr.wave == 0)
+      dma_halo<G>(a.k + bc.b * a.ks_b + bc.g * a.ks_h, a.ks_t, begin, begin + kScoreWaves * a.keys_per_wave, a.T, lane,
+                  s_halo_keys);
+  }
   Staged<DT, DH, NQ> st;
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
@@ -1064,6 +1149,9 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
     else if (tile < a.n_tiles && j < a.W) v = a.lse[((size_t)bc.b * a.Hq + bc.g * a.G + tile / WT) * a.W + j];
     s_lse[threadIdx.x] = v;
   }
+  if constexpr (UTIL) {  // tau and the budgets of a batch element: a wave of its first workgroup
+    if (bc.g == 0 && bc.chunk == 0 && wr.wave == kScoreWaves - 1) write_tau_and_budgets(a.bud, bc.b, lane);
+  }
   __syncthreads();
   // bias of this lane's query row in every tile; padding rows (q = 0) get exp2(-1000) = 0 as weight
   Bias<DT> bias[NQ];
@@ -1076,21 +1164,21 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
   // pipeline's code, and every flush issues exactly N_STORES store instructions.
   const int score_rows = GSUM ? a.Hkv : a.Hq;  // rows of a batch element in the output
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void *)(a.scores + (size_t)bc.b * score_rows * a.T), 0, score_rows * a.T * 4, 0x00020000);
+      (void *)(a.scores + (UTIL ? 0 : (size_t)bc.b * score_rows * a.T)), 0, UTIL ? 0 : score_rows * a.T * 4, 0x00020000);
   // Vector memory operations complete in issue order, stores included. When tile t + 1 is picked up,
   // the loads of tiles t + 2 and t + 3 were issued after its own, and so were the stores of the
   // previous ring cycle if t is the cycle's first or second tile; that many operations may still be
   // in flight. The first cycle has no such stores behind it: dropped stores (offset outside the
   // descriptor) issued after the first loads stand in.
-  // per flush; the fused form adds the utility store, the group-sum form has a single store
-  constexpr int N_STORES = GSUM ? 1 : (NQ / WT + 1) / 2 + (UTIL ? 1 : 0);
-  __shared__ __attribute__((aligned(16))) float s_stage[kScoreWaves][(NQ / WT) * (UTIL ? kUtilRow : kRing * kTile)];
+  // per flush: one for the fused and for the group-sum form
+  constexpr int N_STORES = GSUM || UTIL ? 1 : (NH + 1) / 2;
+  __shared__ __attribute__((aligned(16))) float s_stage[kScoreWaves][NH * (UTIL ? kUtilRow : kRing * kTile)];
   // fused form: descriptor over utility[b] (Hkv * P floats) and the weights of this group's heads
   const __amdgpu_buffer_rsrc_t rsrc_u = __builtin_amdgcn_make_buffer_rsrc(
       (void *)(UTIL ? a.utility + (size_t)bc.b * a.Hkv * a.P : a.scores), 0, UTIL ? a.Hkv * a.P * 4 : 0, 0x00020000);
-  float wgt[NQ / WT];
+  float wgt[NH];
 #pragma unroll
-  for (int h = 0; h < NQ / WT; ++h) {
+  for (int h = 0; h < NH; ++h) {
     const int head = bc.g * a.G + (bc.grp * NQ) / WT + h;
     wgt[h] = UTIL && head < a.Hq ? a.w_row[head] : 0.0f;
   }
@@ -1098,10 +1186,30 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
   const int n_piped = wr.n_full / kRing * kRing;
   // (distinct offsets, all outside the descriptor: identical stores could be merged into one)
 #pragma unroll
-  for (int i = 0; i < N_STORES; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, rsrc, 0x80000000u + 64u * i, 0, 0);
+  for (int i = 0; i < N_STORES; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, UTIL ? rsrc_u : rsrc, 0x80000000u + 64u * i, 0, 0);
 
   chunk_t kreg[2][NCH];
   f32x16 acc[2];
+  if constexpr (UTIL) {  // the sums around the workgroup's range
+    int hoff[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) hoff[c] = image_offset<G>(m & (kUtilHead - 1), c + NCH * hh);
+    read_image<G>(kreg[0], s_halo_keys, hoff);
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      if (wr.wave != h % kScoreWaves) continue;
+      float x = 0.0f;
+#pragma unroll
+      for (int e = 0; e < WT; ++e) {
+        mma_chain<DT, NCH>(acc[0], qf[h * WT + e], kreg[0]);
+        bias[h * WT + e].add(acc[0], ones);
+        const float w = colsum_weights<false>(acc[0], a.c2, hh, 0);
+        x = e == 0 ? w : x + w;
+      }
+      const float tot = (x + __shfl_xor(x, 32)) * a.norm;
+      if (lane < kUtilHead) s_halo[h * kUtilHead + lane] = tot;
+    }
+  }
   if (n_piped > 0) {
     wait_vm<(kRing - 2) * G::NDMA>();
     read_image<G>(kreg[0], ring[wr.wave][0], st.roff);
@@ -1138,15 +1246,15 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
         if (i == READ_AT) interleave_hint<N_MFMA, vector_per_mfma_pass2(NQ), NCH>();
         else interleave_hint<N_MFMA, vector_per_mfma_pass2(NQ), 0>();
       }
-      if constexpr (UTIL) stage_column_sums<NQ, WT, kUtilRow>(cs, a.norm, stage + kUtilCarry, u, m, hh);
-      else stage_column_sums<NQ, WT>(cs, a.norm, stage, u, m, hh);
+      if constexpr (UTIL) stage_column_sums<NQ, WT, kUtilRow>(cs, a.norm, stage + kUtilCarry, u * kTile + m, hh);
+      else stage_column_sums<NQ, WT>(cs, a.norm, stage, u * kTile + m, hh);
       st.kcur += st.tile_stride;
     }
     if (UR == kRing || slot0 + UR == kRing) {  // a ring cycle is complete
       const int c0 = t0 + UR - kRing;          // its first tile
       stage_fence();  // the tiles' sums are staged
       if constexpr (UTIL)
-        flush_utility<NQ, WT>(a, bc, stage, wr.t_begin + c0 * kTile, c0 == 0, c0 + kRing >= n_piped, lane, rsrc, rsrc_u, wgt);
+        flush_utility<NQ, WT>(a, bc, stage, s_edge[wr.wave], wr.t_begin + c0 * kTile, c0 == 0, lane, rsrc_u, wgt);
       else if constexpr (GSUM) flush_group_sums<NQ>(a, bc, stage, wr.t_begin + c0 * kTile, lane, rsrc);
       else flush_column_sums<NQ, WT>(a, bc, stage, wr.t_begin + c0 * kTile, lane, rsrc);
       stage_fence();  // and read, before the next cycle's overwrite them
@@ -1165,12 +1273,26 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
         mma_chain<DT, NCH>(acc[(i + 1) & 1], qf[i + 1], kreg[0]);
         bias[i + 1].add(acc[(i + 1) & 1], ones);
       }
-      cs[i] = colsum_weights<true>(acc[i & 1], a.c2, hh, kt - a.P - j0);
+      cs[i] = colsum_weights<!UTIL>(acc[i & 1], a.c2, hh, kt - a.P - j0);  // keys of the prefix: every row sees them
       if (i + 1 < NQ) interleave_hint<N_MFMA, kTailVectorPerMfma, 0>();
     }
     const int kt_out = kt >= wr.t_begin + t * kTile ? kt : a.T;  // keys in front of the tile are another one's
-    if constexpr (GSUM) store_group_sum<NQ>(a, bc, cs, kt_out, hh);
+    if constexpr (UTIL)
+      stage_column_sums<NQ, WT, kUtilRow>(cs, a.norm, stage + kUtilCarry, kt - wr.t_begin - n_piped * kTile, hh,
+                                          kt >= wr.t_begin + t * kTile);
+    else if constexpr (GSUM) store_group_sum<NQ>(a, bc, cs, kt_out, hh);
     else store_column_sums<NQ>(a, bc, cs, WT, kt_out, hh);
+  }
+  if constexpr (UTIL) {
+    __syncthreads();
+    if (wr.n_all > 0) {
+      // the wave in front has a whole range of the prefix; the one behind left its first sums at s_edge if it had rounds
+      const int w = wr.wave, round = kRing * kTile, behind = min(wr.t_end + a.keys_per_wave, a.P) - wr.t_end;
+      const float *prev = w > 0 ? s_stage[w - 1] + kUtilCarry + a.keys_per_wave % round - kHaloKeys : s_halo;
+      const float *next = w == kScoreWaves - 1 ? s_halo + kHaloKeys : behind >= round ? s_edge[w + 1] : s_stage[w + 1] + kUtilCarry;
+      finish_utility<NQ, WT>(a, bc, wr, n_piped, stage, s_edge[w], prev, w > 0 ? kUtilRow : kUtilHead, next,
+                             w == kScoreWaves - 1 || behind >= round ? kUtilHead : kUtilRow, lane, rsrc_u, wgt);
+    }
   }
   wait_vm<0>();  // the loads beyond the last tile write LDS: not after the wave
 }

@@ -32,6 +32,7 @@ hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Works
   a.utility = fuse ? fuse->utility : nullptr;
   a.pool = fuse ? fuse->pool : CKV_POOL_NONE;
   a.radius = fuse ? fuse->radius : 0;
+  a.bud = fuse ? fuse->bud : BudgetArgs{};
   a.inv_kernel = fuse ? fuse->inv_kernel : 1.0f;
   a.inv_kernel_rest = fuse ? fuse->inv_kernel_rest : 0.0f;
   const bool need_lse = lse_in == nullptr, need_scores = scores != nullptr;

@@ -1,7 +1,6 @@
-// Device code of the tables kernels (ckv_tables.hip): the argument block, the budget rule and the gate
-// lookup (paper Sec. 4.3), the four-position pooling + weighted group maximum (paper Eq. 6), and the
-// enumeration of the positions that the fused utility form of the scan's second pass (ckv_scan.h) leaves
-// to be finished from raw column sums -- the geometry constants both sides use are in ckv_internal.h.
+// Device code of the tables kernels (ckv_tables.hip): the argument block, the four-position pooling + weighted group
+// maximum (paper Eq. 6), and the budget rule and the gate lookup (paper Sec. 4.3), which the fused utility form of
+// the scan's second pass (ckv_scan.h) runs as well.
 #ifndef CKV_TABLES_H_
 #define CKV_TABLES_H_
 #include "ckv_internal.h"
@@ -20,23 +19,17 @@ struct TablesArgs {
   const float *scores;  // [Bz][Hq][T]
   const float *rho;     // [Bz][Hkv][T] or null
   const float *w_row;   // w_head + layer*Hq
-  const float *share_row;  // head_share + layer*Hkv or null
-  const float *gate_layer; // t_gate + layer*n_ent*n_ppl or null
-  const int32_t *risk_bins;
-  int n_ent, n_ppl;
   float *utility;  // [Bz][Hkv][P]
-  int32_t *budget;
-  float *tau;
   int Bz, Hq, Hkv, G, T, W, P;
   int pool, radius, kernel;
-  int B;  // nominal budget per KV head
   int n_tiles;
+  BudgetArgs bud;
 };
 
 // Per-head budgets of one batch element (same rule for every b; written per b for the ABI's layout), by one whole wave: lane i
 // has heads i, i + 64, ... A thread going over the heads by itself was the longest path of the tables kernels (4 heads
 // 2.5 us, 8 heads 4 to 5 with the shares' loads one behind the other).
-__device__ __forceinline__ void write_budgets(const TablesArgs &a, int b, int lane) {
+__device__ __forceinline__ void write_budgets(const BudgetArgs &a, int b, int lane) {
   int32_t *out = a.budget + (size_t)b * a.Hkv;
   if (!a.share_row) {
     for (int g = lane; g < a.Hkv; g += kWave) out[g] = min(a.B, a.T);
@@ -57,11 +50,14 @@ __device__ __forceinline__ void write_budgets(const TablesArgs &a, int b, int la
   };
   int total = 0;  // Hkv * T < 2^29
   for (int g = lane; g < a.Hkv; g += kWave) {
-    double want = floor((double)a.share_row[g] * (double)b_tot);
-    if (!(want >= (double)a.W)) want = (double)a.W;
+    // a share that is no number gives W; told from its bits, since the scan's translation units are compiled without NaNs
+    const uint32_t bits = reinterpret_cast<const uint32_t *>(a.share_row)[g];
+    double want = floor((double)__uint_as_float(bits) * (double)b_tot);
+    if (want < (double)a.W) want = (double)a.W;
     if (want > (double)a.T) want = (double)a.T;
-    set(g, (int)want);
-    total += (int)want;
+    const int keep = (bits & 0x7fffffffu) > 0x7f800000u ? a.W : (int)want;
+    set(g, keep);
+    total += keep;
   }
   // "While the sum exceeds B_tot, the largest budget above W (lowest head on ties) loses one", done
   // a level at a time: the n1 leaders drop together to the runner-up's value (never below W), or,
@@ -100,15 +96,15 @@ __device__ __forceinline__ void write_budgets(const TablesArgs &a, int b, int la
   if (one && lane < a.Hkv) out[lane] = mine;
 }
 
-__device__ __forceinline__ void write_tau_and_budgets(const TablesArgs &a, int b, int lane) {
+__device__ __forceinline__ void write_tau_and_budgets(const BudgetArgs &a, int b, int lane) {
   if (lane == 0) {
-    float tau = 0.0f;
+    uint32_t tau = 0u;
     if (a.gate_layer) {
       const int be = min(max(a.risk_bins[2 * b], 0), a.n_ent - 1);
       const int bp = min(max(a.risk_bins[2 * b + 1], 0), a.n_ppl - 1);
-      tau = a.gate_layer[be * a.n_ppl + bp];
+      tau = reinterpret_cast<const uint32_t *>(a.gate_layer)[be * a.n_ppl + bp];
     }
-    a.tau[b] = tau;
+    reinterpret_cast<uint32_t *>(a.tau)[b] = tau;
   }
   write_budgets(a, b, lane);
 }
@@ -174,46 +170,6 @@ __device__ __forceinline__ void pool_four(const TablesArgs &a, int unit, int t) 
   }
 }
 
-// What the fused utility form of the scan's second pass leaves out. That pass writes the utilities of the
-// keys its pipeline takes (whole rounds of kRing * kTile keys at the front of every wave's key range)
-// except the first four and the last kUtilShift of them (its output windows trail the rounds by that
-// much so that its stores stay 128-byte aligned), and stores raw column sums only around those two
-// places and for the tail of the range. fixup_range computes what is missing from the raw sums, for
-// one wave range of one (batch, KV head): the four-key group at the front, the last kUtilShift / 4
-// groups of the pipelined part, and every group of the tail. Thread tid of n_threads takes every
-// n_threads-th group.
-struct FixupArgs {
-  int keys_per_wave, n_ranges;  // the scan's split of the key axis
-};
-// Groups of four positions that the fix-up computes in wave range `range`: n_edge at the edges of the
-// pipelined part, then n_tail in the tail; group i starts at position group_start(i).
-struct FixupRange {
-  int t_begin, tail0, n_edge, n_tail;
-  __device__ __forceinline__ FixupRange(const TablesArgs &a, const FixupArgs &f, int range) {
-    constexpr int kBlockKeys = kRing * kTile;  // keys per pipeline round of the scan
-    t_begin = range * f.keys_per_wave;
-    const int t_end = min(t_begin + f.keys_per_wave, a.T);
-    const int n_full = max(0, (min(t_end, a.P) - t_begin) / kTile);   // tiles wholly inside the prefix
-    const int n_blocks = n_full / kRing;                               // pipeline rounds
-    tail0 = t_begin + n_blocks * kBlockKeys;
-    const int tail1 = min(t_end, a.P);
-    n_tail = t_begin < a.T && tail1 > tail0 ? (tail1 - tail0 + 3) / 4 : 0;
-    n_edge = t_begin < a.T && n_blocks > 0 ? 1 + kUtilShift / 4 : 0;
-  }
-  __device__ __forceinline__ int groups() const { return n_edge + n_tail; }
-  __device__ __forceinline__ int group_start(int i) const {
-    return i < n_edge ? (i == 0 ? t_begin : tail0 - kUtilShift + (i - 1) * 4) : tail0 + (i - n_edge) * 4;
-  }
-};
-
-// One wave range, thread tid of n_threads taking every n_threads-th group.
-template <int POOL, int R>
-__device__ __forceinline__ void fixup_range(const TablesArgs &a, const FixupArgs &f, int unit, int range, int tid,
-                                            int n_threads) {
-  const FixupRange fr(a, f, range);
-  for (int i = tid; i < fr.groups(); i += n_threads) pool_four<POOL, R>(a, unit, fr.group_start(i));
-}
-
 // Host side: the argument block for one call.
 inline TablesArgs tables_args(const ckv_params *p, const Shape &s, const float *scores,
                               const float *vnorm_ratio, const float *w_head, const float *head_share,
@@ -223,19 +179,12 @@ inline TablesArgs tables_args(const ckv_params *p, const Shape &s, const float *
   a.scores = scores;
   a.rho = (p->flags & CKV_FLAG_VALUE_NORM) ? vnorm_ratio : nullptr;
   a.w_row = w_head + (size_t)p->layer * s.Hq;
-  a.share_row = head_share ? head_share + (size_t)p->layer * s.Hkv : nullptr;
-  a.gate_layer = t_gate ? t_gate + (size_t)p->layer * n_ent * n_ppl : nullptr;
-  a.risk_bins = risk_bins;
-  a.n_ent = n_ent;
-  a.n_ppl = n_ppl;
   a.utility = utility;
-  a.budget = budget;
-  a.tau = tau;
+  a.bud = budget_args(p, s, head_share, t_gate, n_ent, n_ppl, risk_bins, budget, tau);
   a.Bz = s.Bz; a.Hq = s.Hq; a.Hkv = s.Hkv; a.G = s.G; a.T = s.T; a.W = s.W; a.P = s.P;
   a.pool = p->pool;
   a.kernel = p->pool == CKV_POOL_NONE ? 1 : p->pool_kernel;
   a.radius = a.kernel / 2;
-  a.B = p->budget_per_kv_head;
   a.n_tiles = (s.P + kTablesTile - 1) / kTablesTile;
   return a;
 }

@@ -18,7 +18,7 @@ __global__ void __launch_bounds__(kTablesThreads) tables_kernel(TablesArgs a) {
   const int t0 = tile * kTablesTile;
 
   if (tile == a.n_tiles) {  // the workgroups behind the tiles: tau and the budgets
-    if (g == 0 && threadIdx.x < kWave) write_tau_and_budgets(a, b, threadIdx.x);
+    if (g == 0 && threadIdx.x < kWave) write_tau_and_budgets(a.bud, b, threadIdx.x);
     return;
   }
 
@@ -71,25 +71,11 @@ __global__ void __launch_bounds__(kTablesThreads) tables_window_kernel(TablesArg
   const int unit = blockIdx.y;
   const int t = (blockIdx.x * kTablesThreads + threadIdx.x) * 4;  // first of this thread's positions
   if ((int)blockIdx.x == a.n_tiles) {  // the workgroups behind the tiles: tau and the budgets
-    if (unit % a.Hkv == 0 && threadIdx.x < kWave) write_tau_and_budgets(a, unit / a.Hkv, threadIdx.x);
+    if (unit % a.Hkv == 0 && threadIdx.x < kWave) write_tau_and_budgets(a.bud, unit / a.Hkv, threadIdx.x);
     return;
   }
   if (t >= a.P) return;
   pool_four<POOL, R>(a, unit, t);
-}
-
-// Companion of the fused utility form of the scan's second pass (see fixup_range): one workgroup of 64
-// threads per (wave range, unit) finishes what that pass leaves out; also writes tau and the budgets.
-constexpr int kFixupThreads = 64;
-
-template <int POOL, int R>
-__global__ void __launch_bounds__(kFixupThreads) tables_fixup_kernel(TablesArgs a, FixupArgs f) {
-  const int unit = blockIdx.y, range = blockIdx.x;
-  if (range == f.n_ranges) {
-    if (unit % a.Hkv == 0) write_tau_and_budgets(a, unit / a.Hkv, threadIdx.x);
-    return;
-  }
-  fixup_range<POOL, R>(a, f, unit, range, threadIdx.x, kFixupThreads);
 }
 
 template <int POOL>
@@ -104,6 +90,21 @@ static bool launch_window_pool(const TablesArgs &a, dim3 grid, hipStream_t strea
   return false;
 }
 
+BudgetArgs budget_args(const ckv_params *p, const Shape &s, const float *head_share, const float *t_gate, int n_ent,
+                       int n_ppl, const int32_t *risk_bins, int32_t *budget, float *tau) {
+  BudgetArgs a;
+  a.share_row = head_share ? head_share + (size_t)p->layer * s.Hkv : nullptr;
+  a.gate_layer = t_gate ? t_gate + (size_t)p->layer * n_ent * n_ppl : nullptr;
+  a.risk_bins = risk_bins;
+  a.n_ent = n_ent;
+  a.n_ppl = n_ppl;
+  a.budget = budget;
+  a.tau = tau;
+  a.Hkv = s.Hkv; a.T = s.T; a.W = s.W;
+  a.B = p->budget_per_kv_head;
+  return a;
+}
+
 hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float *scores,
                                const float *vnorm_ratio, const float *w_head, const float *head_share,
                                const float *t_gate, int n_ent, int n_ppl, const int32_t *risk_bins,
@@ -116,33 +117,6 @@ hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float 
     done = p->pool == CKV_POOL_MAX ? launch_window_pool<CKV_POOL_MAX>(a, grid, stream)
                                    : launch_window_pool<CKV_POOL_AVG>(a, grid, stream);
   if (!done) hipLaunchKernelGGL(tables_kernel, grid, block, 0, stream, a);
-  return hipGetLastError();
-}
-
-template <int POOL>
-static void launch_fixup_pool(const TablesArgs &a, const FixupArgs &f, dim3 grid, hipStream_t stream) {
-  const dim3 block(kFixupThreads);
-  switch (a.radius) {
-    case 0: hipLaunchKernelGGL((tables_fixup_kernel<POOL, 0>), grid, block, 0, stream, a, f); break;
-    case 1: hipLaunchKernelGGL((tables_fixup_kernel<POOL, 1>), grid, block, 0, stream, a, f); break;
-    case 2: hipLaunchKernelGGL((tables_fixup_kernel<POOL, 2>), grid, block, 0, stream, a, f); break;
-    default: hipLaunchKernelGGL((tables_fixup_kernel<POOL, 3>), grid, block, 0, stream, a, f); break;
-  }
-}
-
-// The caller has checked utility_fast_path(); the ratio is applied afterwards.
-hipError_t launch_utility_fixup(const ckv_params *p, const Shape &s, const float *sparse_scores,
-                                const float *w_head, const float *head_share, const float *t_gate, int n_ent,
-                                int n_ppl, const int32_t *risk_bins, float *utility, int32_t *budget, float *tau,
-                                hipStream_t stream) {
-  const TablesArgs a = tables_args(p, s, sparse_scores, nullptr, w_head, head_share, t_gate, n_ent, n_ppl,
-                                   risk_bins, utility, budget, tau);
-  FixupArgs f;
-  f.keys_per_wave = s.keys_per_wave;
-  f.n_ranges = s.n_chunks * kScoreWaves;
-  const dim3 grid(f.n_ranges + 1, s.Bz * s.Hkv);
-  if (p->pool == CKV_POOL_MAX) launch_fixup_pool<CKV_POOL_MAX>(a, f, grid, stream);
-  else launch_fixup_pool<CKV_POOL_AVG>(a, f, grid, stream);
   return hipGetLastError();
 }
 

@@ -2,11 +2,11 @@
 materialised): against the CPU oracle, and against the two unfused calls on the same tensors.
 
 The fused second pass works on 128-key pipeline rounds per wave: the first and the last round of a
-wave's key range treat their edges specially (raw column sums for the fix-up kernel), rounds in between
+wave's key range treat their edges specially (finished behind a barrier), rounds in between
 only carry the previous round's tail in front. The shapes marked "rounds" give every wave at least
 three rounds (batch x KV heads x T >= 3 * 128 * 1024 keys over the 1024 waves of a launch), so that
 first, middle and last rounds all meet the oracle, for every pooling mode and radius the fused pass
-takes and for both head sizes. wu_short has no whole round at all (range tails and the fix-up kernel
+takes and for both head sizes. wu_short has no whole round at all (range tails
 only). The last group holds shapes the fused pass does not take: they run the two steps through the
 scratch buffer."""
 import numpy as np
