@@ -120,6 +120,13 @@ int vnorm_blocks_per_unit(const Shape &s) {
   return (s.T + kVnormRows - 1) / kVnormRows;
 }
 
+// Four more waves per workgroup of the bf16 scan, where its own leave them registers (up to four query tiles per wave), one
+// workgroup takes all query tiles of its keys, and its range is whole blocks of the norms' sums.
+bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given) {
+  return (p->flags & CKV_FLAG_VALUE_NORM) && !lse_given && p->dtype == CKV_BF16 && s.NQ <= kMaxQTilesNorms && s.n_groups == 1 &&
+         kScoreWaves * s.keys_per_wave % kVnormRows == 0;
+}
+
 void layout(const ckv_params *p, const Shape &s, Workspace *w) {
   const size_t units = (size_t)s.Bz * s.Hkv;
   size_t off = 0;
@@ -178,9 +185,11 @@ extern "C" ckv_status ckv_window_scores(const ckv_params *params, const void *q_
   if ((params->flags & CKV_FLAG_GROUP_MASS) && !(params->dtype == CKV_BF16 && s.n_groups == 1 && s.WT == 1 && s.NQ <= 4))
     return CKV_EUNSUPPORTED;
   hipStream_t stream = (hipStream_t)hip_stream;
-  if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores, (char *)workspace, stream) != hipSuccess)
+  if (vn && !norms_in_scan(params, s, lse != nullptr) &&
+      launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;
-  if (vn && launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream) != hipSuccess)
+  if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores, (char *)workspace, stream, nullptr, v,
+                           vn ? vnorm_ratio : nullptr) != hipSuccess)
     return CKV_EHIP;
   return CKV_OK;
 }
@@ -311,6 +320,10 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
   st = workspace_ok(w, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
   hipStream_t stream = (hipStream_t)hip_stream;
+  float *ratio = vn ? vnorm_ratio : nullptr;
+  if (vn && !norms_in_scan(params, s, lse != nullptr) &&
+      launch_value_norm(params, s, w, v, ratio, (char *)workspace, stream) != hipSuccess)
+    return CKV_EHIP;
   if (utility_fast_path(params, s)) {
     UtilityFusion fuse;
     fuse.w_row = w_head + (size_t)params->layer * s.Hq;
@@ -324,16 +337,13 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
     fuse.inv_kernel_rest = fmaxf((float)(1.0 / kernel - (double)fuse.inv_kernel), FLT_MIN);
     fuse.bud = budget_args(params, s, head_share, t_gate, n_ent, n_ppl, risk_bins, budget, tau);
     if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores_scratch, (char *)workspace, stream,
-                             &fuse) != hipSuccess)
-      return CKV_EHIP;
-    if (vn && launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream, utility) != hipSuccess)
+                             &fuse, v, ratio) != hipSuccess)
       return CKV_EHIP;
     return CKV_OK;
   }
-  if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores_scratch, (char *)workspace, stream) !=
-      hipSuccess)
+  if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores_scratch, (char *)workspace, stream, nullptr,
+                           v, ratio) != hipSuccess)
     return CKV_EHIP;
-  if (vn && launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream) != hipSuccess) return CKV_EHIP;
   if (launch_apply_tables(params, s, scores_scratch, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl,
                           risk_bins, utility, budget, tau, stream) != hipSuccess)
     return CKV_EHIP;

@@ -14,6 +14,7 @@ constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kTile = 32;          // MFMA 32x32 tile edge: query rows and keys per tile
 constexpr int kMaxQTiles = 8;      // query-row tiles a wave keeps in registers (bf16; f32 kernels: kMaxQTilesF32)
 constexpr int kMaxQTilesF32 = 4;
+constexpr int kMaxQTilesNorms = 4; // up to here a wave of the scan's first pass leaves half of its SIMD's registers
 constexpr int kMaxWindowTiles = 4; // 32-row tiles per query head: W <= 128
 constexpr int kScoreWaves = 4;     // waves per workgroup in the scan kernels
 // Compute units of the build target (gfx950: MI355X, 256). A constant on purpose, not a device query: the
@@ -130,6 +131,8 @@ int vnorm_blocks_per_unit(const Shape &s);
 
 // Kernel launchers (each returns hipGetLastError() after its launches).
 // lse_in == nullptr: pass 1 first, LSE into lse_out (or the workspace). scores == nullptr: pass 1 only.
+// ratio: if given, pass 2 makes it of the value norms that launch_value_norm, or with norms_in_scan() and v pass 1, left there
+// (and, in the fused form, multiplies the utilities by it).
 // tau and the per-head budgets of a call (paper Sec. 4.3), written beside the utilities.
 struct BudgetArgs {
   const float *share_row;   // head_share + layer*Hkv or null
@@ -155,10 +158,13 @@ struct UtilityFusion {
 };
 hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Workspace &w, const void *q,
                                 const void *k, const float *lse_in, float *lse_out, float *scores,
-                                char *ws, hipStream_t stream, const UtilityFusion *fuse = nullptr);
-// utility_scaled: if given, [units][P] utilities that the scaling pass multiplies by the ratio
+                                char *ws, hipStream_t stream, const UtilityFusion *fuse = nullptr,
+                                const void *v = nullptr, float *ratio = nullptr);
+// Whether pass 1 of a call takes the value norms beside its scan; the norms and sums are those of launch_value_norm.
+bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given);
+// the norms into `ratio` and their sums per block into the workspace; launch_window_scores turns them into the ratio
 hipError_t launch_value_norm(const ckv_params *p, const Shape &s, const Workspace &w, const void *v,
-                             float *ratio, char *ws, hipStream_t stream, float *utility_scaled = nullptr);
+                             float *ratio, char *ws, hipStream_t stream);
 hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float *scores,
                                const float *vnorm_ratio, const float *w_head, const float *head_share,
                                const float *t_gate, int n_ent, int n_ppl, const int32_t *risk_bins,

@@ -44,6 +44,11 @@ struct ScoreArgs {
   float *lse_out;
   float *scores;     // [Bz][Hq][T]; with group_sum: [Bz][Hkv][T], the sum over each KV head's query heads
   int group_sum;
+  float *ratio;      // [Bz][Hkv][T] or null: the norms of V's rows, which pass 2 turns into their ratio to the mean
+  float *vsum;       // [Bz][Hkv][vnorm_blocks] partial sums of the norms
+  int vnorm_blocks;
+  const char *v;     // pass 1 takes the norms, or null
+  int64_t vs_b, vs_h, vs_t;  // byte strides
   // fused utility form of pass 2 only
   const float *w_row;  // w_head + layer * Hq
   float *utility;      // [Bz][Hkv][P]
@@ -141,16 +146,14 @@ __device__ __forceinline__ void load_q_tiles(const ScoreArgs &a, const BlockCoor
 // of one tile. The maximum is taken on the raw dot products (the scale is positive); scale and
 // subtraction are one FMA per element.
 template <bool EDGE>
-__device__ __forceinline__ void rowstats_update(const f32x16 &acc, float c2, int t0, int hh, int first, int limit,
-                                                float &rm, float &rl) {
+__device__ __forceinline__ void rowstats_update(const f32x16 &acc, float c2, int t0, int hh, int limit, float &rm, float &rl) {
   float v[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) v[r] = acc[r];
-  if (EDGE) {  // keys in front of `first` and beyond `limit` do not count: one unsigned comparison for both
-    const uint32_t span = (uint32_t)max(limit - first + 1, 0);
+  if (EDGE) {  // keys beyond `limit` do not count
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-      if ((uint32_t)(t0 - first + acc_row(r, hh)) >= span) v[r] = -INFINITY;
+      if (acc_row(r, hh) > limit - t0) v[r] = -INFINITY;
   }
   float t[4];
 #pragma unroll
@@ -215,13 +218,13 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) r
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         mma_chain<DT, NCH>(acc, kf, qf[i]);  // rows: keys, cols: query rows
-        rowstats_update<true>(acc, a.c2, t0, hh, t0, limit[i], rm[i], rl[i]);
+        rowstats_update<true>(acc, a.c2, t0, hh, limit[i], rm[i], rl[i]);
       }
     } else {
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         mma_chain<DT, NCH>(acc, kf, qf[i]);
-        rowstats_update<false>(acc, a.c2, t0, hh, t0, limit[i], rm[i], rl[i]);
+        rowstats_update<false>(acc, a.c2, t0, hh, limit[i], rm[i], rl[i]);
       }
     }
   };
@@ -301,6 +304,51 @@ __device__ __forceinline__ float colsum_tile(const chunk_t (&qf)[NCH], const chu
   return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
+// Value-norm ratio of the workgroup's key range: norm / (mean + eps), in place, by pass 2 (as a kernel of its own it took 4 to
+// 5 us). What it reads is asked for before anything else (load) and used while the first key tiles are on their way.
+typedef float f32x4_r __attribute__((ext_vector_type(4), aligned(4)));  // rows start at any multiple of four bytes
+struct RatioScale {
+  static constexpr int AHEAD = 2, STEP = kScoreWaves * kWave * 4;
+  bool on;  // the same for the whole workgroup
+  int begin, end;
+  float *row;
+  float part;
+  f32x4_r r[AHEAD];
+  __device__ __forceinline__ void load(const ScoreArgs &a, const BlockCoord &bc) {
+    on = a.ratio && bc.grp == 0;
+    if (!on) return;
+    begin = bc.chunk * kScoreWaves * a.keys_per_wave;
+    end = min(begin + kScoreWaves * a.keys_per_wave, a.T);
+    row = a.ratio + (size_t)bc.unit * a.T;
+    const float *vsum = a.vsum + (size_t)bc.unit * a.vnorm_blocks;
+    const int lane = threadIdx.x & 63;
+    part = lane < a.vnorm_blocks ? vsum[lane] : 0.0f;
+#pragma unroll
+    for (int e = 0; e < AHEAD; ++e) {
+      const int t = begin + threadIdx.x * 4 + e * STEP;
+      r[e] = f32x4_r{0.0f, 0.0f, 0.0f, 0.0f};
+      if (t + 4 <= end) r[e] = *reinterpret_cast<const f32x4_r *>(row + t);
+    }
+  }
+  __device__ __forceinline__ void store(const ScoreArgs &a, const BlockCoord &bc) {
+    if (!on) return;
+    float total = part;
+    for (int i = kWave + (threadIdx.x & 63); i < a.vnorm_blocks; i += kWave)
+      total += a.vsum[(size_t)bc.unit * a.vnorm_blocks + i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
+    const float inv = 1.0f / (total / (float)a.T + kValueNormEps);
+    for (int t0 = begin + threadIdx.x * 4, e = 0; t0 < end; t0 += STEP, ++e) {
+      if (t0 + 4 <= end) {
+        const f32x4_r x = e == 0 ? r[0] : e == 1 ? r[1] : *reinterpret_cast<const f32x4_r *>(row + t0);
+        *reinterpret_cast<f32x4_r *>(row + t0) = x * inv;
+      } else {
+        for (int t = t0; t < end; ++t) row[t] *= inv;
+      }
+    }
+  }
+};
+
 template <int DT, int DH, int NQ>
 __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) colsum_kernel(ScoreArgs a) {
   constexpr int NCH = DH * (DT == CKV_BF16 ? 2 : 4) / 32;
@@ -324,7 +372,10 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) c
   }
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
+  RatioScale rs;
+  rs.load(a, bc);
   load_q_tiles<NCH, NQ>(a, bc, m, hh, qf, jrow);
+  rs.store(a, bc);
   __syncthreads();
 
   const char *kbase = a.k + bc.b * a.ks_b + bc.g * a.ks_h;
@@ -473,15 +524,16 @@ __device__ __forceinline__ void dma_quad(const char *sbase, uint32_t lds, uint32
       : "memory");
 }
 
-// One whole tile whose first row starts at tile_base. voff[i] already holds the lane's source offset
-// minus the immediate of its instruction plus kDmaBias, so the scalar base is tile_base - kDmaBias.
+// One whole tile whose first row starts at tile_base. voff[i] already holds the lane's source offset in the first quad
+// minus the immediate of its instruction plus kDmaBias, so the scalar base is tile_base - kDmaBias; the second quad reads the
+// same chunks (the swizzle repeats every sixteen rows) quad_stride = 16 rows further on.
 constexpr int kDmaBias = 3072;
 template <class G>
-__device__ __forceinline__ void dma_tile(const char *tile_base, const uint32_t (&voff)[G::NDMA], uint32_t lds_image) {
+__device__ __forceinline__ void dma_tile(const char *tile_base, const uint32_t (&voff)[4], int64_t quad_stride, uint32_t lds_image) {
+  static_assert(G::NDMA == 4 || (G::NDMA == 8 && G::CH == 16), "a quad is sixteen rows of sixteen chunks");
 #pragma unroll
   for (int q = 0; q < G::NDMA / 4; ++q)
-    dma_quad(tile_base - kDmaBias, lds_image + q * 4096, voff[4 * q] + q * 4096, voff[4 * q + 1] + q * 4096,
-             voff[4 * q + 2] + q * 4096, voff[4 * q + 3] + q * 4096);
+    dma_quad(tile_base - kDmaBias + q * quad_stride, lds_image + q * 4096, voff[0], voff[1], voff[2], voff[3]);
 }
 
 // The only tile of a sequence shorter than a tile: row indices are clamped (the logits of the clamped rows are masked by
@@ -543,9 +595,6 @@ struct WaveRange {
   int n_full;   // tiles wholly inside the prefix
   int n_whole;  // tiles wholly inside the keys
   int n_all;    // the tiles to take: one more than n_whole where the keys end inside a tile
-  // First key of the rows that stand for tile t: a tile that the keys end in is taken from the last 32 rows, so that no load
-  // runs past them (rows in front of the tile are masked).
-  __device__ __forceinline__ int tile_key(int t, int T) const { return t < n_whole ? t_begin + t * kTile : max(0, T - kTile); }
 };
 // `last`: the keys whose sums are wanted end here, T or (utilities) P.
 __device__ __forceinline__ WaveRange wave_range(const ScoreArgs &a, const BlockCoord &bc, int last) {
@@ -563,13 +612,15 @@ __device__ __forceinline__ WaveRange wave_range(const ScoreArgs &a, const BlockC
 #ifndef CKV_PIN_Q_ABOVE
 #define CKV_PIN_Q_ABOVE 4
 #endif
-template <int DT, int DH, int NQ>
+// LEAN: registers are short (another wave shares the SIMD), operand addresses are formed at each read.
+template <int DT, int DH, int NQ, bool LEAN = false>
 struct Staged {
   using G = Geom<DT, DH>;
   static constexpr int NCH = G::NCH;
   typedef char Ring[kScoreWaves][kRing][G::TILE];
-  uint32_t voff[G::NDMA];  // lane's biased source offset inside a K tile, per load instruction
+  uint32_t voff[4];        // lane's biased source offset inside a K tile, per load instruction of a quad
   int roff[NCH];           // lane's operand chunks inside a tile image
+  uint32_t rbase;          // LEAN: the first of them in the wave's first image (the others differ in three bits)
   const char *kbase;       // first key row of the unit
   const char *kcur;        // first row of the key tile the pipeline is working on
   const char *kend;        // first row of the wave's last tile (what the loads beyond it fetch again)
@@ -584,10 +635,10 @@ struct Staged {
   __device__ __forceinline__ void start(const ScoreArgs &a, const BlockCoord &bc, const WaveRange &wr, Ring &ring,
                                         int lane, int m, int hh, chunk_t (&qf)[NQ][NCH], int (&jrow)[NQ]) {
 #pragma unroll
-    for (int i = 0; i < G::NDMA; ++i) {
+    for (int i = 0; i < 4; ++i) {
       int r, kappa;
       dma_source<G>(i, lane, r, kappa);
-      voff[i] = (uint32_t)(r * a.ks_t + kappa * 16 + kDmaBias - (i % 4) * 1024 - (i / 4) * 4096);
+      voff[i] = (uint32_t)(r * a.ks_t + kappa * 16 + kDmaBias - i * 1024);
     }
 #pragma unroll
     for (int c = 0; c < NCH; ++c) roff[c] = image_offset<G>(m, c + NCH * hh);
@@ -597,6 +648,7 @@ struct Staged {
     kend = uniform_ptr(wr.n_all > wr.n_whole ? kbase + (int64_t)max(a.T - kTile, 0) * a.ks_t
                                              : kcur + max(wr.n_whole - 1, 0) * tile_stride);
     lds_ring = (uint32_t)(uintptr_t)&ring[wr.wave][0][0];
+    if (LEAN) rbase = lds_ring + image_offset<G>(m, NCH * hh);
 
 #pragma unroll
     for (int qi = 0; qi < QI; ++qi) {
@@ -620,7 +672,7 @@ struct Staged {
       if (!tiny) {
 #pragma unroll
         for (int d = 0; d < N_PRE; ++d)
-          dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, lds_ring + d * G::TILE);
+          dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, tile_stride / 2, lds_ring + d * G::TILE);
       } else {
 #pragma unroll
         for (int d = 0; d < N_PRE; ++d) dma_tile_clamped<G>(kbase, a.ks_t, a.T, lane, ring[wr.wave][d]);
@@ -654,58 +706,181 @@ struct Staged {
     if (wr.n_all > 0 && !tiny) {
 #pragma unroll
       for (int d = N_PRE; d < kRing - 1; ++d)
-        dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, lds_ring + d * G::TILE);
+        dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, tile_stride / 2, lds_ring + d * G::TILE);
     }
   }
 
   // Load of the tile three ahead of the one at kcur (tile index t + 3) into ring image `slot`; past
   // the last tile the last one is fetched again (in bounds, unused).
   __device__ __forceinline__ void prefetch(int t, int n_whole, int slot) {
-    dma_tile<G>(t + 3 < n_whole ? kcur + 3 * tile_stride : kend, voff, lds_ring + slot * G::TILE);
+    dma_tile<G>(t + 3 < n_whole ? kcur + 3 * tile_stride : kend, voff, tile_stride / 2, lds_ring + slot * G::TILE);
   }
 
-  // Tile t (behind the pipeline, at kcur) into registers: its load was issued three tiles ago, as the pipeline's are.
-  __device__ __forceinline__ void tail_tile(const WaveRange &wr, Ring &ring, int t, chunk_t (&kf)[NCH]) {
+  // Operand chunks of the tile in ring image `slot`.
+  __device__ __forceinline__ void read(chunk_t (&f)[NCH], const WaveRange &wr, Ring &ring, int slot) {
+    if constexpr (LEAN) {
+      typedef __attribute__((address_space(3))) const chunk_t lds_chunk_t;
+      uint32_t at = rbase;
+      asm volatile("" : "+v"(at));  // or the eight addresses are kept in registers
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) f[c] = *(lds_chunk_t *)(uintptr_t)((at ^ (c << 4)) + slot * G::TILE);
+    } else {
+      read_image<G>(f, ring[wr.wave][slot], roff);
+    }
+  }
+
+  // Tile t (behind the pipeline, at kcur) into registers: its load was issued three tiles ago, as the pipeline's are. A tile that
+  // the keys end in comes as the last 32 rows of them, `shift` rows in front of it; lanes beyond the keys take the last one.
+  __device__ __forceinline__ void tail_tile(const WaveRange &wr, Ring &ring, int t, int shift, int m, int hh, chunk_t (&kf)[NCH]) {
     if (t + 3 < wr.n_all) {
       prefetch(t, wr.n_whole, (t + 3) % kRing);
       wait_vm<(kRing - 1) * G::NDMA>();
     } else {
       wait_vm<0>();
     }
-    read_image<G>(kf, ring[wr.wave][t % kRing], roff);
+    if (t < wr.n_whole) {
+      read(kf, wr, ring, t % kRing);
+    } else {
+      // fewer than 32 keys at all: the image's rows are clamped already
+      const int row = shift > t * kTile + wr.t_begin ? m : min(m + shift, kTile - 1);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c)
+        kf[c] = *reinterpret_cast<const chunk_t *>(ring[wr.wave][t % kRing] + image_offset<G>(row, c + NCH * hh));
+    }
     kcur += tile_stride;
   }
 };
 
-template <int DT, int DH, int NQ>
-__global__ void __launch_bounds__(kScoreWaves *kWave) rowstats_lds_kernel(ScoreArgs a) {
+// Value norms (paper Eq. 4, r_t = ||v_t||) of the workgroup's key range by four more waves of pass 1. Wave w takes the rows that
+// wave w of vnorm_rows_kernel takes, and the sums of blocks of kVnormRows rows are formed in that kernel's order: the same
+// bits. DEPTH - 1 steps' loads are in flight beside a step; the norm of a row ends in one lane of those that hold it, so
+// that a step takes one root and one store.
+template <int DH>
+struct NormWaves {
+  static constexpr int LPR = DH / 8;                     // lanes (16-byte pieces) per row
+  static constexpr int RPL = kWave / LPR;                // adjacent rows per load
+  static constexpr int APART = kScoreWaves * RPL;        // rows from one load to the next
+  static constexpr int U = 8, STEP = U * APART;          // loads of a step, rows of a step of all waves
+  static constexpr int DEPTH = 3;                        // steps in registers
+  static_assert(U <= LPR, "a lane per load keeps its row's norm");
+  static_assert(kVnormRows % STEP == 0, "whole steps per block");
+  typedef float Sums[4096 * kScoreWaves / kVnormRows][kScoreWaves];  // per block of the longest range and wave
+  static __device__ __forceinline__ void load(uint4 (&c)[U], const char *base, int64_t stride, int row, int end, int sub) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = load_piece<true>(base + (int64_t)min(row + u * APART, end - 1) * stride + sub * 16);
+  }
+  static __device__ __forceinline__ void run(const ScoreArgs &a, const BlockCoord &bc, int wave, int lane, Sums &sums) {
+    const int begin = bc.chunk * kScoreWaves * a.keys_per_wave, end = min(begin + kScoreWaves * a.keys_per_wave, a.T);
+    const char *base = a.v + bc.b * a.vs_b + bc.g * a.vs_h;
+    float *out = a.ratio + (size_t)bc.unit * a.T;
+    const int sub = lane % LPR;
+    float local = 0.0f;
+    uint4 c[DEPTH][U];
+    int row = begin + wave * RPL + lane / LPR;  // of the step's first load
+#pragma unroll
+    for (int i = 0; i < DEPTH - 1; ++i) load(c[i], base, a.vs_t, row + i * STEP, end, sub);
+    const auto step = [&](uint4 (&now)[U], uint4 (&next)[U]) {
+      load(next, base, a.vs_t, row + (DEPTH - 1) * STEP, end, sub);
+      float mine = 0.0f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t w[4] = {now[u].x, now[u].y, now[u].z, now[u].w};
+        float sq = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float lo = __uint_as_float(w[e] << 16), hi = __uint_as_float(w[e] & 0xffff0000u);
+          sq = fmaf(lo, lo, sq);
+          sq = fmaf(hi, hi, sq);
+        }
+        sq = row_sum<LPR>(sq);
+        mine = sub == u ? sq : mine;
+      }
+      const int t = row + sub * APART;
+      float nrm = sqrtf(mine);
+      if (sub < U && t < end) out[t] = nrm;
+      nrm = t < end ? nrm : 0.0f;
+      // lane 0 of a row's lanes adds the step's norms in the order of the rows
+      local += nrm;
+      local += from_lane<1>(nrm);
+      local += from_lane<2>(nrm);
+      local += from_lane<3>(nrm);
+      local += from_lane<4>(nrm);
+      local += from_lane<5>(nrm);
+      local += from_lane<6>(nrm);
+      local += from_lane<7>(nrm);
+      row += STEP;
+    };
+    // the barriers of Staged::start, with the first loads on their way
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_s_barrier();
+    for (int first = begin, i = 0; first < end;) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        if (first >= end) break;
+        step(c[d], c[(d + DEPTH - 1) % DEPTH]);
+        first += STEP;
+        if ((first - begin) % kVnormRows == 0 || first >= end) {
+          float s = sub == 0 ? local : 0.0f;
+#pragma unroll
+          for (int o = 32; o >= LPR; o >>= 1) s += __shfl_xor(s, o);
+          if (lane == 0) sums[i][wave] = s;
+          ++i;
+          local = 0.0f;
+        }
+      }
+    }
+    __syncthreads();  // the one of store_row_partials
+    const int block = wave * kWave + lane, n_blocks = (end - begin + kVnormRows - 1) / kVnormRows;
+    if (block < n_blocks)
+      a.vsum[(size_t)bc.unit * a.vnorm_blocks + begin / kVnormRows + block] =
+          (sums[block][0] + sums[block][1]) + (sums[block][2] + sums[block][3]);
+  }
+  template <int N>
+  static __device__ __forceinline__ float from_lane(float x) {  // of N lanes further on in the row of sixteen
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x100 + N, 0xF, 0xF, true));
+  }
+};
+
+template <int DT, int DH, int NQ, bool NORMS = false>
+__global__ void __launch_bounds__(kScoreWaves *kWave * (NORMS ? 2 : 1)) rowstats_lds_kernel(ScoreArgs a) {
   using G = Geom<DT, DH>;
   constexpr int NCH = G::NCH;
   constexpr int N_MFMA = NCH * (DT == CKV_BF16 ? 1 : 4);
-  constexpr int READ_AT = NQ >= 2 ? NQ - 2 : 0;  // query tile during which the next key tile is picked up
+  constexpr bool LEAN = NORMS && NQ == kMaxQTilesNorms;
+  // query tile during which the next key tile is picked up; LEAN: when the last chain of the present one has been issued, into
+  // the same registers
+  constexpr int READ_AT = LEAN ? NQ - 1 : NQ >= 2 ? NQ - 2 : 0;
+  constexpr int NEXT = LEAN ? 0 : 1;
   __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ>::Ring ring;
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
   const BlockCoord bc = decode_block(a);
+  if constexpr (NORMS) {
+    __shared__ typename NormWaves<DH>::Sums s_norms;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - kScoreWaves;
+    if (wave >= 0) {
+      NormWaves<DH>::run(a, bc, wave, lane, s_norms);
+      return;
+    }
+  }
   const WaveRange wr = wave_range(a, bc, a.T);
 
-  Staged<DT, DH, NQ> st;
+  Staged<DT, DH, NQ, LEAN> st;
   chunk_t qf[NQ][NCH];
-  int jrow[NQ], limit[NQ];
+  int jrow[NQ];
   st.start(a, bc, wr, ring, lane, m, hh, qf, jrow);
   float rm[NQ], rl[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
-    limit[i] = jrow[i] < 0 ? -1 : a.P + jrow[i];  // last key this row may see (causal)
     rm[i] = -1e30f;
     rl[i] = 0.0f;
   }
 
-  chunk_t kreg[2][NCH];
+  chunk_t kreg[1 + NEXT][NCH];
   f32x16 acc[2];
   const int n_piped = wr.n_full / kRing * kRing;  // the pipeline takes key tiles one ring at a time
   if (n_piped > 0) {
     wait_vm<(kRing - 2) * G::NDMA>();
-    read_image<G>(kreg[0], ring[wr.wave][0], st.roff);
+    st.read(kreg[0], wr, ring, 0);
     mma_chain<DT, NCH>(acc[0], kreg[0], qf[0]);
   }
   constexpr int UR = unroll_tiles(NQ);
@@ -720,13 +895,17 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) rowstats_lds_kernel(ScoreA
         const int cur = (v * NQ + i) & 1;  // accumulator set holding this pair's logits
         if (i == READ_AT) {
           wait_vm<(kRing - 2) * G::NDMA>();  // tile t0 + v + 1 has landed
-          read_image<G>(kreg[(v + 1) & 1], ring[wr.wave][(u + 1) % kRing], st.roff);
+          st.read(kreg[(v + 1) & NEXT], wr, ring, (u + 1) % kRing);
         }
         // logits of the next pair; the last pair of a key tile already starts the next key tile
-        if (i + 1 < NQ) mma_chain<DT, NCH>(acc[cur ^ 1], kreg[v & 1], qf[i + 1]);
-        else mma_chain<DT, NCH>(acc[cur ^ 1], kreg[(v + 1) & 1], qf[0]);
-        rowstats_update<false>(acc[cur], a.c2, 0, hh, 0, 0, rm[i], rl[i]);
-        if (i == READ_AT) interleave_hint<N_MFMA, vector_per_mfma_pass1(NQ), NCH>();
+        if (i + 1 < NQ) mma_chain<DT, NCH>(acc[cur ^ 1], kreg[v & NEXT], qf[i + 1]);
+        else mma_chain<DT, NCH>(acc[cur ^ 1], kreg[(v + 1) & NEXT], qf[0]);
+        rowstats_update<false>(acc[cur], a.c2, 0, hh, 0, rm[i], rl[i]);
+        if (LEAN && i == READ_AT) {  // the chain waits for the reads
+          __builtin_amdgcn_sched_group_barrier(0x100, NCH, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 32, 0);
+          interleave_hint<N_MFMA, 4, 0>();
+        } else if (i == READ_AT) interleave_hint<N_MFMA, vector_per_mfma_pass1(NQ), NCH>();
         else interleave_hint<N_MFMA, vector_per_mfma_pass1(NQ), 0>();
       }
       st.kcur += st.tile_stride;
@@ -734,13 +913,15 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) rowstats_lds_kernel(ScoreA
   }
   // What the pipeline left: up to a ring of whole tiles and the masked ones.
   for (int t = n_piped; t < wr.n_all; ++t) {
-    st.tail_tile(wr, ring, t, kreg[0]);
-    const int t0 = wr.t_begin + t * kTile, key0 = wr.tile_key(t, a.T);
+    const int t0 = wr.t_begin + t * kTile;
+    st.tail_tile(wr, ring, t, t0 - (a.T - kTile), m, hh, kreg[0]);
     mma_chain<DT, NCH>(acc[0], kreg[0], qf[0]);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       if (i + 1 < NQ) mma_chain<DT, NCH>(acc[(i + 1) & 1], kreg[0], qf[i + 1]);
-      rowstats_update<true>(acc[i & 1], a.c2, key0, hh, t0, limit[i], rm[i], rl[i]);
+      const int tile = bc.grp * NQ + i, j = (tile % a.WT) * kTile + m;
+      const int limit = tile < a.n_tiles && j < a.W ? a.P + j : -1;  // last key this row may see (causal)
+      rowstats_update<true>(acc[i & 1], a.c2, t0, hh, limit, rm[i], rl[i]);
       if (i + 1 < NQ) interleave_hint<N_MFMA, kTailVectorPerMfma, 0>();
     }
   }
@@ -841,8 +1022,7 @@ __device__ __forceinline__ void store_group_sum(const ScoreArgs &a, const BlockC
 // [head of the group][key of the ring cycle], and once per ring cycle (4 tiles, 128 keys) every lane
 // stores four consecutive keys of one head with one 128-bit buffer store per pair of heads.
 template <int NQ, int WT, int ROW = kRing * kTile>
-__device__ __forceinline__ void stage_column_sums(const float (&cs)[NQ], float norm, float *stage, int at, int hh,
-                                                  bool keep = true) {
+__device__ __forceinline__ void stage_column_sums(const float (&cs)[NQ], float norm, float *stage, int at, int hh) {
   constexpr int NH = NQ / WT;
   float hv[NH];
 #pragma unroll
@@ -856,7 +1036,7 @@ __device__ __forceinline__ void stage_column_sums(const float (&cs)[NQ], float n
     const float x = hv[h], y = hv[(h + 1 < NH) ? h + 1 : h];
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
     const float tot = (__uint_as_float(sw[0]) + __uint_as_float(sw[1])) * norm;
-    if (keep && h + hh < NH) stage[(h + hh) * ROW + at] = tot;
+    if (h + hh < NH) stage[(h + hh) * ROW + at] = tot;
   }
 }
 
@@ -1131,6 +1311,8 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
       dma_halo<G>(a.k + bc.b * a.ks_b + bc.g * a.ks_h, a.ks_t, begin, begin + kScoreWaves * a.keys_per_wave, a.T, lane,
                   s_halo_keys);
   }
+  RatioScale rs;
+  rs.load(a, bc);
   Staged<DT, DH, NQ> st;
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
@@ -1152,6 +1334,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
   if constexpr (UTIL) {  // tau and the budgets of a batch element: a wave of its first workgroup
     if (bc.g == 0 && bc.chunk == 0 && wr.wave == kScoreWaves - 1) write_tau_and_budgets(a.bud, bc.b, lane);
   }
+  rs.store(a, bc);
   __syncthreads();
   // bias of this lane's query row in every tile; padding rows (q = 0) get exp2(-1000) = 0 as weight
   Bias<DT> bias[NQ];
@@ -1261,8 +1444,8 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
     }
   }
   for (int t = n_piped; t < wr.n_all; ++t) {
-    st.tail_tile(wr, ring, t, kreg[0]);
-    const int kt = wr.tile_key(t, a.T) + m;  // this lane's key
+    const int kt = wr.t_begin + t * kTile + m;  // this lane's key
+    st.tail_tile(wr, ring, t, wr.t_begin + t * kTile - (a.T - kTile), m, hh, kreg[0]);
     float cs[NQ];
     mma_chain<DT, NCH>(acc[0], qf[0], kreg[0]);
     bias[0].add(acc[0], ones);
@@ -1276,12 +1459,10 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
       cs[i] = colsum_weights<!UTIL>(acc[i & 1], a.c2, hh, kt - a.P - j0);  // keys of the prefix: every row sees them
       if (i + 1 < NQ) interleave_hint<N_MFMA, kTailVectorPerMfma, 0>();
     }
-    const int kt_out = kt >= wr.t_begin + t * kTile ? kt : a.T;  // keys in front of the tile are another one's
     if constexpr (UTIL)
-      stage_column_sums<NQ, WT, kUtilRow>(cs, a.norm, stage + kUtilCarry, kt - wr.t_begin - n_piped * kTile, hh,
-                                          kt >= wr.t_begin + t * kTile);
-    else if constexpr (GSUM) store_group_sum<NQ>(a, bc, cs, kt_out, hh);
-    else store_column_sums<NQ>(a, bc, cs, WT, kt_out, hh);
+      stage_column_sums<NQ, WT, kUtilRow>(cs, a.norm, stage + kUtilCarry, (t - n_piped) * kTile + m, hh);
+    else if constexpr (GSUM) store_group_sum<NQ>(a, bc, cs, kt, hh);
+    else store_column_sums<NQ>(a, bc, cs, WT, kt, hh);
   }
   if constexpr (UTIL) {
     __syncthreads();
@@ -1293,6 +1474,26 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
       finish_utility<NQ, WT>(a, bc, wr, n_piped, stage, s_edge[w], prev, w > 0 ? kUtilRow : kUtilHead, next,
                              w == kScoreWaves - 1 || behind >= round ? kUtilHead : kUtilRow, lane, rsrc_u, wgt);
     }
+    if (a.ratio) {
+      // times the ratio, which this thread has scaled at the start; the utilities are other waves' stores: read past the L1
+      wait_vm<0>();
+      __syncthreads();
+      const int begin = bc.chunk * kScoreWaves * a.keys_per_wave, end = min(begin + kScoreWaves * a.keys_per_wave, a.P);
+      const float *ratio = a.ratio + (size_t)bc.unit * a.T;
+      float *util = a.utility + (size_t)bc.unit * a.P;
+      for (int t0 = begin + threadIdx.x * 4; t0 < end; t0 += kScoreWaves * kWave * 4) {
+        float u[4], r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int t = min(t0 + e, end - 1);
+          u[e] = __hip_atomic_load(util + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          r[e] = ratio[t];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (t0 + e < end) util[t0 + e] = u[e] * r[e];
+      }
+    }
   }
   wait_vm<0>();  // the loads beyond the last tile write LDS: not after the wave
 }
@@ -1302,9 +1503,14 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
 // ---------------------------------------------------------------------------------------------
 template <int DT, int DH, int NQ>
 static void launch_rowstats(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 block, hipStream_t stream) {
-  if constexpr (DT == CKV_BF16)
-    hipLaunchKernelGGL((rowstats_lds_kernel<DT, DH, NQ>), grid, block, 0, stream, a);
-  else
+  if constexpr (DT == CKV_BF16) {
+    if (a.v) {
+      if constexpr (NQ <= kMaxQTilesNorms)
+        hipLaunchKernelGGL((rowstats_lds_kernel<DT, DH, NQ, true>), grid, dim3(2 * block.x), 0, stream, a);
+    } else {
+      hipLaunchKernelGGL((rowstats_lds_kernel<DT, DH, NQ>), grid, block, 0, stream, a);
+    }
+  } else
     hipLaunchKernelGGL((rowstats_kernel<DT, DH, NQ>), grid, block, 0, stream, a);
   if (a.lse_from_part) return;  // the second pass of the same call merges the partials itself
   const int rows = s.Bz * s.Hkv * s.n_groups * NQ * kTile;

@@ -1,13 +1,14 @@
 // Observation-window scan, host side: fills the kernel arguments and dispatches on element type and
 // head size; each (type, size) pair is compiled in a translation unit of its own (ckv_scan_*.hip) from
-// the templates in ckv_scan.h. Also the value-norm ratio rho of Eq. 4 (two small kernels).
+// the templates in ckv_scan.h. Also the value norms of Eq. 4's ratio rho.
 #include "ckv_scan.h"
 
 namespace ckv {
 
 hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Workspace &w, const void *q,
                                 const void *k, const float *lse_in, float *lse_out, float *scores,
-                                char *ws, hipStream_t stream, const UtilityFusion *fuse) {
+                                char *ws, hipStream_t stream, const UtilityFusion *fuse, const void *v,
+                                float *ratio) {
   ScoreArgs a;
   a.q = (const char *)q;
   a.k = (const char *)k;
@@ -33,6 +34,13 @@ hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Works
   a.pool = fuse ? fuse->pool : CKV_POOL_NONE;
   a.radius = fuse ? fuse->radius : 0;
   a.bud = fuse ? fuse->bud : BudgetArgs{};
+  a.ratio = ratio;
+  a.vsum = (float *)(ws + w.vsum_off);
+  a.v = ratio && norms_in_scan(p, s, lse_in != nullptr) ? (const char *)v : nullptr;
+  a.vs_b = p->v_stride[0] * s.esize;
+  a.vs_h = p->v_stride[1] * s.esize;
+  a.vs_t = p->v_stride[2] * s.esize;
+  a.vnorm_blocks = vnorm_blocks_per_unit(s);
   a.inv_kernel = fuse ? fuse->inv_kernel : 1.0f;
   a.inv_kernel_rest = fuse ? fuse->inv_kernel_rest : 0.0f;
   const bool need_lse = lse_in == nullptr, need_scores = scores != nullptr;
@@ -52,11 +60,10 @@ hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Works
 
 // ---------------------------------------------------------------------------------------------
 // Value-norm ratio (paper Eq. 4, Alg. 1 Stage 1): r_t = ||v_t||_2, rho_t = r_t / (mean_t r_t + eps).
-// Kernel 1 writes r_t and one partial sum per block of 512 rows; kernel 2 adds the partials in a fixed
-// order (no float atomics: results are bit-stable from run to run) and divides. Kernel 1 is bound by HBM: 512 rows per
-// workgroup keep four of them on every CU where 1024 left two at
-// 10006 rows, batch 4 (trace: 21.4 -> 16.2 us; 16384 rows, batch 4 24.4 -> 23.3). Kernel 2 is a
-// launch and two dependent reads: the partials by all lanes at once, then four positions per thread.
+// This kernel writes r_t and one partial sum per block of 512 rows; the scan's second pass, which runs after it, adds the
+// partials in a fixed order (no float atomics: results are bit-stable from run to run) and divides. Bound by HBM: 512 rows
+// per workgroup keep four of them on every CU where 1024 left two at
+// 10006 rows, batch 4 (trace: 21.4 -> 16.2 us; 16384 rows, batch 4 24.4 -> 23.3).
 // ---------------------------------------------------------------------------------------------
 struct VnormArgs {
   const char *v;
@@ -64,8 +71,6 @@ struct VnormArgs {
   int Hkv, T, n_blocks;
   float *ratio;  // [units][T]
   float *vsum;   // [units][n_blocks]
-  float *utility;  // [units][P] multiplied by the ratio in the scaling pass, or null
-  int P;
 };
 
 template <int DT, int DH>
@@ -126,41 +131,8 @@ __global__ void __launch_bounds__(256) vnorm_rows_kernel(VnormArgs a) {
   if (threadIdx.x == 0) a.vsum[(size_t)unit * a.n_blocks + blk] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
 }
 
-constexpr int kScaleThreads = 128;  // four positions each: one block of kVnormRows
-static_assert(kScaleThreads * 4 == kVnormRows, "a workgroup scales what one of kernel 1 wrote");
-
-__global__ void __launch_bounds__(kScaleThreads) vnorm_scale_kernel(VnormArgs a) {
-  typedef float f32x4_v __attribute__((ext_vector_type(4), aligned(4)));  // rows start at any multiple of four bytes
-  const int unit = blockIdx.y, t = blockIdx.x * kVnormRows + threadIdx.x * 4, lane = threadIdx.x & 63;
-  float *ratio = a.ratio + (size_t)unit * a.T + t;
-  float *util = a.utility ? a.utility + (size_t)unit * a.P + t : nullptr;
-  const bool four = t + 4 <= a.T, four_u = util && t + 4 <= a.P;
-  f32x4_v r = {0.0f, 0.0f, 0.0f, 0.0f}, u = r;
-  if (four) r = *reinterpret_cast<const f32x4_v *>(ratio);
-  if (four_u) u = *reinterpret_cast<const f32x4_v *>(util);
-  float total = 0.0f;
-  for (int i = lane; i < a.n_blocks; i += kWave) total += a.vsum[(size_t)unit * a.n_blocks + i];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
-  const float inv = 1.0f / (total / (float)a.T + kValueNormEps);
-  if (four) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] *= inv;
-    *reinterpret_cast<f32x4_v *>(ratio) = r;
-  } else {
-    for (int e = 0; e < 4 && t + e < a.T; ++e) ratio[e] = r[e] = ratio[e] * inv;
-  }
-  if (four_u) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) u[e] *= r[e];
-    *reinterpret_cast<f32x4_v *>(util) = u;
-  } else if (util) {
-    for (int e = 0; e < 4 && t + e < a.P; ++e) util[e] *= r[e];
-  }
-}
-
 hipError_t launch_value_norm(const ckv_params *p, const Shape &s, const Workspace &w, const void *v,
-                             float *ratio, char *ws, hipStream_t stream, float *utility_scaled) {
+                             float *ratio, char *ws, hipStream_t stream) {
   VnormArgs a;
   a.v = (const char *)v;
   a.vs_b = p->v_stride[0] * s.esize;
@@ -171,8 +143,6 @@ hipError_t launch_value_norm(const ckv_params *p, const Shape &s, const Workspac
   a.n_blocks = vnorm_blocks_per_unit(s);
   a.ratio = ratio;
   a.vsum = (float *)(ws + w.vsum_off);
-  a.utility = utility_scaled;
-  a.P = s.P;
   const dim3 grid(a.n_blocks, s.Bz * s.Hkv), block(256);
   if (p->dtype == CKV_BF16) {
     if (s.d == 128) hipLaunchKernelGGL((vnorm_rows_kernel<CKV_BF16, 128>), grid, block, 0, stream, a);
@@ -181,7 +151,6 @@ hipError_t launch_value_norm(const ckv_params *p, const Shape &s, const Workspac
     if (s.d == 128) hipLaunchKernelGGL((vnorm_rows_kernel<CKV_F32, 128>), grid, block, 0, stream, a);
     else hipLaunchKernelGGL((vnorm_rows_kernel<CKV_F32, 64>), grid, block, 0, stream, a);
   }
-  hipLaunchKernelGGL(vnorm_scale_kernel, grid, dim3(kScaleThreads), 0, stream, a);
   return hipGetLastError();
 }
 
