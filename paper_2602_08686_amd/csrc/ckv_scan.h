@@ -308,7 +308,7 @@ __device__ __forceinline__ float colsum_tile(const chunk_t (&qf)[NCH], const chu
 // 5 us). What it reads is asked for before anything else (load) and used while the first key tiles are on their way.
 typedef float f32x4_r __attribute__((ext_vector_type(4), aligned(4)));  // rows start at any multiple of four bytes
 struct RatioScale {
-  static constexpr int AHEAD = 2, STEP = kScoreWaves * kWave * 4;
+  static constexpr int AHEAD = 2, BATCH = 4, STEP = kScoreWaves * kWave * 4;
   bool on;  // the same for the whole workgroup
   int begin, end;
   float *row;
@@ -338,13 +338,20 @@ struct RatioScale {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
     const float inv = 1.0f / (total / (float)a.T + kValueNormEps);
-    for (int t0 = begin + threadIdx.x * 4, e = 0; t0 < end; t0 += STEP, ++e) {
-      if (t0 + 4 <= end) {
-        const f32x4_r x = e == 0 ? r[0] : e == 1 ? r[1] : *reinterpret_cast<const f32x4_r *>(row + t0);
-        *reinterpret_cast<f32x4_r *>(row + t0) = x * inv;
-      } else {
+    const auto scale = [&](int t0, const f32x4_r &x) {
+      if (t0 + 4 <= end) *reinterpret_cast<f32x4_r *>(row + t0) = x * inv;
+      else
         for (int t = t0; t < end; ++t) row[t] *= inv;
-      }
+    };
+    int t0 = begin + threadIdx.x * 4;
+#pragma unroll
+    for (int e = 0; e < AHEAD; ++e, t0 += STEP) scale(t0, r[e]);
+    for (; t0 < end; t0 += BATCH * STEP) {  // longer ranges: several loads in flight
+      f32x4_r x[BATCH];
+#pragma unroll
+      for (int e = 0; e < BATCH; ++e) x[e] = *reinterpret_cast<const f32x4_r *>(row + max(0, min(t0 + e * STEP, end - 4)));
+#pragma unroll
+      for (int e = 0; e < BATCH; ++e) scale(t0 + e * STEP, x[e]);
     }
   }
 };
@@ -1480,18 +1487,35 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArg
       __syncthreads();
       const int begin = bc.chunk * kScoreWaves * a.keys_per_wave, end = min(begin + kScoreWaves * a.keys_per_wave, a.P);
       const float *ratio = a.ratio + (size_t)bc.unit * a.T;
-      float *util = a.utility + (size_t)bc.unit * a.P;
-      for (int t0 = begin + threadIdx.x * 4; t0 < end; t0 += kScoreWaves * kWave * 4) {
-        float u[4], r[4];
+      typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+      constexpr int STEP = kScoreWaves * kWave * 4, BATCH = 4;  // groups of four keys, BATCH of them in flight
+      for (int t0 = begin + threadIdx.x * 4; t0 < end; t0 += BATCH * STEP) {
+        u32x4_t u[BATCH];
+        f32x4_r r[BATCH];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int t = min(t0 + e, end - 1);
-          u[e] = __hip_atomic_load(util + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          r[e] = ratio[t];
+        for (int e = 0; e < BATCH; ++e) {
+          const int t = t0 + e * STEP;
+          u[e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_u, t < end ? (uint32_t)((bc.g * a.P + t) * 4) : 0x80000000u, 0, kOutStoreAux);
+          r[e] = *reinterpret_cast<const f32x4_r *>(ratio + min(t, a.T - 4));
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (t0 + e < end) util[t0 + e] = u[e] * r[e];
+        for (int e = 0; e < BATCH; ++e) {
+          const int t = t0 + e * STEP;
+          if (t + 4 <= end && t + 4 <= a.T) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              const uint32_t bits = u[e][x];
+              u[e][x] = __float_as_uint(__uint_as_float(bits) * r[e][x]);
+            }
+            __builtin_amdgcn_raw_buffer_store_b128(u[e], rsrc_u, (uint32_t)((bc.g * a.P + t) * 4), 0, kOutStoreAux);
+          } else {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              const uint32_t bits = u[e][x];
+              if (t + x < end) a.utility[(size_t)bc.unit * a.P + t + x] = __uint_as_float(bits) * ratio[t + x];
+            }
+          }
+        }
       }
     }
   }
