@@ -121,7 +121,9 @@ int vnorm_blocks_per_unit(const Shape &s) {
 }
 
 // Four more waves per workgroup of the bf16 scan, where its own leave them registers (up to four query tiles per wave), one
-// workgroup takes all query tiles of its keys, and its range is whole blocks of the norms' sums.
+// workgroup takes all query tiles of its keys, and its range is whole blocks of the norms' sums. us, separate / beside the scan:
+// 10006 keys, batch 4, four calls 80.6 / 71.2; 4096 keys, 32/32 heads 51.9 / 40.6; 20011 keys, batch 2 86.2 / 73.9; 32768, batch 16,
+// where both reads are bound by HBM, 587 / 586.
 bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given) {
   return (p->flags & CKV_FLAG_VALUE_NORM) && !lse_given && p->dtype == CKV_BF16 && s.NQ <= kMaxQTilesNorms && s.n_groups == 1 &&
          kScoreWaves * s.keys_per_wave % kVnormRows == 0;
