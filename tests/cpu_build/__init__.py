@@ -1,4 +1,4 @@
-"""The library's selection and decode kernels compiled for the host CPU (see hip/hip_runtime.h), behind the same C ABI with
+"""The library's selection, gather and decode kernels compiled for the host CPU (see hip/hip_runtime.h), behind the same C ABI with
 host pointers. Array indexes are checked (a bad one traps), and memory that the kernels may not touch can be given without access."""
 import ctypes
 import mmap
@@ -21,7 +21,7 @@ def build(where) -> str:
     """Compile into the folder `where`; returns the library's path."""
     objs, procs = [], []
     csrc = ROOT / "paper_2602_08686_amd" / "csrc"
-    for src in (csrc / "ckv_api.hip", csrc / "ckv_select.hip", csrc / "ckv_decode.hip", HERE / "emulator.cpp"):
+    for src in (csrc / "ckv_api.hip", csrc / "ckv_select.hip", csrc / "ckv_decode.hip", csrc / "ckv_gather.hip", HERE / "emulator.cpp"):
         objs.append(str(pathlib.Path(where) / (src.name + ".o")))
         procs.append(subprocess.Popen([CXX, "-x", "c++", "-std=c++17", "-O1", "-fPIC", "-w", "-fsanitize=bounds", "-fsanitize-trap=bounds",
                                        f"-I{HERE}", f"-I{ROOT / 'include'}", f"-I{csrc}", "-c", str(src), "-o", objs[-1]]))

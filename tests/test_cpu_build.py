@@ -1,6 +1,7 @@
 """Kernels on the host CPU, where an access out of bounds ends a child process instead of a GPU: decode attention reads no
-row behind the count (the memory there has no access), and the selection stays inside its buffers whatever another stream
-writes over its input meanwhile, and with a workspace that was sized for another budget."""
+row behind the count (the memory there has no access), the selection stays inside its buffers whatever another stream
+writes over its input meanwhile, and with a workspace that was sized for another budget, and the gather copies every row of lists
+of any length, each once."""
 import ctypes
 import multiprocessing
 
@@ -154,3 +155,52 @@ def _select_with_the_workspace_of_another_budget(path, P, budgets):
 
 def test_one_workspace_serves_every_budget_of_its_shape(lib_path):
     in_child(_select_with_the_workspace_of_another_budget, lib_path, 40000, (20, 600, 5000))
+
+
+def _gather_lists(path, dtype, d, batch, kv, T, budget, cap, kind, shared):
+    lib = cpu.load(path)
+    rng = np.random.default_rng(T + d)
+    size, lists = d * (4 if dtype == "f32" else 2), (batch, 1 if shared else kv)
+    total = budget * lists[1]
+    count = {"even": np.full(lists, min(budget, cap)), "one": np.where(np.arange(lists[1]) == lists[1] - 1, cap, rng.integers(0, 3, lists)),
+             "first": np.where(np.arange(lists[1]) == 0, cap, np.zeros(lists)), "all_full": np.full(lists, cap), "beyond_cap": np.full(lists, cap + 9),
+             "skewed": np.minimum(cap, (rng.dirichlet(np.full(lists[1], 0.3), batch) * total).astype(int)), "empty": np.zeros(lists),
+             "negative": np.full(lists, -5)}[kind].astype(np.int32)
+    idx = rng.integers(0, T, lists + (cap,)).astype(np.int32)
+    idx[..., ::7] = np.where(rng.random(idx[..., ::7].shape) < 0.2, rng.choice([-1, T, 1 << 30], idx[..., ::7].shape), idx[..., ::7])
+    src = [rng.integers(0, 256, (batch, kv, T, size)).astype(np.uint8) for _ in range(2)]
+    mem, outs = [], []
+    for x in src:
+        m, o = cpu.fenced(x.size), cpu.fenced(batch * kv * cap * size)
+        m[:], o[:] = x.ravel(), 7
+        mem.append(m)
+        outs.append(o)
+    im = cpu.fenced(idx.nbytes)
+    im[:] = idx.view(np.uint8).ravel()
+    cm = cpu.fenced(count.nbytes)
+    cm[:] = count.view(np.uint8).ravel()
+    p = B.make_params(batch=batch, n_q_heads=kv, n_kv_heads=kv, head_dim=d, seq_len=T, window=1, dtype=dtype, pool=B.POOL_NONE,
+                      pool_kernel=1, budget=budget, cap=cap)
+    call = lib.ckv_compact_kv_shared if shared else lib.ckv_compact_kv
+    assert call(ctypes.byref(p), cpu.ptr(mem[0]), cpu.ptr(mem[1]), cpu.ptr(im), cpu.ptr(cm), cpu.ptr(outs[0]), cpu.ptr(outs[1]), None) == B.CKV_OK
+    for x, o in zip(src, outs):
+        got = o.reshape(batch, kv, cap, size)
+        for b in range(batch):
+            for g in range(kv):
+                lst = (b, 0) if shared else (b, g)
+                want = np.full((cap, size), 7, np.uint8)
+                n = max(0, min(int(count[lst]), cap))
+                ok = np.flatnonzero((idx[lst][:n] >= 0) & (idx[lst][:n] < T))
+                want[ok] = x[b, g][idx[lst][ok]]
+                np.testing.assert_array_equal(got[b, g], want)
+
+
+@pytest.mark.parametrize("kind", ["even", "one", "first", "all_full", "beyond_cap", "skewed", "empty", "negative"])
+@pytest.mark.parametrize("dtype,d,batch,kv,T,budget,shared", [
+    ("bf16", 128, 2, 8, 700, 40, False), ("bf16", 64, 1, 32, 900, 33, False), ("f32", 128, 1, 3, 2100, 9, False),
+    ("bf16", 64, 1, 70, 300, 5, False),     # more heads than lanes
+    ("f32", 64, 3, 4, 500, 20, True), ("bf16", 128, 1, 1, 400, 16, False),
+])
+def test_gather_copies_lists_of_any_length(lib_path, dtype, d, batch, kv, T, budget, shared, kind):
+    cap = T if kind in ("all_full", "beyond_cap") else min(T, budget * kv)
+    in_child(_gather_lists, lib_path, dtype, d, batch, kv, T, budget, cap, kind, shared)
