@@ -22,7 +22,7 @@ struct TablesArgs {
   float *utility;  // [Bz][Hkv][P]
   int Bz, Hq, Hkv, G, T, W, P;
   int pool, radius, kernel;
-  int n_tiles;
+  int n_tiles, budget_tile;
   BudgetArgs bud;
 };
 
@@ -131,6 +131,10 @@ __device__ __forceinline__ void pool_four(const TablesArgs &a, int unit, int t) 
     for (int e = 0; e < 4; ++e) rho[e] = short_end ? row[min(t + e, a.T - 1)] : r4[e];
   }
   float best[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  // The head's weight comes by a vector load behind those of the row: with a scalar one the compiler puts the four quotients one
+  // behind the other (32768 positions, batch 2, 28/4 heads 4.6 -> 4.9 us).
+  uint32_t no_offset = 0;
+  asm("" : "+v"(no_offset));
   for (int hg = 0; hg < a.G; ++hg) {
     const int h = g * a.G + hg;
     const float *row = a.scores + ((size_t)b * a.Hq + h) * a.T;
@@ -150,7 +154,7 @@ __device__ __forceinline__ void pool_four(const TablesArgs &a, int unit, int t) 
       const int at = t - 4 * SIDE + x;
       w[x] = at >= 0 && at < a.P ? w[x] : pad;
     }
-    const float wgt = a.w_row[h];
+    const float wgt = (a.w_row + h)[no_offset];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float c = w[4 * SIDE + e - R];
@@ -186,6 +190,7 @@ inline TablesArgs tables_args(const ckv_params *p, const Shape &s, const float *
   a.kernel = p->pool == CKV_POOL_NONE ? 1 : p->pool_kernel;
   a.radius = a.kernel / 2;
   a.n_tiles = (s.P + kTablesTile - 1) / kTablesTile;
+  a.budget_tile = head_share || s.P == 0 ? a.n_tiles : a.n_tiles - 1;
   return a;
 }
 

@@ -11,16 +11,24 @@
 
 namespace ckv {
 
+// Tau and the budgets of a batch element are for the last wave of a workgroup of its first head. Where budgets are shared out, a
+// longer chain than the pooling of four positions, that workgroup is one behind the tiles, in a column of its own; without shares it is
+// that of the last tile, once it has pooled: the column's workgroups, all but one per batch element idle, upset launches that fill
+// the CUs evenly (us, no shares, column / last tile: 32768 positions, batch 2, 28/4 heads 5.1 / 4.6; 40000, batch 4, 64/8
+// heads 12.9 / 11.2; with the budgets in front of the pooling, which then waits for its arguments: 32768 positions, batch 16
+// 1.10 of the time).
+__device__ __forceinline__ bool budgets_here(const TablesArgs &a, int tile, int unit) {
+  return tile == a.budget_tile && unit % a.Hkv == 0 && threadIdx.x >= kTablesThreads - kWave;
+}
+
 __global__ void __launch_bounds__(kTablesThreads) tables_kernel(TablesArgs a) {
   __shared__ float sm[kTablesTile + 2 * kMaxHalo];
   const int unit = blockIdx.y, tile = blockIdx.x;
   const int b = unit / a.Hkv, g = unit % a.Hkv;
   const int t0 = tile * kTablesTile;
 
-  if (tile == a.n_tiles) {  // the workgroups behind the tiles: tau and the budgets
-    if (g == 0 && threadIdx.x < kWave) write_tau_and_budgets(a.bud, b, threadIdx.x);
-    return;
-  }
+  if (budgets_here(a, tile, unit)) write_tau_and_budgets(a.bud, b, threadIdx.x & (kWave - 1));
+  if (tile == a.n_tiles) return;
 
   float best[kTablesPerThread];
   float rho[kTablesPerThread];
@@ -70,12 +78,8 @@ template <int POOL, int R>
 __global__ void __launch_bounds__(kTablesThreads) tables_window_kernel(TablesArgs a) {
   const int unit = blockIdx.y;
   const int t = (blockIdx.x * kTablesThreads + threadIdx.x) * 4;  // first of this thread's positions
-  if ((int)blockIdx.x == a.n_tiles) {  // the workgroups behind the tiles: tau and the budgets
-    if (unit % a.Hkv == 0 && threadIdx.x < kWave) write_tau_and_budgets(a.bud, unit / a.Hkv, threadIdx.x);
-    return;
-  }
-  if (t >= a.P) return;
-  pool_four<POOL, R>(a, unit, t);
+  if (t < a.P) pool_four<POOL, R>(a, unit, t);
+  if (budgets_here(a, blockIdx.x, unit)) write_tau_and_budgets(a.bud, unit / a.Hkv, threadIdx.x & (kWave - 1));
 }
 
 template <int POOL>
@@ -111,7 +115,7 @@ hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float 
                                float *utility, int32_t *budget, float *tau, hipStream_t stream) {
   const TablesArgs a = tables_args(p, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins,
                                    utility, budget, tau);
-  const dim3 grid(a.n_tiles + 1, s.Bz * s.Hkv), block(kTablesThreads);
+  const dim3 grid(a.budget_tile + 1, s.Bz * s.Hkv), block(kTablesThreads);
   bool done = false;
   if (s.P > 0 && s.T >= 4 && a.kernel <= kWindowTaps)
     done = p->pool == CKV_POOL_MAX ? launch_window_pool<CKV_POOL_MAX>(a, grid, stream)

@@ -1,5 +1,6 @@
 """The budget rule of the tables kernels, by one wave: fewer heads than lanes, exactly as many, more (several per lane), shares that
-make the heads drop a level at a time, all at once, or not at all. Integers: equal to the oracle's."""
+make the heads drop a level at a time, all at once, or not at all; the copies of the rule in the long-pool kernel and in the fused
+pass, and shares that are no numbers of tokens. Integers, and tau's bits: equal to the oracle's."""
 import numpy as np
 import pytest
 import torch
@@ -27,3 +28,44 @@ def test_budgets_of_any_number_of_heads(heads, kind):
     want = oracle.budgets(heads, T, W, budget, None if share is None else share.astype(np.float32))
     for b in range(2):
         np.testing.assert_array_equal(out[b].cpu().numpy(), want)
+
+
+def _shares(kind, heads, rng):
+    if kind == "none":
+        return None
+    share = {"even": np.full(heads, 1.0 / heads), "ties": rng.integers(1, 4, heads) / (1.5 * heads),
+             "over": rng.uniform(0.0, 6.0, heads) / heads}.get(kind, rng.uniform(0.0, 2.0, heads) / heads).astype(np.float32)
+    if kind in ("inf", "-inf", "nan", "-1"):
+        share[heads // 2] = float(kind)
+    return share
+
+
+@pytest.mark.parametrize("kind", ["none", "even", "ties", "over", "inf", "-inf", "nan", "-1"])
+@pytest.mark.parametrize("entry", ["short_pool", "long_pool", "fused", "no_prefix"])
+@pytest.mark.parametrize("heads", [1, 4, 63, 64, 65, 200])
+def test_every_copy_of_the_rule(entry, heads, kind):
+    T, W, budget, batch = (24, 24, 30, 3) if entry == "no_prefix" else (300, 9, 50, 3)
+    rng = np.random.default_rng(heads)
+    share = _shares(kind, heads, rng)
+    cap = min(T, budget * heads - (heads - 1) * W)
+    kernel = 21 if entry == "long_pool" else 7
+    g = torch.Generator(device="cuda")
+    g.manual_seed(heads)
+    q = torch.randn(batch, heads, W, 64, generator=g, device="cuda").bfloat16()
+    k = torch.randn(batch, heads, T, 64, generator=g, device="cuda").bfloat16()
+    p = B.params_for(q, k, None, pool=B.POOL_AVG, pool_kernel=kernel, budget=budget, cap=cap, n_layers=1)
+    new = lambda *s, dtype=torch.float32: torch.zeros(*s, dtype=dtype, device="cuda")  # noqa: E731
+    out, tau, utility = torch.full((batch, heads), -1, dtype=torch.int32, device="cuda"), new(batch) - 1, new(batch, heads, max(T - W, 1))
+    shares = None if share is None else torch.from_numpy(share)[None].cuda()
+    gate = torch.rand(1, 3, 5, generator=g, device="cuda")
+    bins = torch.tensor([[0, 4], [2, 0], [9, -3]], dtype=torch.int32, device="cuda")  # the last one outside the table: its nearest cell
+    w_head = new(1, heads) + 1
+    if entry == "fused":
+        ws = torch.empty(max(B.ckv_workspace_bytes(p), 256), dtype=torch.uint8, device="cuda")
+        B.ckv_window_utility(p, q, k, None, None, w_head, shares, gate, 3, 5, bins, new(batch, heads, T), None, utility, out, tau, ws)
+    else:
+        B.ckv_apply_tables(p, new(batch, heads, T), None, w_head, shares, gate, 3, 5, bins, utility, out, tau)
+    want = oracle.budgets(heads, T, W, budget, share)
+    for b in range(batch):
+        np.testing.assert_array_equal(out[b].cpu().numpy(), want)
+    assert torch.equal(tau, torch.stack([gate[0, 0, 4], gate[0, 2, 0], gate[0, 2, 0]]))
