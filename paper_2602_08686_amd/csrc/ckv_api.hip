@@ -121,12 +121,16 @@ int vnorm_blocks_per_unit(const Shape &s) {
 }
 
 // Four more waves per workgroup of the bf16 scan, where its own leave them registers (up to four query tiles per wave), one
-// workgroup takes all query tiles of its keys, and its range is whole blocks of the norms' sums. us, separate / beside the scan:
-// 10006 keys, batch 4, four calls 80.6 / 71.2; 4096 keys, 32/32 heads 51.9 / 40.6; 20011 keys, batch 2 86.2 / 73.9; 32768, batch 16,
-// where both reads are bound by HBM, 587 / 586.
+// workgroup takes all query tiles of its keys, its range is whole blocks of the norms' sums, and the launch has one workgroup per CU
+// at most. us, separate / beside the scan: 10006 keys, batch 4, four calls 80.6 / 71.2; 4096 keys, 32/32 heads 51.9 / 40.6;
+// 20011 keys, batch 2 86.2 / 73.9; 32768, batch 16, where both reads are bound by HBM, 587 / 586. Over 200 shapes of head sizes 64 and
+// 128, one to four tiles: 0.87 in the geometric mean, none slower by more than 1 %. More workgroups than CUs, where a workgroup of
+// eight waves keeps a second one of four (rows of 128 bytes) off its CU and the launch's end weighs twice: 0.90 to 1.32
+// of the time (us: 1024 workgroups, 2888 keys of 64 354 / 467, 4733 531 / 668; 384, 33000 keys of 64 379 / 422, 14629 of 128 467 / 518;
+// 1024 of 128, 1192 keys 391 / 360; no line by size or fill parts them).
 bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given) {
   return (p->flags & CKV_FLAG_VALUE_NORM) && !lse_given && p->dtype == CKV_BF16 && s.NQ <= kMaxQTilesNorms && s.n_groups == 1 &&
-         kScoreWaves * s.keys_per_wave % kVnormRows == 0;
+         kScoreWaves * s.keys_per_wave % kVnormRows == 0 && (int64_t)s.Bz * s.Hkv * s.n_chunks <= kComputeUnits;
 }
 
 void layout(const ckv_params *p, const Shape &s, Workspace *w) {

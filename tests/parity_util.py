@@ -2,6 +2,8 @@
 host copies of the same tensors, and the comparison rules."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -94,3 +96,12 @@ def assert_index_sets_match(gpu_idx, gpu_count, ref_idx, ref_count, ref_utility,
             assert np.array_equal(ig[cg - W:], ir[cr - W:]), "window tail differs"
             n_loose += 1
     return n_loose
+
+
+def norms_beside_the_scan(p, lse_given=False) -> bool:
+    """Whether the library takes a call's value norms beside its first pass over K (host code only: the rule itself is asked)."""
+    lib, shape = B.load(), ctypes.create_string_buffer(4096)
+    lib._ZN3ckv6deriveEPK10ckv_paramsPNS_5ShapeE(ctypes.byref(p), shape)
+    rule = lib._ZN3ckv13norms_in_scanEPK10ckv_paramsRKNS_5ShapeEb
+    rule.restype = ctypes.c_bool
+    return rule(ctypes.byref(p), shape, ctypes.c_bool(lse_given))
