@@ -1296,8 +1296,13 @@ __device__ __forceinline__ void finish_utility(const ScoreArgs &a, const BlockCo
   }
 }
 
+// Beyond six query tiles a wave has its SIMD to itself, whatever LDS would allow: the scheduler is told so, or it saves registers where rows
+// are short enough for two workgroups of LDS per CU, misses the half of them that a second wave would need, and puts the
+// exponentials one behind the other (us, 64 dimensions, windows of 100: 70827 keys, batch 8, 32/4 heads 557 -> 483, 4/2 heads 62.9 -> 54.4;
+// 28/4 heads, windows of 32: 40000 keys, batch 4 34.3 -> 31.8). In pass 1, where seven and eight tiles do leave room for a second wave,
+// it gains 5 % in launches of one workgroup per CU and loses 6 % in larger ones.
 template <int DT, int DH, int NQ, int WT, bool UTIL = false, bool GSUM = false>
-__global__ void __launch_bounds__(kScoreWaves *kWave) colsum_lds_kernel(ScoreArgs a) {
+__global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_waves_per_eu(1, NQ > 6 ? 1 : 8))) colsum_lds_kernel(ScoreArgs a) {
   static_assert(!(UTIL && GSUM) && (!GSUM || WT == 1), "one epilogue at a time; group sums take one tile per head");
   static_assert(NQ % WT == 0, "whole heads");
   using G = Geom<DT, DH>;
