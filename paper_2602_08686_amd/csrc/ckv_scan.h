@@ -619,6 +619,15 @@ __device__ __forceinline__ WaveRange wave_range(const ScoreArgs &a, const BlockC
 #ifndef CKV_PIN_Q_ABOVE
 #define CKV_PIN_Q_ABOVE 4
 #endif
+// The barriers of Staged::start, in order. A barrier waits for every wave of the workgroup, so waves that do other work beside the
+// scan's pass all of them as well: one more or one less is a line here, and theirs follow.
+enum StartBarrier { kQueriesLanded, kQueriesRead, kStartBarriers };
+template <int WHICH>
+__device__ __forceinline__ void start_barrier() {
+  static_assert(WHICH < kStartBarriers, "every barrier of the start has a name");
+  __syncthreads();
+}
+
 // LEAN: registers are short (another wave shares the SIMD), operand addresses are formed at each read.
 template <int DT, int DH, int NQ, bool LEAN = false>
 struct Staged {
@@ -688,7 +697,7 @@ struct Staged {
     } else {
       wait_vm<0>();
     }
-    __syncthreads();
+    start_barrier<kQueriesLanded>();
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int tile = bc.grp * NQ + i;
@@ -709,7 +718,7 @@ struct Staged {
         for (int c = 0; c < NCH; ++c) asm volatile("" : "+a"(qf[i][c]));
       }
     }
-    __syncthreads();  // the images that held Q are free for key tiles from here on
+    start_barrier<kQueriesRead>();  // the images that held Q are free for key tiles from here on
     if (wr.n_all > 0 && !tiny) {
 #pragma unroll
       for (int d = N_PRE; d < kRing - 1; ++d)
@@ -818,9 +827,8 @@ struct NormWaves {
       local += from_lane<7>(nrm);
       row += STEP;
     };
-    // the barriers of Staged::start, with the first loads on their way
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int i = 0; i < kStartBarriers; ++i) __builtin_amdgcn_s_barrier();  // with the first loads on their way
     for (int first = begin, i = 0; first < end;) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
