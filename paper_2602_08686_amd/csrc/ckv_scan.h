@@ -188,7 +188,7 @@ __device__ __forceinline__ void store_row_partials(const ScoreArgs &a, const Blo
 }
 
 // ---------------------------------------------------------------------------------------------
-// Plain kernels: every dtype / tile count. Two waves per SIMD, K double-buffered in registers; one wave where two or
+// Plain kernels (f32): every tile count. Two waves per SIMD, K double-buffered in registers; one wave where two or
 // more query tiles of 512-byte rows would not fit 256 registers beside it (they spilled 100 to 400).
 // ---------------------------------------------------------------------------------------------
 __host__ __device__ constexpr int plain_waves(int dt, int dh, int nq) { return dt == CKV_F32 && dh == 128 && nq >= 2 ? 1 : 2; }
@@ -1585,8 +1585,8 @@ static void launch_colsum(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 bl
         return;
       }
     }
-  }
-  hipLaunchKernelGGL((colsum_kernel<DT, DH, NQ>), grid, block, 0, stream, a);
+  } else
+    hipLaunchKernelGGL((colsum_kernel<DT, DH, NQ>), grid, block, 0, stream, a);
 }
 
 // Launches for the query-tile counts NQ_LO..NQ_HI (the instantiations are spread over several translation
