@@ -21,8 +21,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Wall", "-Wno-unused-command-line-argument"]
 
 
-# The scan kernels never produce or consume NaN (masked logits are -inf, never inf - inf), so the
-# compiler may skip the NaN-quieting moves it otherwise puts in front of every max.
+# The scan never produces or consumes NaN (masked logits are -inf, never inf - inf), so the compiler may skip the
+# NaN-quieting moves it otherwise puts in front of every max. What is no part of the scan but runs in its kernels may see
+# NaN: the shares and tau are read as bits; the value norms, their ratio and the utilities times it go through sums,
+# products, roots and quotients only, no minimum or maximum (tests/test_gpu_norms_in_scan.py: rows of V that are not finite).
 # MFMA results stay in ordinary vector registers (the vector ALU consumes every one of them); the
 # register allocator then parks the MFMA-only operands (Q, K) in accumulation registers instead.
 EXTRA_FLAGS = {src: ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"] for src in SCAN_SOURCES}

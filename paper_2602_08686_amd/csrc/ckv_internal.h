@@ -130,9 +130,6 @@ void layout(const ckv_params *p, const Shape &s, Workspace *w);
 int vnorm_blocks_per_unit(const Shape &s);
 
 // Kernel launchers (each returns hipGetLastError() after its launches).
-// lse_in == nullptr: pass 1 first, LSE into lse_out (or the workspace). scores == nullptr: pass 1 only.
-// ratio: if given, pass 2 makes it of the value norms that launch_value_norm, or with norms_in_scan() and v pass 1, left there
-// (and, in the fused form, multiplies the utilities by it).
 // tau and the per-head budgets of a call (paper Sec. 4.3), written beside the utilities.
 struct BudgetArgs {
   const float *share_row;   // head_share + layer*Hkv or null
@@ -156,6 +153,9 @@ struct UtilityFusion {
   float inv_kernel, inv_kernel_rest;  // 1 / kernel: the largest float that is not above it, and what that leaves
   BudgetArgs bud;
 };
+// lse_in == nullptr: pass 1 first, LSE into lse_out (or the workspace). scores == nullptr: pass 1 only.
+// ratio: if given, pass 2 makes it of the value norms that launch_value_norm, or with norms_in_scan() and v pass 1, left there
+// (and, in the fused form, multiplies the utilities by it).
 hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Workspace &w, const void *q,
                                 const void *k, const float *lse_in, float *lse_out, float *scores,
                                 char *ws, hipStream_t stream, const UtilityFusion *fuse = nullptr,
