@@ -145,7 +145,7 @@ __device__ __forceinline__ void load_q_tiles(const ScoreArgs &a, const BlockCoor
 // Pass 1, vector part: online (max, sum) update of this lane's query row with the 16 logits it holds
 // of one tile. The maximum is taken on the raw dot products (the scale is positive); scale and
 // subtraction are one FMA per element.
-template <bool EDGE>
+template <bool EDGE, bool PLAIN = false>
 __device__ __forceinline__ void rowstats_update(const f32x16 &acc, float c2, int t0, int hh, int limit, float &rm, float &rl) {
   float v[16];
 #pragma unroll
@@ -153,7 +153,7 @@ __device__ __forceinline__ void rowstats_update(const f32x16 &acc, float c2, int
   if (EDGE) {  // keys beyond `limit` do not count
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-      if (acc_row(r, hh) > limit - t0) v[r] = -INFINITY;
+      if (PLAIN ? t0 + acc_row(r, hh) > limit : acc_row(r, hh) > limit - t0) v[r] = -INFINITY;
   }
   float t[4];
 #pragma unroll
@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) r
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         mma_chain<DT, NCH>(acc, kf, qf[i]);  // rows: keys, cols: query rows
-        rowstats_update<true>(acc, a.c2, t0, hh, limit[i], rm[i], rl[i]);
+        rowstats_update<true, true>(acc, a.c2, t0, hh, limit[i], rm[i], rl[i]);
       }
     } else {
 #pragma unroll
@@ -356,7 +356,7 @@ struct RatioScale {
   }
 };
 
-template <int DT, int DH, int NQ>
+template <int DT, int DH, int NQ, bool RATIO>
 __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) colsum_kernel(ScoreArgs a) {
   constexpr int NCH = DH * (DT == CKV_BF16 ? 2 : 4) / 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 31, hh = lane >> 5;
@@ -380,9 +380,9 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) c
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
   RatioScale rs;
-  rs.load(a, bc);
+  if constexpr (RATIO) rs.load(a, bc);
   load_q_tiles<NCH, NQ>(a, bc, m, hh, qf, jrow);
-  rs.store(a, bc);
+  if constexpr (RATIO) rs.store(a, bc);
   __syncthreads();
 
   const char *kbase = a.k + bc.b * a.ks_b + bc.g * a.ks_h;
@@ -1585,8 +1585,11 @@ static void launch_colsum(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 bl
         return;
       }
     }
-  } else
-    hipLaunchKernelGGL((colsum_kernel<DT, DH, NQ>), grid, block, 0, stream, a);
+  } else if (a.ratio) {
+    hipLaunchKernelGGL((colsum_kernel<DT, DH, NQ, true>), grid, block, 0, stream, a);
+  } else {
+    hipLaunchKernelGGL((colsum_kernel<DT, DH, NQ, false>), grid, block, 0, stream, a);
+  }
 }
 
 // Launches for the query-tile counts NQ_LO..NQ_HI (the instantiations are spread over several translation
