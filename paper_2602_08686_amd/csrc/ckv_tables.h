@@ -22,7 +22,8 @@ struct TablesArgs {
   float *utility;  // [Bz][Hkv][P]
   int Bz, Hq, Hkv, G, T, W, P;
   int pool, radius, kernel;
-  int n_tiles, budget_tile;
+  int n_tiles;
+  int budget_rows;  // rows of workgroups in front of the tiles' that write tau and the budgets
   BudgetArgs bud;
 };
 
@@ -189,8 +190,8 @@ inline TablesArgs tables_args(const ckv_params *p, const Shape &s, const float *
   a.pool = p->pool;
   a.kernel = p->pool == CKV_POOL_NONE ? 1 : p->pool_kernel;
   a.radius = a.kernel / 2;
-  a.n_tiles = (s.P + kTablesTile - 1) / kTablesTile;
-  a.budget_tile = head_share || s.P == 0 ? a.n_tiles : a.n_tiles - 1;
+  a.n_tiles = s.P > 0 ? (s.P + kTablesTile - 1) / kTablesTile : 1;
+  a.budget_rows = (s.Bz + a.n_tiles - 1) / a.n_tiles;
   return a;
 }
 

@@ -11,24 +11,24 @@
 
 namespace ckv {
 
-// Tau and the budgets of a batch element are for the last wave of a workgroup of its first head. Where budgets are shared out, a
-// longer chain than the pooling of four positions, that workgroup is one behind the tiles, in a column of its own; without shares it is
-// that of the last tile, once it has pooled: the column's workgroups, all but one per batch element idle, upset launches that fill
-// the CUs evenly (us, no shares, column / last tile: 32768 positions, batch 2, 28/4 heads 5.1 / 4.6; 40000, batch 4, 64/8
-// heads 12.9 / 11.2; with the budgets in front of the pooling, which then waits for its arguments: 32768 positions, batch 16
-// 1.10 of the time).
-__device__ __forceinline__ bool budgets_here(const TablesArgs &a, int tile, int unit) {
-  return tile == a.budget_tile && unit % a.Hkv == 0 && threadIdx.x >= kTablesThreads - kWave;
+// Tau and the budgets of a batch element are for one wave, alone in its workgroup: with shares a longer chain than the pooling of four
+// positions. These workgroups fill the launch's first rows, which they share with up to n_tiles - 1 idle ones. As a column behind the
+// tiles they and the idle ones among them put more tiles on some XCDs than on others, and launches that fill the CUs evenly waited
+// for those (us, column / rows in front: 5960 positions, batch 31, 8/4 heads 4.5 / 4.2; 6705, batch 35, 28/4 9.5 / 8.1; 20989, batch 3,
+// 32/4, 15 taps 6.4 / 5.4; 23011, batch 11, 32/8, 41 taps 32.5 / 28.7; without shares 32768, batch 2, 28/4 5.0 / 4.3, and 4.4
+// by the last tile's workgroup behind its pooling).
+__device__ __forceinline__ void budgets_in_front(const TablesArgs &a, int unit) {
+  const int b = (int)blockIdx.y * a.n_tiles + (int)blockIdx.x;
+  if (threadIdx.x >= kTablesThreads - kWave && unit < 0 && b < a.Bz) write_tau_and_budgets(a.bud, b, threadIdx.x & (kWave - 1));
 }
 
 __global__ void __launch_bounds__(kTablesThreads) tables_kernel(TablesArgs a) {
   __shared__ float sm[kTablesTile + 2 * kMaxHalo];
-  const int unit = blockIdx.y, tile = blockIdx.x;
+  const int unit = (int)blockIdx.y - a.budget_rows, tile = blockIdx.x;
+  budgets_in_front(a, unit);
+  if (unit < 0) return;
   const int b = unit / a.Hkv, g = unit % a.Hkv;
   const int t0 = tile * kTablesTile;
-
-  if (budgets_here(a, tile, unit)) write_tau_and_budgets(a.bud, b, threadIdx.x & (kWave - 1));
-  if (tile == a.n_tiles) return;
 
   float best[kTablesPerThread];
   float rho[kTablesPerThread];
@@ -76,10 +76,10 @@ __global__ void __launch_bounds__(kTablesThreads) tables_kernel(TablesArgs a) {
 
 template <int POOL, int R>
 __global__ void __launch_bounds__(kTablesThreads) tables_window_kernel(TablesArgs a) {
-  const int unit = blockIdx.y;
+  const int unit = (int)blockIdx.y - a.budget_rows;
   const int t = (blockIdx.x * kTablesThreads + threadIdx.x) * 4;  // first of this thread's positions
-  if (t < a.P) pool_four<POOL, R>(a, unit, t);
-  if (budgets_here(a, blockIdx.x, unit)) write_tau_and_budgets(a.bud, unit / a.Hkv, threadIdx.x & (kWave - 1));
+  if (unit >= 0 && t < a.P) pool_four<POOL, R>(a, unit, t);
+  budgets_in_front(a, unit);  // behind the pooling's code: in front of it 1 to 3 % slower
 }
 
 template <int POOL>
@@ -92,6 +92,15 @@ static bool launch_window_pool(const TablesArgs &a, dim3 grid, hipStream_t strea
   }
 #undef CKV_WINDOW
   return false;
+}
+
+// `rows` rows of workgroups, the first a.budget_rows of which write tau and the budgets.
+static void launch_rows(const TablesArgs &a, int rows, hipStream_t stream) {
+  const dim3 grid(a.n_tiles, rows);
+  bool done = false;
+  if (a.T >= 4 && a.kernel <= kWindowTaps)
+    done = a.pool == CKV_POOL_MAX ? launch_window_pool<CKV_POOL_MAX>(a, grid, stream) : launch_window_pool<CKV_POOL_AVG>(a, grid, stream);
+  if (!done) hipLaunchKernelGGL(tables_kernel, grid, dim3(kTablesThreads), 0, stream, a);
 }
 
 BudgetArgs budget_args(const ckv_params *p, const Shape &s, const float *head_share, const float *t_gate, int n_ent,
@@ -113,14 +122,16 @@ hipError_t launch_apply_tables(const ckv_params *p, const Shape &s, const float 
                                const float *vnorm_ratio, const float *w_head, const float *head_share,
                                const float *t_gate, int n_ent, int n_ppl, const int32_t *risk_bins,
                                float *utility, int32_t *budget, float *tau, hipStream_t stream) {
-  const TablesArgs a = tables_args(p, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins,
-                                   utility, budget, tau);
-  const dim3 grid(a.budget_tile + 1, s.Bz * s.Hkv), block(kTablesThreads);
-  bool done = false;
-  if (s.P > 0 && s.T >= 4 && a.kernel <= kWindowTaps)
-    done = p->pool == CKV_POOL_MAX ? launch_window_pool<CKV_POOL_MAX>(a, grid, stream)
-                                   : launch_window_pool<CKV_POOL_AVG>(a, grid, stream);
-  if (!done) hipLaunchKernelGGL(tables_kernel, grid, block, 0, stream, a);
+  TablesArgs a = tables_args(p, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins,
+                             utility, budget, tau);
+  const int units = s.P > 0 ? s.Bz * s.Hkv : 0;
+  if (a.budget_rows + units <= 65535) {  // the grid's second dimension, and what units are limited to
+    launch_rows(a, a.budget_rows + units, stream);
+  } else {
+    launch_rows(a, a.budget_rows, stream);
+    a.budget_rows = 0;
+    launch_rows(a, units, stream);
+  }
   return hipGetLastError();
 }
 

@@ -1,6 +1,7 @@
 """The budget rule of the tables kernels, by one wave: fewer heads than lanes, exactly as many, more (several per lane), shares that
 make the heads drop a level at a time, all at once, or not at all; the copies of the rule in the long-pool kernel and in the fused
-pass, and shares that are no numbers of tokens. Integers, and tau's bits: equal to the oracle's."""
+pass, and shares that are no numbers of tokens; batches that fill several rows of workgroups, or more than a launch's second dimension
+holds beside the tiles. Integers, and tau's bits: equal to the oracle's."""
 import numpy as np
 import pytest
 import torch
@@ -69,3 +70,32 @@ def test_every_copy_of_the_rule(entry, heads, kind):
     for b in range(batch):
         np.testing.assert_array_equal(out[b].cpu().numpy(), want)
     assert torch.equal(tau, torch.stack([gate[0, 0, 4], gate[0, 2, 0], gate[0, 2, 0]]))
+
+
+@pytest.mark.parametrize("batch,heads,T,kernel", [
+    (3, 1, 3100, 1), (4, 2, 3100, 7), (7, 2, 3100, 21), (300, 1, 1100, 1),  # a row of four or two tiles: one row in front, more, with a rest
+    (32767, 1, 5, 1), (32768, 1, 5, 1), (65535, 1, 2, 1), (257, 255, 8, 3),  # one launch and two
+])
+@pytest.mark.parametrize("shares", [False, True])
+def test_rows_in_front_of_the_tiles(batch, heads, T, kernel, shares):
+    W, budget = 1, 2
+    cap = min(T, budget * heads - (heads - 1) * W)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(batch)
+    p = B.make_params(batch=batch, n_q_heads=heads, n_kv_heads=heads, head_dim=64, seq_len=T, window=W, dtype="bf16", pool=B.POOL_MAX,
+                      pool_kernel=kernel, budget=budget, cap=cap)
+    scores = torch.rand(batch, heads, T, generator=g, device="cuda")
+    share = np.random.default_rng(heads).uniform(0.0, 3.0, heads).astype(np.float32) / heads if shares else None
+    gate = torch.rand(1, 7, 11, generator=g, device="cuda")
+    bins = torch.stack([torch.randint(0, n, (batch,), generator=g, device="cuda", dtype=torch.int32) for n in (7, 11)], 1)
+    utility = torch.full((batch, heads, T - W), float("nan"), device="cuda")
+    out, tau = torch.full((batch, heads), -1, dtype=torch.int32, device="cuda"), torch.full((batch,), -1.0, device="cuda")
+    w_head = torch.ones(1, heads, device="cuda")
+    B.ckv_apply_tables(p, scores, None, w_head, None if share is None else torch.from_numpy(share)[None].cuda(), gate, 7, 11, bins, utility,
+                       out, tau)
+    want = torch.from_numpy(oracle.budgets(heads, T, W, budget, share)).cuda()
+    assert (out == want).all() and torch.equal(tau, gate[0, bins[:, 0].long(), bins[:, 1].long()])
+    pooled = scores[..., : T - W]  # maxima: the same bits
+    if kernel > 1:
+        pooled = torch.nn.functional.max_pool1d(pooled, kernel, 1, kernel // 2)
+    assert torch.equal(utility, pooled)
