@@ -297,9 +297,9 @@ extern "C" ckv_status ckv_apply_tables(const ckv_params *params, const float *sc
 // unfused steps through the scratch buffer): the pipelined bf16 kernels with at most two 32-row tiles per
 // head and all query tiles of a group in one wave (at most eight), pooling kernels of at most 7 taps. Rows may start
 // at any multiple of four bytes: with lengths that are no multiple of four the stores cover five lines where they
-// would four (us, both passes and tables, fused / unfused: 32767 positions, batch 16: 383 / 392; 32768: 356 / 397; 20011,
-// batch 2: 45.3 / 45.4). With the value-norm flag the ratio, which is common to
-// a group's heads and non-negative, multiplies the group maximum afterwards (in the value-norm scaling pass).
+// would four (us, both passes and tables, fused / unfused: 32767 positions, batch 16: 374 / 398; 32768: 375 / 404; 20011,
+// batch 2: 44.2 / 45.7; 4096, 32/32 heads 23.3 / 25.0). With the value-norm flag the ratio, which is common to
+// a group's heads and non-negative, multiplies the group maximum afterwards (at the end of the same pass).
 static bool utility_fast_path(const ckv_params *p, const Shape &s) {
   const int kernel = p->pool == CKV_POOL_NONE ? 1 : p->pool_kernel;
   return p->dtype == CKV_BF16 && s.n_groups == 1 && s.WT <= 2 && kernel / 2 <= kUtilMaxRadius && s.P > 0 && s.T >= 4 &&
