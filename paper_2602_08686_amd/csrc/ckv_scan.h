@@ -459,9 +459,6 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) c
 // -LSE / scale split into three bf16 terms (exact to 2^-24) and whose K-side operand is ones.
 // Tiles that touch the window or the end of the keys are handled after the pipeline, masked.
 // ---------------------------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) const void glb_void_t;
-
 // Cache policy of the pipeline's output stores (column sums, group sums, utilities): sc1. The outputs
 // are consumed by a later kernel, never by this one; with the default policy the stores, although a
 // few percent of the pass's bytes, cost it 6-8 us more (measured on the 32k / batch-16 shape).
@@ -531,6 +528,38 @@ __device__ __forceinline__ void dma_quad(const char *sbase, uint32_t lds, uint32
       : "memory");
 }
 
+// The same with an address of its own for every lane: lane l of instruction j moves 16 bytes from p_j to lds + 1024 * j + 16 * l. In asm like
+// the others, since the compiler waits for every load into LDS that it knows of before the next barrier, and by then the first
+// key tiles are among them (a barrier behind vmcnt(0) where Q alone had to be there): all waits for these loads are wait_vm()'s. us per
+// layer, known to the compiler / not: 4096 keys, 32/32 heads 31.1 / 30.0, 20011, batch 2 56.4 / 55.0, 32768, batch 16 394.3 / 392.7.
+__device__ __forceinline__ void dma_quad_rows(uint32_t lds, const char *p0, const char *p1, const char *p2, const char *p3) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off\n\t"
+      "global_load_lds_dwordx4 %2, off offset:1024\n\t"
+      "global_load_lds_dwordx4 %3, off offset:2048\n\t"
+      "global_load_lds_dwordx4 %4, off offset:3072"
+      :
+      : "s"(lds), "v"(p0), "v"(p1 - 1024), "v"(p2 - 2048), "v"(p3 - 3072)
+      : "memory");
+}
+
+// A tile of 32 rows whose row r starts at row_of(r), into the image at LDS address lds.
+template <class G, class Row>
+__device__ __forceinline__ void dma_rows(Row row_of, int lane, uint32_t lds) {
+#pragma unroll
+  for (int q = 0; q < G::NDMA; q += 4) {
+    const char *src[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int r, kappa;
+      dma_source<G>(q + i, lane, r, kappa);
+      src[i] = row_of(r) + kappa * 16;
+    }
+    dma_quad_rows(lds + q * 1024, src[0], src[1], src[2], src[3]);
+  }
+}
+
 // One whole tile whose first row starts at tile_base. voff[i] already holds the lane's source offset in the first quad
 // minus the immediate of its instruction plus kDmaBias, so the scalar base is tile_base - kDmaBias; the second quad reads the
 // same chunks (the swizzle repeats every sixteen rows) quad_stride = 16 rows further on.
@@ -541,19 +570,6 @@ __device__ __forceinline__ void dma_tile(const char *tile_base, const uint32_t (
 #pragma unroll
   for (int q = 0; q < G::NDMA / 4; ++q)
     dma_quad(tile_base - kDmaBias + q * quad_stride, lds_image + q * 4096, voff[0], voff[1], voff[2], voff[3]);
-}
-
-// The only tile of a sequence shorter than a tile: row indices are clamped (the logits of the clamped rows are masked by
-// the caller).
-template <class G>
-__device__ __forceinline__ void dma_tile_clamped(const char *kbase, int64_t ks_t, int T, int lane, char *image) {
-#pragma unroll
-  for (int i = 0; i < G::NDMA; ++i) {
-    int r, kappa;
-    dma_source<G>(i, lane, r, kappa);
-    const char *src = kbase + (int64_t)min(r, T - 1) * ks_t + kappa * 16;
-    __builtin_amdgcn_global_load_lds((glb_void_t *)src, (lds_void_t *)(uintptr_t)(image + i * 1024), 16, 0, 0);
-  }
 }
 
 template <class G>
@@ -672,14 +688,7 @@ struct Staged {
         const int tile = min(bc.grp * NQ + wr.wave + qi * kScoreWaves, a.n_tiles - 1);
         const char *qhead = a.q + bc.b * a.qs_b + (bc.g * a.G + tile / a.WT) * a.qs_h;
         const int j0 = (tile % a.WT) * kTile;
-#pragma unroll
-        for (int i = 0; i < G::NDMA; ++i) {
-          int r, kappa;
-          dma_source<G>(i, lane, r, kappa);
-          const char *src = qhead + (int64_t)min(j0 + r, a.W - 1) * a.qs_w + kappa * 16;
-          __builtin_amdgcn_global_load_lds((glb_void_t *)src,
-                                           (lds_void_t *)(uintptr_t)(ring[wr.wave][kRing - 1 - qi] + i * 1024), 16, 0, 0);
-        }
+        dma_rows<G>([&](int r) { return qhead + (int64_t)min(j0 + r, a.W - 1) * a.qs_w; }, lane, lds_ring + (kRing - 1 - qi) * G::TILE);
       }
     }
     constexpr int N_PRE = kRing - QI;  // key tiles whose images are free while Q passes through
@@ -689,9 +698,10 @@ struct Staged {
 #pragma unroll
         for (int d = 0; d < N_PRE; ++d)
           dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, tile_stride / 2, lds_ring + d * G::TILE);
-      } else {
+      } else {  // the only tile of a sequence shorter than one: rows are clamped (whoever uses them masks their logits)
 #pragma unroll
-        for (int d = 0; d < N_PRE; ++d) dma_tile_clamped<G>(kbase, a.ks_t, a.T, lane, ring[wr.wave][d]);
+        for (int d = 0; d < N_PRE; ++d)
+          dma_rows<G>([&](int r) { return kbase + (int64_t)min(r, a.T - 1) * a.ks_t; }, lane, lds_ring + d * G::TILE);
       }
       wait_vm<N_PRE * G::NDMA>();  // Q has landed, the key tiles may still be on their way
     } else {
@@ -699,12 +709,13 @@ struct Staged {
     }
     start_barrier<kQueriesLanded>();
 #pragma unroll
+    for (int i = 0; i < NQ; ++i) read_image<G>(qf[i], ring[i % kScoreWaves][kRing - 1 - i / kScoreWaves], roff);
+#pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int tile = bc.grp * NQ + i;
       const int j = (tile % a.WT) * kTile + m;
       const bool valid = tile < a.n_tiles && j < a.W;
       jrow[i] = valid ? j : -1;
-      read_image<G>(qf[i], ring[i % kScoreWaves][kRing - 1 - i / kScoreWaves], roff);
       if (!valid) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) qf[i][c] = chunk_t{0u, 0u, 0u, 0u};
@@ -1237,14 +1248,14 @@ __device__ __forceinline__ void flush_utility(const ScoreArgs &a, const BlockCoo
 constexpr int kHaloKeys = 4;
 static_assert(kHaloKeys >= kUtilMaxRadius && 2 * kHaloKeys == kUtilHead, "one row of eight sums");
 template <class G>
-__device__ __forceinline__ void dma_halo(const char *kbase, int64_t ks_t, int begin, int end, int T, int lane, char *image) {
+__device__ __forceinline__ void dma_halo(const char *kbase, int64_t ks_t, int begin, int end, int T, int lane, uint32_t lds) {
 #pragma unroll
   for (int i = 0; i < 2 * kHaloKeys * G::ROW / 1024; ++i) {
     int r, kappa;
     dma_source<G>(i, lane, r, kappa);
     const int t = r < kHaloKeys ? max(begin - kHaloKeys + r, 0) : min(end + r - kHaloKeys, T - 1);
-    __builtin_amdgcn_global_load_lds((glb_void_t *)(kbase + (int64_t)min(t, T - 1) * ks_t + kappa * 16),
-                                     (lds_void_t *)(uintptr_t)(image + i * 1024), 16, 0, 0);
+    const char *src = kbase + (int64_t)min(t, T - 1) * ks_t + kappa * 16;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds + i * 1024), "v"(src) : "memory");
   }
 }
 
@@ -1330,7 +1341,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
     const int begin = bc.chunk * kScoreWaves * a.keys_per_wave;
     if (wr.wave == 0)
       dma_halo<G>(a.k + bc.b * a.ks_b + bc.g * a.ks_h, a.ks_t, begin, begin + kScoreWaves * a.keys_per_wave, a.T, lane,
-                  s_halo_keys);
+                  (uint32_t)(uintptr_t)s_halo_keys);
   }
   RatioScale rs;
   rs.load(a, bc);
