@@ -241,8 +241,8 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) r
   store_row_partials<NQ>(a, bc, wave, m, hh, rm, rl);
 }
 
-// LSE_j = ln2 * (M + log2 sum_c l_c 2^(m_c - M)) from the n_chunks partials of one row (`stride` apart), in chunk order,
-// eight loads in flight.
+// LSE_j = ln2 * (M + log2 sum_c l_c 2^(m_c - M)) from the n_chunks partials of one row (`stride` apart), in chunk order, eight
+// loads in flight.
 __device__ __forceinline__ float merge_row_partials(const float2 *p, int n_chunks, int stride) {
   constexpr int BATCH = 8;
   float M = -1e30f, L = 0.0f;
@@ -544,6 +544,11 @@ __device__ __forceinline__ void dma_quad_rows(uint32_t lds, const char *p0, cons
       : "memory");
 }
 
+// 16 bytes per lane from p to lds + 16 * lane.
+__device__ __forceinline__ void dma_one(uint32_t lds, const char *p) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(p) : "memory");
+}
+
 // A tile of 32 rows whose row r starts at row_of(r), into the image at LDS address lds.
 template <class G, class Row>
 __device__ __forceinline__ void dma_rows(Row row_of, int lane, uint32_t lds) {
@@ -664,8 +669,11 @@ struct Staged {
   // three key tiles are in flight, in order. jrow[i] = window row of tile i, row m, or -1 on padding.
   static constexpr int QI = (NQ + kScoreWaves - 1) / kScoreWaves;  // ring images per wave that first hold Q
   static_assert(QI >= 1 && QI <= kRing - 2, "query tiles pass through the ring's last images");
-  __device__ __forceinline__ void start(const ScoreArgs &a, const BlockCoord &bc, const WaveRange &wr, Ring &ring,
-                                        int lane, int m, int hh, chunk_t (&qf)[NQ][NCH], int (&jrow)[NQ]) {
+  // `first` queues loads in front of all others, which have landed as Q has; `between` runs when every wave's have, with the query
+  // tiles still in their images (image_of_tile), in front of the start's last barrier.
+  template <class First, class Between>
+  __device__ __forceinline__ void start(const ScoreArgs &a, const BlockCoord &bc, const WaveRange &wr, Ring &ring, int lane, int m,
+                                        int hh, chunk_t (&qf)[NQ][NCH], int (&jrow)[NQ], First first, Between between) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       int r, kappa;
@@ -682,6 +690,7 @@ struct Staged {
     lds_ring = (uint32_t)(uintptr_t)&ring[wr.wave][0][0];
     if (LEAN) rbase = lds_ring + image_offset<G>(m, NCH * hh);
 
+    first();
 #pragma unroll
     for (int qi = 0; qi < QI; ++qi) {
       if (wr.wave + qi * kScoreWaves < NQ) {
@@ -709,7 +718,7 @@ struct Staged {
     }
     start_barrier<kQueriesLanded>();
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) read_image<G>(qf[i], ring[i % kScoreWaves][kRing - 1 - i / kScoreWaves], roff);
+    for (int i = 0; i < NQ; ++i) read_image<G>(qf[i], image_of_tile(ring, i), roff);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int tile = bc.grp * NQ + i;
@@ -729,12 +738,17 @@ struct Staged {
         for (int c = 0; c < NCH; ++c) asm volatile("" : "+a"(qf[i][c]));
       }
     }
+    between();
     start_barrier<kQueriesRead>();  // the images that held Q are free for key tiles from here on
     if (wr.n_all > 0 && !tiny) {
 #pragma unroll
       for (int d = N_PRE; d < kRing - 1; ++d)
         dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, tile_stride / 2, lds_ring + d * G::TILE);
     }
+  }
+
+  static __device__ __forceinline__ const char *image_of_tile(Ring &ring, int i) {
+    return ring[i % kScoreWaves][kRing - 1 - i / kScoreWaves];
   }
 
   // Load of the tile three ahead of the one at kcur (tile index t + 3) into ring image `slot`; past
@@ -894,7 +908,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave * (NORMS ? 2 : 1)) rowstats
   Staged<DT, DH, NQ, LEAN> st;
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
-  st.start(a, bc, wr, ring, lane, m, hh, qf, jrow);
+  st.start(a, bc, wr, ring, lane, m, hh, qf, jrow, [] {}, [] {});
   float rm[NQ], rl[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
@@ -956,19 +970,41 @@ __global__ void __launch_bounds__(kScoreWaves *kWave * (NORMS ? 2 : 1)) rowstats
   wait_vm<0>();  // the loads beyond the last tile write LDS: not after the wave
 }
 
-// The extra contraction step of pass 2 that adds bias_j = -LSE_j / scale to every logit of query row
-// j. bf16: the bias as hi + mid + lo bf16 terms in the first three slots of the Q-side operand of the
-// lanes with hh = 0, ones in the same slots on the K side. f32: one 32x32x2 step with (bias, 1).
+// How pass 2 takes a row's normaliser off its logits. Up to four query tiles per wave the registers hold it for the sixteen rows
+// of a lane's accumulator, and the scale's multiplication takes it along: an MFMA less per pair, and as
+// exact (one rounding of the exponent). us per layer, as the extra step below / so: 20011 keys, batch 2 56.5 / 56.0, 32768, batch 16
+// 399.4 / 394.7, 16384 with given normalisers 44.9 / 44.4.
+// Beyond that it is an extra step of the contraction, which adds bias_j = -LSE_j / scale to every logit of query row j: the bias as
+// hi + mid + lo bf16 terms in the first three slots of the Q-side operand of the lanes with hh = 0, ones in the same slots on the
+// K side. Either way padding rows (q = 0) get exp2(-1000) = 0 as weight.
+constexpr int kShiftInRegisters = 4;
+constexpr float kNoWeight = -1000.0f;
 __device__ __forceinline__ uint32_t bf16_bits(float x) {  // round to nearest even; x is finite
   const uint32_t u = __float_as_uint(x);
   return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
-template <int DT>
-struct Bias;
+template <bool IN_REGISTERS>
+struct RowShift;
 template <>
-struct Bias<CKV_BF16> {
+struct RowShift<true> {
+  float shift[16];
+  // shifts: of the tile's rows, in the log2 domain
+  __device__ __forceinline__ void set(const float *shifts, float, int, int hh) {
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(shifts + 8 * q4 + 4 * hh);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) shift[4 * q4 + e] = v[e];
+    }
+  }
+  __device__ __forceinline__ void add(f32x16 &, int) const {}
+  __device__ __forceinline__ float exponent(float dot, int r, float c2) const { return fmaf(dot, c2, shift[r]); }
+};
+template <>
+struct RowShift<false> {
   chunk_t q;
-  __device__ __forceinline__ void set(float bias, int hh) {
+  __device__ __forceinline__ void set(const float *shifts, float c2, int m, int hh) {
+    const float bias = shifts[m] / c2;
     const uint32_t hi = bf16_bits(bias);
     const float r1 = bias - __uint_as_float(hi << 16);
     const uint32_t mid = bf16_bits(r1);
@@ -976,31 +1012,20 @@ struct Bias<CKV_BF16> {
     const uint32_t lo = bf16_bits(r2);
     q = hh == 0 ? chunk_t{hi | (mid << 16), lo, 0u, 0u} : chunk_t{0u, 0u, 0u, 0u};
   }
-  static __device__ __forceinline__ chunk_t ones(int hh) {
-    return hh == 0 ? chunk_t{0x3f803f80u, 0x3f80u, 0u, 0u} : chunk_t{0u, 0u, 0u, 0u};
+  __device__ __forceinline__ void add(f32x16 &acc, int hh) const {
+    const chunk_t ones = hh == 0 ? chunk_t{0x3f803f80u, 0x3f80u, 0u, 0u} : chunk_t{0u, 0u, 0u, 0u};
+    Mma<CKV_BF16>::step(acc, q, ones);
   }
-  __device__ __forceinline__ void add(f32x16 &acc, const chunk_t &one) const { Mma<CKV_BF16>::step(acc, q, one); }
-};
-template <>
-struct Bias<CKV_F32> {
-  float q;
-  __device__ __forceinline__ void set(float bias, int hh) { q = hh == 0 ? bias : 0.0f; }
-  static __device__ __forceinline__ chunk_t ones(int hh) {
-    return chunk_t{hh == 0 ? 0x3f800000u : 0u, 0u, 0u, 0u};
-  }
-  __device__ __forceinline__ void add(f32x16 &acc, const chunk_t &one) const {
-    const uint32_t o = one[0];
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(q, __uint_as_float(o), acc, 0, 0, 0);
-  }
+  __device__ __forceinline__ float exponent(float dot, int, float c2) const { return dot * c2; }
 };
 
-// Weights exp(z - LSE) of one tile from acc = <q, k> - LSE / scale, summed over this lane's 16 rows.
-template <bool EDGE>
-__device__ __forceinline__ float colsum_weights(const f32x16 &acc, float c2, int hh, int first_masked_row) {
+// Weights exp(z - LSE) of one tile, summed over this lane's 16 rows.
+template <bool EDGE, class Shift>
+__device__ __forceinline__ float colsum_weights(const f32x16 &acc, const Shift &shift, float c2, int hh, int first_masked_row) {
   float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    float pr = __builtin_amdgcn_exp2f(acc[r] * c2);
+    float pr = __builtin_amdgcn_exp2f(shift.exponent(acc[r], r, c2));
     // causal: key kt is visible to window row j iff kt <= P + j, i.e. tile row >= kt - P - j0
     if (EDGE && acc_row(r, hh) < first_masked_row) pr = 0.0f;
     s[r & 3] += pr;
@@ -1038,7 +1063,7 @@ __device__ __forceinline__ void store_column_sums(const ScoreArgs &a, const Bloc
 template <int NQ>
 __device__ __forceinline__ void store_group_sum(const ScoreArgs &a, const BlockCoord &bc, const float (&cs)[NQ], int kt,
                                                 int hh) {
-  float x = cs[0];  // padding heads have zero query rows and bias -1000: their weights are exactly 0
+  float x = cs[0];  // padding heads have zero query rows and kNoWeight: their weights are exactly 0
 #pragma unroll
   for (int i = 1; i < NQ; ++i) x += cs[i];
   const float tot = (x + __shfl_xor(x, 32)) * a.norm;
@@ -1254,8 +1279,7 @@ __device__ __forceinline__ void dma_halo(const char *kbase, int64_t ks_t, int be
     int r, kappa;
     dma_source<G>(i, lane, r, kappa);
     const int t = r < kHaloKeys ? max(begin - kHaloKeys + r, 0) : min(end + r - kHaloKeys, T - 1);
-    const char *src = kbase + (int64_t)min(t, T - 1) * ks_t + kappa * 16;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds + i * 1024), "v"(src) : "memory");
+    dma_one(lds + i * 1024, kbase + (int64_t)min(t, T - 1) * ks_t + kappa * 16);
   }
 }
 
@@ -1326,7 +1350,9 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   static_assert(NQ % WT == 0, "whole heads");
   using G = Geom<DT, DH>;
   constexpr int NCH = G::NCH;
-  constexpr int N_MFMA = NCH * (DT == CKV_BF16 ? 1 : 4) + 1;
+  static_assert(DT == CKV_BF16, "row shifts");
+  constexpr bool SHIFT_IN_REGISTERS = NQ <= kShiftInRegisters;
+  constexpr int N_MFMA = NCH + (SHIFT_IN_REGISTERS ? 0 : 1);
   constexpr int READ_AT = NQ >= 2 ? NQ - 2 : 0;
   __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ>::Ring ring;
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
@@ -1337,43 +1363,86 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   __shared__ __attribute__((aligned(1024))) char s_halo_keys[UTIL ? 2 * kHaloKeys * G::ROW : 16];
   __shared__ __attribute__((aligned(16))) float s_halo[UTIL ? NH * kUtilHead : 4];
   __shared__ __attribute__((aligned(16))) float s_edge[UTIL ? kScoreWaves : 1][UTIL ? NH * kUtilHead : 4];
-  if constexpr (UTIL) {
-    const int begin = bc.chunk * kScoreWaves * a.keys_per_wave;
-    if (wr.wave == 0)
-      dma_halo<G>(a.k + bc.b * a.ks_b + bc.g * a.ks_h, a.ks_t, begin, begin + kScoreWaves * a.keys_per_wave, a.T, lane,
-                  (uint32_t)(uintptr_t)s_halo_keys);
-  }
+  __shared__ __attribute__((aligned(1024))) float s_stage[kScoreWaves][NH * (UTIL ? kUtilRow : kRing * kTile)];
   RatioScale rs;
   rs.load(a, bc);
   Staged<DT, DH, NQ> st;
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
-  st.start(a, bc, wr, ring, lane, m, hh, qf, jrow);
-  // Both passes in one call: every workgroup merges the first pass's row partials, a thread per row (NQ * 32 <= 256 of
-  // them), while its first key tiles are on their way. (A kernel in between cost 5 us, 11 with eight tiles and 32
-  // workgroups along the keys; a lane merging all its rows by itself cost more than that from 16 partials on.)
-  __shared__ float s_lse[NQ * kTile];
-  static_assert(NQ * kTile <= kScoreWaves * kWave, "a thread per row");
-  if (threadIdx.x < NQ * kTile) {
-    const int tile = bc.grp * NQ + threadIdx.x / kTile, j = (tile % WT) * kTile + threadIdx.x % kTile;
-    float v = 0.0f;
-    if (a.lse_from_part)
-      v = merge_row_partials(a.part + ((size_t)bc.unit * a.n_groups + bc.grp) * a.n_chunks * (NQ * kTile) + threadIdx.x,
-                             a.n_chunks, NQ * kTile);
-    else if (tile < a.n_tiles && j < a.W) v = a.lse[((size_t)bc.b * a.Hq + bc.g * a.G + tile / WT) * a.W + j];
-    s_lse[threadIdx.x] = v;
-  }
+  // The normalisers of the rows, in the log2 domain and negated, a thread per row (NQ * 32 <= 256 of them): given, or, both passes in one call, merged from the first
+  // pass's row partials by every workgroup of a unit. (A kernel in between cost 5 us, 11 with eight tiles and 32
+  // workgroups along the keys; a lane merging all its rows by itself cost more than that from 16 partials on.) What they are made
+  // of comes into the stage, which is not used yet, in front of everything else: a load into registers would have to be waited
+  // for behind the first key tiles, since the compiler does not know of those. More partials than the stage holds are loaded that way.
+  // With that, and the sums around the range contracted while the query tiles are in their images, 16384 keys with given normalisers
+  // 45.5 -> 44.9 us per layer, 32/8 heads of 131072 177.8 -> 175.9.
+  constexpr int ROWS = NQ * kTile;
+  constexpr int STAGED_CHUNKS = (int)sizeof(s_stage) / 1024 * 1024 / (ROWS * (int)sizeof(float2));  // whole loads of 1 KiB
+  static_assert(ROWS <= kScoreWaves * kWave && sizeof(s_stage) >= kScoreWaves * kWave * sizeof(float), "a thread per row");
+  __shared__ __attribute__((aligned(16))) float s_shift[ROWS];
+  const float2 *part = a.part + ((size_t)bc.unit * a.n_groups + bc.grp) * a.n_chunks * ROWS;
+  // The sums around the workgroup's range (fused form): wave w takes the heads w and w + 4, the tiles of a head one after the other
+  constexpr int HALO_TILES = UTIL ? WT * ((NH + kScoreWaves - 1) / kScoreWaves) : 1;
+  const auto halo_head = [&](int u) { return wr.wave + u / WT * kScoreWaves; };
+  f32x16 halo[HALO_TILES];
+  st.start(
+      a, bc, wr, ring, lane, m, hh, qf, jrow,
+      [&] {
+        const uint32_t stage_lds = (uint32_t)(uintptr_t)&s_stage[0][0];
+        if (a.lse_from_part) {
+          const int bytes = a.n_chunks * ROWS * (int)sizeof(float2);
+          if (a.n_chunks <= STAGED_CHUNKS)
+            for (int at = wr.wave * 1024; at < bytes; at += kScoreWaves * 1024)
+              dma_one(stage_lds + at, reinterpret_cast<const char *>(part) + min(at + lane * 16, bytes - 16));
+        } else if (wr.wave * kWave < ROWS) {
+          const int row = wr.wave * kWave + lane, tile = min(bc.grp * NQ + row / kTile, a.n_tiles - 1);
+          const int j = min(tile % WT * kTile + row % kTile, a.W - 1);
+          const float *src = a.lse + ((size_t)bc.b * a.Hq + bc.g * a.G + tile / WT) * a.W + j;
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(stage_lds + wr.wave * (kWave * 4)), "v"(src) : "memory");
+        }
+        if constexpr (UTIL) {
+          const int begin = bc.chunk * kScoreWaves * a.keys_per_wave;
+          if (wr.wave == 0)
+            dma_halo<G>(a.k + bc.b * a.ks_b + bc.g * a.ks_h, a.ks_t, begin, begin + kScoreWaves * a.keys_per_wave, a.T, lane,
+                        (uint32_t)(uintptr_t)s_halo_keys);
+        }
+      },
+      [&] {
+        if constexpr (UTIL) {
+          int hoff[NCH];
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) hoff[c] = image_offset<G>(m & (kUtilHead - 1), c + NCH * hh);
+          chunk_t kh[NCH], qh[NCH];
+          read_image<G>(kh, s_halo_keys, hoff);
+#pragma unroll
+          for (int u = 0; u < HALO_TILES; ++u) {
+            if (halo_head(u) >= NH) continue;
+            const int tile = halo_head(u) * WT + u % WT;
+            read_image<G>(qh, Staged<DT, DH, NQ>::image_of_tile(ring, tile), st.roff);
+            if (bc.grp * NQ + tile >= a.n_tiles || tile % WT * kTile + m >= a.W) {
+#pragma unroll
+              for (int c = 0; c < NCH; ++c) qh[c] = chunk_t{0u, 0u, 0u, 0u};
+            }
+            mma_chain<DT, NCH>(halo[u], qh, kh);
+          }
+        }
+        if (threadIdx.x < ROWS) {
+          float v;
+          if (!a.lse_from_part) v = s_stage[0][threadIdx.x];
+          else if (a.n_chunks <= STAGED_CHUNKS)
+            v = merge_row_partials(reinterpret_cast<const float2 *>(&s_stage[0][0]) + threadIdx.x, a.n_chunks, ROWS);
+          else v = merge_row_partials(part + threadIdx.x, a.n_chunks, ROWS);
+          const bool valid = bc.grp * NQ + (int)threadIdx.x / kTile < a.n_tiles && (int)threadIdx.x / kTile % WT * kTile + (int)threadIdx.x % kTile < a.W;
+          s_shift[threadIdx.x] = valid ? v * -kLog2e : kNoWeight;
+        }
+      });
   if constexpr (UTIL) {  // tau and the budgets of a batch element: a wave of its first workgroup
     if (bc.g == 0 && bc.chunk == 0 && wr.wave == kScoreWaves - 1) write_tau_and_budgets(a.bud, bc.b, lane);
   }
   rs.store(a, bc);
-  __syncthreads();
-  // bias of this lane's query row in every tile; padding rows (q = 0) get exp2(-1000) = 0 as weight
-  Bias<DT> bias[NQ];
-  const float to_raw = -kLog2e / a.c2;  // LSE (natural log) -> units of the raw dot product, negated
+  RowShift<SHIFT_IN_REGISTERS> shift[NQ];
 #pragma unroll
-  for (int i = 0; i < NQ; ++i) bias[i].set(jrow[i] >= 0 ? s_lse[i * kTile + m] * to_raw : -1000.0f / a.c2, hh);
-  const chunk_t ones = Bias<DT>::ones(hh);
+  for (int i = 0; i < NQ; ++i) shift[i].set(s_shift + i * kTile, a.c2, m, hh);
   // Descriptor over scores[b]: Hq * T floats (the host checks that this stays below 2 GiB). Lanes with
   // nothing to store present an offset outside it, which the hardware drops: no branch splits the
   // pipeline's code, and every flush issues exactly N_STORES store instructions.
@@ -1387,7 +1456,6 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   // descriptor) issued after the first loads stand in.
   // per flush: one for the fused and for the group-sum form
   constexpr int N_STORES = GSUM || UTIL ? 1 : (NH + 1) / 2;
-  __shared__ __attribute__((aligned(16))) float s_stage[kScoreWaves][NH * (UTIL ? kUtilRow : kRing * kTile)];
   // fused form: descriptor over utility[b] (Hkv * P floats) and the weights of this group's heads
   const __amdgpu_buffer_rsrc_t rsrc_u = __builtin_amdgcn_make_buffer_rsrc(
       (void *)(UTIL ? a.utility + (size_t)bc.b * a.Hkv * a.P : a.scores), 0, UTIL ? a.Hkv * a.P * 4 : 0, 0x00020000);
@@ -1405,31 +1473,28 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
 
   chunk_t kreg[2][NCH];
   f32x16 acc[2];
-  if constexpr (UTIL) {  // the sums around the workgroup's range
-    int hoff[NCH];
+  if constexpr (UTIL) {
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) hoff[c] = image_offset<G>(m & (kUtilHead - 1), c + NCH * hh);
-    read_image<G>(kreg[0], s_halo_keys, hoff);
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      if (wr.wave != h % kScoreWaves) continue;
+    for (int u = 0; u < HALO_TILES; u += WT) {
+      if (halo_head(u) >= NH) continue;
       float x = 0.0f;
 #pragma unroll
       for (int e = 0; e < WT; ++e) {
-        mma_chain<DT, NCH>(acc[0], qf[h * WT + e], kreg[0]);
-        bias[h * WT + e].add(acc[0], ones);
-        const float w = colsum_weights<false>(acc[0], a.c2, hh, 0);
+        RowShift<SHIFT_IN_REGISTERS> own;
+        own.set(s_shift + (halo_head(u) * WT + e) * kTile, a.c2, m, hh);
+        own.add(halo[u + e], hh);
+        const float w = colsum_weights<false>(halo[u + e], own, a.c2, hh, 0);
         x = e == 0 ? w : x + w;
       }
       const float tot = (x + __shfl_xor(x, 32)) * a.norm;
-      if (lane < kUtilHead) s_halo[h * kUtilHead + lane] = tot;
+      if (lane < kUtilHead) s_halo[halo_head(u) * kUtilHead + lane] = tot;
     }
   }
   if (n_piped > 0) {
     wait_vm<(kRing - 2) * G::NDMA>();
     read_image<G>(kreg[0], ring[wr.wave][0], st.roff);
     mma_chain<DT, NCH>(acc[0], qf[0], kreg[0]);
-    bias[0].add(acc[0], ones);
+    shift[0].add(acc[0], hh);
   }
   constexpr int UR = unroll_tiles(NQ);
   for (int t0 = 0; t0 < n_piped; t0 += UR) {
@@ -1452,12 +1517,12 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
         }
         if (i + 1 < NQ) {
           mma_chain<DT, NCH>(acc[cur ^ 1], qf[i + 1], kreg[v & 1]);  // rows: query rows, cols: keys
-          bias[i + 1].add(acc[cur ^ 1], ones);
+          shift[i + 1].add(acc[cur ^ 1], hh);
         } else {
           mma_chain<DT, NCH>(acc[cur ^ 1], qf[0], kreg[(v + 1) & 1]);
-          bias[0].add(acc[cur ^ 1], ones);
+          shift[0].add(acc[cur ^ 1], hh);
         }
-        cs[i] = colsum_weights<false>(acc[cur], a.c2, hh, 0);
+        cs[i] = colsum_weights<false>(acc[cur], shift[i], a.c2, hh, 0);
         if (i == READ_AT) interleave_hint<N_MFMA, vector_per_mfma_pass2(NQ), NCH>();
         else interleave_hint<N_MFMA, vector_per_mfma_pass2(NQ), 0>();
       }
@@ -1480,15 +1545,15 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
     st.tail_tile(wr, ring, t, wr.t_begin + t * kTile - (a.T - kTile), m, hh, kreg[0]);
     float cs[NQ];
     mma_chain<DT, NCH>(acc[0], qf[0], kreg[0]);
-    bias[0].add(acc[0], ones);
+    shift[0].add(acc[0], hh);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int j0 = ((bc.grp * NQ + i) % WT) * kTile;
       if (i + 1 < NQ) {
         mma_chain<DT, NCH>(acc[(i + 1) & 1], qf[i + 1], kreg[0]);
-        bias[i + 1].add(acc[(i + 1) & 1], ones);
+        shift[i + 1].add(acc[(i + 1) & 1], hh);
       }
-      cs[i] = colsum_weights<!UTIL>(acc[i & 1], a.c2, hh, kt - a.P - j0);  // keys of the prefix: every row sees them
+      cs[i] = colsum_weights<!UTIL>(acc[i & 1], shift[i], a.c2, hh, kt - a.P - j0);  // keys of the prefix: every row sees them
       if (i + 1 < NQ) interleave_hint<N_MFMA, kTailVectorPerMfma, 0>();
     }
     if constexpr (UTIL)
