@@ -160,9 +160,12 @@ __device__ __forceinline__ void rowstats_update(const f32x16 &acc, float c2, int
   for (int e = 0; e < 4; ++e) t[e] = fmaxf(fmaxf(v[4 * e], v[4 * e + 1]), fmaxf(v[4 * e + 2], v[4 * e + 3]));
   const float tmax = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
   const float mn = fmaxf(rm, tmax * c2);
-  float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  float s[4];  // begun with the first weights: a zero added to them would be an instruction
 #pragma unroll
-  for (int r = 0; r < 16; ++r) s[r & 3] += __builtin_amdgcn_exp2f(fmaf(v[r], c2, -mn));
+  for (int r = 0; r < 16; ++r) {
+    const float p = __builtin_amdgcn_exp2f(fmaf(v[r], c2, -mn));
+    s[r & 3] = r < 4 ? p : s[r & 3] + p;
+  }
   rl = fmaf(rl, __builtin_amdgcn_exp2f(rm - mn), (s[0] + s[1]) + (s[2] + s[3]));
   rm = mn;
 }
@@ -603,15 +606,14 @@ __host__ __device__ constexpr int unroll_tiles(int nq) { return nq > 4 ? 2 : kRi
 static_assert(kRing % 2 == 0, "half a ring cycle starts at an even image");
 
 // Vector instructions that the hint places behind each MFMA of the next pair's chain. Fewer than an even
-// spread (pass 1 has ~63 per 8 MFMAs, pass 2 ~52 per 9): the chain is then issued early, and what is left
+// spread (pass 1 has ~59 per 8 MFMAs, pass 2 ~48 per 8 or 9): the chain is then issued early, and what is left
 // of the current pair's vector work runs after its last MFMA -- the 18 wait states between an MFMA and the
 // first read of its result are filled with work instead of s_nop (one `s_nop 11` per pair with an even
-// spread). Measured in cycles per pair where memory does not limit (T = 128k, W = 64, eight tiles per
-// wave): pass 1 492 (8 per MFMA), 426 (6), 439 (5); pass 2 517 (6), 492 (5), 428 (4), 443 (3). With
-// four tiles per wave on the 32k / batch-16 shape, which sits at the memory ceiling, pass 1 gains 3 us with
-// 6 and pass 2 is best left at 6 (5 and 4: 2-3 us slower).
-__host__ __device__ constexpr int vector_per_mfma_pass1(int nq) { return 6; }
-__host__ __device__ constexpr int vector_per_mfma_pass2(int nq) { return nq > 4 ? 4 : 6; }
+// spread). us per layer (passes 1 / 2, instructions per MFMA): 131072 keys, W = 64, eight tiles per wave: 172.2 (6 / 4), 175.0 (6 / 5), 169.7
+// (6 / 3), 170.8 (5 / 4); another card 176.9 (6 / 3), 175.5 (5 / 3), 178.3 (4 / 3), 180.6 (5 / 2); 65536 keys, seven tiles, the same order. Four tiles,
+// 32768 keys, batch 16: 400.7 (6 / 6), 395.3 (5 / 6), 393.3 (5 / 5), 403.8 (4 / 6); 10006 keys with value norms 69.6 (5 / 5), 70.6 (5 / 4).
+__host__ __device__ constexpr int vector_per_mfma_pass1(int nq) { return 5; }
+__host__ __device__ constexpr int vector_per_mfma_pass2(int nq) { return nq > 4 ? 3 : 5; }
 
 // The tiles behind the pipeline run the same two stages over the query tiles of one key tile (the masks make their vector part
 // half as long again).
@@ -1022,13 +1024,13 @@ struct RowShift<false> {
 // Weights exp(z - LSE) of one tile, summed over this lane's 16 rows.
 template <bool EDGE, class Shift>
 __device__ __forceinline__ float colsum_weights(const f32x16 &acc, const Shift &shift, float c2, int hh, int first_masked_row) {
-  float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  float s[4];
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     float pr = __builtin_amdgcn_exp2f(shift.exponent(acc[r], r, c2));
     // causal: key kt is visible to window row j iff kt <= P + j, i.e. tile row >= kt - P - j0
     if (EDGE && acc_row(r, hh) < first_masked_row) pr = 0.0f;
-    s[r & 3] += pr;
+    s[r & 3] = r < 4 ? pr : s[r & 3] + pr;
   }
   return (s[0] + s[1]) + (s[2] + s[3]);
 }
