@@ -245,6 +245,19 @@ ckv_status ckv_compact_kv(const ckv_params *params, const void *k, const void *v
                           const int32_t *count, void *k_out, void *v_out, void *hip_stream);
 
 /*
+ * A layer's whole step as one call: ckv_window_utility (scores_wanted = 0; `scores` is its scratch) or
+ * ckv_window_scores + ckv_apply_tables (scores_wanted != 0), then ckv_select_topk and ckv_compact_kv, with the
+ * same arguments, outputs, refusals and order on the stream. `v` is read by the gather and, with
+ * CKV_FLAG_VALUE_NORM, by the scan; workspace as for ckv_window_scores.
+ */
+ckv_status ckv_retention_layer(const ckv_params *params, const void *q_win, const void *k, const void *v,
+                               const float *lse, const float *w_head, const float *head_share,
+                               const float *t_gate, int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins,
+                               float *scores, int32_t scores_wanted, float *vnorm_ratio, float *utility,
+                               int32_t *budget, float *tau, int32_t *idx, int32_t *count, void *k_out,
+                               void *v_out, void *workspace, size_t workspace_bytes, void *hip_stream);
+
+/*
  * Layer-shared mode: the paper's Alg. 1 as printed, where ONE window mass alpha serves every layer and
  * head and every layer keeps ONE index set for all its heads. Order of calls for a prompt:
  *   for each layer: ckv_window_scores (with CKV_FLAG_VALUE_NORM: rho of that layer) and

@@ -21,7 +21,7 @@ FLAG_VALUE_NORM = 1
 FLAG_GROUP_MASS = 8         # ckv_window_scores writes per-KV-head sums [Bz,Hkv,T] (layer-shared mode)
 
 EXPORTS = ("ckv_workspace_bytes", "ckv_window_lse", "ckv_window_lse_static_bytes", "ckv_window_lse_static", "ckv_window_scores", "ckv_window_utility", "ckv_apply_tables", "ckv_select_topk",
-           "ckv_compact_kv", "ckv_alpha_accumulate", "ckv_risk_struct", "ckv_shared_utility", "ckv_compact_kv_shared",
+           "ckv_compact_kv", "ckv_retention_layer", "ckv_alpha_accumulate", "ckv_risk_struct", "ckv_shared_utility", "ckv_compact_kv_shared",
            "ckv_decode_workspace_bytes", "ckv_decode_attention", "ckv_discarded_mass", "ckv_map_table_depth",
            "ckv_status_string")
 
@@ -75,6 +75,9 @@ def load(path: Optional[Path] = None):
     lib.ckv_select_topk.restype = ctypes.c_int
     lib.ckv_compact_kv.argtypes = [pp, vp, vp, vp, vp, vp, vp, vp]
     lib.ckv_compact_kv.restype = ctypes.c_int
+    lib.ckv_retention_layer.argtypes = [pp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_int32, ctypes.c_int32, vp, vp, ctypes.c_int32,
+                                        vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
+    lib.ckv_retention_layer.restype = ctypes.c_int
     lib.ckv_alpha_accumulate.argtypes = [pp, vp, ctypes.c_float, vp, vp]
     lib.ckv_alpha_accumulate.restype = ctypes.c_int
     lib.ckv_risk_struct.argtypes = [pp, vp, vp, ctypes.c_int32, vp, vp, vp]
@@ -290,18 +293,13 @@ class LayerBuffers:
 
 def retention_layer(params: CkvParams, q, k, v, tables: dict, buf: LayerBuffers, lse=None, stream=None,
                     fused_utility=False):
-    """Queues the calls of one layer back-to-back on the stream; returns nothing (outputs in buf).
-    fused_utility: ckv_window_utility in place of ckv_window_scores + ckv_apply_tables (buf.scores is
+    """Queues the kernels of one layer back-to-back on the stream, by one call of the library; returns nothing (outputs in
+    buf). fused_utility: those of ckv_window_utility in place of ckv_window_scores + ckv_apply_tables (buf.scores is
     then scratch)."""
-    vv = v if params.flags & FLAG_VALUE_NORM else None
-    if fused_utility:
-        ckv_window_utility(params, q, k, vv, lse, tables["w_head"], tables.get("head_share"), tables.get("t_gate"),
-                           tables.get("n_ent", 0), tables.get("n_ppl", 0), tables.get("risk_bins"), buf.scores,
-                           buf.vnorm_ratio, buf.utility, buf.budget, buf.tau, buf.workspace, stream)
-    else:
-        ckv_window_scores(params, q, k, vv, lse, buf.scores, buf.vnorm_ratio, buf.workspace, stream)
-        ckv_apply_tables(params, buf.scores, buf.vnorm_ratio, tables["w_head"], tables.get("head_share"),
-                         tables.get("t_gate"), tables.get("n_ent", 0), tables.get("n_ppl", 0),
-                         tables.get("risk_bins"), buf.utility, buf.budget, buf.tau, stream)
-    ckv_select_topk(params, buf.utility, buf.budget, buf.tau, buf.idx, buf.count, buf.workspace, stream)
-    ckv_compact_kv(params, k, v, buf.idx, buf.count, buf.k_out, buf.v_out, stream)
+    at = lambda t: None if t is None else t.data_ptr()  # noqa: E731
+    get, ws = tables.get, buf.workspace
+    _check(load().ckv_retention_layer(
+        ctypes.byref(params), at(q), at(k), at(v), at(lse), at(tables["w_head"]), at(get("head_share")), at(get("t_gate")),
+        int(get("n_ent", 0)), int(get("n_ppl", 0)), at(get("risk_bins")), at(buf.scores), 0 if fused_utility else 1,
+        at(buf.vnorm_ratio), at(buf.utility), at(buf.budget), at(buf.tau), at(buf.idx), at(buf.count), at(buf.k_out), at(buf.v_out),
+        at(ws), 0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)), "ckv_retention_layer")

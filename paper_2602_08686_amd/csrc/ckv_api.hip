@@ -172,25 +172,18 @@ extern "C" size_t ckv_workspace_bytes(const ckv_params *params) {
   return w.total;
 }
 
-extern "C" ckv_status ckv_window_scores(const ckv_params *params, const void *q_win, const void *k,
-                                        const void *v, const float *lse, float *scores,
-                                        float *vnorm_ratio, void *workspace, size_t workspace_bytes,
-                                        void *hip_stream) {
-  ckv_status st = validate(params);
-  if (st != CKV_OK) return st;
+// The calls of a layer behind validate(), derive() and layout(), which ckv_retention_layer has done once for all of them.
+static ckv_status scores_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
+                            const void *v, const float *lse, float *scores, float *vnorm_ratio, void *workspace,
+                            size_t workspace_bytes, hipStream_t stream) {
   if (!q_win || !k || !scores) return CKV_EINVAL;
   const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
   if (vn && (!v || !vnorm_ratio)) return CKV_EINVAL;
-  Shape s;
-  Workspace w;
-  derive(params, &s);
-  layout(params, s, &w);
-  st = workspace_ok(w, workspace, workspace_bytes);
+  const ckv_status st = workspace_ok(w, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
   // the group-mass output exists where one wave holds all query heads of a KV head, one tile each
   if ((params->flags & CKV_FLAG_GROUP_MASS) && !(params->dtype == CKV_BF16 && s.n_groups == 1 && s.WT == 1 && s.NQ <= 4))
     return CKV_EUNSUPPORTED;
-  hipStream_t stream = (hipStream_t)hip_stream;
   if (vn && !norms_in_scan(params, s, lse != nullptr) &&
       launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;
@@ -198,6 +191,19 @@ extern "C" ckv_status ckv_window_scores(const ckv_params *params, const void *q_
                            vn ? vnorm_ratio : nullptr) != hipSuccess)
     return CKV_EHIP;
   return CKV_OK;
+}
+
+extern "C" ckv_status ckv_window_scores(const ckv_params *params, const void *q_win, const void *k,
+                                        const void *v, const float *lse, float *scores,
+                                        float *vnorm_ratio, void *workspace, size_t workspace_bytes,
+                                        void *hip_stream) {
+  const ckv_status st = validate(params);
+  if (st != CKV_OK) return st;
+  Shape s;
+  Workspace w;
+  derive(params, &s);
+  layout(params, s, &w);
+  return scores_of(params, s, w, q_win, k, v, lse, scores, vnorm_ratio, workspace, workspace_bytes, (hipStream_t)hip_stream);
 }
 
 extern "C" ckv_status ckv_window_lse(const ckv_params *params, const void *q_win, const void *k,
@@ -274,23 +280,30 @@ extern "C" ckv_status ckv_window_lse_static(const ckv_params *params, const void
   return CKV_OK;
 }
 
+static ckv_status tables_of(const ckv_params *params, const Shape &s, const float *scores, const float *vnorm_ratio,
+                            const float *w_head, const float *head_share, const float *t_gate, int32_t n_ent, int32_t n_ppl,
+                            const int32_t *risk_bins, float *utility, int32_t *budget, float *tau, hipStream_t stream) {
+  if (!scores || !w_head || !utility || !budget || !tau) return CKV_EINVAL;
+  if (params->flags & CKV_FLAG_GROUP_MASS) return CKV_EINVAL;  // needs per-head masses
+  if ((params->flags & CKV_FLAG_VALUE_NORM) && !vnorm_ratio) return CKV_EINVAL;
+  if (t_gate && (n_ent < 1 || n_ppl < 1 || !risk_bins)) return CKV_EINVAL;
+  if (launch_apply_tables(params, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl,
+                          risk_bins, utility, budget, tau, stream) != hipSuccess)
+    return CKV_EHIP;
+  return CKV_OK;
+}
+
 extern "C" ckv_status ckv_apply_tables(const ckv_params *params, const float *scores,
                                        const float *vnorm_ratio, const float *w_head,
                                        const float *head_share, const float *t_gate, int32_t n_ent,
                                        int32_t n_ppl, const int32_t *risk_bins, float *utility,
                                        int32_t *budget, float *tau, void *hip_stream) {
-  ckv_status st = validate(params);
+  const ckv_status st = validate(params);
   if (st != CKV_OK) return st;
-  if (!scores || !w_head || !utility || !budget || !tau) return CKV_EINVAL;
-  if (params->flags & CKV_FLAG_GROUP_MASS) return CKV_EINVAL;  // needs per-head masses
-  if ((params->flags & CKV_FLAG_VALUE_NORM) && !vnorm_ratio) return CKV_EINVAL;
-  if (t_gate && (n_ent < 1 || n_ppl < 1 || !risk_bins)) return CKV_EINVAL;
   Shape s;
   derive(params, &s);
-  if (launch_apply_tables(params, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl,
-                          risk_bins, utility, budget, tau, (hipStream_t)hip_stream) != hipSuccess)
-    return CKV_EHIP;
-  return CKV_OK;
+  return tables_of(params, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, utility, budget, tau,
+                   (hipStream_t)hip_stream);
 }
 
 // Whether ckv_window_utility can run its fused second pass for this call (else it runs the two
@@ -306,26 +319,18 @@ static bool utility_fast_path(const ckv_params *p, const Shape &s) {
          (int64_t)s.Hkv * s.P < (1 << 29);
 }
 
-extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q_win, const void *k,
-                                         const void *v, const float *lse, const float *w_head,
-                                         const float *head_share, const float *t_gate, int32_t n_ent,
-                                         int32_t n_ppl, const int32_t *risk_bins, float *scores_scratch,
-                                         float *vnorm_ratio, float *utility, int32_t *budget, float *tau,
-                                         void *workspace, size_t workspace_bytes, void *hip_stream) {
-  ckv_status st = validate(params);
-  if (st != CKV_OK) return st;
+static ckv_status utility_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
+                             const void *v, const float *lse, const float *w_head, const float *head_share, const float *t_gate,
+                             int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins, float *scores_scratch, float *vnorm_ratio,
+                             float *utility, int32_t *budget, float *tau, void *workspace, size_t workspace_bytes,
+                             hipStream_t stream) {
   if (!q_win || !k || !scores_scratch || !w_head || !utility || !budget || !tau) return CKV_EINVAL;
   if (params->flags & CKV_FLAG_GROUP_MASS) return CKV_EINVAL;  // needs per-head masses
   const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
   if (vn && (!v || !vnorm_ratio)) return CKV_EINVAL;
   if (t_gate && (n_ent < 1 || n_ppl < 1 || !risk_bins)) return CKV_EINVAL;
-  Shape s;
-  Workspace w;
-  derive(params, &s);
-  layout(params, s, &w);
-  st = workspace_ok(w, workspace, workspace_bytes);
+  const ckv_status st = workspace_ok(w, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
-  hipStream_t stream = (hipStream_t)hip_stream;
   float *ratio = vn ? vnorm_ratio : nullptr;
   if (vn && !norms_in_scan(params, s, lse != nullptr) &&
       launch_value_norm(params, s, w, v, ratio, (char *)workspace, stream) != hipSuccess)
@@ -356,41 +361,96 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
   return CKV_OK;
 }
 
-extern "C" ckv_status ckv_select_topk(const ckv_params *params, const float *utility,
-                                      const int32_t *budget, const float *tau, int32_t *idx,
-                                      int32_t *count, void *workspace, size_t workspace_bytes,
-                                      void *hip_stream) {
-  ckv_status st = validate(params);
+extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q_win, const void *k,
+                                         const void *v, const float *lse, const float *w_head,
+                                         const float *head_share, const float *t_gate, int32_t n_ent,
+                                         int32_t n_ppl, const int32_t *risk_bins, float *scores_scratch,
+                                         float *vnorm_ratio, float *utility, int32_t *budget, float *tau,
+                                         void *workspace, size_t workspace_bytes, void *hip_stream) {
+  const ckv_status st = validate(params);
   if (st != CKV_OK) return st;
-  if (!utility || !budget || !tau || !idx || !count) return CKV_EINVAL;
   Shape s;
+  Workspace w;
   derive(params, &s);
+  layout(params, s, &w);
+  return utility_of(params, s, w, q_win, k, v, lse, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, scores_scratch, vnorm_ratio,
+                    utility, budget, tau, workspace, workspace_bytes, (hipStream_t)hip_stream);
+}
+
+static ckv_status select_of(const ckv_params *params, const Shape &s, const Workspace &w, const float *utility,
+                            const int32_t *budget, const float *tau, int32_t *idx, int32_t *count, void *workspace,
+                            size_t workspace_bytes, hipStream_t stream) {
+  if (!utility || !budget || !tau || !idx || !count) return CKV_EINVAL;
   // Optional: short prefixes are selected by one workgroup per unit, everything on chip; for long ones a
   // workspace lets the selection split a unit over several workgroups.
-  Workspace w;
-  layout(params, s, &w);
   bool split = workspace && w.select_bytes > 0;
   if (split && (((uintptr_t)workspace & 255) || workspace_bytes < w.select_off + select_split_bytes(s))) {
     if (s.P % 4 == 0) return CKV_EWORKSPACE;
     split = false;
   }
   if (launch_select(params, s, utility, budget, tau, idx, count, split ? (char *)workspace + w.select_off : nullptr,
-                    split ? workspace_bytes - w.select_off : 0, (hipStream_t)hip_stream) != hipSuccess)
+                    split ? workspace_bytes - w.select_off : 0, stream) != hipSuccess)
     return CKV_EHIP;
+  return CKV_OK;
+}
+
+extern "C" ckv_status ckv_select_topk(const ckv_params *params, const float *utility,
+                                      const int32_t *budget, const float *tau, int32_t *idx,
+                                      int32_t *count, void *workspace, size_t workspace_bytes,
+                                      void *hip_stream) {
+  const ckv_status st = validate(params);
+  if (st != CKV_OK) return st;
+  Shape s;
+  Workspace w;
+  derive(params, &s);
+  layout(params, s, &w);
+  return select_of(params, s, w, utility, budget, tau, idx, count, workspace, workspace_bytes, (hipStream_t)hip_stream);
+}
+
+static ckv_status gather_of(const ckv_params *params, const Shape &s, const void *k, const void *v, const int32_t *idx,
+                            const int32_t *count, void *k_out, void *v_out, hipStream_t stream, bool shared_list) {
+  if (!k || !v || !idx || !count || !k_out || !v_out) return CKV_EINVAL;
+  if (launch_gather(params, s, k, v, idx, count, k_out, v_out, stream, shared_list) != hipSuccess) return CKV_EHIP;
   return CKV_OK;
 }
 
 extern "C" ckv_status ckv_compact_kv(const ckv_params *params, const void *k, const void *v,
                                      const int32_t *idx, const int32_t *count, void *k_out,
                                      void *v_out, void *hip_stream) {
-  ckv_status st = validate(params);
+  const ckv_status st = validate(params);
   if (st != CKV_OK) return st;
-  if (!k || !v || !idx || !count || !k_out || !v_out) return CKV_EINVAL;
   Shape s;
   derive(params, &s);
-  if (launch_gather(params, s, k, v, idx, count, k_out, v_out, (hipStream_t)hip_stream) != hipSuccess)
-    return CKV_EHIP;
-  return CKV_OK;
+  return gather_of(params, s, k, v, idx, count, k_out, v_out, (hipStream_t)hip_stream, false);
+}
+
+// A layer's kernels queued by one call: what its separate calls cost the host besides the launches (marshalling of four calls,
+// validation and the split of the key axis for each) is as much as a short layer takes on the GPU. us per layer on a stream of
+// them, separate / one call: f32, 1024 keys, 4/4 heads 26.1 / 20.5, host time of 4096 keys, 32/32 heads 19.0 / 14.7.
+extern "C" ckv_status ckv_retention_layer(const ckv_params *params, const void *q_win, const void *k, const void *v,
+                                          const float *lse, const float *w_head, const float *head_share,
+                                          const float *t_gate, int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins,
+                                          float *scores, int32_t scores_wanted, float *vnorm_ratio, float *utility,
+                                          int32_t *budget, float *tau, int32_t *idx, int32_t *count, void *k_out,
+                                          void *v_out, void *workspace, size_t workspace_bytes, void *hip_stream) {
+  ckv_status st = validate(params);
+  if (st != CKV_OK) return st;
+  Shape s;
+  Workspace w;
+  derive(params, &s);
+  layout(params, s, &w);
+  hipStream_t stream = (hipStream_t)hip_stream;
+  if (scores_wanted) {
+    st = scores_of(params, s, w, q_win, k, v, lse, scores, vnorm_ratio, workspace, workspace_bytes, stream);
+    if (st == CKV_OK)
+      st = tables_of(params, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, utility, budget, tau, stream);
+  } else {
+    st = utility_of(params, s, w, q_win, k, v, lse, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, scores, vnorm_ratio, utility,
+                    budget, tau, workspace, workspace_bytes, stream);
+  }
+  if (st == CKV_OK) st = select_of(params, s, w, utility, budget, tau, idx, count, workspace, workspace_bytes, stream);
+  if (st == CKV_OK) st = gather_of(params, s, k, v, idx, count, k_out, v_out, stream, false);
+  return st;
 }
 
 extern "C" ckv_status ckv_alpha_accumulate(const ckv_params *params, const float *scores, float weight,
@@ -435,14 +495,11 @@ extern "C" ckv_status ckv_shared_utility(const ckv_params *params, const float *
 extern "C" ckv_status ckv_compact_kv_shared(const ckv_params *params, const void *k, const void *v,
                                             const int32_t *idx, const int32_t *count, void *k_out, void *v_out,
                                             void *hip_stream) {
-  ckv_status st = validate(params);
+  const ckv_status st = validate(params);
   if (st != CKV_OK) return st;
-  if (!k || !v || !idx || !count || !k_out || !v_out) return CKV_EINVAL;
   Shape s;
   derive(params, &s);
-  if (launch_gather(params, s, k, v, idx, count, k_out, v_out, (hipStream_t)hip_stream, true) != hipSuccess)
-    return CKV_EHIP;
-  return CKV_OK;
+  return gather_of(params, s, k, v, idx, count, k_out, v_out, (hipStream_t)hip_stream, true);
 }
 
 extern "C" ckv_status ckv_map_table_depth(const float *table, int32_t n_layers_src, int32_t row_elems, float *mapped,
