@@ -514,21 +514,33 @@ __device__ __forceinline__ const char *uniform_ptr(const char *p) {
 }
 
 // Four loads with one M0 write: instruction j reads 16 bytes per lane at sbase + voff_j + 1024 * j
-// and writes them at LDS address lds + 1024 * j + 16 * lane. K is read once per pass and never again
-// before everything else has gone through the caches: the loads are marked non-temporal (streaming),
-// which measurably raises the rate at which HBM delivers them and leaves L2 and the memory-side cache
-// to the data that is reused (Q, the column sums on their way to the next kernel).
+// and writes them at LDS address lds + 1024 * j + 16 * lane. STREAM: keys that are not read again before everything else has gone through
+// the caches are marked non-temporal, which measurably raises the rate at which HBM delivers them and leaves L2 and the
+// memory-side cache to the data that is reused (Q, the column sums on their way to the next kernel). Without it the first pass leaves
+// them to the second in the memory-side cache: kKeptKeyBytes draws the line.
+template <bool STREAM>
 __device__ __forceinline__ void dma_quad(const char *sbase, uint32_t lds, uint32_t v0, uint32_t v1, uint32_t v2,
                                          uint32_t v3) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, %1 offset:0 nt\n\t"
-      "global_load_lds_dwordx4 %3, %1 offset:1024 nt\n\t"
-      "global_load_lds_dwordx4 %4, %1 offset:2048 nt\n\t"
-      "global_load_lds_dwordx4 %5, %1 offset:3072 nt"
-      :
-      : "s"(lds), "s"(sbase), "v"(v0), "v"(v1), "v"(v2), "v"(v3)
-      : "memory");
+  if constexpr (STREAM)
+    asm volatile(
+        "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %2, %1 offset:0 nt\n\t"
+        "global_load_lds_dwordx4 %3, %1 offset:1024 nt\n\t"
+        "global_load_lds_dwordx4 %4, %1 offset:2048 nt\n\t"
+        "global_load_lds_dwordx4 %5, %1 offset:3072 nt"
+        :
+        : "s"(lds), "s"(sbase), "v"(v0), "v"(v1), "v"(v2), "v"(v3)
+        : "memory");
+  else
+    asm volatile(
+        "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %2, %1 offset:0\n\t"
+        "global_load_lds_dwordx4 %3, %1 offset:1024\n\t"
+        "global_load_lds_dwordx4 %4, %1 offset:2048\n\t"
+        "global_load_lds_dwordx4 %5, %1 offset:3072"
+        :
+        : "s"(lds), "s"(sbase), "v"(v0), "v"(v1), "v"(v2), "v"(v3)
+        : "memory");
 }
 
 // The same with an address of its own for every lane: lane l of instruction j moves 16 bytes from p_j to lds + 1024 * j + 16 * l. In asm like
@@ -572,12 +584,12 @@ __device__ __forceinline__ void dma_rows(Row row_of, int lane, uint32_t lds) {
 // minus the immediate of its instruction plus kDmaBias, so the scalar base is tile_base - kDmaBias; the second quad reads the
 // same chunks (the swizzle repeats every sixteen rows) quad_stride = 16 rows further on.
 constexpr int kDmaBias = 3072;
-template <class G>
+template <class G, bool STREAM>
 __device__ __forceinline__ void dma_tile(const char *tile_base, const uint32_t (&voff)[4], int64_t quad_stride, uint32_t lds_image) {
   static_assert(G::NDMA == 4 || (G::NDMA == 8 && G::CH == 16), "a quad is sixteen rows of sixteen chunks");
 #pragma unroll
   for (int q = 0; q < G::NDMA / 4; ++q)
-    dma_quad(tile_base - kDmaBias + q * quad_stride, lds_image + q * 4096, voff[0], voff[1], voff[2], voff[3]);
+    dma_quad<STREAM>(tile_base - kDmaBias + q * quad_stride, lds_image + q * 4096, voff[0], voff[1], voff[2], voff[3]);
 }
 
 template <class G>
@@ -652,7 +664,7 @@ __device__ __forceinline__ void start_barrier() {
 }
 
 // LEAN: registers are short (another wave shares the SIMD), operand addresses are formed at each read.
-template <int DT, int DH, int NQ, bool LEAN = false>
+template <int DT, int DH, int NQ, bool STREAM, bool LEAN = false>
 struct Staged {
   using G = Geom<DT, DH>;
   static constexpr int NCH = G::NCH;
@@ -708,7 +720,7 @@ struct Staged {
       if (!tiny) {
 #pragma unroll
         for (int d = 0; d < N_PRE; ++d)
-          dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, tile_stride / 2, lds_ring + d * G::TILE);
+          dma_tile<G, STREAM>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, tile_stride / 2, lds_ring + d * G::TILE);
       } else {  // the only tile of a sequence shorter than one: rows are clamped (whoever uses them masks their logits)
 #pragma unroll
         for (int d = 0; d < N_PRE; ++d)
@@ -745,7 +757,7 @@ struct Staged {
     if (wr.n_all > 0 && !tiny) {
 #pragma unroll
       for (int d = N_PRE; d < kRing - 1; ++d)
-        dma_tile<G>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, tile_stride / 2, lds_ring + d * G::TILE);
+        dma_tile<G, STREAM>(d < wr.n_whole ? kcur + d * tile_stride : kend, voff, tile_stride / 2, lds_ring + d * G::TILE);
     }
   }
 
@@ -756,7 +768,7 @@ struct Staged {
   // Load of the tile three ahead of the one at kcur (tile index t + 3) into ring image `slot`; past
   // the last tile the last one is fetched again (in bounds, unused).
   __device__ __forceinline__ void prefetch(int t, int n_whole, int slot) {
-    dma_tile<G>(t + 3 < n_whole ? kcur + 3 * tile_stride : kend, voff, tile_stride / 2, lds_ring + slot * G::TILE);
+    dma_tile<G, STREAM>(t + 3 < n_whole ? kcur + 3 * tile_stride : kend, voff, tile_stride / 2, lds_ring + slot * G::TILE);
   }
 
   // Operand chunks of the tile in ring image `slot`.
@@ -884,17 +896,18 @@ struct NormWaves {
   }
 };
 
-template <int DT, int DH, int NQ, bool NORMS = false>
+template <int DT, int DH, int NQ, bool NORMS = false, bool KEEP = false>
 __global__ void __launch_bounds__(kScoreWaves *kWave * (NORMS ? 2 : 1)) rowstats_lds_kernel(ScoreArgs a) {
   using G = Geom<DT, DH>;
   constexpr int NCH = G::NCH;
   constexpr int N_MFMA = NCH * (DT == CKV_BF16 ? 1 : 4);
+  constexpr bool STREAM = !KEEP;
   constexpr bool LEAN = NORMS && NQ == kMaxQTilesNorms;
   // query tile during which the next key tile is picked up; LEAN: when the last chain of the present one has been issued, into
   // the same registers (with a second set 18 registers spilled, and a reload waits for the loads in flight: 54 us for 50)
   constexpr int READ_AT = LEAN ? NQ - 1 : NQ >= 2 ? NQ - 2 : 0;
   constexpr int NEXT = LEAN ? 0 : 1;
-  __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ>::Ring ring;
+  __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ, STREAM>::Ring ring;
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
   const BlockCoord bc = decode_block(a);
   if constexpr (NORMS) {
@@ -907,7 +920,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave * (NORMS ? 2 : 1)) rowstats
   }
   const WaveRange wr = wave_range(a, bc, a.T);
 
-  Staged<DT, DH, NQ, LEAN> st;
+  Staged<DT, DH, NQ, STREAM, LEAN> st;
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
   st.start(a, bc, wr, ring, lane, m, hh, qf, jrow, [] {}, [] {});
@@ -1352,11 +1365,12 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   static_assert(NQ % WT == 0, "whole heads");
   using G = Geom<DT, DH>;
   constexpr int NCH = G::NCH;
+  constexpr bool STREAM = true;
   static_assert(DT == CKV_BF16, "row shifts");
   constexpr bool SHIFT_IN_REGISTERS = NQ <= kShiftInRegisters;
   constexpr int N_MFMA = NCH + (SHIFT_IN_REGISTERS ? 0 : 1);
   constexpr int READ_AT = NQ >= 2 ? NQ - 2 : 0;
-  __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ>::Ring ring;
+  __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ, STREAM>::Ring ring;
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
   const BlockCoord bc = decode_block(a);
   const WaveRange wr = wave_range(a, bc, UTIL ? a.P : a.T);  // utilities: of the prefix only
@@ -1368,7 +1382,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   __shared__ __attribute__((aligned(1024))) float s_stage[kScoreWaves][NH * (UTIL ? kUtilRow : kRing * kTile)];
   RatioScale rs;
   rs.load(a, bc);
-  Staged<DT, DH, NQ> st;
+  Staged<DT, DH, NQ, STREAM> st;
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
   // The normalisers of the rows, in the log2 domain and negated, a thread per row (NQ * 32 <= 256 of them): given, or, both passes in one call, merged from the first
@@ -1420,7 +1434,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
           for (int u = 0; u < HALO_TILES; ++u) {
             if (halo_head(u) >= NH) continue;
             const int tile = halo_head(u) * WT + u % WT;
-            read_image<G>(qh, Staged<DT, DH, NQ>::image_of_tile(ring, tile), st.roff);
+            read_image<G>(qh, Staged<DT, DH, NQ, STREAM>::image_of_tile(ring, tile), st.roff);
             if (bc.grp * NQ + tile >= a.n_tiles || tile % WT * kTile + m >= a.W) {
 #pragma unroll
               for (int c = 0; c < NCH; ++c) qh[c] = chunk_t{0u, 0u, 0u, 0u};
@@ -1617,12 +1631,21 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
 // ---------------------------------------------------------------------------------------------
 // Launch
 // ---------------------------------------------------------------------------------------------
+// Bytes of K up to which the first pass of a call leaves the keys in the memory-side cache (256 MiB) for the second. us per
+// layer, streamed / kept, keys in the cache before the call (as a prefill that has just written them leaves them, or a call on the
+// same ones) and then keys from HBM: 4096 keys, 32/32 heads 30.5 / 27.5, 31.1 / 31.4; 16384, 32/8 37.2 / 34.5, 37.5 / 36.2; 1024, 32/32 19.3 / 18.7, 21.7
+// / 20.7; 8192, 32/8 28.5 / 27.4, 29.3 / 29.7. At 57 and 61 MB (28000, 32/8; 7500, batch 4) 44.3 / 44.7, 45.1 / 44.9 and no gain from HBM,
+// at 82 MB 55.4 / 56.0 from HBM, at 1 GiB 392 / 408. In the second pass, whose keys nobody reads again, the streaming form loses
+// nothing (16384, 32/8: 34.9 against 34.1 from the cache, but 20011, batch 2 57.1 against 58.8 from HBM).
+constexpr int64_t kKeptKeyBytes = 48 << 20;
 template <int DT, int DH, int NQ>
 static void launch_rowstats(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 block, hipStream_t stream) {
   if constexpr (DT == CKV_BF16) {
     if (a.v) {
       if constexpr (NQ <= kMaxQTilesNorms)
         hipLaunchKernelGGL((rowstats_lds_kernel<DT, DH, NQ, true>), grid, dim3(2 * block.x), 0, stream, a);
+    } else if (a.lse_from_part && (int64_t)s.Bz * s.Hkv * s.T * s.d * s.esize <= kKeptKeyBytes) {
+      hipLaunchKernelGGL((rowstats_lds_kernel<DT, DH, NQ, false, true>), grid, block, 0, stream, a);
     } else {
       hipLaunchKernelGGL((rowstats_lds_kernel<DT, DH, NQ>), grid, block, 0, stream, a);
     }
