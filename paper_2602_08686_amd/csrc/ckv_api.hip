@@ -4,6 +4,8 @@
 #include <float.h>
 #include <math.h>
 
+#include <atomic>
+#include <chrono>
 #include <mutex>
 
 #include "ckv_internal.h"
@@ -133,6 +135,23 @@ bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given) {
          kScoreWaves * s.keys_per_wave % kVnormRows == 0 && (int64_t)s.Bz * s.Hkv * s.n_chunks <= kComputeUnits;
 }
 
+// One launch for both passes where a wave's range is no longer than its ring of key tiles, so that the keys stay in LDS between
+// them, and every workgroup has a CU of its own (more of them would wait for
+// ones that start when they end). Up to four query tiles per wave: with eight 13 registers spill. 0.80 to 0.96 of the two launches'
+// time per layer over nine shapes of 1000 to 16384 keys (scan_short_kernel); without value norms, whose ratio needs a unit's sum of them, too.
+bool one_launch(const ckv_params *p, const Shape &s) {
+  return p->dtype == CKV_BF16 && s.n_groups == 1 && !(p->flags & (CKV_FLAG_VALUE_NORM | CKV_FLAG_GROUP_MASS)) && s.NQ <= kShortTiles &&
+         s.keys_per_wave <= kRing * kTile && (int64_t)s.Bz * s.Hkv * s.n_chunks <= kComputeUnits;
+}
+
+// The upper bits are those of a negative NaN, which no sum, position or key ends up as; the rest counts launches from the
+// time the process began, in steps that touch all bits.
+tag_t launch_tag() {
+  static std::atomic<uint64_t> count{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count()};
+  const uint64_t mixed = count.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;
+  return 0xFFF8000000000000ull | mixed >> 13;
+}
+
 void layout(const ckv_params *p, const Shape &s, Workspace *w) {
   const size_t units = (size_t)s.Bz * s.Hkv;
   size_t off = 0;
@@ -151,6 +170,10 @@ void layout(const ckv_params *p, const Shape &s, Workspace *w) {
   // of a length that is no multiple of four: nothing for the selection, which takes them with any workspace).
   w->least = align256(off + (s.P % 4 == 0 ? select_split_bytes(s) : 0));
   off = align256(off + w->select_bytes);
+  // behind what calls asked for before there were marks: with less, the scan is two launches
+  w->marks_off = off;
+  w->marks_bytes = one_launch(p, s) ? 2 * units * (size_t)s.n_chunks * sizeof(tag_t) : 0;
+  off = align256(off + w->marks_bytes);
   w->total = off;
 }
 
@@ -172,6 +195,17 @@ extern "C" size_t ckv_workspace_bytes(const ckv_params *params) {
   return w.total;
 }
 
+// How long a workgroup of the one-launch form waits for the others' row sums (units of 10 ns) before it makes them itself: they
+// are there within 2 us where all run at once, and come late only where another kernel holds CUs.
+constexpr uint32_t kExchangeWait = 3000;
+
+static Exchange exchange_of(const Workspace &w, const float *lse, void *workspace, size_t workspace_bytes, uint32_t wait) {
+  Exchange e;
+  if (w.marks_bytes && !lse && workspace_bytes >= w.marks_off + w.marks_bytes) e.marks = (tag_t *)((char *)workspace + w.marks_off);
+  e.wait = wait;
+  return e;
+}
+
 // The calls of a layer behind validate(), derive() and layout(), which ckv_retention_layer has done once for all of them.
 static ckv_status scores_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
                             const void *v, const float *lse, float *scores, float *vnorm_ratio, void *workspace,
@@ -188,7 +222,7 @@ static ckv_status scores_of(const ckv_params *params, const Shape &s, const Work
       launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;
   if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores, (char *)workspace, stream, nullptr, v,
-                           vn ? vnorm_ratio : nullptr) != hipSuccess)
+                           vn ? vnorm_ratio : nullptr, exchange_of(w, lse, workspace, workspace_bytes, kExchangeWait)) != hipSuccess)
     return CKV_EHIP;
   return CKV_OK;
 }
@@ -323,7 +357,7 @@ static ckv_status utility_of(const ckv_params *params, const Shape &s, const Wor
                              const void *v, const float *lse, const float *w_head, const float *head_share, const float *t_gate,
                              int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins, float *scores_scratch, float *vnorm_ratio,
                              float *utility, int32_t *budget, float *tau, void *workspace, size_t workspace_bytes,
-                             hipStream_t stream) {
+                             hipStream_t stream, uint32_t wait = kExchangeWait) {
   if (!q_win || !k || !scores_scratch || !w_head || !utility || !budget || !tau) return CKV_EINVAL;
   if (params->flags & CKV_FLAG_GROUP_MASS) return CKV_EINVAL;  // needs per-head masses
   const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
@@ -332,6 +366,7 @@ static ckv_status utility_of(const ckv_params *params, const Shape &s, const Wor
   const ckv_status st = workspace_ok(w, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
   float *ratio = vn ? vnorm_ratio : nullptr;
+  const Exchange exchange = exchange_of(w, lse, workspace, workspace_bytes, wait);
   if (vn && !norms_in_scan(params, s, lse != nullptr) &&
       launch_value_norm(params, s, w, v, ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;
@@ -348,12 +383,12 @@ static ckv_status utility_of(const ckv_params *params, const Shape &s, const Wor
     fuse.inv_kernel_rest = fmaxf((float)(1.0 / kernel - (double)fuse.inv_kernel), FLT_MIN);
     fuse.bud = budget_args(params, s, head_share, t_gate, n_ent, n_ppl, risk_bins, budget, tau);
     if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores_scratch, (char *)workspace, stream,
-                             &fuse, v, ratio) != hipSuccess)
+                             &fuse, v, ratio, exchange) != hipSuccess)
       return CKV_EHIP;
     return CKV_OK;
   }
   if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores_scratch, (char *)workspace, stream, nullptr,
-                           v, ratio) != hipSuccess)
+                           v, ratio, exchange) != hipSuccess)
     return CKV_EHIP;
   if (launch_apply_tables(params, s, scores_scratch, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl,
                           risk_bins, utility, budget, tau, stream) != hipSuccess)
@@ -375,6 +410,21 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
   layout(params, s, &w);
   return utility_of(params, s, w, q_win, k, v, lse, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, scores_scratch, vnorm_ratio,
                     utility, budget, tau, workspace, workspace_bytes, (hipStream_t)hip_stream);
+}
+
+// ckv_window_utility with another bound on the one-launch form's wait; for tests, in no header. With 0 a workgroup makes whatever the
+// others have not left by the time it looks.
+extern "C" ckv_status ckv_window_utility_wait(const ckv_params *params, const void *q_win, const void *k, const float *w_head,
+                                              float *scores_scratch, float *utility, int32_t *budget, float *tau,
+                                              void *workspace, size_t workspace_bytes, uint32_t wait, void *hip_stream) {
+  const ckv_status st = validate(params);
+  if (st != CKV_OK) return st;
+  Shape s;
+  Workspace w;
+  derive(params, &s);
+  layout(params, s, &w);
+  return utility_of(params, s, w, q_win, k, nullptr, nullptr, w_head, nullptr, nullptr, 0, 0, nullptr, scores_scratch, nullptr, utility,
+                    budget, tau, workspace, workspace_bytes, (hipStream_t)hip_stream, wait);
 }
 
 static ckv_status select_of(const ckv_params *params, const Shape &s, const Workspace &w, const float *utility,

@@ -15,6 +15,7 @@ constexpr int kTile = 32;          // MFMA 32x32 tile edge: query rows and keys 
 constexpr int kMaxQTiles = 8;      // query-row tiles a wave keeps in registers (bf16; f32 kernels: kMaxQTilesF32)
 constexpr int kMaxQTilesF32 = 4;
 constexpr int kMaxQTilesNorms = 4; // up to here a wave of the scan's first pass leaves half of its SIMD's registers
+constexpr int kShortTiles = 4;     // up to here both passes of a short call fit one kernel's registers
 constexpr int kMaxWindowTiles = 4; // 32-row tiles per query head: W <= 128
 constexpr int kScoreWaves = 4;     // waves per workgroup in the scan kernels
 // Compute units of the build target (gfx950: MI355X, 256). A constant on purpose, not a device query: the
@@ -114,6 +115,21 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask, uint32_
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, c));
 }
 
+// Values that pass between workgroups of one launch: past the first-level caches and the XCD's own L2, both ways (agent scope).
+template <class T>
+__device__ __forceinline__ void store_across(T *p, T v) {
+  __scoped_atomic_store_n(p, v, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+}
+template <class T>
+__device__ __forceinline__ T load_across(const T *p) {
+  return __scoped_atomic_load_n(p, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+}
+// Marks that workgroups of a launch leave for one another in memory that nobody has cleared: equal to the launch's tag or not.
+// A launch takes its marks back before it ends, so that a replay of it, which has the same tag, finds none; what else the memory
+// may have held is no tag (launch_tag: another value for every launch of the process, such as nothing else leaves there).
+typedef uint64_t tag_t;
+tag_t launch_tag();
+
 ckv_status validate(const ckv_params *p);
 void derive(const ckv_params *p, Shape *s);
 
@@ -123,6 +139,7 @@ struct Workspace {
   size_t lse_off, lse_bytes;     // float  [Bz][Hq][W]
   size_t vsum_off, vsum_bytes;   // float  [units][vnorm blocks] partial sums of value norms
   size_t select_off, select_bytes;  // the long selection's: slices' pairs, or the split's histograms, counts and thresholds
+  size_t marks_off, marks_bytes;    // tag_t [2][workgroups] of the scan's one-launch form
   size_t least;  // what a call has to be given: less than total where total has room for the slices' pairs
   size_t total;
 };
@@ -153,13 +170,20 @@ struct UtilityFusion {
   float inv_kernel, inv_kernel_rest;  // 1 / kernel: the largest float that is not above it, and what that leaves
   BudgetArgs bud;
 };
+// Both passes as one launch, whose workgroups keep their keys on chip and exchange the row sums: where one_launch() says so and
+// there are marks.
+struct Exchange {
+  tag_t *marks = nullptr;  // tag_t [2][workgroups], or null: two launches
+  uint32_t wait = 0;       // how long a workgroup waits for another's part of the row sums, in units of 10 ns
+};
+bool one_launch(const ckv_params *p, const Shape &s);
 // lse_in == nullptr: pass 1 first, LSE into lse_out (or the workspace). scores == nullptr: pass 1 only.
 // ratio: if given, pass 2 makes it of the value norms that launch_value_norm, or with norms_in_scan() and v pass 1, left there
 // (and, in the fused form, multiplies the utilities by it).
 hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Workspace &w, const void *q,
                                 const void *k, const float *lse_in, float *lse_out, float *scores,
                                 char *ws, hipStream_t stream, const UtilityFusion *fuse = nullptr,
-                                const void *v = nullptr, float *ratio = nullptr);
+                                const void *v = nullptr, float *ratio = nullptr, const Exchange &exchange = {});
 // Whether pass 1 of a call takes the value norms beside its scan; the norms and sums are those of launch_value_norm.
 bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given);
 // the norms into `ratio` and their sums per block into the workspace; launch_window_scores turns them into the ratio

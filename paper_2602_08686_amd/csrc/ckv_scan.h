@@ -55,6 +55,10 @@ struct ScoreArgs {
   int pool, radius;    // pooling mode and radius (kernel / 2, at most kUtilMaxRadius)
   float inv_kernel, inv_kernel_rest;  // 1 / pool_kernel in two terms
   BudgetArgs bud;
+  // one-launch form only
+  tag_t *marks;  // [2][workgroups]: row sums left, row sums read
+  tag_t tag;
+  uint32_t wait;  // units of 10 ns
 };
 
 template <int DT> struct Mma;
@@ -246,20 +250,46 @@ __global__ void __launch_bounds__(kScoreWaves *kWave, plain_waves(DT, DH, NQ)) r
 
 // LSE_j = ln2 * (M + log2 sum_c l_c 2^(m_c - M)) from the n_chunks partials of one row (`stride` apart), in chunk order, eight
 // loads in flight.
+__device__ __forceinline__ void merge_eight(const float2 *v, float &M, float &L) {
+  float top = M;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) top = fmaxf(top, v[e].x);
+  L *= __builtin_amdgcn_exp2f(M - top);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) L += v[e].y * __builtin_amdgcn_exp2f(v[e].x - top);
+  M = top;
+}
 __device__ __forceinline__ float merge_row_partials(const float2 *p, int n_chunks, int stride) {
-  constexpr int BATCH = 8;
   float M = -1e30f, L = 0.0f;
-  for (int c0 = 0; c0 < n_chunks; c0 += BATCH) {
-    float2 v[BATCH];
+  for (int c0 = 0; c0 < n_chunks; c0 += 8) {
+    float2 v[8];
 #pragma unroll
-    for (int e = 0; e < BATCH; ++e) v[e] = c0 + e < n_chunks ? p[(size_t)(c0 + e) * stride] : make_float2(-1e30f, 0.0f);
-    float top = M;
+    for (int e = 0; e < 8; ++e) v[e] = c0 + e < n_chunks ? p[(size_t)(c0 + e) * stride] : make_float2(-1e30f, 0.0f);
+    merge_eight(v, M, L);
+  }
+  return (M + __log2f(L)) * kLn2;
+}
+// The same of partials that other workgroups of the launch have left; these loads take a microsecond, so 32 are in flight.
+__device__ __forceinline__ float merge_partials_across(const float2 *p, int n_chunks, int stride) {
+  constexpr int AHEAD = 32;
+  float M = -1e30f, L = 0.0f;
+  for (int c0 = 0; c0 < n_chunks; c0 += AHEAD) {
+    float2 v[AHEAD];
 #pragma unroll
-    for (int e = 0; e < BATCH; ++e) top = fmaxf(top, v[e].x);
-    L *= __builtin_amdgcn_exp2f(M - top);
+    for (int b = 0; b < AHEAD; b += 8) {
+      if (c0 + b >= n_chunks) continue;
 #pragma unroll
-    for (int e = 0; e < BATCH; ++e) L += v[e].y * __builtin_amdgcn_exp2f(v[e].x - top);
-    M = top;
+      for (int e = b; e < b + 8; ++e)
+        v[e] = __builtin_bit_cast(float2, load_across(reinterpret_cast<const uint64_t *>(p + (size_t)min(c0 + e, n_chunks - 1) * stride)));
+    }
+#pragma unroll
+    for (int b = 0; b < AHEAD; b += 8) {
+      if (c0 + b >= n_chunks) continue;
+#pragma unroll
+      for (int e = b; e < b + 8; ++e)
+        if (c0 + e >= n_chunks) v[e] = make_float2(-1e30f, 0.0f);
+      merge_eight(v + b, M, L);
+    }
   }
   return (M + __log2f(L)) * kLn2;
 }
@@ -793,6 +823,10 @@ struct Staged {
     } else {
       wait_vm<0>();
     }
+    read_tail(wr, ring, t, shift, m, hh, kf);
+    kcur += tile_stride;
+  }
+  __device__ __forceinline__ void read_tail(const WaveRange &wr, Ring &ring, int t, int shift, int m, int hh, chunk_t (&kf)[NCH]) {
     if (t < wr.n_whole) {
       read(kf, wr, ring, t % kRing);
     } else {
@@ -802,7 +836,6 @@ struct Staged {
       for (int c = 0; c < NCH; ++c)
         kf[c] = *reinterpret_cast<const chunk_t *>(ring[wr.wave][t % kRing] + image_offset<G>(row, c + NCH * hh));
     }
-    kcur += tile_stride;
   }
 };
 
@@ -1629,6 +1662,239 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
 }
 
 // ---------------------------------------------------------------------------------------------
+// Both passes of a fused call in one launch, for ranges that fit the ring: the key tiles stay in LDS between the passes. What a short
+// call takes is launches, the way of the first loads and the fetch of code, not bytes or arithmetic; here the second pass has
+// neither a launch nor loads of its own, and as a range is four tiles at most, nothing is unrolled over them.
+//
+// The workgroups of a unit exchange their row sums: each leaves its own and a mark (behind them, when they have arrived), waits until
+// it sees all marks, and merges all sums. No workgroup depends on another one's progress: after a.wait it makes the sums that are
+// missing itself, from the keys in memory, the same ones to the last bit (a launch whose workgroups do not all find a CU, because
+// another stream's kernel holds some, would wait for workgroups that wait for it otherwise). Who has read all sums leaves a second
+// mark; who sees all of those at its end takes all marks back, and the last one to leave its own does see them.
+// us per layer, two launches / one, keys in the memory-side cache before the call and from HBM: 4096 keys, 32/32 heads 27.4 / 25.1, 31.4 /
+// 26.0; 8192, 32/8 27.3 / 25.0, 29.7 / 25.7; 4096, batch 4, 32/8 35.9 / 29.7, 37.2 / 30.1; 1000, 32/8 21.8 / 20.5, 21.9 / 21.1. The keys are
+// streamed, since nothing reads them again (kept in the cache 1 to 5 % faster if they were there before, 2 to 7 % slower if not).
+// ---------------------------------------------------------------------------------------------
+template <int DT, int DH, int NQ, int WT, bool UTIL>
+__global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArgs a) {
+  static_assert(DT == CKV_BF16 && NQ % WT == 0 && NQ <= kShortTiles, "whole heads");
+  static_assert(kRing == 4, "the waits below");
+  using G = Geom<DT, DH>;
+  constexpr int NCH = G::NCH, NH = NQ / WT, ROWS = NQ * kTile;
+  static_assert(NQ <= kShiftInRegisters, "row shifts");
+  typedef Staged<DT, DH, NQ, true> Scan;
+  __shared__ __attribute__((aligned(1024))) typename Scan::Ring ring;
+  __shared__ __attribute__((aligned(1024))) char s_halo_keys[UTIL ? 2 * kHaloKeys * G::ROW : 16];
+  __shared__ __attribute__((aligned(16))) float s_halo[UTIL ? NH * kUtilHead : 4];
+  __shared__ __attribute__((aligned(16))) float s_stage[kScoreWaves][UTIL ? NH * kUtilRow : 2 * ROWS];  // first: the waves' row sums
+  __shared__ __attribute__((aligned(16))) float s_shift[ROWS];
+  __shared__ uint64_t s_missing[kComputeUnits / kWave];
+  static_assert(sizeof(s_stage) >= kScoreWaves * ROWS * sizeof(float2), "row sums pass through the stage");
+  const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
+  const BlockCoord bc = decode_block(a);
+  const WaveRange wr = wave_range(a, bc, a.T);
+  const int n_sums = wave_range(a, bc, UTIL ? a.P : a.T).n_all;  // tiles whose column sums are wanted
+
+  Scan st;
+  chunk_t qf[NQ][NCH];
+  int jrow[NQ];
+  constexpr int HALO_TILES = !UTIL ? 1 : WT * ((NH + kScoreWaves - 1) / kScoreWaves);  // as in colsum_lds_kernel
+  const auto halo_head = [&](int u) { return wr.wave + u / WT * kScoreWaves; };
+  f32x16 halo[HALO_TILES];
+  st.start(
+      a, bc, wr, ring, lane, m, hh, qf, jrow,
+      [&] {
+        if constexpr (!UTIL) return;
+        const int begin = bc.chunk * kScoreWaves * a.keys_per_wave;
+        if (wr.wave == 0)
+          dma_halo<G>(a.k + bc.b * a.ks_b + bc.g * a.ks_h, a.ks_t, begin, begin + kScoreWaves * a.keys_per_wave, a.T, lane,
+                      (uint32_t)(uintptr_t)s_halo_keys);
+      },
+      [&] {
+        if constexpr (!UTIL) return;
+        int hoff[NCH];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) hoff[c] = image_offset<G>(m & (kUtilHead - 1), c + NCH * hh);
+        chunk_t kh[NCH], qh[NCH];
+        read_image<G>(kh, s_halo_keys, hoff);
+#pragma unroll
+        for (int u = 0; u < HALO_TILES; ++u) {
+          if (halo_head(u) >= NH) continue;
+          const int tile = halo_head(u) * WT + u % WT;
+          read_image<G>(qh, Scan::image_of_tile(ring, tile), st.roff);
+          if (bc.grp * NQ + tile >= a.n_tiles || tile % WT * kTile + m >= a.W) {
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) qh[c] = chunk_t{0u, 0u, 0u, 0u};
+          }
+          mma_chain<DT, NCH>(halo[u], qh, kh);
+        }
+      });
+
+  // -- pass 1: the rows' (max, sum) over a range, left for the unit's workgroups
+  float2 *const parts = a.part + (size_t)bc.unit * a.n_chunks * ROWS;
+  chunk_t kf[NCH];
+  f32x16 acc[2];
+  const auto row_sums = [&](const WaveRange &range, int chunk, auto read_tile) {
+    float rm[NQ], rl[NQ];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      rm[i] = -1e30f;
+      rl[i] = 0.0f;
+    }
+    for (int t = 0; t < range.n_all; ++t) {
+      const int t0 = range.t_begin + t * kTile;
+      read_tile(t, t0);
+      mma_chain<DT, NCH>(acc[0], kf, qf[0]);
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) {
+        if (i + 1 < NQ) mma_chain<DT, NCH>(acc[(i + 1) & 1], kf, qf[i + 1]);
+        if (t >= range.n_full) {  // uniform: the window's rows see no later keys, and there are none beyond T
+          const int limit = jrow[i] >= 0 ? a.P + jrow[i] : -1;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i & 1][r] = acc_row(r, hh) > limit - t0 ? -INFINITY : acc[i & 1][r];
+        }
+        rowstats_update<false>(acc[i & 1], a.c2, 0, hh, 0, rm[i], rl[i]);
+      }
+    }
+    float2 *sums = reinterpret_cast<float2 *>(&s_stage[0][0]);
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const float om = __shfl_xor(rm[i], 32), ol = __shfl_xor(rl[i], 32);
+      merge_stats(rm[i], rl[i], om, ol);
+      if (hh == 0) sums[range.wave * ROWS + i * kTile + m] = make_float2(rm[i], rl[i]);
+    }
+    __syncthreads();
+    if (threadIdx.x < ROWS) {
+      float2 s = sums[threadIdx.x];
+#pragma unroll
+      for (int w = 1; w < kScoreWaves; ++w) merge_stats(s.x, s.y, sums[w * ROWS + threadIdx.x].x, sums[w * ROWS + threadIdx.x].y);
+      store_across(reinterpret_cast<uint64_t *>(parts + chunk * ROWS + threadIdx.x), __builtin_bit_cast(uint64_t, s));
+    }
+    wait_vm<0>();  // what was left has arrived
+    __syncthreads();
+  };
+  if (wr.n_all == kRing) st.prefetch(0, wr.n_whole, kRing - 1);
+  row_sums(wr, bc.chunk, [&](int t, int t0) {
+    switch ((wr.n_all == kRing ? kRing - 1 : kRing - 2) - t) {  // tiles asked for behind this one
+      case 3: wait_vm<3 * G::NDMA>(); break;
+      case 2: wait_vm<2 * G::NDMA>(); break;
+      case 1: wait_vm<G::NDMA>(); break;
+      default: wait_vm<0>();
+    }
+    st.read_tail(wr, ring, t, t0 - (a.T - kTile), m, hh, kf);
+  });
+  tag_t *const left = a.marks + (size_t)bc.unit * a.n_chunks, *const seen = left + gridDim.x;
+  if (threadIdx.x == 0) store_across(left + bc.chunk, a.tag);
+  if (UTIL && bc.g == 0 && bc.chunk == 0 && wr.wave == kScoreWaves - 1) write_tau_and_budgets(a.bud, bc.b, lane);
+
+  // -- the others' sums
+  if (wr.wave == 0) {
+    const uint64_t start = __builtin_amdgcn_s_memrealtime();
+    for (;;) {
+      const uint64_t now = __builtin_amdgcn_s_memrealtime();
+      bool some = false;
+      for (int c0 = 0; c0 < a.n_chunks; c0 += kWave) {
+        const int c = c0 + lane;
+        const uint64_t missing = __ballot(c < a.n_chunks && load_across(left + c) != a.tag);
+        if (lane == 0) s_missing[c0 / kWave] = missing;
+        some |= missing != 0;
+      }
+      if (!some || now - start >= a.wait) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  __syncthreads();
+  for (int c0 = 0; c0 < a.n_chunks; c0 += kWave) {
+    const uint64_t missing = s_missing[c0 / kWave];
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)missing), hi = __builtin_amdgcn_readfirstlane((uint32_t)(missing >> 32));
+    for (uint64_t rest = (uint64_t)hi << 32 | lo; rest; rest &= rest - 1) {
+      BlockCoord other = bc;
+      other.chunk = c0 + __ffsll((long long)rest) - 1;
+      row_sums(wave_range(a, other, a.T), other.chunk, [&](int, int t0) {
+        const char *row = st.kbase + (int64_t)min(t0 + m, a.T - 1) * a.ks_t;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) kf[c] = *reinterpret_cast<const chunk_t *>(row + (c + NCH * hh) * 16);
+      });
+    }
+  }
+  if (threadIdx.x < ROWS) {
+    const int tile = bc.grp * NQ + (int)threadIdx.x / kTile;
+    const bool valid = tile < a.n_tiles && tile % WT * kTile + (int)threadIdx.x % kTile < a.W;
+    const float lse = merge_partials_across(parts + threadIdx.x, a.n_chunks, ROWS);
+    s_shift[threadIdx.x] = valid ? lse * -kLog2e : kNoWeight;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) store_across(seen + bc.chunk, a.tag);
+
+  // -- pass 2
+  RowShift<true> shift[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) shift[i].set(s_shift + i * kTile, a.c2, m, hh);
+  if constexpr (UTIL) {
+#pragma unroll
+    for (int u = 0; u < HALO_TILES; u += WT) {
+      if (halo_head(u) >= NH) continue;
+      float x = 0.0f;
+#pragma unroll
+      for (int e = 0; e < WT; ++e) {
+        RowShift<true> own;
+        own.set(s_shift + (halo_head(u) * WT + e) * kTile, a.c2, m, hh);
+        const float w = colsum_weights<false>(halo[u + e], own, a.c2, hh, 0);
+        x = e == 0 ? w : x + w;
+      }
+      const float tot = (x + __shfl_xor(x, 32)) * a.norm;
+      if (lane < kUtilHead) s_halo[halo_head(u) * kUtilHead + lane] = tot;
+    }
+  }
+  const __amdgpu_buffer_rsrc_t rsrc_u = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(UTIL ? a.utility + (size_t)bc.b * a.Hkv * a.P : a.scores), 0, UTIL ? a.Hkv * a.P * 4 : 0, 0x00020000);
+  float wgt[NH];
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    const int head = bc.g * a.G + (bc.grp * NQ) / WT + h;
+    wgt[h] = UTIL && head < a.Hq ? a.w_row[head] : 0.0f;
+  }
+  float *stage = s_stage[wr.wave];
+  for (int t = 0; t < n_sums; ++t) {
+    const int kt = wr.t_begin + t * kTile + m;  // this lane's key
+    st.read_tail(wr, ring, t, kt - m - (a.T - kTile), m, hh, kf);
+    float cs[NQ];
+    mma_chain<DT, NCH>(acc[0], qf[0], kf);
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      if (i + 1 < NQ) mma_chain<DT, NCH>(acc[(i + 1) & 1], qf[i + 1], kf);
+      // utilities: keys of the prefix, which every row sees
+      cs[i] = colsum_weights<!UTIL>(acc[i & 1], shift[i], a.c2, hh, kt - a.P - i % WT * kTile);
+    }
+    if constexpr (UTIL) stage_column_sums<NQ, WT, kUtilRow>(cs, a.norm, stage + kUtilCarry, t * kTile + m, hh);
+    else store_column_sums<NQ>(a, bc, cs, WT, kt, hh);
+  }
+  if constexpr (UTIL) __syncthreads();
+  // The second marks, asked for when the workgroup's own one has arrived.
+  constexpr int MARKS = kComputeUnits / kWave;
+  bool all = true;
+  if (wr.wave == 0) {
+    wait_vm<0>();
+#pragma unroll
+    for (int e = 0; e < MARKS; ++e)
+      if (e * kWave + lane < a.n_chunks) all &= load_across(seen + e * kWave + lane) == a.tag;
+  }
+  if (UTIL && n_sums > 0) {
+    const int w = wr.wave;
+    const float *prev = w > 0 ? s_stage[w - 1] + kUtilCarry + a.keys_per_wave - kHaloKeys : s_halo;
+    const float *next = w == kScoreWaves - 1 ? s_halo + kHaloKeys : s_stage[w + 1] + kUtilCarry;
+    finish_utility<NQ, WT>(a, bc, wr, 0, stage, s_halo, prev, w > 0 ? kUtilRow : kUtilHead, next,
+                           w == kScoreWaves - 1 ? kUtilHead : kUtilRow, lane, rsrc_u, wgt);
+  }
+  if (wr.wave == 0 && __ballot(!all) == 0)
+    for (int c = lane; c < a.n_chunks; c += kWave) {
+      store_across(left + c, (tag_t)0);
+      store_across(seen + c, (tag_t)0);
+    }
+  wait_vm<0>();
+}
+
+// ---------------------------------------------------------------------------------------------
 // Launch
 // ---------------------------------------------------------------------------------------------
 // Bytes of K up to which the first pass of a call leaves the keys in the memory-side cache (256 MiB) for the second. us per
@@ -1693,6 +1959,30 @@ static void launch_colsum(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 bl
   }
 }
 
+template <int DT, int DH, int NQ, int WT>
+static void launch_short_wt(const ScoreArgs &a, dim3 grid, dim3 block, hipStream_t stream) {
+  if constexpr (NQ % WT == 0) {
+    if constexpr (WT <= 2) {
+      if (a.utility) {
+        hipLaunchKernelGGL((scan_short_kernel<DT, DH, NQ, WT, true>), grid, block, 0, stream, a);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((scan_short_kernel<DT, DH, NQ, WT, false>), grid, block, 0, stream, a);
+  }
+}
+template <int DT, int DH, int NQ>
+static void launch_short(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 block, hipStream_t stream) {
+  if constexpr (DT == CKV_BF16 && NQ <= kShortTiles) {
+    switch (s.WT) {  // NQ is a multiple of WT (whole heads per wave)
+      case 1: launch_short_wt<DT, DH, NQ, 1>(a, grid, block, stream); break;
+      case 2: launch_short_wt<DT, DH, NQ, 2>(a, grid, block, stream); break;
+      case 3: launch_short_wt<DT, DH, NQ, 3>(a, grid, block, stream); break;
+      default: launch_short_wt<DT, DH, NQ, 4>(a, grid, block, stream);
+    }
+  }
+}
+
 // Launches for the query-tile counts NQ_LO..NQ_HI (the instantiations are spread over several translation
 // units, each covering a range, to keep compile times apart).
 template <int DT, int DH, int NQ_LO, int NQ_HI>
@@ -1703,6 +1993,10 @@ static hipError_t launch_scores_t(const Shape &s, ScoreArgs &a, bool need_lse, b
   case NQ:                                                                         \
     if constexpr (NQ >= NQ_LO && NQ <= NQ_HI) {                                    \
       a.lse_from_part = need_lse && need_scores;                                   \
+      if (a.marks) {                                                               \
+        launch_short<DT, DH, NQ>(s, a, grid, block, stream);                       \
+        break;                                                                     \
+      }                                                                            \
       if (need_lse) launch_rowstats<DT, DH, NQ>(s, a, grid, block, stream);        \
       if (need_scores) launch_colsum<DT, DH, NQ>(s, a, grid, block, stream);       \
       break;                                                                       \

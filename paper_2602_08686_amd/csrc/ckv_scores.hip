@@ -8,7 +8,7 @@ namespace ckv {
 hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Workspace &w, const void *q,
                                 const void *k, const float *lse_in, float *lse_out, float *scores,
                                 char *ws, hipStream_t stream, const UtilityFusion *fuse, const void *v,
-                                float *ratio) {
+                                float *ratio, const Exchange &exchange) {
   ScoreArgs a;
   a.q = (const char *)q;
   a.k = (const char *)k;
@@ -41,6 +41,9 @@ hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Works
   a.vs_h = p->v_stride[1] * s.esize;
   a.vs_t = p->v_stride[2] * s.esize;
   a.vnorm_blocks = vnorm_blocks_per_unit(s);
+  a.marks = exchange.marks;
+  a.tag = a.marks ? launch_tag() : 0;
+  a.wait = exchange.wait;
   a.inv_kernel = fuse ? fuse->inv_kernel : 1.0f;
   a.inv_kernel_rest = fuse ? fuse->inv_kernel_rest : 0.0f;
   const bool need_lse = lse_in == nullptr, need_scores = scores != nullptr;

@@ -1,0 +1,117 @@
+"""Both scan passes of a short fused call in one launch: ranges of one to four key tiles per wave, with and without keys that fill them,
+against the two launches (a workspace without room for the marks); workgroups that make the missing row sums themselves give
+the same bits as workgroups that wait for them; marks of an earlier call, or anything else, in the workspace do no harm."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2602_08686_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+SHAPES = [  # batch, query heads, KV heads, d, T, W, pooling, kernel
+    (1, 32, 32, 128, 4096, 32, B.POOL_MAX, 7), (1, 32, 8, 128, 4097, 32, B.POOL_AVG, 7), (2, 32, 8, 64, 1000, 17, B.POOL_AVG, 5),
+    (1, 8, 8, 128, 33, 1, B.POOL_NONE, 1), (1, 4, 1, 128, 20, 4, B.POOL_MAX, 3), (3, 6, 2, 128, 511, 32, B.POOL_AVG, 3), (1, 4, 2, 64, 3001, 64, B.POOL_MAX, 7),
+    (1, 4, 4, 128, 16384, 32, B.POOL_AVG, 7), (1, 2, 1, 128, 16383, 40, B.POOL_AVG, 7), (16, 8, 8, 128, 777, 32, B.POOL_MAX, 5),
+    (1, 4, 1, 128, 10000, 32, B.POOL_AVG, 7), (1, 3, 1, 64, 11111, 32, B.POOL_MAX, 3),   # 40 workgroups and more of a unit
+]
+
+
+def _call(shape, seed):
+    batch, hq, kv, d, T, W, pool, kernel = shape
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    q = torch.randn(batch, hq, W, d, generator=g, device=DEV).bfloat16()
+    k = (torch.randn(batch, kv, T, d, generator=g, device=DEV) * (1 + 3 * torch.rand(batch, kv, T, 1, generator=g, device=DEV))).bfloat16()
+    w_head = 0.5 + torch.rand(1, hq, generator=g, device=DEV)
+    p = B.make_params(batch=batch, n_q_heads=hq, n_kv_heads=kv, head_dim=d, seq_len=T, window=W, dtype=torch.bfloat16, pool=pool,
+                      pool_kernel=kernel, budget=W, cap=T)
+    return p, q, k, w_head
+
+
+def _ptr(t):
+    return ctypes.c_void_p(t.data_ptr())
+
+
+def _run(p, q, k, w_head, ws, nbytes, wait=None):
+    lib = B.load()
+    n = p.batch * p.n_kv_heads
+    u = torch.full((n, max(p.seq_len - p.window, 1)), float("nan"), device=DEV)
+    scratch = torch.empty(p.batch, p.n_q_heads, p.seq_len, device=DEV)
+    budget, tau = torch.empty(n, dtype=torch.int32, device=DEV), torch.full((p.batch,), float("nan"), device=DEV)
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if wait is None:
+        st = lib.ckv_window_utility(ctypes.byref(p), _ptr(q), _ptr(k), None, None, _ptr(w_head), None, None, 0, 0, None, _ptr(scratch),
+                                    None, _ptr(u), _ptr(budget), _ptr(tau), _ptr(ws), nbytes, stream)
+    else:
+        call = lib.ckv_window_utility_wait
+        call.argtypes = [ctypes.POINTER(B.CkvParams)] + [ctypes.c_void_p] * 8 + [ctypes.c_size_t, ctypes.c_uint32, ctypes.c_void_p]
+        st = call(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(w_head), _ptr(scratch), _ptr(u), _ptr(budget), _ptr(tau), _ptr(ws), nbytes, wait, stream)
+    assert st == B.CKV_OK
+    torch.cuda.synchronize()
+    assert (tau == 0).all() and (budget == min(p.budget_per_kv_head, p.seq_len)).all()
+    return u
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
+def test_one_launch_matches_two(shape):
+    print("case", shape, flush=True)
+    p, q, k, w_head = _call(shape, 1)
+    whole = B.ckv_workspace_bytes(p)
+    ws = torch.full((whole,), 0x5A, dtype=torch.uint8, device=DEV)
+    small = whole - 256   # without room for all marks the call takes its two launches
+    two = _run(p, q, k, w_head, ws, small)
+    one = _run(p, q, k, w_head, ws, whole)
+    # the same sums in the same order but for what is finished behind the rounds: roundings of exponents of a few tens
+    torch.testing.assert_close(one, two, rtol=1e-5, atol=0)
+    for wait in (0, 1, 3000):
+        ws.random_(0, 256)
+        assert torch.equal(_run(p, q, k, w_head, ws, whole, wait), one), wait
+
+
+@pytest.mark.parametrize("shape", SHAPES + [(1, 1, 1, 128, 2000, 100, B.POOL_NONE, 1), (1, 2, 2, 64, 5000, 128, B.POOL_NONE, 1)],
+                         ids=lambda s: "-".join(map(str, s)))
+def test_scores_in_one_launch_match_two(shape):
+    print("case", shape, flush=True)
+    p, q, k, _ = _call(shape, 3)
+    ws = torch.full((B.ckv_workspace_bytes(p),), 0xA5, dtype=torch.uint8, device=DEV)
+    outs = []
+    for part in (ws[:-256], ws, ws):
+        scores = torch.full((p.batch, p.n_q_heads, p.seq_len), float("nan"), device=DEV)
+        B.ckv_window_scores(p, q, k, None, None, scores, None, part)
+        outs.append(scores)
+    torch.testing.assert_close(outs[1], outs[0], rtol=1e-5, atol=1e-30)
+    assert torch.equal(outs[1], outs[2])
+    torch.testing.assert_close(outs[1].double().sum(-1), torch.full((p.batch, p.n_q_heads), float(p.seq_len), dtype=torch.float64, device=DEV),
+                               rtol=1e-4, atol=0)
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1], SHAPES[5]], ids=lambda s: "-".join(map(str, s)))
+def test_replays_with_other_inputs(shape):
+    """A replayed launch has the marks' tag of the first one: none of them may be left."""
+    p, q, k, w_head = _call(shape, 1)
+    ws = torch.zeros(B.ckv_workspace_bytes(p), dtype=torch.uint8, device=DEV)
+    n = p.batch * p.n_kv_heads
+    u = torch.empty(n, p.seq_len - p.window, device=DEV)
+    scratch = torch.empty(p.batch, p.n_q_heads, p.seq_len, device=DEV)
+    budget, tau = torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(p.batch, device=DEV)
+
+    def call():
+        B.ckv_window_utility(p, q, k, None, None, w_head, None, None, 0, 0, None, scratch, None, u, budget, tau, ws)
+
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(3):
+            call()
+    for seed in range(2, 7):
+        _, q2, k2, _ = _call(shape, seed)
+        q.copy_(q2)
+        k.copy_(k2)
+        u.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = u.clone()
+        assert torch.equal(got, _run(p, q, k, w_head, torch.zeros_like(ws), ws.numel()).view_as(got)), seed
