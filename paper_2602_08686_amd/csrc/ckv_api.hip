@@ -140,16 +140,16 @@ bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given) {
 // ones that start when they end). Up to four query tiles per wave: with eight 13 registers spill. 0.80 to 0.96 of the two launches'
 // time per layer over nine shapes of 1000 to 16384 keys (scan_short_kernel); without value norms, whose ratio needs a unit's sum of them, too.
 bool one_launch(const ckv_params *p, const Shape &s) {
-  return p->dtype == CKV_BF16 && s.n_groups == 1 && !(p->flags & (CKV_FLAG_VALUE_NORM | CKV_FLAG_GROUP_MASS)) && s.NQ <= kShortTiles &&
+  return p->dtype == CKV_BF16 && s.n_groups == 1 && s.NQ <= kShortTiles &&
          s.keys_per_wave <= kRing * kTile && (int64_t)s.Bz * s.Hkv * s.n_chunks <= kComputeUnits;
 }
 
-// The upper bits are those of a negative NaN, which no sum, position or key ends up as; the rest counts launches from the
+// Even. The upper bits are those of a negative NaN, which no sum, position or key ends up as; the rest counts launches from the
 // time the process began, in steps that touch all bits.
 tag_t launch_tag() {
   static std::atomic<uint64_t> count{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count()};
   const uint64_t mixed = count.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;
-  return 0xFFF8000000000000ull | mixed >> 13;
+  return 0xFFF8000000000000ull | mixed >> 14 << 1;
 }
 
 void layout(const ckv_params *p, const Shape &s, Workspace *w) {
@@ -170,10 +170,6 @@ void layout(const ckv_params *p, const Shape &s, Workspace *w) {
   // of a length that is no multiple of four: nothing for the selection, which takes them with any workspace).
   w->least = align256(off + (s.P % 4 == 0 ? select_split_bytes(s) : 0));
   off = align256(off + w->select_bytes);
-  // behind what calls asked for before there were marks: with less, the scan is two launches
-  w->marks_off = off;
-  w->marks_bytes = one_launch(p, s) ? 2 * units * (size_t)s.n_chunks * sizeof(tag_t) : 0;
-  off = align256(off + w->marks_bytes);
   w->total = off;
 }
 
@@ -199,9 +195,13 @@ extern "C" size_t ckv_workspace_bytes(const ckv_params *params) {
 // are there within 2 us where all run at once, and come late only where another kernel holds CUs.
 constexpr uint32_t kExchangeWait = 3000;
 
-static Exchange exchange_of(const Workspace &w, const float *lse, void *workspace, size_t workspace_bytes, uint32_t wait) {
+// The marks lie where a call that makes the normalisers and uses them leaves its workspace alone, in the place for those: four
+// bytes for each row of a unit's heads against eight for each of its workgroups. Where that is not room enough, two launches.
+static Exchange exchange_of(const ckv_params *p, const Shape &s, const Workspace &w, const float *lse, void *workspace, uint32_t wait) {
   Exchange e;
-  if (w.marks_bytes && !lse && workspace_bytes >= w.marks_off + w.marks_bytes) e.marks = (tag_t *)((char *)workspace + w.marks_off);
+  if (!lse && !(p->flags & (CKV_FLAG_VALUE_NORM | CKV_FLAG_GROUP_MASS)) && one_launch(p, s) &&
+      (size_t)s.Bz * s.Hkv * s.n_chunks * sizeof(tag_t) <= w.vsum_off - w.lse_off)
+    e.marks = (tag_t *)((char *)workspace + w.lse_off);
   e.wait = wait;
   return e;
 }
@@ -222,7 +222,7 @@ static ckv_status scores_of(const ckv_params *params, const Shape &s, const Work
       launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;
   if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores, (char *)workspace, stream, nullptr, v,
-                           vn ? vnorm_ratio : nullptr, exchange_of(w, lse, workspace, workspace_bytes, kExchangeWait)) != hipSuccess)
+                           vn ? vnorm_ratio : nullptr, exchange_of(params, s, w, lse, workspace, kExchangeWait)) != hipSuccess)
     return CKV_EHIP;
   return CKV_OK;
 }
@@ -366,7 +366,7 @@ static ckv_status utility_of(const ckv_params *params, const Shape &s, const Wor
   const ckv_status st = workspace_ok(w, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
   float *ratio = vn ? vnorm_ratio : nullptr;
-  const Exchange exchange = exchange_of(w, lse, workspace, workspace_bytes, wait);
+  const Exchange exchange = exchange_of(params, s, w, lse, workspace, wait);
   if (vn && !norms_in_scan(params, s, lse != nullptr) &&
       launch_value_norm(params, s, w, v, ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;

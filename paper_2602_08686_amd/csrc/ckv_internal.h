@@ -139,7 +139,6 @@ struct Workspace {
   size_t lse_off, lse_bytes;     // float  [Bz][Hq][W]
   size_t vsum_off, vsum_bytes;   // float  [units][vnorm blocks] partial sums of value norms
   size_t select_off, select_bytes;  // the long selection's: slices' pairs, or the split's histograms, counts and thresholds
-  size_t marks_off, marks_bytes;    // tag_t [2][workgroups] of the scan's one-launch form
   size_t least;  // what a call has to be given: less than total where total has room for the slices' pairs
   size_t total;
 };
@@ -170,10 +169,10 @@ struct UtilityFusion {
   float inv_kernel, inv_kernel_rest;  // 1 / kernel: the largest float that is not above it, and what that leaves
   BudgetArgs bud;
 };
-// Both passes as one launch, whose workgroups keep their keys on chip and exchange the row sums: where one_launch() says so and
-// there are marks.
+// Both passes as one launch, whose workgroups keep their keys on chip and exchange the row sums: where the shape allows it
+// (one_launch) and the call gives marks.
 struct Exchange {
-  tag_t *marks = nullptr;  // tag_t [2][workgroups], or null: two launches
+  tag_t *marks = nullptr;  // one for each workgroup, or null: two launches
   uint32_t wait = 0;       // how long a workgroup waits for another's part of the row sums, in units of 10 ns
 };
 bool one_launch(const ckv_params *p, const Shape &s);

@@ -56,7 +56,7 @@ struct ScoreArgs {
   float inv_kernel, inv_kernel_rest;  // 1 / pool_kernel in two terms
   BudgetArgs bud;
   // one-launch form only
-  tag_t *marks;  // [2][workgroups]: row sums left, row sums read
+  tag_t *marks;  // [workgroups]: the tag when the workgroup has left its row sums, tag + 1 when it has read all of its unit's
   tag_t tag;
   uint32_t wait;  // units of 10 ns
 };
@@ -1669,8 +1669,8 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
 // The workgroups of a unit exchange their row sums: each leaves its own and a mark (behind them, when they have arrived), waits until
 // it sees all marks, and merges all sums. No workgroup depends on another one's progress: after a.wait it makes the sums that are
 // missing itself, from the keys in memory, the same ones to the last bit (a launch whose workgroups do not all find a CU, because
-// another stream's kernel holds some, would wait for workgroups that wait for it otherwise). Who has read all sums leaves a second
-// mark; who sees all of those at its end takes all marks back, and the last one to leave its own does see them.
+// another stream's kernel holds some, would wait for workgroups that wait for it otherwise). Who has read all sums changes its
+// mark; who sees all of them changed at its end takes them back, and the last one to change its own does see that.
 // us per layer, two launches / one, keys in the memory-side cache before the call and from HBM: 4096 keys, 32/32 heads 27.4 / 25.1, 31.4 /
 // 26.0; 8192, 32/8 27.3 / 25.0, 29.7 / 25.7; 4096, batch 4, 32/8 35.9 / 29.7, 37.2 / 30.1; 1000, 32/8 21.8 / 20.5, 21.9 / 21.1. The keys are
 // streamed, since nothing reads them again (kept in the cache 1 to 5 % faster if they were there before, 2 to 7 % slower if not).
@@ -1783,8 +1783,8 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
     }
     st.read_tail(wr, ring, t, t0 - (a.T - kTile), m, hh, kf);
   });
-  tag_t *const left = a.marks + (size_t)bc.unit * a.n_chunks, *const seen = left + gridDim.x;
-  if (threadIdx.x == 0) store_across(left + bc.chunk, a.tag);
+  tag_t *const marks = a.marks + (size_t)bc.unit * a.n_chunks;
+  if (threadIdx.x == 0) store_across(marks + bc.chunk, a.tag);
   if (UTIL && bc.g == 0 && bc.chunk == 0 && wr.wave == kScoreWaves - 1) write_tau_and_budgets(a.bud, bc.b, lane);
 
   // -- the others' sums
@@ -1795,7 +1795,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
       bool some = false;
       for (int c0 = 0; c0 < a.n_chunks; c0 += kWave) {
         const int c = c0 + lane;
-        const uint64_t missing = __ballot(c < a.n_chunks && load_across(left + c) != a.tag);
+        const uint64_t missing = __ballot(c < a.n_chunks && (load_across(marks + c) | 1) != (a.tag | 1));
         if (lane == 0) s_missing[c0 / kWave] = missing;
         some |= missing != 0;
       }
@@ -1824,7 +1824,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
     s_shift[threadIdx.x] = valid ? lse * -kLog2e : kNoWeight;
   }
   __syncthreads();
-  if (threadIdx.x == 0) store_across(seen + bc.chunk, a.tag);
+  if (threadIdx.x == 0) store_across(marks + bc.chunk, a.tag | 1);
 
   // -- pass 2
   RowShift<true> shift[NQ];
@@ -1870,14 +1870,14 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
     else store_column_sums<NQ>(a, bc, cs, WT, kt, hh);
   }
   if constexpr (UTIL) __syncthreads();
-  // The second marks, asked for when the workgroup's own one has arrived.
+  // All marks, asked for when the workgroup's own one has arrived as it stays.
   constexpr int MARKS = kComputeUnits / kWave;
   bool all = true;
   if (wr.wave == 0) {
     wait_vm<0>();
 #pragma unroll
     for (int e = 0; e < MARKS; ++e)
-      if (e * kWave + lane < a.n_chunks) all &= load_across(seen + e * kWave + lane) == a.tag;
+      if (e * kWave + lane < a.n_chunks) all &= load_across(marks + e * kWave + lane) == (a.tag | 1);
   }
   if (UTIL && n_sums > 0) {
     const int w = wr.wave;
@@ -1887,10 +1887,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
                            w == kScoreWaves - 1 ? kUtilHead : kUtilRow, lane, rsrc_u, wgt);
   }
   if (wr.wave == 0 && __ballot(!all) == 0)
-    for (int c = lane; c < a.n_chunks; c += kWave) {
-      store_across(left + c, (tag_t)0);
-      store_across(seen + c, (tag_t)0);
-    }
+    for (int c = lane; c < a.n_chunks; c += kWave) store_across(marks + c, (tag_t)0);
   wait_vm<0>();
 }
 

@@ -1,5 +1,5 @@
-"""Both scan passes of a short fused call in one launch: ranges of one to four key tiles per wave, with and without keys that fill them,
-against the two launches (a workspace without room for the marks); workgroups that make the missing row sums themselves give
+"""Both scan passes of a short call in one launch: ranges of one to four key tiles per wave, with and without keys that fill them,
+against two launches (the normalisers by a call of their own, then a call that is given them); workgroups that make the missing row sums themselves give
 the same bits as workgroups that wait for them; marks of an earlier call, or anything else, in the workspace do no harm."""
 import ctypes
 
@@ -34,7 +34,13 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
 
-def _run(p, q, k, w_head, ws, nbytes, wait=None):
+def _lse(p, q, k, ws):
+    lse = torch.empty(p.batch, p.n_q_heads, p.window, device=DEV)
+    B.ckv_window_lse(p, q, k, lse, ws)
+    return lse
+
+
+def _run(p, q, k, w_head, ws, nbytes, wait=None, lse=None):
     lib = B.load()
     n = p.batch * p.n_kv_heads
     u = torch.full((n, max(p.seq_len - p.window, 1)), float("nan"), device=DEV)
@@ -42,7 +48,7 @@ def _run(p, q, k, w_head, ws, nbytes, wait=None):
     budget, tau = torch.empty(n, dtype=torch.int32, device=DEV), torch.full((p.batch,), float("nan"), device=DEV)
     stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     if wait is None:
-        st = lib.ckv_window_utility(ctypes.byref(p), _ptr(q), _ptr(k), None, None, _ptr(w_head), None, None, 0, 0, None, _ptr(scratch),
+        st = lib.ckv_window_utility(ctypes.byref(p), _ptr(q), _ptr(k), None, None if lse is None else _ptr(lse), _ptr(w_head), None, None, 0, 0, None, _ptr(scratch),
                                     None, _ptr(u), _ptr(budget), _ptr(tau), _ptr(ws), nbytes, stream)
     else:
         call = lib.ckv_window_utility_wait
@@ -60,8 +66,7 @@ def test_one_launch_matches_two(shape):
     p, q, k, w_head = _call(shape, 1)
     whole = B.ckv_workspace_bytes(p)
     ws = torch.full((whole,), 0x5A, dtype=torch.uint8, device=DEV)
-    small = whole - 256   # without room for all marks the call takes its two launches
-    two = _run(p, q, k, w_head, ws, small)
+    two = _run(p, q, k, w_head, ws, whole, lse=_lse(p, q, k, ws))
     one = _run(p, q, k, w_head, ws, whole)
     # the same sums in the same order but for what is finished behind the rounds: roundings of exponents of a few tens
     torch.testing.assert_close(one, two, rtol=1e-5, atol=0)
@@ -77,9 +82,9 @@ def test_scores_in_one_launch_match_two(shape):
     p, q, k, _ = _call(shape, 3)
     ws = torch.full((B.ckv_workspace_bytes(p),), 0xA5, dtype=torch.uint8, device=DEV)
     outs = []
-    for part in (ws[:-256], ws, ws):
+    for lse in (_lse(p, q, k, ws), None, None):
         scores = torch.full((p.batch, p.n_q_heads, p.seq_len), float("nan"), device=DEV)
-        B.ckv_window_scores(p, q, k, None, None, scores, None, part)
+        B.ckv_window_scores(p, q, k, None, lse, scores, None, ws)
         outs.append(scores)
     torch.testing.assert_close(outs[1], outs[0], rtol=1e-5, atol=1e-30)
     assert torch.equal(outs[1], outs[2])
