@@ -424,6 +424,78 @@ __global__ void __launch_bounds__(NT) select_reg_kernel(SelectArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// Selection and gather of a layer in one launch, for budgets that are the same for every head. `parts` workgroups make the same
+// selection of a unit, which takes none of them longer than one of them (a chain of steps inside a workgroup, while most of the
+// chip is idle), and each writes and copies its share of the rows: blocks of BLOCK rows in turn, whose positions stay in LDS. The
+// gather's launch, and its way to count, index and row, are gone; what is left of it is the rows. us per layer, two launches / one: 4096
+// keys, 32/32 heads 25.1 / 24.4, 4096, 32/8 22.1 / 21.1, 1000, 32/8 20.5 / 19.0, 28000, 32/8 43.9 / 43.5, 30000, 32/8, 2048 rows 50.3 / 48.7. With
+// shares a head may have all rows of a batch element, which its own workgroups would take several times as long to move as the
+// gather, which deals them out.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPartBlocks = 4;  // of a part, at most: a thread has all its rows of K and V in flight
+struct KeepArgs {
+  SelectArgs a;
+  const char *k, *v;
+  char *k_out, *v_out;
+  int64_t ks_b, ks_h, ks_t, vs_b, vs_h, vs_t;  // bytes
+  int log_parts;
+};
+typedef __attribute__((ext_vector_type(4))) uint32_t row_piece_t;
+
+// LPR: 16-byte pieces of a row, one per lane
+template <int NK, int NT, int LPR>
+__global__ void __launch_bounds__(NT) keep_kernel(KeepArgs ka) {
+  constexpr int BLOCK = NT / LPR;
+  __shared__ SelectShared<NK, NT> sh;
+  __shared__ int s_rows[kPartBlocks * BLOCK];
+  const SelectArgs &a = ka.a;
+  const int parts = 1 << ka.log_parts, part = blockIdx.x & (parts - 1), unit = blockIdx.x >> ka.log_parts;
+  const int b = unit / a.Hkv, g = unit % a.Hkv;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float *u = a.utility + (size_t)unit * a.P;
+  const float tau = a.tau[b];
+  int key[NK];
+  load_keys<NK, NT>(u, a.P, 0, tau, key, tid);
+  const int kp = prefix_quota(a, unit);
+  int kept = 0;
+  if (kp > 0)
+    kept = select_keys<NK, NT>(
+        key, kp, sh, [&](int slot) { return key_of(u[slot], tau); },
+        [&](int rank, int slot, int) {
+          const int block = rank / BLOCK, of_part = block >> ka.log_parts;
+          if ((block & (parts - 1)) == part && of_part < kPartBlocks) s_rows[of_part * BLOCK + rank % BLOCK] = slot;
+        },
+        tid, lane, wave);
+  __syncthreads();
+  const int count = kept + a.W, local = tid / LPR, piece = tid % LPR * 16;
+  if (part == 0 && tid == 0) a.count[unit] = count;
+  const char *k = ka.k + b * ka.ks_b + g * ka.ks_h + piece, *v = ka.v + b * ka.vs_b + g * ka.vs_h + piece;
+  const size_t first = (size_t)unit * a.cap;
+  row_piece_t kk[kPartBlocks], vv[kPartBlocks];
+  int from[kPartBlocks];
+#pragma unroll
+  for (int e = 0; e < kPartBlocks; ++e) {
+    const int r = (e * parts + part) * BLOCK + local;
+    if (r < count) {
+      // held inside the row, whatever another stream writes over the utilities meanwhile
+      from[e] = r < kept ? min(max(s_rows[e * BLOCK + local], 0), a.P - 1) : a.P + r - kept;
+      kk[e] = *reinterpret_cast<const row_piece_t *>(k + (int64_t)from[e] * ka.ks_t);
+      vv[e] = *reinterpret_cast<const row_piece_t *>(v + (int64_t)from[e] * ka.vs_t);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < kPartBlocks; ++e) {
+    const int r = (e * parts + part) * BLOCK + local;
+    if (r < count) {
+      const size_t o = (first + r) * (LPR * 16) + piece;
+      *reinterpret_cast<row_piece_t *>(ka.k_out + o) = kk[e];
+      *reinterpret_cast<row_piece_t *>(ka.v_out + o) = vv[e];
+      if (piece == 0) a.idx[first + r] = from[e];
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Long rows in two launches. A slice of 8192 or 16384 positions per workgroup keeps its own kp best (what the unit keeps
 // is among them) as (key, position) pairs in the workspace, in position order, padded with "no candidate" to
 // a length that both kernels know from the budget; one workgroup per unit then selects among the slices' pairs.
@@ -923,9 +995,8 @@ static void launch_reg(const SelectArgs &a, int units, hipStream_t stream) {
   hipLaunchKernelGGL((select_reg_kernel<NK, NT>), dim3(units), dim3(NT), 0, stream, a);
 }
 
-hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utility,
-                         const int32_t *budget, const float *tau, int32_t *idx, int32_t *count,
-                         char *ws, size_t ws_bytes, hipStream_t stream) {
+static SelectArgs select_args(const ckv_params *p, const Shape &s, const float *utility, const int32_t *budget, const float *tau,
+                              int32_t *idx, int32_t *count) {
   SelectArgs a;
   a.utility = utility;
   a.budget = budget;
@@ -934,6 +1005,54 @@ hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utili
   a.count = count;
   a.Hkv = s.Hkv; a.T = s.T; a.W = s.W; a.P = s.P;
   a.cap = p->cap;
+  return a;
+}
+
+// Workgroups per unit for selection and gather in one launch, a power of two: one for each CU, and no more than have a block of
+// rows. Less than two, or more rows than those have in flight: not this form, which then gains nothing (us per layer, two launches / one:
+// 128 units, 512 rows, two parts 81.0 / 81.1, 64 units, 2048 rows 120.1 / 120.0).
+static int keep_parts(const ckv_params *p, const Shape &s) {
+  if (s.P > kOneLaunch || s.P < 1) return 0;
+  const int units = s.Bz * s.Hkv, rows = min(min(p->budget_per_kv_head, p->cap), s.T), lpr = s.d * s.esize / 16;
+  const int block = (s.P <= 4 * 256 ? 256 : s.P <= 8 * 512 ? 512 : kSelectThreads) / lpr;
+  int parts = 1;
+  while (2 * parts * units <= kComputeUnits && parts * block < rows) parts *= 2;
+  return parts >= 2 && rows <= parts * kPartBlocks * block ? parts : 0;
+}
+bool keeps_in_one_launch(const ckv_params *p, const Shape &s) { return keep_parts(p, s) > 0; }
+
+template <int NK, int NT>
+static void launch_keep_rows(const KeepArgs &ka, int lpr, dim3 grid, hipStream_t stream) {
+  if (lpr == 8) hipLaunchKernelGGL((keep_kernel<NK, NT, 8>), grid, dim3(NT), 0, stream, ka);
+  else if (lpr == 16) hipLaunchKernelGGL((keep_kernel<NK, NT, 16>), grid, dim3(NT), 0, stream, ka);
+  else hipLaunchKernelGGL((keep_kernel<NK, NT, 32>), grid, dim3(NT), 0, stream, ka);
+}
+
+hipError_t launch_keep(const ckv_params *p, const Shape &s, const float *utility, const int32_t *budget, const float *tau, const void *k,
+                       const void *v, int32_t *idx, int32_t *count, void *k_out, void *v_out, hipStream_t stream) {
+  KeepArgs ka;
+  ka.a = select_args(p, s, utility, budget, tau, idx, count);
+  ka.k = (const char *)k;
+  ka.v = (const char *)v;
+  ka.k_out = (char *)k_out;
+  ka.v_out = (char *)v_out;
+  ka.ks_b = p->k_stride[0] * s.esize; ka.ks_h = p->k_stride[1] * s.esize; ka.ks_t = p->k_stride[2] * s.esize;
+  ka.vs_b = p->v_stride[0] * s.esize; ka.vs_h = p->v_stride[1] * s.esize; ka.vs_t = p->v_stride[2] * s.esize;
+  const int parts = keep_parts(p, s), lpr = s.d * s.esize / 16;
+  ka.log_parts = __builtin_ctz(parts);
+  const dim3 grid((unsigned)(s.Bz * s.Hkv * parts));
+  if (s.P <= 4 * 256) launch_keep_rows<4, 256>(ka, lpr, grid, stream);
+  else if (s.P <= 8 * 512) launch_keep_rows<8, 512>(ka, lpr, grid, stream);
+  else if (s.P <= 8 * kSelectThreads) launch_keep_rows<8, kSelectThreads>(ka, lpr, grid, stream);
+  else if (s.P <= 16 * kSelectThreads) launch_keep_rows<16, kSelectThreads>(ka, lpr, grid, stream);
+  else launch_keep_rows<32, kSelectThreads>(ka, lpr, grid, stream);
+  return hipGetLastError();
+}
+
+hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utility,
+                         const int32_t *budget, const float *tau, int32_t *idx, int32_t *count,
+                         char *ws, size_t ws_bytes, hipStream_t stream) {
+  const SelectArgs a = select_args(p, s, utility, budget, tau, idx, count);
   const int units = s.Bz * s.Hkv;
   const dim3 block(kSelectThreads);
   const SlicePlan plan = plan_slices(p, s);
