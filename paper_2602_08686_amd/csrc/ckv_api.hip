@@ -498,9 +498,9 @@ extern "C" ckv_status ckv_retention_layer(const ckv_params *params, const void *
     st = utility_of(params, s, w, q_win, k, v, lse, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, scores, vnorm_ratio, utility,
                     budget, tau, workspace, workspace_bytes, stream);
   }
-  // without shares every head has the nominal budget, and its rows are dealt out beforehand
-  if (st == CKV_OK && !head_share && keeps_in_one_launch(params, s) && k && v && idx && count && k_out && v_out)
-    return launch_keep(params, s, utility, budget, tau, k, v, idx, count, k_out, v_out, stream) == hipSuccess ? CKV_OK : CKV_EHIP;
+  const bool shares = head_share != nullptr;
+  if (st == CKV_OK && keeps_in_one_launch(params, s, shares) && k && v && idx && count && k_out && v_out)
+    return launch_keep(params, s, utility, budget, tau, k, v, idx, count, k_out, v_out, shares, stream) == hipSuccess ? CKV_OK : CKV_EHIP;
   if (st == CKV_OK) st = select_of(params, s, w, utility, budget, tau, idx, count, workspace, workspace_bytes, stream);
   if (st == CKV_OK) st = gather_of(params, s, k, v, idx, count, k_out, v_out, stream, false);
   return st;

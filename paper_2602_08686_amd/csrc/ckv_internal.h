@@ -200,10 +200,10 @@ size_t select_workspace_bytes(const ckv_params *p, const Shape &s);
 hipError_t launch_select(const ckv_params *p, const Shape &s, const float *utility,
                          const int32_t *budget, const float *tau, int32_t *idx, int32_t *count,
                          char *ws, size_t ws_bytes, hipStream_t stream);
-// Selection and gather together, where keeps_in_one_launch() and no head's budget is above the nominal one.
-bool keeps_in_one_launch(const ckv_params *p, const Shape &s);
+// Selection and gather together, where keeps_in_one_launch(); without shares no head's budget is above the nominal one.
+bool keeps_in_one_launch(const ckv_params *p, const Shape &s, bool shares);
 hipError_t launch_keep(const ckv_params *p, const Shape &s, const float *utility, const int32_t *budget, const float *tau, const void *k,
-                       const void *v, int32_t *idx, int32_t *count, void *k_out, void *v_out, hipStream_t stream);
+                       const void *v, int32_t *idx, int32_t *count, void *k_out, void *v_out, bool shares, hipStream_t stream);
 hipError_t launch_gather(const ckv_params *p, const Shape &s, const void *k, const void *v,
                          const int32_t *idx, const int32_t *count, void *k_out, void *v_out,
                          hipStream_t stream, bool shared_list = false);

@@ -424,13 +424,15 @@ __global__ void __launch_bounds__(NT) select_reg_kernel(SelectArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Selection and gather of a layer in one launch, for budgets that are the same for every head. `parts` workgroups make the same
+// Selection and gather of a layer in one launch, where the most that one head may keep is in flight at once. `parts` workgroups make the same
 // selection of a unit, which takes none of them longer than one of them (a chain of steps inside a workgroup, while most of the
 // chip is idle), and each writes and copies its share of the rows: blocks of BLOCK rows in turn, whose positions stay in LDS. The
 // gather's launch, and its way to count, index and row, are gone; what is left of it is the rows. us per layer, two launches / one: 4096
 // keys, 32/32 heads 25.1 / 24.4, 4096, 32/8 22.1 / 21.1, 1000, 32/8 20.5 / 19.0, 28000, 32/8 43.9 / 43.5, 30000, 32/8, 2048 rows 50.3 / 48.7. With
-// shares a head may have all rows of a batch element, which its own workgroups would take several times as long to move as the
-// gather, which deals them out.
+// shares a head may have all rows of a batch element: it is this form where its workgroups take those with two blocks each; where they
+// have more to move, the gather, which deals long lists out, is the faster one. Shares drawn from 0.5 to 1.5 and all in one head, us: 8192 keys,
+// 32/8 heads 25.9 / 24.8, 28.1 / 27.4; f32, 1024, 4/4 (four calls' kernels) 21.6 / 18.3, 20.5 / 19.1; but with up to four blocks each 20011, batch 2
+// 55.1 / 54.0, 65.4 / 68.0 and 16384, batch 4, given normalisers 43.5 / 43.6, 48.8 / 51.5.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPartBlocks = 4;  // of a part, at most: a thread has all its rows of K and V in flight
 struct KeepArgs {
@@ -1011,15 +1013,16 @@ static SelectArgs select_args(const ckv_params *p, const Shape &s, const float *
 // Workgroups per unit for selection and gather in one launch, a power of two: one for each CU, and no more than have a block of
 // rows. Less than two, or more rows than those have in flight: not this form, which then gains nothing (us per layer, two launches / one:
 // 128 units, 512 rows, two parts 81.0 / 81.1, 64 units, 2048 rows 120.1 / 120.0).
-static int keep_parts(const ckv_params *p, const Shape &s) {
+static int keep_parts(const ckv_params *p, const Shape &s, bool shares) {
   if (s.P > kOneLaunch || s.P < 1) return 0;
-  const int units = s.Bz * s.Hkv, rows = min(min(p->budget_per_kv_head, p->cap), s.T), lpr = s.d * s.esize / 16;
+  const int units = s.Bz * s.Hkv, lpr = s.d * s.esize / 16;
+  const int rows = min(shares ? p->cap : min(p->budget_per_kv_head, p->cap), s.T);  // the most that a head can keep
   const int block = (s.P <= 4 * 256 ? 256 : s.P <= 8 * 512 ? 512 : kSelectThreads) / lpr;
   int parts = 1;
   while (2 * parts * units <= kComputeUnits && parts * block < rows) parts *= 2;
-  return parts >= 2 && rows <= parts * kPartBlocks * block ? parts : 0;
+  return parts >= 2 && rows <= parts * (shares ? kPartBlocks / 2 : kPartBlocks) * block ? parts : 0;
 }
-bool keeps_in_one_launch(const ckv_params *p, const Shape &s) { return keep_parts(p, s) > 0; }
+bool keeps_in_one_launch(const ckv_params *p, const Shape &s, bool shares) { return keep_parts(p, s, shares) > 0; }
 
 template <int NK, int NT>
 static void launch_keep_rows(const KeepArgs &ka, int lpr, dim3 grid, hipStream_t stream) {
@@ -1029,7 +1032,7 @@ static void launch_keep_rows(const KeepArgs &ka, int lpr, dim3 grid, hipStream_t
 }
 
 hipError_t launch_keep(const ckv_params *p, const Shape &s, const float *utility, const int32_t *budget, const float *tau, const void *k,
-                       const void *v, int32_t *idx, int32_t *count, void *k_out, void *v_out, hipStream_t stream) {
+                       const void *v, int32_t *idx, int32_t *count, void *k_out, void *v_out, bool shares, hipStream_t stream) {
   KeepArgs ka;
   ka.a = select_args(p, s, utility, budget, tau, idx, count);
   ka.k = (const char *)k;
@@ -1038,7 +1041,7 @@ hipError_t launch_keep(const ckv_params *p, const Shape &s, const float *utility
   ka.v_out = (char *)v_out;
   ka.ks_b = p->k_stride[0] * s.esize; ka.ks_h = p->k_stride[1] * s.esize; ka.ks_t = p->k_stride[2] * s.esize;
   ka.vs_b = p->v_stride[0] * s.esize; ka.vs_h = p->v_stride[1] * s.esize; ka.vs_t = p->v_stride[2] * s.esize;
-  const int parts = keep_parts(p, s), lpr = s.d * s.esize / 16;
+  const int parts = keep_parts(p, s, shares), lpr = s.d * s.esize / 16;
   ka.log_parts = __builtin_ctz(parts);
   const dim3 grid((unsigned)(s.Bz * s.Hkv * parts));
   if (s.P <= 4 * 256) launch_keep_rows<4, 256>(ka, lpr, grid, stream);
