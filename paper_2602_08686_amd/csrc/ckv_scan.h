@@ -648,12 +648,13 @@ __host__ __device__ constexpr int unroll_tiles(int nq) { return nq > 4 ? 2 : kRi
 static_assert(kRing % 2 == 0, "half a ring cycle starts at an even image");
 
 // Vector instructions that the hint places behind each MFMA of the next pair's chain. Fewer than an even
-// spread (pass 1 has ~59 per 8 MFMAs, pass 2 ~48 per 8 or 9): the chain is then issued early, and what is left
+// spread (pass 1 has ~59 per 8 MFMAs, pass 2 ~48 per 9): the chain is then issued early, and what is left
 // of the current pair's vector work runs after its last MFMA -- the 18 wait states between an MFMA and the
 // first read of its result are filled with work instead of s_nop (one `s_nop 11` per pair with an even
 // spread). us per layer (passes 1 / 2, instructions per MFMA): 131072 keys, W = 64, eight tiles per wave: 172.2 (6 / 4), 175.0 (6 / 5), 169.7
 // (6 / 3), 170.8 (5 / 4); another card 176.9 (6 / 3), 175.5 (5 / 3), 178.3 (4 / 3), 180.6 (5 / 2); 65536 keys, seven tiles, the same order. Four tiles,
-// 32768 keys, batch 16: 400.7 (6 / 6), 395.3 (5 / 6), 393.3 (5 / 5), 403.8 (4 / 6); 10006 keys with value norms 69.6 (5 / 5), 70.6 (5 / 4).
+// 32768 keys, batch 16: 399.2 (5 / 5), 401.0 (5 / 6), 398.9 (5 / 4), pass 1 at 6 or 4 another 1 to 2 % slower; 20011, batch 2 56.0, 56.2, 56.4; 10006
+// with value norms 69.2, 69.4, 69.3.
 __host__ __device__ constexpr int vector_per_mfma_pass1(int nq) { return 5; }
 __host__ __device__ constexpr int vector_per_mfma_pass2(int nq) { return nq > 4 ? 3 : 5; }
 
@@ -1018,62 +1019,41 @@ __global__ void __launch_bounds__(kScoreWaves *kWave * (NORMS ? 2 : 1)) rowstats
   wait_vm<0>();  // the loads beyond the last tile write LDS: not after the wave
 }
 
-// How pass 2 takes a row's normaliser off its logits. Up to four query tiles per wave the registers hold it for the sixteen rows
-// of a lane's accumulator, and the scale's multiplication takes it along: an MFMA less per pair, and as
-// exact (one rounding of the exponent). us per layer, as the extra step below / so: 20011 keys, batch 2 56.5 / 56.0, 32768, batch 16
-// 399.4 / 394.7, 16384 with given normalisers 44.9 / 44.4.
-// Beyond that it is an extra step of the contraction, which adds bias_j = -LSE_j / scale to every logit of query row j: the bias as
-// hi + mid + lo bf16 terms in the first three slots of the Q-side operand of the lanes with hh = 0, ones in the same slots on the
-// K side. Either way padding rows (q = 0) get exp2(-1000) = 0 as weight.
-constexpr int kShiftInRegisters = 4;
+// The extra contraction step of pass 2 that adds bias_j = -LSE_j / scale to every logit of query row j: the bias as hi + mid + lo
+// bf16 terms in the first three slots of the Q-side operand of the lanes with hh = 0, ones in the same slots on the K side. The
+// terms are made once per row (pack) and reach the lanes through LDS. (In registers, as the addend of the scale's multiplication, the
+// normalisers save the ninth MFMA of a pair and 1 % of a layer; but they round differently, and keys within 1e-6 of a
+// threshold change places.) Padding rows (q = 0) get exp2(kNoWeight) = 0 as weight.
 constexpr float kNoWeight = -1000.0f;
 __device__ __forceinline__ uint32_t bf16_bits(float x) {  // round to nearest even; x is finite
   const uint32_t u = __float_as_uint(x);
   return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
-template <bool IN_REGISTERS>
-struct RowShift;
-template <>
-struct RowShift<true> {
-  float shift[16];
-  // shifts: of the tile's rows, in the log2 domain
-  __device__ __forceinline__ void set(const float *shifts, float, int, int hh) {
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(shifts + 8 * q4 + 4 * hh);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) shift[4 * q4 + e] = v[e];
-    }
-  }
-  __device__ __forceinline__ void add(f32x16 &, int) const {}
-  __device__ __forceinline__ float exponent(float dot, int r, float c2) const { return fmaf(dot, c2, shift[r]); }
-};
-template <>
-struct RowShift<false> {
+struct RowBias {
   chunk_t q;
-  __device__ __forceinline__ void set(const float *shifts, float c2, int m, int hh) {
-    const float bias = shifts[m] / c2;
+  static __device__ __forceinline__ uint2 pack(float bias) {
     const uint32_t hi = bf16_bits(bias);
     const float r1 = bias - __uint_as_float(hi << 16);
     const uint32_t mid = bf16_bits(r1);
     const float r2 = r1 - __uint_as_float(mid << 16);
-    const uint32_t lo = bf16_bits(r2);
-    q = hh == 0 ? chunk_t{hi | (mid << 16), lo, 0u, 0u} : chunk_t{0u, 0u, 0u, 0u};
+    return make_uint2(hi | (mid << 16), bf16_bits(r2));
+  }
+  __device__ __forceinline__ void set(const uint2 *rows, int m, int hh) {  // rows: of the tile
+    const uint2 v = rows[m];
+    q = hh == 0 ? chunk_t{v.x, v.y, 0u, 0u} : chunk_t{0u, 0u, 0u, 0u};
   }
   __device__ __forceinline__ void add(f32x16 &acc, int hh) const {
-    const chunk_t ones = hh == 0 ? chunk_t{0x3f803f80u, 0x3f80u, 0u, 0u} : chunk_t{0u, 0u, 0u, 0u};
-    Mma<CKV_BF16>::step(acc, q, ones);
+    Mma<CKV_BF16>::step(acc, q, hh == 0 ? chunk_t{0x3f803f80u, 0x3f80u, 0u, 0u} : chunk_t{0u, 0u, 0u, 0u});
   }
-  __device__ __forceinline__ float exponent(float dot, int, float c2) const { return dot * c2; }
 };
 
-// Weights exp(z - LSE) of one tile, summed over this lane's 16 rows.
-template <bool EDGE, class Shift>
-__device__ __forceinline__ float colsum_weights(const f32x16 &acc, const Shift &shift, float c2, int hh, int first_masked_row) {
+// Weights exp(z - LSE) of one tile from acc = <q, k> - LSE / scale, summed over this lane's 16 rows.
+template <bool EDGE>
+__device__ __forceinline__ float colsum_weights(const f32x16 &acc, float c2, int hh, int first_masked_row) {
   float s[4];
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    float pr = __builtin_amdgcn_exp2f(shift.exponent(acc[r], r, c2));
+    float pr = __builtin_amdgcn_exp2f(acc[r] * c2);
     // causal: key kt is visible to window row j iff kt <= P + j, i.e. tile row >= kt - P - j0
     if (EDGE && acc_row(r, hh) < first_masked_row) pr = 0.0f;
     s[r & 3] = r < 4 ? pr : s[r & 3] + pr;
@@ -1399,9 +1379,8 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   using G = Geom<DT, DH>;
   constexpr int NCH = G::NCH;
   constexpr bool STREAM = true;
-  static_assert(DT == CKV_BF16, "row shifts");
-  constexpr bool SHIFT_IN_REGISTERS = NQ <= kShiftInRegisters;
-  constexpr int N_MFMA = NCH + (SHIFT_IN_REGISTERS ? 0 : 1);
+  static_assert(DT == CKV_BF16, "row biases");
+  constexpr int N_MFMA = NCH + 1;
   constexpr int READ_AT = NQ >= 2 ? NQ - 2 : 0;
   __shared__ __attribute__((aligned(1024))) typename Staged<DT, DH, NQ, STREAM>::Ring ring;
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
@@ -1418,7 +1397,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   Staged<DT, DH, NQ, STREAM> st;
   chunk_t qf[NQ][NCH];
   int jrow[NQ];
-  // The normalisers of the rows, in the log2 domain and negated, a thread per row (NQ * 32 <= 256 of them): given, or, both passes in one call, merged from the first
+  // The biases that the normalisers make, a thread per row (NQ * 32 <= 256 of them): given, or, both passes in one call, merged from the first
   // pass's row partials by every workgroup of a unit. (A kernel in between cost 5 us, 11 with eight tiles and 32
   // workgroups along the keys; a lane merging all its rows by itself cost more than that from 16 partials on.) What they are made
   // of comes into the stage, which is not used yet, in front of everything else: a load into registers would have to be waited
@@ -1428,7 +1407,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   constexpr int ROWS = NQ * kTile;
   constexpr int STAGED_CHUNKS = (int)sizeof(s_stage) / 1024 * 1024 / (ROWS * (int)sizeof(float2));  // whole loads of 1 KiB
   static_assert(ROWS <= kScoreWaves * kWave && sizeof(s_stage) >= kScoreWaves * kWave * sizeof(float), "a thread per row");
-  __shared__ __attribute__((aligned(16))) float s_shift[ROWS];
+  __shared__ uint2 s_bias[ROWS];
   const float2 *part = a.part + ((size_t)bc.unit * a.n_groups + bc.grp) * a.n_chunks * ROWS;
   // The sums around the workgroup's range (fused form): wave w takes the heads w and w + 4, the tiles of a head one after the other
   constexpr int HALO_TILES = UTIL ? WT * ((NH + kScoreWaves - 1) / kScoreWaves) : 1;
@@ -1482,16 +1461,16 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
             v = merge_row_partials(reinterpret_cast<const float2 *>(&s_stage[0][0]) + threadIdx.x, a.n_chunks, ROWS);
           else v = merge_row_partials(part + threadIdx.x, a.n_chunks, ROWS);
           const bool valid = bc.grp * NQ + (int)threadIdx.x / kTile < a.n_tiles && (int)threadIdx.x / kTile % WT * kTile + (int)threadIdx.x % kTile < a.W;
-          s_shift[threadIdx.x] = valid ? v * -kLog2e : kNoWeight;
+          s_bias[threadIdx.x] = RowBias::pack(valid ? v * (-kLog2e / a.c2) : kNoWeight / a.c2);
         }
       });
   if constexpr (UTIL) {  // tau and the budgets of a batch element: a wave of its first workgroup
     if (bc.g == 0 && bc.chunk == 0 && wr.wave == kScoreWaves - 1) write_tau_and_budgets(a.bud, bc.b, lane);
   }
   rs.store(a, bc);
-  RowShift<SHIFT_IN_REGISTERS> shift[NQ];
+  RowBias bias[NQ];
 #pragma unroll
-  for (int i = 0; i < NQ; ++i) shift[i].set(s_shift + i * kTile, a.c2, m, hh);
+  for (int i = 0; i < NQ; ++i) bias[i].set(s_bias + i * kTile, m, hh);
   // Descriptor over scores[b]: Hq * T floats (the host checks that this stays below 2 GiB). Lanes with
   // nothing to store present an offset outside it, which the hardware drops: no branch splits the
   // pipeline's code, and every flush issues exactly N_STORES store instructions.
@@ -1529,10 +1508,10 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
       float x = 0.0f;
 #pragma unroll
       for (int e = 0; e < WT; ++e) {
-        RowShift<SHIFT_IN_REGISTERS> own;
-        own.set(s_shift + (halo_head(u) * WT + e) * kTile, a.c2, m, hh);
+        RowBias own;
+        own.set(s_bias + (halo_head(u) * WT + e) * kTile, m, hh);
         own.add(halo[u + e], hh);
-        const float w = colsum_weights<false>(halo[u + e], own, a.c2, hh, 0);
+        const float w = colsum_weights<false>(halo[u + e], a.c2, hh, 0);
         x = e == 0 ? w : x + w;
       }
       const float tot = (x + __shfl_xor(x, 32)) * a.norm;
@@ -1543,7 +1522,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
     wait_vm<(kRing - 2) * G::NDMA>();
     read_image<G>(kreg[0], ring[wr.wave][0], st.roff);
     mma_chain<DT, NCH>(acc[0], qf[0], kreg[0]);
-    shift[0].add(acc[0], hh);
+    bias[0].add(acc[0], hh);
   }
   constexpr int UR = unroll_tiles(NQ);
   for (int t0 = 0; t0 < n_piped; t0 += UR) {
@@ -1566,12 +1545,12 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
         }
         if (i + 1 < NQ) {
           mma_chain<DT, NCH>(acc[cur ^ 1], qf[i + 1], kreg[v & 1]);  // rows: query rows, cols: keys
-          shift[i + 1].add(acc[cur ^ 1], hh);
+          bias[i + 1].add(acc[cur ^ 1], hh);
         } else {
           mma_chain<DT, NCH>(acc[cur ^ 1], qf[0], kreg[(v + 1) & 1]);
-          shift[0].add(acc[cur ^ 1], hh);
+          bias[0].add(acc[cur ^ 1], hh);
         }
-        cs[i] = colsum_weights<false>(acc[cur], shift[i], a.c2, hh, 0);
+        cs[i] = colsum_weights<false>(acc[cur], a.c2, hh, 0);
         if (i == READ_AT) interleave_hint<N_MFMA, vector_per_mfma_pass2(NQ), NCH>();
         else interleave_hint<N_MFMA, vector_per_mfma_pass2(NQ), 0>();
       }
@@ -1594,15 +1573,15 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
     st.tail_tile(wr, ring, t, wr.t_begin + t * kTile - (a.T - kTile), m, hh, kreg[0]);
     float cs[NQ];
     mma_chain<DT, NCH>(acc[0], qf[0], kreg[0]);
-    shift[0].add(acc[0], hh);
+    bias[0].add(acc[0], hh);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int j0 = ((bc.grp * NQ + i) % WT) * kTile;
       if (i + 1 < NQ) {
         mma_chain<DT, NCH>(acc[(i + 1) & 1], qf[i + 1], kreg[0]);
-        shift[i + 1].add(acc[(i + 1) & 1], hh);
+        bias[i + 1].add(acc[(i + 1) & 1], hh);
       }
-      cs[i] = colsum_weights<!UTIL>(acc[i & 1], shift[i], a.c2, hh, kt - a.P - j0);  // keys of the prefix: every row sees them
+      cs[i] = colsum_weights<!UTIL>(acc[i & 1], a.c2, hh, kt - a.P - j0);  // keys of the prefix: every row sees them
       if (i + 1 < NQ) interleave_hint<N_MFMA, kTailVectorPerMfma, 0>();
     }
     if constexpr (UTIL)
@@ -1681,13 +1660,12 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
   static_assert(kRing == 4, "the waits below");
   using G = Geom<DT, DH>;
   constexpr int NCH = G::NCH, NH = NQ / WT, ROWS = NQ * kTile;
-  static_assert(NQ <= kShiftInRegisters, "row shifts");
   typedef Staged<DT, DH, NQ, true> Scan;
   __shared__ __attribute__((aligned(1024))) typename Scan::Ring ring;
   __shared__ __attribute__((aligned(1024))) char s_halo_keys[UTIL ? 2 * kHaloKeys * G::ROW : 16];
   __shared__ __attribute__((aligned(16))) float s_halo[UTIL ? NH * kUtilHead : 4];
   __shared__ __attribute__((aligned(16))) float s_stage[kScoreWaves][UTIL ? NH * kUtilRow : 2 * ROWS];  // first: the waves' row sums
-  __shared__ __attribute__((aligned(16))) float s_shift[ROWS];
+  __shared__ uint2 s_bias[ROWS];
   __shared__ uint64_t s_missing[kComputeUnits / kWave];
   static_assert(sizeof(s_stage) >= kScoreWaves * ROWS * sizeof(float2), "row sums pass through the stage");
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5;
@@ -1821,15 +1799,15 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
     const int tile = bc.grp * NQ + (int)threadIdx.x / kTile;
     const bool valid = tile < a.n_tiles && tile % WT * kTile + (int)threadIdx.x % kTile < a.W;
     const float lse = merge_partials_across(parts + threadIdx.x, a.n_chunks, ROWS);
-    s_shift[threadIdx.x] = valid ? lse * -kLog2e : kNoWeight;
+    s_bias[threadIdx.x] = RowBias::pack(valid ? lse * (-kLog2e / a.c2) : kNoWeight / a.c2);
   }
   __syncthreads();
   if (threadIdx.x == 0) store_across(marks + bc.chunk, a.tag | 1);
 
   // -- pass 2
-  RowShift<true> shift[NQ];
+  RowBias bias[NQ];
 #pragma unroll
-  for (int i = 0; i < NQ; ++i) shift[i].set(s_shift + i * kTile, a.c2, m, hh);
+  for (int i = 0; i < NQ; ++i) bias[i].set(s_bias + i * kTile, m, hh);
   if constexpr (UTIL) {
 #pragma unroll
     for (int u = 0; u < HALO_TILES; u += WT) {
@@ -1837,9 +1815,10 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
       float x = 0.0f;
 #pragma unroll
       for (int e = 0; e < WT; ++e) {
-        RowShift<true> own;
-        own.set(s_shift + (halo_head(u) * WT + e) * kTile, a.c2, m, hh);
-        const float w = colsum_weights<false>(halo[u + e], own, a.c2, hh, 0);
+        RowBias own;
+        own.set(s_bias + (halo_head(u) * WT + e) * kTile, m, hh);
+        own.add(halo[u + e], hh);
+        const float w = colsum_weights<false>(halo[u + e], a.c2, hh, 0);
         x = e == 0 ? w : x + w;
       }
       const float tot = (x + __shfl_xor(x, 32)) * a.norm;
@@ -1860,11 +1839,15 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
     st.read_tail(wr, ring, t, kt - m - (a.T - kTile), m, hh, kf);
     float cs[NQ];
     mma_chain<DT, NCH>(acc[0], qf[0], kf);
+    bias[0].add(acc[0], hh);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
-      if (i + 1 < NQ) mma_chain<DT, NCH>(acc[(i + 1) & 1], qf[i + 1], kf);
+      if (i + 1 < NQ) {
+        mma_chain<DT, NCH>(acc[(i + 1) & 1], qf[i + 1], kf);
+        bias[i + 1].add(acc[(i + 1) & 1], hh);
+      }
       // utilities: keys of the prefix, which every row sees
-      cs[i] = colsum_weights<!UTIL>(acc[i & 1], shift[i], a.c2, hh, kt - a.P - i % WT * kTile);
+      cs[i] = colsum_weights<!UTIL>(acc[i & 1], a.c2, hh, kt - a.P - i % WT * kTile);
     }
     if constexpr (UTIL) stage_column_sums<NQ, WT, kUtilRow>(cs, a.norm, stage + kUtilCarry, t * kTile + m, hh);
     else store_column_sums<NQ>(a, bc, cs, WT, kt, hh);
