@@ -120,3 +120,30 @@ def test_replays_with_other_inputs(shape):
         torch.cuda.synchronize()
         got = u.clone()
         assert torch.equal(got, _run(p, q, k, w_head, torch.zeros_like(ws), ws.numel()).view_as(got)), seed
+
+
+def test_streams_and_a_kernel_that_holds_the_chip():
+    """Short calls on four streams, each with buffers of its own, beside matrix products that fill the chip: workgroups of a launch start far
+    apart, some wait in vain and make the missing sums themselves; all results are those of a call by itself."""
+    shape = SHAPES[0]
+    calls = [_call(shape, 20 + i) for i in range(4)]
+    nbytes = B.ckv_workspace_bytes(calls[0][0])
+    want = [_run(*c, torch.zeros(nbytes, dtype=torch.uint8, device=DEV), nbytes) for c in calls]
+    big = torch.randn(8192, 8192, device=DEV).bfloat16()
+    streams = [torch.cuda.Stream() for _ in calls]
+    state = []
+    for p, q, k, w_head in calls:
+        n = p.batch * p.n_kv_heads
+        state.append((torch.zeros(nbytes, dtype=torch.uint8, device=DEV), torch.empty(p.batch, p.n_q_heads, p.seq_len, device=DEV),
+                      torch.zeros(30, n, p.seq_len - p.window, device=DEV), torch.empty(n, dtype=torch.int32, device=DEV),
+                      torch.empty(p.batch, device=DEV)))
+    torch.cuda.synchronize()
+    for r in range(30):
+        if r % 10 == 0:
+            big @ big
+        for (p, q, k, w_head), (ws, scratch, u, budget, tau), stream in zip(calls, state, streams):
+            B.ckv_window_utility(p, q, k, None, None, w_head, None, None, 0, 0, None, scratch, None, u[r], budget, tau, ws, stream)
+    torch.cuda.synchronize()
+    for w, (_, _, u, _, _) in zip(want, state):
+        for r in range(30):
+            assert torch.equal(u[r], w.view_as(u[r])), r
