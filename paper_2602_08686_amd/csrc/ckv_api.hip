@@ -137,11 +137,10 @@ bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given) {
 
 // One launch for both passes where a wave's range is no longer than its ring of key tiles, so that the keys stay in LDS between
 // them, and every workgroup has a CU of its own (more of them would wait for
-// ones that start when they end). Up to four query tiles per wave: with eight 13 registers spill. 0.80 to 0.96 of the two launches'
-// time per layer over nine shapes of 1000 to 16384 keys (scan_short_kernel); without value norms, whose ratio needs a unit's sum of them, too.
+// ones that start when they end). 0.80 to 0.99 of the two launches'
+// time per layer over nineteen shapes of 1000 to 16384 keys (scan_short_kernel). Without value norms, whose ratio needs a unit's sum of them, too.
 bool one_launch(const ckv_params *p, const Shape &s) {
-  return p->dtype == CKV_BF16 && s.n_groups == 1 && s.NQ <= kShortTiles &&
-         s.keys_per_wave <= kRing * kTile && (int64_t)s.Bz * s.Hkv * s.n_chunks <= kComputeUnits;
+  return p->dtype == CKV_BF16 && s.n_groups == 1 && s.keys_per_wave <= kRing * kTile && (int64_t)s.Bz * s.Hkv * s.n_chunks <= kComputeUnits;
 }
 
 // Even. The upper bits are those of a negative NaN, which no sum, position or key ends up as; the rest counts launches from the

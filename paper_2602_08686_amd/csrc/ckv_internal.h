@@ -15,7 +15,6 @@ constexpr int kTile = 32;          // MFMA 32x32 tile edge: query rows and keys 
 constexpr int kMaxQTiles = 8;      // query-row tiles a wave keeps in registers (bf16; f32 kernels: kMaxQTilesF32)
 constexpr int kMaxQTilesF32 = 4;
 constexpr int kMaxQTilesNorms = 4; // up to here a wave of the scan's first pass leaves half of its SIMD's registers
-constexpr int kShortTiles = 4;     // up to here both passes of a short call fit one kernel's registers
 constexpr int kMaxWindowTiles = 4; // 32-row tiles per query head: W <= 128
 constexpr int kScoreWaves = 4;     // waves per workgroup in the scan kernels
 // Compute units of the build target (gfx950: MI355X, 256). A constant on purpose, not a device query: the

@@ -1651,12 +1651,13 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
 // another stream's kernel holds some, would wait for workgroups that wait for it otherwise). Who has read all sums changes its
 // mark; who sees all of them changed at its end takes them back, and the last one to change its own does see that.
 // us per layer, two launches / one, keys in the memory-side cache before the call and from HBM: 4096 keys, 32/32 heads 27.4 / 25.1, 31.4 /
-// 26.0; 8192, 32/8 27.3 / 25.0, 29.7 / 25.7; 4096, batch 4, 32/8 35.9 / 29.7, 37.2 / 30.1; 1000, 32/8 21.8 / 20.5, 21.9 / 21.1. The keys are
+// 26.0; 8192, 32/8 27.3 / 25.0, 29.7 / 25.7; 4096, batch 4, 32/8 35.9 / 29.7, 37.2 / 30.1; 1000, 32/8 21.8 / 20.5, 21.9 / 21.1; seven tiles, 6000,
+// batch 2, 28/4 29.6 / 27.7, 31.7 / 28.2; eight, 8192, batch 2, 32/4 33.9 / 30.5, 35.1 / 30.6; 3001, W = 64, 32/8 28.9 / 28.5, 30.4 / 29.0. The keys are
 // streamed, since nothing reads them again (kept in the cache 1 to 5 % faster if they were there before, 2 to 7 % slower if not).
 // ---------------------------------------------------------------------------------------------
 template <int DT, int DH, int NQ, int WT, bool UTIL>
 __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArgs a) {
-  static_assert(DT == CKV_BF16 && NQ % WT == 0 && NQ <= kShortTiles, "whole heads");
+  static_assert(DT == CKV_BF16 && NQ % WT == 0, "whole heads");
   static_assert(kRing == 4, "the waits below");
   using G = Geom<DT, DH>;
   constexpr int NCH = G::NCH, NH = NQ / WT, ROWS = NQ * kTile;
@@ -1727,7 +1728,8 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
       for (int i = 0; i < NQ; ++i) {
         if (i + 1 < NQ) mma_chain<DT, NCH>(acc[(i + 1) & 1], kf, qf[i + 1]);
         if (t >= range.n_full) {  // uniform: the window's rows see no later keys, and there are none beyond T
-          const int limit = jrow[i] >= 0 ? a.P + jrow[i] : -1;
+          const int tile = bc.grp * NQ + i, j = tile % WT * kTile + m;
+          const int limit = tile < a.n_tiles && j < a.W ? a.P + j : -1;
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i & 1][r] = acc_row(r, hh) > limit - t0 ? -INFINITY : acc[i & 1][r];
         }
@@ -1953,7 +1955,7 @@ static void launch_short_wt(const ScoreArgs &a, dim3 grid, dim3 block, hipStream
 }
 template <int DT, int DH, int NQ>
 static void launch_short(const Shape &s, const ScoreArgs &a, dim3 grid, dim3 block, hipStream_t stream) {
-  if constexpr (DT == CKV_BF16 && NQ <= kShortTiles) {
+  if constexpr (DT == CKV_BF16) {
     switch (s.WT) {  // NQ is a multiple of WT (whole heads per wave)
       case 1: launch_short_wt<DT, DH, NQ, 1>(a, grid, block, stream); break;
       case 2: launch_short_wt<DT, DH, NQ, 2>(a, grid, block, stream); break;

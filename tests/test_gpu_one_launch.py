@@ -15,6 +15,8 @@ SHAPES = [  # batch, query heads, KV heads, d, T, W, pooling, kernel
     (1, 8, 8, 128, 33, 1, B.POOL_NONE, 1), (1, 4, 1, 128, 20, 4, B.POOL_MAX, 3), (3, 6, 2, 128, 511, 32, B.POOL_AVG, 3), (1, 4, 2, 64, 3001, 64, B.POOL_MAX, 7),
     (1, 4, 4, 128, 16384, 32, B.POOL_AVG, 7), (1, 2, 1, 128, 16383, 40, B.POOL_AVG, 7), (16, 8, 8, 128, 777, 32, B.POOL_MAX, 5),
     (1, 4, 1, 128, 10000, 32, B.POOL_AVG, 7), (1, 3, 1, 64, 11111, 32, B.POOL_MAX, 3),   # 40 workgroups and more of a unit
+    (2, 28, 4, 128, 2600, 32, B.POOL_AVG, 7), (1, 16, 2, 128, 9001, 32, B.POOL_MAX, 5), (1, 10, 2, 64, 3100, 32, B.POOL_AVG, 3),   # 7, 8, 5 tiles
+    (1, 32, 8, 128, 1999, 64, B.POOL_AVG, 7), (1, 12, 4, 128, 777, 50, B.POOL_MAX, 7),                                            # 8, 6: two per head
 ]
 
 
