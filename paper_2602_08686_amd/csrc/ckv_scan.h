@@ -4,6 +4,7 @@
 //   pass 2  colsum kernels   : stream K again, recompute QK^T, exp(z - LSE_j), sum over window rows;
 //                              in the fused form also the pooling, head weights and group maximum of
 //                              Eq. 6 (Alg. 1 Stage 3), so that the per-head mass is never written
+//   scan_short_kernel        : both passes of a short call, whose keys stay in LDS between them
 //
 // Work decomposition. A "unit" is one (batch, KV head): its G*W window query rows all contract with
 // the same K. Rows are cut into 32-row tiles (one MFMA 32x32 edge), whole heads only; a wave keeps its

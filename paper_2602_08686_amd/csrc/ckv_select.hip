@@ -27,7 +27,8 @@
 // the streaming kernel: 44.3 -> 9.3. Inside a 32k call of 10 us: loads 1.9, keys and maxima 1.6, their histogram 1.0,
 // list 2.5, threshold 1.5, output 1.3. A launch costs 4.6 of them.
 //
-// Who calls the core: select_reg_kernel, one workgroup per (batch, KV head) with up to 65536 positions;
+// Who calls the core: select_reg_kernel, one workgroup per (batch, KV head) with up to 65536 positions; keep_kernel, several
+// workgroups per head that also copy the rows they keep;
 // select_slice_kernel + select_merge_kernel, for longer rows a workgroup per 8192 or 16384 positions and one per unit
 // on what the slices kept. select_split_kernel (budgets so large that slices keep nearly everything) and
 // select_kernel (no workspace) stay for the rest.
