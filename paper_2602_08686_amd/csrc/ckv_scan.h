@@ -712,9 +712,13 @@ struct Staged {
 
   // Starts the loads of Q (wave w moves query tiles w and w + 4 into the last images of its ring) and of the
   // first key tiles, then hands every wave all NQ query tiles in registers; on return the wave's first
-  // three key tiles are in flight, in order. jrow[i] = window row of tile i, row m, or -1 on padding.
+  // tiles_asked() key tiles are in flight, in order. jrow[i] = window row of tile i, row m, or -1 on padding.
   static constexpr int QI = (NQ + kScoreWaves - 1) / kScoreWaves;  // ring images per wave that first hold Q
   static_assert(QI >= 1 && QI <= kRing - 2, "query tiles pass through the ring's last images");
+  static constexpr int N_PRE = kRing - QI;  // key tiles whose images are free while Q passes through
+  // Key tiles of a wave with any whose loads start() has queued; the only tile of a sequence shorter than one fills the images
+  // that are free beside Q, and no more.
+  static __device__ __forceinline__ int tiles_asked(const ScoreArgs &a) { return a.T < kTile ? N_PRE : kRing - 1; }
   // `first` queues loads in front of all others, which have landed as Q has; `between` runs when every wave's have, with the query
   // tiles still in their images (image_of_tile), in front of the start's last barrier.
   template <class First, class Between>
@@ -746,7 +750,6 @@ struct Staged {
         dma_rows<G>([&](int r) { return qhead + (int64_t)min(j0 + r, a.W - 1) * a.qs_w; }, lane, lds_ring + (kRing - 1 - qi) * G::TILE);
       }
     }
-    constexpr int N_PRE = kRing - QI;  // key tiles whose images are free while Q passes through
     const bool tiny = a.T < kTile;
     if (wr.n_all > 0) {
       if (!tiny) {
@@ -1755,8 +1758,9 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
     __syncthreads();
   };
   if (wr.n_all == kRing) st.prefetch(0, wr.n_whole, kRing - 1);
+  const int asked = Scan::tiles_asked(a) + (wr.n_all == kRing ? 1 : 0);
   row_sums(wr, bc.chunk, [&](int t, int t0) {
-    switch ((wr.n_all == kRing ? kRing - 1 : kRing - 2) - t) {  // tiles asked for behind this one
+    switch (asked - 1 - t) {  // tiles asked for behind this one
       case 3: wait_vm<3 * G::NDMA>(); break;
       case 2: wait_vm<2 * G::NDMA>(); break;
       case 1: wait_vm<G::NDMA>(); break;

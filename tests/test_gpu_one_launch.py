@@ -6,7 +6,9 @@ import ctypes
 import pytest
 import torch
 
+import oracle
 from paper_2602_08686_amd import binding as B
+from parity_util import assert_scores_close, f32
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -92,6 +94,37 @@ def test_scores_in_one_launch_match_two(shape):
     assert torch.equal(outs[1], outs[2])
     torch.testing.assert_close(outs[1].double().sum(-1), torch.full((p.batch, p.n_q_heads), float(p.seq_len), dtype=torch.float64, device=DEV),
                                rtol=1e-4, atol=0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [4, 5, 6, 7, 8])
+@pytest.mark.parametrize("T,W", [(1, 1), (9, 4), (20, 4), (31, 9), (32, 9), (33, 33)])
+def test_sequences_of_a_tile_or_less(T, W, heads, d):
+    """The only key tile's loads are the last that a wave waits for, however many images they fill: with five and more query tiles fewer than
+    for a longer sequence. The ring holds another call's keys before."""
+    print("case", T, W, heads, d, flush=True)
+    batch, kv = 3, 2
+    p, q, k, w_head = _call((batch, heads * kv, kv, d, T, W, B.POOL_MAX, 3), 7 * T + heads)
+    other, oq, ok, ow = _call((64, heads, 1, d, 512, 32, B.POOL_NONE, 1), 5)
+    ws = torch.zeros(max(B.ckv_workspace_bytes(p), B.ckv_workspace_bytes(other)), dtype=torch.uint8, device=DEV)
+    outs = []
+    for lse in (_lse(p, q, k, ws), None, None):
+        _run(other, oq, ok, ow, ws, ws.numel())
+        scores = torch.full((batch, heads * kv, T), float("nan"), device=DEV)
+        B.ckv_window_scores(p, q, k, None, lse, scores, None, ws)
+        outs.append(scores)
+    torch.testing.assert_close(outs[1], outs[0], rtol=1e-5, atol=1e-30)
+    assert torch.equal(outs[1], outs[2])
+    want = oracle.window_scores(f32(q), f32(k))
+    assert_scores_close(outs[1].cpu().numpy(), want)
+    if T > W:
+        two = _run(p, q, k, w_head, ws, ws.numel(), lse=_lse(p, q, k, ws))
+        for wait in (None, 0):
+            _run(other, oq, ok, ow, ws, ws.numel())
+            one = _run(p, q, k, w_head, ws, ws.numel(), wait)
+            torch.testing.assert_close(one, two, rtol=1e-5, atol=0)
+            ref = oracle.utility(want, W, kv, B.POOL_MAX, 3, f32(w_head[0]))
+            assert_scores_close(one.cpu().numpy().reshape(ref.shape), ref, "utility")
 
 
 @pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1], SHAPES[5]], ids=lambda s: "-".join(map(str, s)))
