@@ -10,6 +10,8 @@ PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 INCLUDE = PKG.parent / "include"
 LIB = PKG / "libckv.so"
+HOOKS = PKG.parent / "tests" / "hooks"
+HOOKS_LIB = HOOKS / "libckv_hooks.so"
 SCAN_SOURCES = ["ckv_scan_bf16_d128_nq78.hip", "ckv_scan_bf16_d128_nq56.hip", "ckv_scan_bf16_d64_nq78.hip",
                 "ckv_scan_bf16_d64_nq56.hip", "ckv_scan_bf16_d128.hip", "ckv_scan_bf16_d64.hip", "ckv_scan_f32_d64.hip",
                 "ckv_scan_f32_d128.hip"]
@@ -68,6 +70,17 @@ def build_probes() -> list:
                         "-packed-fp32-ops", str(probes / (name + ".hip")), "-o", str(exe)], check=True)
         out.append(exe)
     return out
+
+
+def build_test_hooks() -> Path:
+    """Compile the tests' way to libckv.so's internal functions (host code only; loads the library beside it)."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    tmp = HOOKS_LIB.with_suffix(f".tmp{os.getpid()}.so")
+    subprocess.run([hipcc, "--offload-host-only", "-O2", "-std=c++17", "-fPIC", "-Wall", "-shared", f"-I{INCLUDE}", f"-I{CSRC}",
+                    str(HOOKS / "scan_forms.hip"), f"-L{PKG}", f"-l:{LIB.name}", f"-Wl,-rpath,$ORIGIN/../../{PKG.name}",
+                    "-o", str(tmp)], check=True)
+    os.replace(tmp, HOOKS_LIB)
+    return HOOKS_LIB
 
 
 if __name__ == "__main__":

@@ -196,19 +196,19 @@ constexpr uint32_t kExchangeWait = 3000;
 
 // The marks lie where a call that makes the normalisers and uses them leaves its workspace alone, in the place for those: four
 // bytes for each row of a unit's heads against eight for each of its workgroups. Where that is not room enough, two launches.
-static Exchange exchange_of(const ckv_params *p, const Shape &s, const Workspace &w, const float *lse, void *workspace, uint32_t wait) {
+Exchange ckv::exchange_of(const ckv_params *p, const Shape &s, const Workspace &w, const float *lse, void *workspace) {
   Exchange e;
   if (!lse && !(p->flags & (CKV_FLAG_VALUE_NORM | CKV_FLAG_GROUP_MASS)) && one_launch(p, s) &&
       (size_t)s.Bz * s.Hkv * s.n_chunks * sizeof(tag_t) <= w.vsum_off - w.lse_off)
     e.marks = (tag_t *)((char *)workspace + w.lse_off);
-  e.wait = wait;
+  e.wait = kExchangeWait;
   return e;
 }
 
 // The calls of a layer behind validate(), derive() and layout(), which ckv_retention_layer has done once for all of them.
-static ckv_status scores_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
-                            const void *v, const float *lse, float *scores, float *vnorm_ratio, void *workspace,
-                            size_t workspace_bytes, hipStream_t stream) {
+ckv_status ckv::scores_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
+                          const void *v, const float *lse, float *scores, float *vnorm_ratio, void *workspace,
+                          size_t workspace_bytes, hipStream_t stream, const Exchange &exchange) {
   if (!q_win || !k || !scores) return CKV_EINVAL;
   const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
   if (vn && (!v || !vnorm_ratio)) return CKV_EINVAL;
@@ -221,7 +221,7 @@ static ckv_status scores_of(const ckv_params *params, const Shape &s, const Work
       launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;
   if (launch_window_scores(params, s, w, q_win, k, lse, nullptr, scores, (char *)workspace, stream, nullptr, v,
-                           vn ? vnorm_ratio : nullptr, exchange_of(params, s, w, lse, workspace, kExchangeWait)) != hipSuccess)
+                           vn ? vnorm_ratio : nullptr, exchange) != hipSuccess)
     return CKV_EHIP;
   return CKV_OK;
 }
@@ -236,7 +236,8 @@ extern "C" ckv_status ckv_window_scores(const ckv_params *params, const void *q_
   Workspace w;
   derive(params, &s);
   layout(params, s, &w);
-  return scores_of(params, s, w, q_win, k, v, lse, scores, vnorm_ratio, workspace, workspace_bytes, (hipStream_t)hip_stream);
+  return scores_of(params, s, w, q_win, k, v, lse, scores, vnorm_ratio, workspace, workspace_bytes, (hipStream_t)hip_stream,
+                   exchange_of(params, s, w, lse, workspace));
 }
 
 extern "C" ckv_status ckv_window_lse(const ckv_params *params, const void *q_win, const void *k,
@@ -352,11 +353,11 @@ static bool utility_fast_path(const ckv_params *p, const Shape &s) {
          (int64_t)s.Hkv * s.P < (1 << 29);
 }
 
-static ckv_status utility_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
-                             const void *v, const float *lse, const float *w_head, const float *head_share, const float *t_gate,
-                             int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins, float *scores_scratch, float *vnorm_ratio,
-                             float *utility, int32_t *budget, float *tau, void *workspace, size_t workspace_bytes,
-                             hipStream_t stream, uint32_t wait = kExchangeWait) {
+ckv_status ckv::utility_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
+                           const void *v, const float *lse, const float *w_head, const float *head_share, const float *t_gate,
+                           int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins, float *scores_scratch, float *vnorm_ratio,
+                           float *utility, int32_t *budget, float *tau, void *workspace, size_t workspace_bytes,
+                           hipStream_t stream, const Exchange &exchange) {
   if (!q_win || !k || !scores_scratch || !w_head || !utility || !budget || !tau) return CKV_EINVAL;
   if (params->flags & CKV_FLAG_GROUP_MASS) return CKV_EINVAL;  // needs per-head masses
   const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
@@ -365,7 +366,6 @@ static ckv_status utility_of(const ckv_params *params, const Shape &s, const Wor
   const ckv_status st = workspace_ok(w, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
   float *ratio = vn ? vnorm_ratio : nullptr;
-  const Exchange exchange = exchange_of(params, s, w, lse, workspace, wait);
   if (vn && !norms_in_scan(params, s, lse != nullptr) &&
       launch_value_norm(params, s, w, v, ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;
@@ -408,22 +408,7 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
   derive(params, &s);
   layout(params, s, &w);
   return utility_of(params, s, w, q_win, k, v, lse, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, scores_scratch, vnorm_ratio,
-                    utility, budget, tau, workspace, workspace_bytes, (hipStream_t)hip_stream);
-}
-
-// ckv_window_utility with another bound on the one-launch form's wait; for tests, in no header. With 0 a workgroup makes whatever the
-// others have not left by the time it looks.
-extern "C" ckv_status ckv_window_utility_wait(const ckv_params *params, const void *q_win, const void *k, const float *w_head,
-                                              float *scores_scratch, float *utility, int32_t *budget, float *tau,
-                                              void *workspace, size_t workspace_bytes, uint32_t wait, void *hip_stream) {
-  const ckv_status st = validate(params);
-  if (st != CKV_OK) return st;
-  Shape s;
-  Workspace w;
-  derive(params, &s);
-  layout(params, s, &w);
-  return utility_of(params, s, w, q_win, k, nullptr, nullptr, w_head, nullptr, nullptr, 0, 0, nullptr, scores_scratch, nullptr, utility,
-                    budget, tau, workspace, workspace_bytes, (hipStream_t)hip_stream, wait);
+                    utility, budget, tau, workspace, workspace_bytes, (hipStream_t)hip_stream, exchange_of(params, s, w, lse, workspace));
 }
 
 static ckv_status select_of(const ckv_params *params, const Shape &s, const Workspace &w, const float *utility,
@@ -489,13 +474,14 @@ extern "C" ckv_status ckv_retention_layer(const ckv_params *params, const void *
   derive(params, &s);
   layout(params, s, &w);
   hipStream_t stream = (hipStream_t)hip_stream;
+  const Exchange exchange = exchange_of(params, s, w, lse, workspace);
   if (scores_wanted) {
-    st = scores_of(params, s, w, q_win, k, v, lse, scores, vnorm_ratio, workspace, workspace_bytes, stream);
+    st = scores_of(params, s, w, q_win, k, v, lse, scores, vnorm_ratio, workspace, workspace_bytes, stream, exchange);
     if (st == CKV_OK)
       st = tables_of(params, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, utility, budget, tau, stream);
   } else {
     st = utility_of(params, s, w, q_win, k, v, lse, w_head, head_share, t_gate, n_ent, n_ppl, risk_bins, scores, vnorm_ratio, utility,
-                    budget, tau, workspace, workspace_bytes, stream);
+                    budget, tau, workspace, workspace_bytes, stream, exchange);
   }
   const bool shares = head_share != nullptr;
   if (st == CKV_OK && keeps_in_one_launch(params, s, shares) && k && v && idx && count && k_out && v_out)

@@ -182,6 +182,17 @@ hipError_t launch_window_scores(const ckv_params *p, const Shape &s, const Works
                                 const void *k, const float *lse_in, float *lse_out, float *scores,
                                 char *ws, hipStream_t stream, const UtilityFusion *fuse = nullptr,
                                 const void *v = nullptr, float *ratio = nullptr, const Exchange &exchange = {});
+// What ckv_window_scores and ckv_window_utility do behind validate(), derive() and layout(), with the exchange that exchange_of()
+// gives them (or none: two launches).
+Exchange exchange_of(const ckv_params *p, const Shape &s, const Workspace &w, const float *lse, void *workspace);
+ckv_status scores_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k, const void *v,
+                     const float *lse, float *scores, float *vnorm_ratio, void *workspace, size_t workspace_bytes,
+                     hipStream_t stream, const Exchange &exchange);
+ckv_status utility_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k, const void *v,
+                      const float *lse, const float *w_head, const float *head_share, const float *t_gate, int32_t n_ent,
+                      int32_t n_ppl, const int32_t *risk_bins, float *scores_scratch, float *vnorm_ratio, float *utility,
+                      int32_t *budget, float *tau, void *workspace, size_t workspace_bytes, hipStream_t stream,
+                      const Exchange &exchange);
 // Whether pass 1 of a call takes the value norms beside its scan; the norms and sums are those of launch_value_norm.
 bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given);
 // the norms into `ratio` and their sums per block into the workspace; launch_window_scores turns them into the ratio

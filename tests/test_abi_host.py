@@ -3,11 +3,14 @@ declares, sizes its workspace, and rejects bad arguments before anything would b
 import ctypes
 import pathlib
 import re
+import shutil
+import subprocess
 
 import pytest
 import torch
 
 from paper_2602_08686_amd import binding as B
+from paper_2602_08686_amd import build
 
 HEADER = pathlib.Path(__file__).resolve().parents[1] / "include" / "ckv.h"
 
@@ -26,6 +29,13 @@ def test_exports_match_header():
     assert declared == set(B.EXPORTS)
     for name in declared:
         assert hasattr(lib, name), name
+
+
+def test_the_library_has_no_other_entry_points():
+    nm = shutil.which("nm") or "/opt/rocm/llvm/bin/llvm-nm"
+    out = subprocess.run([nm, "-D", "--defined-only", str(build.LIB)], check=True, capture_output=True, text=True).stdout
+    names = {line.split()[-1] for line in out.splitlines() if line.split()[-2] == "T"}
+    assert {n for n in names if n.startswith("ckv")} == set(B.EXPORTS)
 
 
 def test_struct_layout_matches_header():

@@ -1,11 +1,12 @@
 """Both scan passes of a short call in one launch: ranges of one to four key tiles per wave, with and without keys that fill them,
-against two launches (the normalisers by a call of their own, then a call that is given them); workgroups that make the missing row sums themselves give
+against two launches, bit by bit, and against normalisers by a call of their own and a call that is given them; workgroups that make the missing row sums themselves give
 the same bits as workgroups that wait for them; marks of an earlier call, or anything else, in the workspace do no harm."""
 import ctypes
 
 import pytest
 import torch
 
+import hooks
 import oracle
 from paper_2602_08686_amd import binding as B
 from parity_util import assert_scores_close, f32
@@ -44,21 +45,19 @@ def _lse(p, q, k, ws):
     return lse
 
 
-def _run(p, q, k, w_head, ws, nbytes, wait=None, lse=None):
+def _run(p, q, k, w_head, ws, nbytes, lse=None, **form):
+    """form: the hooks' two_launches or wait; without it the call that a program makes."""
     lib = B.load()
     n = p.batch * p.n_kv_heads
     u = torch.full((n, max(p.seq_len - p.window, 1)), float("nan"), device=DEV)
     scratch = torch.empty(p.batch, p.n_q_heads, p.seq_len, device=DEV)
     budget, tau = torch.empty(n, dtype=torch.int32, device=DEV), torch.full((p.batch,), float("nan"), device=DEV)
-    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if wait is None:
-        st = lib.ckv_window_utility(ctypes.byref(p), _ptr(q), _ptr(k), None, None if lse is None else _ptr(lse), _ptr(w_head), None, None, 0, 0, None, _ptr(scratch),
-                                    None, _ptr(u), _ptr(budget), _ptr(tau), _ptr(ws), nbytes, stream)
+    if form:
+        hooks.window_utility(p, q, k, w_head, scratch, u, budget, tau, ws[:nbytes], torch.cuda.current_stream(), **form)
     else:
-        call = lib.ckv_window_utility_wait
-        call.argtypes = [ctypes.POINTER(B.CkvParams)] + [ctypes.c_void_p] * 8 + [ctypes.c_size_t, ctypes.c_uint32, ctypes.c_void_p]
-        st = call(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(w_head), _ptr(scratch), _ptr(u), _ptr(budget), _ptr(tau), _ptr(ws), nbytes, wait, stream)
-    assert st == B.CKV_OK
+        st = lib.ckv_window_utility(ctypes.byref(p), _ptr(q), _ptr(k), None, None if lse is None else _ptr(lse), _ptr(w_head), None, None, 0, 0, None, _ptr(scratch),
+                                    None, _ptr(u), _ptr(budget), _ptr(tau), _ptr(ws), nbytes, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == B.CKV_OK
     torch.cuda.synchronize()
     assert (tau == 0).all() and (budget == min(p.budget_per_kv_head, p.seq_len)).all()
     return u
@@ -72,11 +71,12 @@ def test_one_launch_matches_two(shape):
     ws = torch.full((whole,), 0x5A, dtype=torch.uint8, device=DEV)
     two = _run(p, q, k, w_head, ws, whole, lse=_lse(p, q, k, ws))
     one = _run(p, q, k, w_head, ws, whole)
-    # the same sums in the same order but for what is finished behind the rounds: roundings of exponents of a few tens
+    assert torch.equal(_run(p, q, k, w_head, ws, whole, two_launches=True), one)
+    # given normalisers: the same sums in the same order but for what is finished behind the rounds: roundings of exponents of a few tens
     torch.testing.assert_close(one, two, rtol=1e-5, atol=0)
     for wait in (0, 1, 3000):
         ws.random_(0, 256)
-        assert torch.equal(_run(p, q, k, w_head, ws, whole, wait), one), wait
+        assert torch.equal(_run(p, q, k, w_head, ws, whole, wait=wait), one), wait
 
 
 @pytest.mark.parametrize("shape", SHAPES + [(1, 1, 1, 128, 2000, 100, B.POOL_NONE, 1), (1, 2, 2, 64, 5000, 128, B.POOL_NONE, 1)],
@@ -92,6 +92,11 @@ def test_scores_in_one_launch_match_two(shape):
         outs.append(scores)
     torch.testing.assert_close(outs[1], outs[0], rtol=1e-5, atol=1e-30)
     assert torch.equal(outs[1], outs[2])
+    for form in ({"two_launches": True}, {"wait": 0}, {"wait": 1}):
+        scores = torch.full((p.batch, p.n_q_heads, p.seq_len), float("nan"), device=DEV)
+        ws.random_(0, 256)
+        hooks.window_scores(p, q, k, scores, ws, torch.cuda.current_stream(), **form)
+        assert torch.equal(scores, outs[1]), form
     torch.testing.assert_close(outs[1].double().sum(-1), torch.full((p.batch, p.n_q_heads), float(p.seq_len), dtype=torch.float64, device=DEV),
                                rtol=1e-4, atol=0)
 
@@ -119,9 +124,9 @@ def test_sequences_of_a_tile_or_less(T, W, heads, d):
     assert_scores_close(outs[1].cpu().numpy(), want)
     if T > W:
         two = _run(p, q, k, w_head, ws, ws.numel(), lse=_lse(p, q, k, ws))
-        for wait in (None, 0):
+        for form in ({}, {"wait": 0}):
             _run(other, oq, ok, ow, ws, ws.numel())
-            one = _run(p, q, k, w_head, ws, ws.numel(), wait)
+            one = _run(p, q, k, w_head, ws, ws.numel(), **form)
             torch.testing.assert_close(one, two, rtol=1e-5, atol=0)
             ref = oracle.utility(want, W, kv, B.POOL_MAX, 3, f32(w_head[0]))
             assert_scores_close(one.cpu().numpy().reshape(ref.shape), ref, "utility")
