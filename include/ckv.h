@@ -247,8 +247,9 @@ ckv_status ckv_compact_kv(const ckv_params *params, const void *k, const void *v
 /*
  * A layer's whole step as one call: ckv_window_utility (scores_wanted = 0; `scores` is its scratch) or
  * ckv_window_scores + ckv_apply_tables (scores_wanted != 0), then ckv_select_topk and ckv_compact_kv, with the
- * same arguments, outputs, refusals and order on the stream. `v` is read by the gather and, with
- * CKV_FLAG_VALUE_NORM, by the scan; workspace as for ckv_window_scores.
+ * same arguments, outputs and order on the stream. What one of them would refuse is refused with its status, the first one's
+ * first, before anything is launched. `v` is read by the gather and, with CKV_FLAG_VALUE_NORM, by the scan;
+ * workspace as for ckv_window_scores.
  */
 ckv_status ckv_retention_layer(const ckv_params *params, const void *q_win, const void *k, const void *v,
                                const float *lse, const float *w_head, const float *head_share,

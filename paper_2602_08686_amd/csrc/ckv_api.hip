@@ -205,18 +205,27 @@ Exchange ckv::exchange_of(const ckv_params *p, const Shape &s, const Workspace &
   return e;
 }
 
-// The calls of a layer behind validate(), derive() and layout(), which ckv_retention_layer has done once for all of them.
-ckv_status ckv::scores_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
-                          const void *v, const float *lse, float *scores, float *vnorm_ratio, void *workspace,
-                          size_t workspace_bytes, hipStream_t stream, const Exchange &exchange) {
+// The calls of a layer behind validate(), derive() and layout(), which ckv_retention_layer has done once for all of them. What a step
+// refuses is a function of its own: the layer asks for all of its steps' before it queues the first.
+static ckv_status scores_refused(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
+                                 const void *v, const float *scores, const float *vnorm_ratio, const void *workspace,
+                                 size_t workspace_bytes) {
   if (!q_win || !k || !scores) return CKV_EINVAL;
-  const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
-  if (vn && (!v || !vnorm_ratio)) return CKV_EINVAL;
+  if ((params->flags & CKV_FLAG_VALUE_NORM) && (!v || !vnorm_ratio)) return CKV_EINVAL;
   const ckv_status st = workspace_ok(w, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
   // the group-mass output exists where one wave holds all query heads of a KV head, one tile each
   if ((params->flags & CKV_FLAG_GROUP_MASS) && !(params->dtype == CKV_BF16 && s.n_groups == 1 && s.WT == 1 && s.NQ <= 4))
     return CKV_EUNSUPPORTED;
+  return CKV_OK;
+}
+
+ckv_status ckv::scores_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
+                          const void *v, const float *lse, float *scores, float *vnorm_ratio, void *workspace,
+                          size_t workspace_bytes, hipStream_t stream, const Exchange &exchange) {
+  const ckv_status st = scores_refused(params, s, w, q_win, k, v, scores, vnorm_ratio, workspace, workspace_bytes);
+  if (st != CKV_OK) return st;
+  const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
   if (vn && !norms_in_scan(params, s, lse != nullptr) &&
       launch_value_norm(params, s, w, v, vnorm_ratio, (char *)workspace, stream) != hipSuccess)
     return CKV_EHIP;
@@ -314,13 +323,21 @@ extern "C" ckv_status ckv_window_lse_static(const ckv_params *params, const void
   return CKV_OK;
 }
 
-static ckv_status tables_of(const ckv_params *params, const Shape &s, const float *scores, const float *vnorm_ratio,
-                            const float *w_head, const float *head_share, const float *t_gate, int32_t n_ent, int32_t n_ppl,
-                            const int32_t *risk_bins, float *utility, int32_t *budget, float *tau, hipStream_t stream) {
+static ckv_status tables_refused(const ckv_params *params, const float *scores, const float *vnorm_ratio, const float *w_head,
+                                 const float *t_gate, int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins, const float *utility,
+                                 const int32_t *budget, const float *tau) {
   if (!scores || !w_head || !utility || !budget || !tau) return CKV_EINVAL;
   if (params->flags & CKV_FLAG_GROUP_MASS) return CKV_EINVAL;  // needs per-head masses
   if ((params->flags & CKV_FLAG_VALUE_NORM) && !vnorm_ratio) return CKV_EINVAL;
   if (t_gate && (n_ent < 1 || n_ppl < 1 || !risk_bins)) return CKV_EINVAL;
+  return CKV_OK;
+}
+
+static ckv_status tables_of(const ckv_params *params, const Shape &s, const float *scores, const float *vnorm_ratio,
+                            const float *w_head, const float *head_share, const float *t_gate, int32_t n_ent, int32_t n_ppl,
+                            const int32_t *risk_bins, float *utility, int32_t *budget, float *tau, hipStream_t stream) {
+  const ckv_status st = tables_refused(params, scores, vnorm_ratio, w_head, t_gate, n_ent, n_ppl, risk_bins, utility, budget, tau);
+  if (st != CKV_OK) return st;
   if (launch_apply_tables(params, s, scores, vnorm_ratio, w_head, head_share, t_gate, n_ent, n_ppl,
                           risk_bins, utility, budget, tau, stream) != hipSuccess)
     return CKV_EHIP;
@@ -353,18 +370,26 @@ static bool utility_fast_path(const ckv_params *p, const Shape &s) {
          (int64_t)s.Hkv * s.P < (1 << 29);
 }
 
+static ckv_status utility_refused(const ckv_params *params, const Workspace &w, const void *q_win, const void *k, const void *v,
+                                  const float *w_head, const float *t_gate, int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins,
+                                  const float *scores_scratch, const float *vnorm_ratio, const float *utility, const int32_t *budget,
+                                  const float *tau, const void *workspace, size_t workspace_bytes) {
+  if (!q_win || !k) return CKV_EINVAL;
+  if ((params->flags & CKV_FLAG_VALUE_NORM) && !v) return CKV_EINVAL;
+  const ckv_status st =
+      tables_refused(params, scores_scratch, vnorm_ratio, w_head, t_gate, n_ent, n_ppl, risk_bins, utility, budget, tau);
+  return st != CKV_OK ? st : workspace_ok(w, workspace, workspace_bytes);
+}
+
 ckv_status ckv::utility_of(const ckv_params *params, const Shape &s, const Workspace &w, const void *q_win, const void *k,
                            const void *v, const float *lse, const float *w_head, const float *head_share, const float *t_gate,
                            int32_t n_ent, int32_t n_ppl, const int32_t *risk_bins, float *scores_scratch, float *vnorm_ratio,
                            float *utility, int32_t *budget, float *tau, void *workspace, size_t workspace_bytes,
                            hipStream_t stream, const Exchange &exchange) {
-  if (!q_win || !k || !scores_scratch || !w_head || !utility || !budget || !tau) return CKV_EINVAL;
-  if (params->flags & CKV_FLAG_GROUP_MASS) return CKV_EINVAL;  // needs per-head masses
-  const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
-  if (vn && (!v || !vnorm_ratio)) return CKV_EINVAL;
-  if (t_gate && (n_ent < 1 || n_ppl < 1 || !risk_bins)) return CKV_EINVAL;
-  const ckv_status st = workspace_ok(w, workspace, workspace_bytes);
+  const ckv_status st = utility_refused(params, w, q_win, k, v, w_head, t_gate, n_ent, n_ppl, risk_bins, scores_scratch, vnorm_ratio,
+                                        utility, budget, tau, workspace, workspace_bytes);
   if (st != CKV_OK) return st;
+  const bool vn = params->flags & CKV_FLAG_VALUE_NORM;
   float *ratio = vn ? vnorm_ratio : nullptr;
   if (vn && !norms_in_scan(params, s, lse != nullptr) &&
       launch_value_norm(params, s, w, v, ratio, (char *)workspace, stream) != hipSuccess)
@@ -411,17 +436,24 @@ extern "C" ckv_status ckv_window_utility(const ckv_params *params, const void *q
                     utility, budget, tau, workspace, workspace_bytes, (hipStream_t)hip_stream, exchange_of(params, s, w, lse, workspace));
 }
 
+// The workspace is optional here: short prefixes are selected by one workgroup per unit, everything on chip; for long ones it
+// lets the selection split a unit over several workgroups.
+static bool select_workspace_short(const Shape &s, const Workspace &w, const void *workspace, size_t workspace_bytes) {
+  return ((uintptr_t)workspace & 255) || workspace_bytes < w.select_off + select_split_bytes(s);
+}
+static ckv_status select_refused(const Shape &s, const Workspace &w, const float *utility, const int32_t *budget, const float *tau,
+                                 const int32_t *idx, const int32_t *count, const void *workspace, size_t workspace_bytes) {
+  if (!utility || !budget || !tau || !idx || !count) return CKV_EINVAL;
+  const bool given = workspace && w.select_bytes > 0;
+  return given && s.P % 4 == 0 && select_workspace_short(s, w, workspace, workspace_bytes) ? CKV_EWORKSPACE : CKV_OK;
+}
+
 static ckv_status select_of(const ckv_params *params, const Shape &s, const Workspace &w, const float *utility,
                             const int32_t *budget, const float *tau, int32_t *idx, int32_t *count, void *workspace,
                             size_t workspace_bytes, hipStream_t stream) {
-  if (!utility || !budget || !tau || !idx || !count) return CKV_EINVAL;
-  // Optional: short prefixes are selected by one workgroup per unit, everything on chip; for long ones a
-  // workspace lets the selection split a unit over several workgroups.
-  bool split = workspace && w.select_bytes > 0;
-  if (split && (((uintptr_t)workspace & 255) || workspace_bytes < w.select_off + select_split_bytes(s))) {
-    if (s.P % 4 == 0) return CKV_EWORKSPACE;
-    split = false;
-  }
+  const ckv_status st = select_refused(s, w, utility, budget, tau, idx, count, workspace, workspace_bytes);
+  if (st != CKV_OK) return st;
+  const bool split = workspace && w.select_bytes > 0 && !select_workspace_short(s, w, workspace, workspace_bytes);
   if (launch_select(params, s, utility, budget, tau, idx, count, split ? (char *)workspace + w.select_off : nullptr,
                     split ? workspace_bytes - w.select_off : 0, stream) != hipSuccess)
     return CKV_EHIP;
@@ -441,9 +473,15 @@ extern "C" ckv_status ckv_select_topk(const ckv_params *params, const float *uti
   return select_of(params, s, w, utility, budget, tau, idx, count, workspace, workspace_bytes, (hipStream_t)hip_stream);
 }
 
+static ckv_status gather_refused(const void *k, const void *v, const int32_t *idx, const int32_t *count, const void *k_out,
+                                 const void *v_out) {
+  return !k || !v || !idx || !count || !k_out || !v_out ? CKV_EINVAL : CKV_OK;
+}
+
 static ckv_status gather_of(const ckv_params *params, const Shape &s, const void *k, const void *v, const int32_t *idx,
                             const int32_t *count, void *k_out, void *v_out, hipStream_t stream, bool shared_list) {
-  if (!k || !v || !idx || !count || !k_out || !v_out) return CKV_EINVAL;
+  const ckv_status st = gather_refused(k, v, idx, count, k_out, v_out);
+  if (st != CKV_OK) return st;
   if (launch_gather(params, s, k, v, idx, count, k_out, v_out, stream, shared_list) != hipSuccess) return CKV_EHIP;
   return CKV_OK;
 }
@@ -473,6 +511,17 @@ extern "C" ckv_status ckv_retention_layer(const ckv_params *params, const void *
   Workspace w;
   derive(params, &s);
   layout(params, s, &w);
+  if (scores_wanted) {
+    st = scores_refused(params, s, w, q_win, k, v, scores, vnorm_ratio, workspace, workspace_bytes);
+    if (st == CKV_OK)
+      st = tables_refused(params, scores, vnorm_ratio, w_head, t_gate, n_ent, n_ppl, risk_bins, utility, budget, tau);
+  } else {
+    st = utility_refused(params, w, q_win, k, v, w_head, t_gate, n_ent, n_ppl, risk_bins, scores, vnorm_ratio, utility, budget, tau,
+                         workspace, workspace_bytes);
+  }
+  if (st == CKV_OK) st = select_refused(s, w, utility, budget, tau, idx, count, workspace, workspace_bytes);
+  if (st == CKV_OK) st = gather_refused(k, v, idx, count, k_out, v_out);
+  if (st != CKV_OK) return st;
   hipStream_t stream = (hipStream_t)hip_stream;
   const Exchange exchange = exchange_of(params, s, w, lse, workspace);
   if (scores_wanted) {
@@ -484,7 +533,7 @@ extern "C" ckv_status ckv_retention_layer(const ckv_params *params, const void *
                     budget, tau, workspace, workspace_bytes, stream, exchange);
   }
   const bool shares = head_share != nullptr;
-  if (st == CKV_OK && keeps_in_one_launch(params, s, shares) && k && v && idx && count && k_out && v_out)
+  if (st == CKV_OK && keeps_in_one_launch(params, s, shares))
     return launch_keep(params, s, utility, budget, tau, k, v, idx, count, k_out, v_out, shares, stream) == hipSuccess ? CKV_OK : CKV_EHIP;
   if (st == CKV_OK) st = select_of(params, s, w, utility, budget, tau, idx, count, workspace, workspace_bytes, stream);
   if (st == CKV_OK) st = gather_of(params, s, k, v, idx, count, k_out, v_out, stream, false);
