@@ -1665,6 +1665,10 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
   static_assert(kRing == 4, "the waits below");
   using G = Geom<DT, DH>;
   constexpr int NCH = G::NCH, NH = NQ / WT, ROWS = NQ * kTile;
+  // Eight query tiles of 256-byte rows fill the registers: the sums around the range are contracted behind the exchange, not held through
+  // it (eight registers spilled, and each reload waited for all key tiles in flight: us per layer 8192 keys, batch 2, 32/4 heads 31.7
+  // with spills / 31.0, 3001 keys, W = 64 29.3 / 28.4, 65536 keys, batch 2, 8/1 56.5 / 55.4).
+  constexpr bool FULL = NQ == kMaxQTiles && G::ROW == 256 && UTIL;
   typedef Staged<DT, DH, NQ, true> Scan;
   __shared__ __attribute__((aligned(1024))) typename Scan::Ring ring;
   __shared__ __attribute__((aligned(1024))) char s_halo_keys[UTIL ? 2 * kHaloKeys * G::ROW : 16];
@@ -1684,6 +1688,12 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
   constexpr int HALO_TILES = !UTIL ? 1 : WT * ((NH + kScoreWaves - 1) / kScoreWaves);  // as in colsum_lds_kernel
   const auto halo_head = [&](int u) { return wr.wave + u / WT * kScoreWaves; };
   f32x16 halo[HALO_TILES];
+  const auto read_halo = [&](chunk_t(&kh)[NCH]) {
+    int hoff[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) hoff[c] = image_offset<G>(m & (kUtilHead - 1), c + NCH * hh);
+    read_image<G>(kh, s_halo_keys, hoff);
+  };
   st.start(
       a, bc, wr, ring, lane, m, hh, qf, jrow,
       [&] {
@@ -1694,12 +1704,9 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
                       (uint32_t)(uintptr_t)s_halo_keys);
       },
       [&] {
-        if constexpr (!UTIL) return;
-        int hoff[NCH];
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) hoff[c] = image_offset<G>(m & (kUtilHead - 1), c + NCH * hh);
+        if constexpr (!UTIL || FULL) return;
         chunk_t kh[NCH], qh[NCH];
-        read_image<G>(kh, s_halo_keys, hoff);
+        read_halo(kh);
 #pragma unroll
         for (int u = 0; u < HALO_TILES; ++u) {
           if (halo_head(u) >= NH) continue;
@@ -1815,6 +1822,13 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
   RowBias bias[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) bias[i].set(s_bias + i * kTile, m, hh);
+  if constexpr (FULL) {
+    chunk_t kh[NCH];
+    read_halo(kh);
+#pragma unroll
+    for (int i = 0; i < NQ; ++i)
+      if (wr.wave == i / WT % kScoreWaves) mma_chain<DT, NCH>(halo[i / (WT * kScoreWaves) * WT + i % WT], qf[i], kh);
+  }
   if constexpr (UTIL) {
 #pragma unroll
     for (int u = 0; u < HALO_TILES; u += WT) {
