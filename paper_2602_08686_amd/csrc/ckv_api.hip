@@ -190,9 +190,11 @@ extern "C" size_t ckv_workspace_bytes(const ckv_params *params) {
   return w.total;
 }
 
-// How long a workgroup of the one-launch form waits for the others' row sums (units of 10 ns) before it makes them itself: they
-// are there within 2 us where all run at once, and come late only where another kernel holds CUs.
-constexpr uint32_t kExchangeWait = 3000;
+// How long a workgroup of the one-launch form waits for the others' row sums (units of 10 ns) before it makes some itself: they
+// are there within 2 us where all run at once, and come late only where another kernel holds CUs. us per call, 5 / 10 / 30 us: beside a
+// scan that holds 136 CUs 4096 keys, 32/32 heads 56 / 50 / 49, 16384, batch 2, 8/2 71 / 71 / 63; on four streams 65536, batch 2, 8/1 56 /
+// 51 / 62; without either no difference.
+constexpr uint32_t kExchangeWait = 1000;
 
 // The marks lie where a call that makes the normalisers and uses them leaves its workspace alone, in the place for those: four
 // bytes for each row of a unit's heads against eight for each of its workgroups. Where that is not room enough, two launches.

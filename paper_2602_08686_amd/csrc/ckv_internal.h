@@ -123,6 +123,10 @@ template <class T>
 __device__ __forceinline__ T load_across(const T *p) {
   return __scoped_atomic_load_n(p, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
 }
+template <class T>
+__device__ __forceinline__ void replace_across(T *p, T old, T v) {  // nothing where *p is not `old` any more
+  __scoped_atomic_compare_exchange_n(p, &old, v, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+}
 // Marks that workgroups of a launch leave for one another in memory that nobody has cleared: equal to the launch's tag or not.
 // A launch takes its marks back before it ends, so that a replay of it, which has the same tag, finds none; what else the memory
 // may have held is no tag (launch_tag: another value for every launch of the process, such as nothing else leaves there).

@@ -1644,16 +1644,26 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) __attribute__((amdgpu_wave
   wait_vm<0>();  // the loads beyond the last tile write LDS: not after the wave
 }
 
+// The mark of a range whose sums another workgroup has made, unless the range's own one has left its mark, or changed it already.
+__device__ __forceinline__ void leave_mark(tag_t *mark, tag_t tag) {
+  const tag_t seen = load_across(mark);
+  if ((seen | 1) != (tag | 1)) replace_across(mark, seen, tag);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Both passes of a fused call in one launch, for ranges that fit the ring: the key tiles stay in LDS between the passes. What a short
 // call takes is launches, the way of the first loads and the fetch of code, not bytes or arithmetic; here the second pass has
 // neither a launch nor loads of its own, and as a range is four tiles at most, nothing is unrolled over them.
 //
 // The workgroups of a unit exchange their row sums: each leaves its own and a mark (behind them, when they have arrived), waits until
-// it sees all marks, and merges all sums. No workgroup depends on another one's progress: after a.wait it makes the sums that are
-// missing itself, from the keys in memory, the same ones to the last bit (a launch whose workgroups do not all find a CU, because
-// another stream's kernel holds some, would wait for workgroups that wait for it otherwise). Who has read all sums changes its
-// mark; who sees all of them changed at its end takes them back, and the last one to change its own does see that.
+// it sees all marks, and merges all sums. No workgroup depends on another one's progress: after a.wait it makes the sums of one of the missing
+// ranges, from the keys in memory, the same ones to the last bit, leaves that range's mark and looks again (a launch whose workgroups do not all
+// find a CU, because another stream's kernel holds some, would wait for workgroups that wait for it otherwise). Each begins at
+// another of the missing ranges, so that they share them: with all of them made by every waiting workgroup, four streams of 65536 keys,
+// batch 2, 8/1 heads (128 ranges a unit) took 646 us per call, now 51, two launches 33; beside matrix products 220 us more than two launches, now none
+// (the same beside a scan that holds 136 CUs, us: 239, 151, 142; 8192 keys, batch 2, 32/4 heads 78, 78, 102).
+// Who has read all sums changes its mark; who sees all of them changed at its end takes them back, and the last one to change its
+// own does see that.
 // us per layer, two launches / one, keys in the memory-side cache before the call and from HBM: 4096 keys, 32/32 heads 27.4 / 25.1, 31.4 /
 // 26.0; 8192, 32/8 27.3 / 25.0, 29.7 / 25.7; 4096, batch 4, 32/8 35.9 / 29.7, 37.2 / 30.1; 1000, 32/8 21.8 / 20.5, 21.9 / 21.1; seven tiles, 6000,
 // batch 2, 28/4 29.6 / 27.7, 31.7 / 28.2; eight, 8192, batch 2, 32/4 33.9 / 30.5, 35.1 / 30.6; 3001, W = 64, 32/8 28.9 / 28.5, 30.4 / 29.0. The keys are
@@ -1779,35 +1789,56 @@ __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArg
   if (threadIdx.x == 0) store_across(marks + bc.chunk, a.tag);
   if (UTIL && bc.g == 0 && bc.chunk == 0 && wr.wave == kScoreWaves - 1) write_tau_and_budgets(a.bud, bc.b, lane);
 
-  // -- the others' sums
-  if (wr.wave == 0) {
-    const uint64_t start = __builtin_amdgcn_s_memrealtime();
-    for (;;) {
-      const uint64_t now = __builtin_amdgcn_s_memrealtime();
-      bool some = false;
-      for (int c0 = 0; c0 < a.n_chunks; c0 += kWave) {
-        const int c = c0 + lane;
-        const uint64_t missing = __ballot(c < a.n_chunks && (load_across(marks + c) | 1) != (a.tag | 1));
-        if (lane == 0) s_missing[c0 / kWave] = missing;
-        some |= missing != 0;
+  // -- the others' sums: all of them within a.wait, or one of the missing ranges by this workgroup, and the marks again
+  for (;;) {
+    if (wr.wave == 0) {
+      const uint64_t start = __builtin_amdgcn_s_memrealtime();
+      for (;;) {
+        const uint64_t now = __builtin_amdgcn_s_memrealtime();
+        bool some = false;
+        for (int c0 = 0; c0 < a.n_chunks; c0 += kWave) {
+          const int c = c0 + lane;
+          const uint64_t missing = __ballot(c < a.n_chunks && (load_across(marks + c) | 1) != (a.tag | 1));
+          if (lane == 0) s_missing[c0 / kWave] = missing;
+          some |= missing != 0;
+        }
+        if (!some || now - start >= a.wait) break;
+        __builtin_amdgcn_s_sleep(1);
       }
-      if (!some || now - start >= a.wait) break;
-      __builtin_amdgcn_s_sleep(1);
     }
-  }
-  __syncthreads();
-  for (int c0 = 0; c0 < a.n_chunks; c0 += kWave) {
-    const uint64_t missing = s_missing[c0 / kWave];
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)missing), hi = __builtin_amdgcn_readfirstlane((uint32_t)(missing >> 32));
-    for (uint64_t rest = (uint64_t)hi << 32 | lo; rest; rest &= rest - 1) {
-      BlockCoord other = bc;
-      other.chunk = c0 + __ffsll((long long)rest) - 1;
-      row_sums(wave_range(a, other, a.T), other.chunk, [&](int, int t0) {
-        const char *row = st.kbase + (int64_t)min(t0 + m, a.T - 1) * a.ks_t;
+    __syncthreads();
+    const auto missing = [&](int c0) {
+      const uint64_t x = s_missing[c0 / kWave];
+      return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)x);
+    };
+    int n_missing = 0, rank = bc.chunk;  // rank: of this workgroup among those whose sums are there
+    for (int c0 = 0; c0 < a.n_chunks; c0 += kWave) {
+      const uint64_t x = missing(c0);
+      const int in_front = bc.chunk - c0;
+      n_missing += __popcll(x);
+      rank -= in_front >= kWave ? __popcll(x) : in_front > 0 ? __popcll(x & ((1ull << in_front) - 1)) : 0;
+    }
+    if (n_missing == 0) break;
+    int skip = rank % n_missing;
+    BlockCoord other = bc;
+    for (int c0 = 0; c0 < a.n_chunks; c0 += kWave) {
+      uint64_t x = missing(c0);
+      const int here = __popcll(x);
+      if (skip >= here) {
+        skip -= here;
+        continue;
+      }
+      for (; skip > 0; --skip) x &= x - 1;
+      other.chunk = c0 + __ffsll((long long)x) - 1;
+      break;
+    }
+    row_sums(wave_range(a, other, a.T), other.chunk, [&](int, int t0) {
+      const char *row = st.kbase + (int64_t)min(t0 + m, a.T - 1) * a.ks_t;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) kf[c] = *reinterpret_cast<const chunk_t *>(row + (c + NCH * hh) * 16);
-      });
-    }
+      for (int c = 0; c < NCH; ++c) kf[c] = *reinterpret_cast<const chunk_t *>(row + (c + NCH * hh) * 16);
+    });
+    if (threadIdx.x == 0) leave_mark(marks + other.chunk, a.tag);
+    wait_vm<0>();
   }
   if (threadIdx.x < ROWS) {
     const int tile = bc.grp * NQ + (int)threadIdx.x / kTile;

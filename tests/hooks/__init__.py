@@ -4,7 +4,7 @@ import ctypes
 from paper_2602_08686_amd import binding as B
 from paper_2602_08686_amd import build
 
-RULE = 3000   # units of 10 ns that the rule's form waits
+RULE = 1000   # units of 10 ns that the rule's form waits
 
 _lib = None
 

@@ -18,6 +18,7 @@ SHAPES = [  # batch, query heads, KV heads, d, T, W, pooling, kernel
     (1, 8, 8, 128, 33, 1, B.POOL_NONE, 1), (1, 4, 1, 128, 20, 4, B.POOL_MAX, 3), (3, 6, 2, 128, 511, 32, B.POOL_AVG, 3), (1, 4, 2, 64, 3001, 64, B.POOL_MAX, 7),
     (1, 4, 4, 128, 16384, 32, B.POOL_AVG, 7), (1, 2, 1, 128, 16383, 40, B.POOL_AVG, 7), (16, 8, 8, 128, 777, 32, B.POOL_MAX, 5),
     (1, 4, 1, 128, 10000, 32, B.POOL_AVG, 7), (1, 3, 1, 64, 11111, 32, B.POOL_MAX, 3),   # 40 workgroups and more of a unit
+    (2, 8, 1, 128, 65536, 32, B.POOL_AVG, 7), (3, 8, 1, 64, 43001, 32, B.POOL_MAX, 5),   # more than a wave has lanes
     (2, 28, 4, 128, 2600, 32, B.POOL_AVG, 7), (1, 16, 2, 128, 9001, 32, B.POOL_MAX, 5), (1, 10, 2, 64, 3100, 32, B.POOL_AVG, 3),   # 7, 8, 5 tiles
     (1, 32, 8, 128, 1999, 64, B.POOL_AVG, 7), (1, 12, 4, 128, 777, 50, B.POOL_MAX, 7),                                            # 8, 6: two per head
 ]
@@ -99,6 +100,41 @@ def test_scores_in_one_launch_match_two(shape):
         assert torch.equal(scores, outs[1]), form
     torch.testing.assert_close(outs[1].double().sum(-1), torch.full((p.batch, p.n_q_heads), float(p.seq_len), dtype=torch.float64, device=DEV),
                                rtol=1e-4, atol=0)
+
+
+def _graph_us(p, q, k, w_head, **form):
+    """us per call of 20 in a graph, the least of five replays."""
+    n, stream = p.batch * p.n_kv_heads, torch.cuda.Stream()
+    out = dict(scratch=torch.empty(p.batch, p.n_q_heads, p.seq_len, device=DEV), utility=torch.empty(n, p.seq_len - p.window, device=DEV),
+               budget=torch.empty(n, dtype=torch.int32, device=DEV), tau=torch.empty(p.batch, device=DEV),
+               ws=torch.zeros(B.ckv_workspace_bytes(p), dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    hooks.window_utility(p, q, k, w_head, stream=stream, **out, **form)
+    torch.cuda.synchronize()
+    graph, times = torch.cuda.CUDAGraph(), []
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(20):
+            hooks.window_utility(p, q, k, w_head, stream=stream, **out, **form)
+    for _ in range(5):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        graph.replay()
+        end.record()
+        torch.cuda.synchronize()
+        times.append(begin.elapsed_time(end) * 1e3 / 20)
+    return min(times), out["utility"]
+
+
+@pytest.mark.parametrize("shape", [(2, 8, 1, 128, 65536, 32, B.POOL_AVG, 7), (1, 32, 8, 128, 8192, 32, B.POOL_AVG, 7)], ids=lambda s: "-".join(map(str, s)))
+def test_workgroups_that_do_not_wait_share_the_missing_ranges(shape):
+    """Nobody waits: what a launch beside a busy stream comes to. With every missing range made by every workgroup it took 31 and 8 times as long as
+    two launches."""
+    print("case", shape, flush=True)
+    p, q, k, w_head = _call(shape, 11)
+    two, want = _graph_us(p, q, k, w_head, two_launches=True)
+    none, got = _graph_us(p, q, k, w_head, wait=0)
+    assert torch.equal(got, want)
+    assert none < 4 * two, (none, two)
 
 
 @pytest.mark.parametrize("d", [64, 128])
