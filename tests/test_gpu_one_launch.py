@@ -13,10 +13,11 @@ from parity_util import assert_scores_close, f32
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
+NO_ROOM = (1, 4, 4, 128, 16384, 32, B.POOL_AVG, 7)   # more workgroups per unit than the normalisers' place has room for: two launches, by the rule
 SHAPES = [  # batch, query heads, KV heads, d, T, W, pooling, kernel
     (1, 32, 32, 128, 4096, 32, B.POOL_MAX, 7), (1, 32, 8, 128, 4097, 32, B.POOL_AVG, 7), (2, 32, 8, 64, 1000, 17, B.POOL_AVG, 5),
     (1, 8, 8, 128, 33, 1, B.POOL_NONE, 1), (1, 4, 1, 128, 20, 4, B.POOL_MAX, 3), (3, 6, 2, 128, 511, 32, B.POOL_AVG, 3), (1, 4, 2, 64, 3001, 64, B.POOL_MAX, 7),
-    (1, 4, 4, 128, 16384, 32, B.POOL_AVG, 7), (1, 2, 1, 128, 16383, 40, B.POOL_AVG, 7), (16, 8, 8, 128, 777, 32, B.POOL_MAX, 5),
+    NO_ROOM, (4, 4, 4, 128, 4096, 32, B.POOL_AVG, 7), (1, 2, 1, 128, 16383, 40, B.POOL_AVG, 7), (16, 8, 8, 128, 777, 32, B.POOL_MAX, 5),
     (1, 4, 1, 128, 10000, 32, B.POOL_AVG, 7), (1, 3, 1, 64, 11111, 32, B.POOL_MAX, 3),   # 40 workgroups and more of a unit
     (2, 8, 1, 128, 65536, 32, B.POOL_AVG, 7), (3, 8, 1, 64, 43001, 32, B.POOL_MAX, 5),   # more than a wave has lanes
     (2, 28, 4, 128, 2600, 32, B.POOL_AVG, 7), (1, 16, 2, 128, 9001, 32, B.POOL_MAX, 5), (1, 10, 2, 64, 3100, 32, B.POOL_AVG, 3),   # 7, 8, 5 tiles
@@ -64,6 +65,12 @@ def _run(p, q, k, w_head, ws, nbytes, lse=None, **form):
     return u
 
 
+def _no_marks(p, ws):
+    """The call took its marks back."""
+    at, n = hooks.marks(p)
+    assert (n > 0) == (p.seq_len != NO_ROOM[4]) and (ws[at:at + 8 * n].view(torch.int64) == 0).all()
+
+
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
 def test_one_launch_matches_two(shape):
     print("case", shape, flush=True)
@@ -78,6 +85,7 @@ def test_one_launch_matches_two(shape):
     for wait in (0, 1, 3000):
         ws.random_(0, 256)
         assert torch.equal(_run(p, q, k, w_head, ws, whole, wait=wait), one), wait
+        _no_marks(p, ws)
 
 
 @pytest.mark.parametrize("shape", SHAPES + [(1, 1, 1, 128, 2000, 100, B.POOL_NONE, 1), (1, 2, 2, 64, 5000, 128, B.POOL_NONE, 1)],
@@ -98,6 +106,8 @@ def test_scores_in_one_launch_match_two(shape):
         ws.random_(0, 256)
         hooks.window_scores(p, q, k, scores, ws, torch.cuda.current_stream(), **form)
         assert torch.equal(scores, outs[1]), form
+        if "wait" in form:
+            _no_marks(p, ws)
     torch.testing.assert_close(outs[1].double().sum(-1), torch.full((p.batch, p.n_q_heads), float(p.seq_len), dtype=torch.float64, device=DEV),
                                rtol=1e-4, atol=0)
 
@@ -168,25 +178,24 @@ def test_sequences_of_a_tile_or_less(T, W, heads, d):
             assert_scores_close(one.cpu().numpy().reshape(ref.shape), ref, "utility")
 
 
-@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1], SHAPES[5]], ids=lambda s: "-".join(map(str, s)))
-def test_replays_with_other_inputs(shape):
-    """A replayed launch has the marks' tag of the first one: none of them may be left."""
+@pytest.mark.parametrize("wait", [hooks.RULE, 0])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1], SHAPES[5], (2, 8, 1, 128, 65536, 32, B.POOL_AVG, 7)], ids=lambda s: "-".join(map(str, s)))
+def test_replays_with_other_inputs(shape, wait):
+    """A replayed launch has the marks' tag of the first one: none of them may be left. One call in the graph, so that no other one's tag
+    lies over its marks before it comes again."""
+    print("case", shape, wait, flush=True)
     p, q, k, w_head = _call(shape, 1)
     ws = torch.zeros(B.ckv_workspace_bytes(p), dtype=torch.uint8, device=DEV)
-    n = p.batch * p.n_kv_heads
+    n, stream = p.batch * p.n_kv_heads, torch.cuda.Stream()
     u = torch.empty(n, p.seq_len - p.window, device=DEV)
     scratch = torch.empty(p.batch, p.n_q_heads, p.seq_len, device=DEV)
     budget, tau = torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(p.batch, device=DEV)
-
-    def call():
-        B.ckv_window_utility(p, q, k, None, None, w_head, None, None, 0, 0, None, scratch, None, u, budget, tau, ws)
-
-    call()
+    torch.cuda.synchronize()
+    hooks.window_utility(p, q, k, w_head, scratch, u, budget, tau, ws, stream, wait=wait)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
-        for _ in range(3):
-            call()
+    with torch.cuda.graph(graph, stream=stream):
+        hooks.window_utility(p, q, k, w_head, scratch, u, budget, tau, ws, stream, wait=wait)
     for seed in range(2, 7):
         _, q2, k2, _ = _call(shape, seed)
         q.copy_(q2)
@@ -194,8 +203,9 @@ def test_replays_with_other_inputs(shape):
         u.zero_()
         graph.replay()
         torch.cuda.synchronize()
+        _no_marks(p, ws)
         got = u.clone()
-        assert torch.equal(got, _run(p, q, k, w_head, torch.zeros_like(ws), ws.numel()).view_as(got)), seed
+        assert torch.equal(got, _run(p, q, k, w_head, torch.zeros_like(ws), ws.numel(), two_launches=True).view_as(got)), seed
 
 
 def test_streams_and_a_kernel_that_holds_the_chip():
@@ -220,6 +230,7 @@ def test_streams_and_a_kernel_that_holds_the_chip():
         for (p, q, k, w_head), (ws, scratch, u, budget, tau), stream in zip(calls, state, streams):
             B.ckv_window_utility(p, q, k, None, None, w_head, None, None, 0, 0, None, scratch, None, u[r], budget, tau, ws, stream)
     torch.cuda.synchronize()
-    for w, (_, _, u, _, _) in zip(want, state):
+    for w, (ws, _, u, _, _) in zip(want, state):
+        _no_marks(calls[0][0], ws)
         for r in range(30):
             assert torch.equal(u[r], w.view_as(u[r])), r
