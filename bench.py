@@ -588,7 +588,8 @@ def main() -> int:
                    "kv_heads": w.n_kv_heads, "head_dim": w.head_dim, "seq_len": w.seq_len, "window": w.window,
                    "budget_per_kv_head": w.budget, "pool": ["none", "avg", "max"][w.pool] + str(w.pool_kernel),
                    "value_norm": bool(args.value_norm), "lse": "given" if args.given_lse else "computed",
-                   "calls": ("window_scores+apply_tables" if args.unfused else "window_utility") + "+select_topk+compact_kv",
+                   "calls": "retention_layer, steps of " + ("window_scores+apply_tables" if args.unfused else "window_utility")
+                            + "+select_topk+compact_kv",
                    "buffers": "every layer its own K, V, outputs and scratch",
                    "streams": max(args.streams, 1),
                    "algorithmic_bytes_per_layer": layer_bytes, "kept_rows_last_layer": kept},

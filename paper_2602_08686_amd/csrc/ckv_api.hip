@@ -136,15 +136,15 @@ bool norms_in_scan(const ckv_params *p, const Shape &s, bool lse_given) {
 }
 
 // One launch for both passes where a wave's range is no longer than its ring of key tiles, so that the keys stay in LDS between
-// them, and every workgroup has a CU of its own (more of them would wait for
-// ones that start when they end). 0.80 to 0.99 of the two launches'
-// time per layer over nineteen shapes of 1000 to 16384 keys (scan_short_kernel). Without value norms, whose ratio needs a unit's sum of them, too.
+// them, and every workgroup has a CU of its own (more of them would wait for ones that start when they end). 0.80 to 0.98 of the two
+// launches' time per layer over twelve shapes of 1000 to 65536 keys (scan_short_kernel). Without value norms, whose ratio needs a
+// unit's sum of them, too.
 bool one_launch(const ckv_params *p, const Shape &s) {
   return p->dtype == CKV_BF16 && s.n_groups == 1 && s.keys_per_wave <= kRing * kTile && (int64_t)s.Bz * s.Hkv * s.n_chunks <= kComputeUnits;
 }
 
-// Even. The upper bits are those of a negative NaN, which no sum, position or key ends up as; the rest counts launches from the
-// time the process began, in steps that touch all bits.
+// Even. The upper bits are those of a negative NaN, which no sum, position or key ends up as; the rest counts the process's launches
+// from the monotonic clock's value at the first of them, in steps that touch all bits.
 tag_t launch_tag() {
   static std::atomic<uint64_t> count{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count()};
   const uint64_t mixed = count.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;

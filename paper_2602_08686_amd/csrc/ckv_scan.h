@@ -1026,7 +1026,7 @@ __global__ void __launch_bounds__(kScoreWaves *kWave * (NORMS ? 2 : 1)) rowstats
 // The extra contraction step of pass 2 that adds bias_j = -LSE_j / scale to every logit of query row j: the bias as hi + mid + lo
 // bf16 terms in the first three slots of the Q-side operand of the lanes with hh = 0, ones in the same slots on the K side. The
 // terms are made once per row (pack) and reach the lanes through LDS. (In registers, as the addend of the scale's multiplication, the
-// normalisers save the ninth MFMA of a pair and 1 % of a layer; but they round differently, and keys within 1e-6 of a
+// normalisers save the ninth MFMA of a pair and 0.5 to 1.4 % of a layer; but they round differently, and keys within 1e-6 of a
 // threshold change places.) Padding rows (q = 0) get exp2(kNoWeight) = 0 as weight.
 constexpr float kNoWeight = -1000.0f;
 __device__ __forceinline__ uint32_t bf16_bits(float x) {  // round to nearest even; x is finite
@@ -1664,10 +1664,12 @@ __device__ __forceinline__ void leave_mark(tag_t *mark, tag_t tag) {
 // (the same beside a scan that holds 136 CUs, us: 239, 151, 142; 8192 keys, batch 2, 32/4 heads 78, 78, 102).
 // Who has read all sums changes its mark; who sees all of them changed at its end takes them back, and the last one to change its
 // own does see that.
-// us per layer, two launches / one, keys in the memory-side cache before the call and from HBM: 4096 keys, 32/32 heads 27.4 / 25.1, 31.4 /
-// 26.0; 8192, 32/8 27.3 / 25.0, 29.7 / 25.7; 4096, batch 4, 32/8 35.9 / 29.7, 37.2 / 30.1; 1000, 32/8 21.8 / 20.5, 21.9 / 21.1; seven tiles, 6000,
-// batch 2, 28/4 29.6 / 27.7, 31.7 / 28.2; eight, 8192, batch 2, 32/4 33.9 / 30.5, 35.1 / 30.6; 3001, W = 64, 32/8 28.9 / 28.5, 30.4 / 29.0. The keys are
-// streamed, since nothing reads them again (kept in the cache 1 to 5 % faster if they were there before, 2 to 7 % slower if not).
+// us per layer on a stream of layers, two launches / one, keys in the memory-side cache before the call and from HBM: 4096 keys, 32/32 heads
+// 26.3 / 24.1, 30.4 / 24.7; 8192, 32/8 27.6 / 25.1, 28.9 / 25.0; 4096, batch 4, 32/8 36.0 / 30.7, 38.2 / 31.4; 1000, 32/8 20.2 / 18.9, 20.5 / 19.9; seven
+// tiles, 6000, batch 2, 28/4 30.2 / 28.8, 32.1 / 29.0; eight, 8192, batch 2, 32/4 33.4 / 30.9, 35.6 / 31.0; 3001, W = 64, 32/8 28.8 / 28.2, 30.7 / 28.7;
+// 65536, batch 2, 8/1 60.7 / 57.2, 63.9 / 57.2. One layer that is waited for, keys from HBM (launch and host included): 45.1 / 39.8 for the first, 42.9 / 39.5
+// for the second. The keys are streamed, since nothing reads them again (kept in the cache 1 to 5 % faster if they were there
+// before, 2 to 7 % slower if not).
 // ---------------------------------------------------------------------------------------------
 template <int DT, int DH, int NQ, int WT, bool UTIL>
 __global__ void __launch_bounds__(kScoreWaves *kWave) scan_short_kernel(ScoreArgs a) {

@@ -429,7 +429,7 @@ __global__ void __launch_bounds__(NT) select_reg_kernel(SelectArgs a) {
 // selection of a unit, which takes none of them longer than one of them (a chain of steps inside a workgroup, while most of the
 // chip is idle), and each writes and copies its share of the rows: blocks of BLOCK rows in turn, whose positions stay in LDS. The
 // gather's launch, and its way to count, index and row, are gone; what is left of it is the rows. us per layer, two launches / one: 4096
-// keys, 32/32 heads 25.1 / 24.4, 4096, 32/8 22.1 / 21.1, 1000, 32/8 20.5 / 19.0, 28000, 32/8 43.9 / 43.5, 30000, 32/8, 2048 rows 50.3 / 48.7. With
+// keys, 32/32 heads 25.6 / 24.2, 8192, 32/8 25.6 / 24.7, 1000, 32/8 20.6 / 19.1, 28000, 32/8 46.8 / 46.4, 30000, 32/8, 2048 rows 50.3 / 48.7. With
 // shares a head may have all rows of a batch element: it is this form where its workgroups take those with two blocks each; where they
 // have more to move, the gather, which deals long lists out, is the faster one. Shares drawn from 0.5 to 1.5 and all in one head, us: 8192 keys,
 // 32/8 heads 25.9 / 24.8, 28.1 / 27.4; f32, 1024, 4/4 (four calls' kernels) 21.6 / 18.3, 20.5 / 19.1; but with up to four blocks each 20011, batch 2

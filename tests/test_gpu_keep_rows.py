@@ -1,6 +1,6 @@
-"""Selection and gather of a layer in one launch against the two calls on the same
-utilities, bit by bit: without shares and with all of the budget in one head; prefixes at the kernels' limits, quotas of nothing, of less than a block of rows and of several, fewer
-candidates than the quota, strided rows, both head sizes and types."""
+"""Selection and gather of a layer in one launch against the two calls on the same utilities, bit by bit: without shares and with
+all of the budget in one head; prefixes at the kernels' limits, quotas of nothing, of less than a block of rows and of several,
+fewer candidates than the quota, strided rows, both head sizes and types."""
 import pytest
 import torch
 
