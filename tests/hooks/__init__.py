@@ -13,7 +13,8 @@ def _load():
     global _lib
     if _lib is None:
         B.load()
-        if not build.HOOKS_LIB.exists():
+        # they share structures: one built against an older library is not used
+        if not build.HOOKS_LIB.exists() or build.HOOKS_LIB.stat().st_mtime < build.LIB.stat().st_mtime:
             build.build_test_hooks()
         lib, vp, n = ctypes.CDLL(str(build.HOOKS_LIB)), ctypes.c_void_p, ctypes.c_size_t
         pp = ctypes.POINTER(B.CkvParams)
